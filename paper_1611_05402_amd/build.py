@@ -9,8 +9,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libzipml.so")
-SOURCES = ["zipml_quantize.hip", "zipml_sgd.hip", "zipml_loss.hip", "zipml_levels.hip"]
-HEADERS = ["zipml_device.h", "zipml_host.h", "zipml_mfma_ops.h", "zipml_sgd_mfma.h", "zipml_sgd_rows.h"]
+# (source, further flags, object): the SGD kernels of each code width are a compilation of their own
+UNITS = [("zipml_sgd.hip", [f"-DZIPML_SGD_BITS={b}"], f"zipml_sgd_{b}.o") for b in (8, 4, 2, 7, 6, 5, 3, 1)]
+UNITS += [(s, [], s.replace(".hip", ".o")) for s in ("zipml_sgd.hip", "zipml_quantize.hip", "zipml_loss.hip", "zipml_levels.hip")]
 
 # -ffp-contract=off: fp32/fp64 decision sequences must stay single IEEE operations (fused
 #   multiply-adds are written explicitly where they are wanted).
@@ -31,13 +32,14 @@ def _stale(target: str, deps) -> bool:
 def build(force: bool = False, verbose: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    hdrs = [os.path.join(CSRC, h) for h in HEADERS] + [os.path.join(HERE, "..", "include", "zipml.h")]
+    hdrs = [os.path.join(CSRC, h) for h in sorted(os.listdir(CSRC)) if h.endswith(".h")]
+    hdrs.append(os.path.join(HERE, "..", "include", "zipml.h"))
     jobs = []
-    for src in SOURCES:
+    for src, more, obj in UNITS:
         s = os.path.join(CSRC, src)
-        o = os.path.join(objdir, src.replace(".hip", ".o"))
+        o = os.path.join(objdir, obj)
         if force or _stale(o, [s] + hdrs):
-            jobs.append(["hipcc", *FLAGS, "-c", s, "-o", o])
+            jobs.append(["hipcc", *FLAGS, *more, "-c", s, "-o", o])
 
     def run(cmd):
         if verbose:
@@ -50,9 +52,9 @@ def build(force: bool = False, verbose: bool = False) -> str:
             lines = [l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l]
             sys.stderr.write("\n".join(lines) + "\n")
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         list(ex.map(run, jobs))
-    objs = [os.path.join(objdir, s.replace(".hip", ".o")) for s in SOURCES]
+    objs = [os.path.join(objdir, obj) for _, _, obj in UNITS]
     if force or jobs or _stale(OUT, objs):
         run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", OUT, "-lpthread"])
     return OUT

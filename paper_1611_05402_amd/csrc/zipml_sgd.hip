@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
 // together; with 256 the launch took 10 us on 2,048 x 256 levels, now 5.5.  The bounds' block reads a
 // cache line per feature through one compute unit: 19 us at 16,384 features, of an epoch of 3.3 ms.)
 constexpr int kPrepThreads = 1024;
-__global__ __launch_bounds__(kPrepThreads) void k_sgd_prepare(int *status, uint32_t *sync, uint64_t *acc,
+static __global__ __launch_bounds__(kPrepThreads) void k_sgd_prepare(int *status, uint32_t *sync, uint64_t *acc,
                                                       int words, int clear_status,
                                                       const float *__restrict__ levels,
                                                       const float *__restrict__ x, int d, int K,
@@ -1310,7 +1310,7 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
 }
 
 template <int BITS>
-static int launch_sgd_mode(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
+int launch_sgd_mode(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
 {
     return a.model_bits > 0 ? launch_sgd<BITS, true>(s, a, p, stepwise)
                             : launch_sgd<BITS, false>(s, a, p, stepwise);
@@ -1318,7 +1318,7 @@ static int launch_sgd_mode(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwi
 
 // Sample-owner kernel for very large minibatches (zipml_sgd_rows.h).
 template <int BITS>
-static int launch_rows(hipStream_t s, RowsArgs &r, const float *levels, int wgs, int *even, uint64_t *acc)
+int launch_rows(hipStream_t s, RowsArgs &r, const float *levels, int wgs, int *even, uint64_t *acc)
 {
     const int K = 1 << BITS;
     const int nfeat = r.NKB * 64;
@@ -1374,6 +1374,27 @@ static int launch_rows(hipStream_t s, RowsArgs &r, const float *levels, int wgs,
     void *params[] = {&r};
     return launch_resident(kern, wgs, params, lds_bytes, s);
 }
+
+// The kernels of one code width are a compilation of their own (this file with ZIPML_SGD_BITS set): eight
+// of them side by side take a quarter of the time of one.
+#ifdef ZIPML_SGD_BITS
+template int launch_sgd_mode<ZIPML_SGD_BITS>(hipStream_t, SgdArgs &, const Plan &, bool);
+#if ZIPML_SGD_BITS == 2 || ZIPML_SGD_BITS == 4 || ZIPML_SGD_BITS == 8
+template int launch_rows<ZIPML_SGD_BITS>(hipStream_t, RowsArgs &, const float *, int, int *, uint64_t *);
+#endif
+}  // namespace zipml
+#else
+extern template int launch_sgd_mode<1>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<2>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<3>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<4>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<5>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<6>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<7>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_sgd_mode<8>(hipStream_t, SgdArgs &, const Plan &, bool);
+extern template int launch_rows<2>(hipStream_t, RowsArgs &, const float *, int, int *, uint64_t *);
+extern template int launch_rows<4>(hipStream_t, RowsArgs &, const float *, int, int *, uint64_t *);
+extern template int launch_rows<8>(hipStream_t, RowsArgs &, const float *, int, int *, uint64_t *);
 
 static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_dev,
                    const void *packed1s_dev, const void *packed2s_dev, const float *levels_dev, const uint16_t *grid_idx_dev, float grid_lo,
@@ -1830,3 +1851,4 @@ extern "C" int zipml_sgd_status(void *stream, const void *workspace_dev, size_t 
     if (HIP_FAILED(hipStreamSynchronize(s))) return ZIPML_ELAUNCH;
     return st;
 }
+#endif   // ZIPML_SGD_BITS
