@@ -1,12 +1,12 @@
 // zipml_loss: F(x) = 1/(2n) sum_i (a_i^T x - b_i)^2  (Sec. 1 eq. (1) with the square loss; Sec. 2).
 //
-// Streaming, sync-free kernels: every workgroup reduces a range of samples to one fp64 partial,
-// a second one-block kernel adds the partials in a fixed order.
+// Streaming, sync-free kernels: every workgroup reduces a range of samples to one fp64 partial in
+// pinned host memory, and the call adds the partials in a fixed order.
 #include "zipml_device.h"
 #include "zipml_host.h"
 #include "zipml_mfma_ops.h"
 
-#include <stdlib.h>
+#include <mutex>
 
 namespace zipml {
 
@@ -50,145 +50,224 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_fp32(
     if (tid == 0) partial[blockIdx.x] = tot;
 }
 
-// Packed copy 2 (sample-major units): one sample per thread, feature groups in sequence.
-template <int BITS>
-__device__ __forceinline__ double loss_copy2_rows(const uint32_t *__restrict__ p2,
-                                                  const float *__restrict__ levels,
-                                                  const float *__restrict__ b,
-                                                  const float *__restrict__ x, int64_t n, int64_t d,
-                                                  int64_t n_pad, int64_t d32, int threads)
+// Launch before the packed copy-2 kernel, kLossPrepBlocks blocks: are the level tables evenly spaced (fp64
+// formula, rounded once; the same test as in the preparation of the SGD kernels) -- one flag per block --,
+// y_j = delta_j x_j, and per block the largest |y_j| and the sum of mid_j x_j.  (Every block of the main
+// kernel needs all of y; taking it from the ends of the level rows there, a cache line per feature, was
+// a quarter of its time at 4,096 features.)
+constexpr int kLossPrepBlocks = 64;
+struct LossPrep {
+    int even[kLossPrepBlocks];
+    float ymax[kLossPrepBlocks], midx[kLossPrepBlocks];
+};
+__global__ __launch_bounds__(256) void k_loss_prepare(const float *__restrict__ levels, const float *__restrict__ x,
+                                                      int64_t d, int K, float off, LossPrep *__restrict__ prep,
+                                                      float *__restrict__ y)
 {
-    constexpr int K = 1 << BITS;
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * threads + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * threads) {
-        float z = 0.0f;
-        for (int64_t g = 0; g < d32; ++g) {
-            uint32_t u[BITS];
-#pragma unroll
-            for (int q = 0; q < BITS; ++q) u[q] = p2[(g * n_pad + i) * BITS + q];
-#pragma unroll
-            for (int k = 0; k < 32; ++k) {
-                const int64_t j = g * 32 + k;
-                if (j < d) z = fmaf(levels[j * K + unit_code<BITS>(u, k)], x[j], z);
-            }
+    __shared__ float fmax_s[4], fsum_s[4];
+    int ok = 1;
+    if (K >= 4) {                                          // (two levels are always evenly spaced)
+        const int spf = K / 4;
+        const int64_t total = d * spf;
+        const int64_t per = (total + kLossPrepBlocks - 1) / kLossPrepBlocks;
+        const int64_t s_end = (blockIdx.x + 1) * per < total ? (blockIdx.x + 1) * per : total;
+        for (int64_t sg = blockIdx.x * per + threadIdx.x; sg < s_end; sg += 256) {
+            const int64_t j = sg / spf;
+            const int c0 = (int)(sg % spf) * 4;
+            const float *row = levels + j * K;
+            const double lo = (double)row[0], wdt = (double)row[K - 1] - lo;
+            const float4 v = *reinterpret_cast<const float4 *>(row + c0);
+            ok &= (v.x == (float)(lo + ((double)(c0 + 0) * wdt) / (double)(K - 1)));
+            ok &= (v.y == (float)(lo + ((double)(c0 + 1) * wdt) / (double)(K - 1)));
+            ok &= (v.z == (float)(lo + ((double)(c0 + 2) * wdt) / (double)(K - 1)));
+            ok &= (v.w == (float)(lo + ((double)(c0 + 3) * wdt) / (double)(K - 1)));
         }
-        const double r = (double)z - (double)b[i];
-        acc += r * r;
+    }
+    float ymax = 0.0f, cq = 0.0f;
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < d; j += (int64_t)kLossPrepBlocks * 256) {
+        const float lo = levels[j * K], hi = levels[j * K + K - 1];
+        const float dl = (float)(((double)hi - (double)lo) / (double)(K - 1));
+        const float xj = x[j], yj = dl * xj;
+        cq += (lo + off * dl) * xj;
+        ymax = fmaxf(ymax, fabsf(yj));
+        y[j] = yj;
+    }
+    ymax = wave_reduce_dpp(ymax, [](float u, float v) { return fmaxf(u, v); });
+    cq = wave_sum_dpp(cq);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & (kWave - 1)) == 0) { fmax_s[wave] = ymax; fsum_s[wave] = cq; }
+    ok = __syncthreads_and(ok);
+    if (threadIdx.x == 0) {
+        prep->even[blockIdx.x] = ok;
+        prep->ymax[blockIdx.x] = fmaxf(fmaxf(fmax_s[0], fmax_s[1]), fmaxf(fmax_s[2], fmax_s[3]));
+        prep->midx[blockIdx.x] = (fsum_s[0] + fsum_s[1]) + (fsum_s[2] + fsum_s[3]);
+    }
+}
+
+// The level tables of a chunk of features, multiplied by x, in LDS.  One look-up serves kPer features:
+// with at most 3 bits the sums T_j[c] + T_j'[c'] of two neighbouring features are tabled, so that a look-up
+// in 16 or 64 words -- words apart, so the lanes' gathers meet no bank conflicts -- takes the place of two,
+// one multiply-add each.  64 KiB of tables (512 features at 3 bits) leave room for two blocks per compute unit.
+// 131,072 x 4,096 codes of 3 bits (201 MB): 632 us a call with a look-up per code in the table in memory, 116 us
+// now, 98 of them the kernel; bound by the LDS gathers and the field extraction (three vector operations
+// and a gather per pair).
+template <int BITS> struct LossTable {
+    static constexpr int K = 1 << BITS;
+    static constexpr int kPer = BITS <= 3 ? 2 : 1;         // features per look-up
+    static constexpr int kRow = 1 << (BITS * kPer);        // entries of a look-up's table
+    static constexpr int kFeatures = 16384 / kRow * kPer < 512 ? 16384 / kRow * kPer : 512;   // per chunk
+    static constexpr size_t kTab = (size_t)kFeatures / kPer * kRow * 4;
+    static constexpr size_t kSingle = kPer == 2 ? (size_t)kFeatures * K * 4 : 0;   // the single tables, on the way
+    static constexpr size_t kBytes = kTab + kSingle;
+};
+
+// Packed copy 2 (sample-major units) through the tables.  A block takes `spb` samples (64 to 512, a power of
+// two), a thread one of them and every (512 / spb)-th feature group; the parts of a sample meet in LDS.
+constexpr int kLossPackedThreads = 512;
+template <int BITS>
+__device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ p2, const float *__restrict__ levels,
+                                                   const float *__restrict__ b, const float *__restrict__ x, int64_t n,
+                                                   int64_t d, int64_t n_pad, int spb, unsigned char *smem)
+{
+    using LT = LossTable<BITS>;
+    constexpr int K = LT::K, kPer = LT::kPer, kRow = LT::kRow, kT = kLossPackedThreads;
+    constexpr int kBatch = BITS <= 4 ? 4 : 2;              // units in use, and as many on the way
+    float *const tab = (float *)smem, *const one = (float *)(smem + LT::kTab);
+    float *const zs = (float *)smem;                       // [512 / spb][spb], after the last chunk
+    const int tid = threadIdx.x, splits = kT / spb;
+    const int smp = tid & (spb - 1), fs = tid / spb;       // (whole waves share fs)
+    double acc = 0.0;
+    for (int64_t T = blockIdx.x; T * spb < n; T += gridDim.x) {
+        const int64_t i = T * spb + smp, row = i < n_pad ? i : n_pad - 1;
+        float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int64_t c0 = 0; c0 < d; c0 += LT::kFeatures) {
+            const int nf = d - c0 < LT::kFeatures ? (int)(d - c0) : LT::kFeatures, nfp = (nf + 31) & ~31;
+            // the first units are requested before the tables are built, the next ones before a batch is used
+            const uint32_t *src = p2 + ((c0 / 32) * n_pad + row) * BITS;
+            const int ng = nfp / 32;
+            uint32_t u[kBatch][BITS], un[kBatch][BITS];
+            auto request = [&](int g0, uint32_t (&dst)[kBatch][BITS]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int m = 0; m < kBatch; ++m) {
+                    const int g = g0 + m * splits < ng ? g0 + m * splits : ng - 1;
+#pragma unroll
+                    for (int q = 0; q < BITS; ++q) dst[m][q] = __builtin_nontemporal_load(src + g * n_pad * BITS + q);
+                }
+            };
+            request(fs, u);
+            // tables (entries of padding features are zero)
+            float *const dst = kPer == 2 ? one : tab;
+            for (int e = tid; e < nfp * K; e += kT) {
+                const int j = e / K;
+                dst[e] = j < nf ? levels[(c0 + j) * K + e % K] * x[c0 + j] : 0.0f;
+            }
+            __syncthreads();
+            if constexpr (kPer == 2) {
+                for (int r = tid; r < nfp / 2 * K; r += kT) {
+                    const int p = r / K, hi = r % K;
+                    const float v = one[(2 * p + 1) * K + hi];
+#pragma unroll
+                    for (int q = 0; q < K; q += K < 4 ? K : 4) {
+                        if constexpr (K >= 4) {
+                            float4 t = *reinterpret_cast<const float4 *>(one + 2 * p * K + q);
+                            t.x += v; t.y += v; t.z += v; t.w += v;
+                            *reinterpret_cast<float4 *>(tab + p * kRow + hi * K + q) = t;
+                        } else {
+                            tab[p * kRow + hi * K + q] = one[2 * p * K + q] + v;
+                            tab[p * kRow + hi * K + q + 1] = one[2 * p * K + q + 1] + v;
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+            for (int g0 = fs; g0 < ng; g0 += kBatch * splits) {
+                request(g0 + kBatch * splits, un);
+#pragma unroll
+                for (int m = 0; m < kBatch; ++m) {
+                    const int g = g0 + m * splits;
+                    if (g < ng) {
+                        const unsigned char *t = (const unsigned char *)(tab + g * (32 / kPer) * kRow);
+#pragma unroll
+                        for (int k = 0; k < 32 / kPer; ++k) {
+                            constexpr int kField = BITS * kPer;
+                            const int bit = k * kField, wi = bit >> 5, sh = bit & 31;
+                            uint32_t at;                    // byte offset in the look-up's table
+                            if (sh + kField > 32) at = (__builtin_amdgcn_alignbit(u[m][wi + 1 < BITS ? wi + 1 : wi], u[m][wi], sh) << 2) & (4u * kRow - 4u);
+                            else at = (sh >= 2 ? u[m][wi] >> (sh - 2) : u[m][wi] << (2 - sh)) & (4u * kRow - 4u);
+                            z[k & 3] += *reinterpret_cast<const float *>(t + k * kRow * 4 + at);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < kBatch; ++m)
+#pragma unroll
+                    for (int q = 0; q < BITS; ++q) u[m][q] = un[m][q];
+            }
+            __syncthreads();
+        }
+        zs[fs * spb + smp] = (z[0] + z[1]) + (z[2] + z[3]);
+        __syncthreads();
+        if (tid < spb && i < n) {
+            double zt = 0.0;
+            for (int v = 0; v < splits; ++v) zt += (double)zs[v * spb + tid];
+            const double r = zt - (double)b[i];
+            acc += r * r;
+        }
+        __syncthreads();
     }
     return acc;
 }
 
+// Packed copy 2.  Evenly spaced levels go to the matrix cores: a value is mid_j + (code - off) delta_j, so
+// a_i^T x = sum_j mid_j x_j + sum_j (code_ij - off) y_j  with y_j = delta_j x_j.  y goes to 32-bit fixed
+// point in four signed base-256 digits kept in LDS; a workgroup takes tiles of 64 samples, its eight waves
+// split the 64-feature blocks (one v_mfma_i32_16x16x64_i8 per 16 samples x 64 features, four sample tiles
+// sharing one accumulator as in the SGD kernels), the partial sums meet in LDS and wave 0 squares the
+// residuals.  Exact integer sums; the only rounding before the residual is y_j -> fixed point (2^-29 of max
+// |y|).  Other level tables (the flags of k_loss_prepare say so; all blocks alike), and problems whose
+// digits do not fit in LDS (NKB == 0), go through loss_copy2_table.
 template <int BITS>
-__global__ __launch_bounds__(kLossThreads) void k_loss_copy2(
+__global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     const uint32_t *__restrict__ p2, const float *__restrict__ levels, const float *__restrict__ b,
-    const float *__restrict__ x, int64_t n, int64_t d, int64_t n_pad, int64_t d32,
-    double *__restrict__ partial)
+    const float *__restrict__ x, int64_t n, int64_t d, int64_t n_pad, int64_t d32, int NKB, int spb,
+    const LossPrep *__restrict__ prep, const float *__restrict__ y, double *__restrict__ partial)
 {
-    __shared__ double scratch[kLossThreads / kWave + 1];
-    const double acc = loss_copy2_rows<BITS>(p2, levels, b, x, n, d, n_pad, d32, kLossThreads);
-    const double tot = block_sum<double>(acc, scratch);
-    if (threadIdx.x == 0) partial[blockIdx.x] = tot;
-}
-
-// Are the level tables evenly spaced (fp64 formula, rounded once)?  One flag per block; K a
-// multiple of 4.  (The same test as in the preparation of the SGD kernels.)
-constexpr int kLossEvenBlocks = 64;
-__global__ __launch_bounds__(256) void k_loss_even(const float *__restrict__ levels, int64_t d, int K,
-                                                   int *__restrict__ even)
-{
-    const int spf = K / 4;
-    const int64_t total = d * spf;
-    const int64_t per = (total + kLossEvenBlocks - 1) / kLossEvenBlocks;
-    const int64_t s_end = (blockIdx.x + 1) * per < total ? (blockIdx.x + 1) * per : total;
-    int ok = 1;
-    for (int64_t sg = blockIdx.x * per + threadIdx.x; sg < s_end; sg += 256) {
-        const int64_t j = sg / spf;
-        const int c0 = (int)(sg % spf) * 4;
-        const float *row = levels + j * K;
-        const double lo = (double)row[0], wdt = (double)row[K - 1] - lo;
-        const float4 v = *reinterpret_cast<const float4 *>(row + c0);
-        ok &= (v.x == (float)(lo + ((double)(c0 + 0) * wdt) / (double)(K - 1)));
-        ok &= (v.y == (float)(lo + ((double)(c0 + 1) * wdt) / (double)(K - 1)));
-        ok &= (v.z == (float)(lo + ((double)(c0 + 2) * wdt) / (double)(K - 1)));
-        ok &= (v.w == (float)(lo + ((double)(c0 + 3) * wdt) / (double)(K - 1)));
-    }
-    ok = __syncthreads_and(ok);
-    if (threadIdx.x == 0) even[blockIdx.x] = ok;
-}
-
-// Packed copy 2 with evenly spaced 2-, 4- or 8-bit levels, on the matrix cores: a value is
-// mid_j + (code - off) delta_j, so  a_i^T x = sum_j mid_j x_j + sum_j (code_ij - off) y_j  with
-// y_j = delta_j x_j.  y goes to 32-bit fixed point in four signed base-256 digits kept in LDS; a
-// workgroup takes tiles of 64 samples, its eight waves split the 64-feature blocks (one
-// v_mfma_i32_16x16x64_i8 per 16 samples x 64 features, four sample tiles sharing one accumulator
-// as in the SGD kernels), the partial sums meet in LDS and wave 0 squares the residuals.  Exact
-// integer sums; the only rounding before the residual is y_j -> fixed point (2^-29 of max |y|).
-// If the tables turn out not to be evenly spaced (flags from k_loss_even) the kernel takes the
-// one-sample-per-thread path above.
-constexpr int kLossMfmaThreads = 512;
-template <int BITS>
-__global__ __launch_bounds__(kLossMfmaThreads) void k_loss_copy2_mfma(
-    const uint32_t *__restrict__ p2, const float *__restrict__ levels, const float *__restrict__ b,
-    const float *__restrict__ x, int64_t n, int64_t d, int64_t n_pad, int64_t d32, int NKB,
-    const int *__restrict__ even, double *__restrict__ partial)
-{
-    constexpr int K = 1 << BITS, HW = BITS / 2, kW = kLossMfmaThreads / kWave;
-    constexpr float kOff = BITS == 8 ? 128.0f : 0.0f;
+    constexpr int HW = kOpDwords<BITS>, kW = kLossPackedThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double scratch[kW + 1];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int n16 = lane & 15, q4 = lane >> 4;
-    int ok_all = 1;
-    if (tid < kLossEvenBlocks) ok_all = even[tid];
+    int ok_all = NKB > 0;
+    float ymax = 0.0f, cq = 0.0f;
+    if (NKB > 0) {
+        ok_all = prep->even[lane];                         // (kLossPrepBlocks == kWave)
+        ymax = wave_reduce_dpp(prep->ymax[lane], [](float u, float v) { return fmaxf(u, v); });
+        cq = wave_sum_dpp(prep->midx[lane]);
+    }
     if (!__syncthreads_and(ok_all)) {
-        const double acc = loss_copy2_rows<BITS>(p2, levels, b, x, n, d, n_pad, d32, kLossMfmaThreads);
+        const double acc = loss_copy2_table<BITS>(p2, levels, b, x, n, d, n_pad, spb, smem);
         const double tot = block_sum<double>(acc, scratch);
         if (tid == 0) partial[blockIdx.x] = tot;
         return;
     }
     const int nfeat = NKB * 64;
     int8_t *const ydig = (int8_t *)smem;                                  // [NKB][4 digits][4 q][16]
-    float *const ytmp = (float *)(smem + (size_t)NKB * 256);              // [nfeat] y_j until the scale is known
-    long long *const zpart = (long long *)(smem + (size_t)NKB * 512);     // [kW][64]
-    float *const red = (float *)(smem + (size_t)NKB * 512 + kW * 64 * 8); // [2 kW]
-    int8_t *const zeros = (int8_t *)(red + 2 * kW);                       // [16]
+    long long *const zpart = (long long *)(smem + (size_t)NKB * 256);     // [kW][64]
+    int8_t *const zeros = (int8_t *)(smem + (size_t)NKB * 256 + kW * 64 * 8);   // [16]
     if (tid < 4) reinterpret_cast<int *>(zeros)[tid] = 0;
-
-    // ---- digits of y_j = delta_j x_j and sum_j mid_j x_j (every workgroup: the same numbers)
-    float ymax = 0.0f, cqp = 0.0f;
-    for (int j = tid; j < nfeat; j += kLossMfmaThreads) {
-        float y = 0.0f;
-        if (j < d) {
-            const float lo = levels[(size_t)j * K], hi = levels[(size_t)j * K + K - 1];
-            const float dl = (float)(((double)hi - (double)lo) / (double)(K - 1));
-            const float xj = x[j];
-            y = dl * xj;
-            cqp += (lo + kOff * dl) * xj;
-        }
-        ymax = fmaxf(ymax, fabsf(y));
-        ytmp[j] = y;
-    }
-    ymax = wave_reduce_dpp(ymax, [](float u, float v) { return fmaxf(u, v); });
-    cqp = wave_sum_dpp(cqp);
-    if (lane == 0) { red[wave] = ymax; red[kW + wave] = cqp; }
-    __syncthreads();
-    float cq = 0.0f;
-    ymax = 0.0f;
-#pragma unroll
-    for (int v = 0; v < kW; ++v) { ymax = fmaxf(ymax, red[v]); cq += red[kW + v]; }
     const int ky = scale_exponent(ymax, 29);
-    for (int j = tid; j < nfeat; j += kLossMfmaThreads) {
+    for (int j = tid; j < nfeat; j += kLossPackedThreads) {
         int half, byte;
         code_slot<BITS>(j & 31, half, byte);
         const int pos = (2 * ((j >> 5) & 1) + half) * 16 + byte;
-        store_digits(ydig + (j >> 6) * 256 + pos, signed_digits(__float2int_rn(ldexpf(ytmp[j], ky))));
+        store_digits(ydig + (j >> 6) * 256 + pos, signed_digits(__float2int_rn(ldexpf(j < d ? y[j] : 0.0f, ky))));
     }
     __syncthreads();
 
     // ---- tiles of 64 samples
     const int dig_off = (n16 & 3) * 64 + q4 * 16, slot_of = n16 >> 2;
     const int zero_off = (int)(zeros - ydig);
+    const uint32_t shift = op_shift<BITS>(q4 & 1);
     const int64_t NT = n_pad / 64;
     double acc = 0.0;
     for (int64_t T = blockIdx.x; T < NT; T += gridDim.x) {
@@ -203,14 +282,14 @@ __global__ __launch_bounds__(kLossMfmaThreads) void k_loss_copy2_mfma(
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) {
                 const uint32_t *q = static_cast<const uint32_t *>(__builtin_assume_aligned(
-                    p2 + (g * n_pad + row0 + 16 * sl + n16) * BITS + (q4 & 1) * HW, 4 * HW));
+                    p2 + (g * n_pad + row0 + 16 * sl + n16) * BITS + (q4 & 1) * kOpStride<BITS>, kOpAlign<BITS>));
 #pragma unroll
                 for (int h = 0; h < HW; ++h) w[sl][h] = __builtin_nontemporal_load(q + h);
             }
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) {
                 const v4i ad = *reinterpret_cast<const v4i *>(ydig + (slot_of == sl ? kb * 256 + dig_off : zero_off));
-                c = __builtin_amdgcn_mfma_i32_16x16x64_i8(ad, expand_codes<BITS>(w[sl]), c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_i32_16x16x64_i8(ad, expand_codes<BITS>(w[sl], shift), c, 0, 0, 0);
             }
         }
         zpart[wave * 64 + lane] = combine_digits(c);      // lane = sample of the tile
@@ -230,98 +309,169 @@ __global__ __launch_bounds__(kLossMfmaThreads) void k_loss_copy2_mfma(
     if (tid == 0) partial[blockIdx.x] = tot;
 }
 
-// LDS of k_loss_copy2_mfma.
+// LDS of k_loss_copy2's matrix-core path.
 inline size_t loss_mfma_lds_bytes(int NKB)
 {
-    return (size_t)NKB * 512 + (kLossMfmaThreads / kWave) * 64 * 8 + 2 * (kLossMfmaThreads / kWave) * 4 + 16;
+    return (size_t)NKB * 256 + (kLossPackedThreads / kWave) * 64 * 8 + 16;
 }
 
-// Packed copy 1 (feature-major units): one workgroup per group of 32 samples; threads stride over
-// the features and keep 32 partial dot products each, which are then added across the block.
+// Packed copy 1 (feature-major units: one feature x 32 samples).  A lane takes one feature of a group of 64
+// (or of 32, two sample groups to a wave, where the problem has no more) and keeps the 32 partial dot products
+// of its sample group in registers through all its features; the level tables of a chunk of features,
+// multiplied by x, are in LDS with their rows K + 1 words apart (the lanes look up different rows).  At
+// the end the 32 sums of a lane are added over the lanes by halving: a lane hands half of its sums to the lane
+// it is paired with and takes the other half of that lane's, 31 exchanges instead of 32 for each of
+// five or six steps.  A block's eight waves take `sgb` (1 to 8) sample groups, and share the features of
+// one where there are fewer groups than that.
+constexpr int kLoss1Threads = 512;
+template <int BITS> constexpr int kLoss1Features = 16384 / ((1 << BITS) + 1) / 64 * 64 < 512 ? 16384 / ((1 << BITS) + 1) / 64 * 64 : 512;
+template <int BITS> constexpr int kLoss1Chunk = kLoss1Features<BITS> < 64 ? 64 : kLoss1Features<BITS>;
+template <int BITS> constexpr size_t kLoss1Lds = (size_t)kLoss1Chunk<BITS> * ((1 << BITS) + 1) * 4;
 template <int BITS>
-__global__ __launch_bounds__(kLossThreads) void k_loss_copy1(
+__global__ __launch_bounds__(kLoss1Threads) void k_loss_copy1(
     const uint32_t *__restrict__ p1, const float *__restrict__ levels, const float *__restrict__ b,
-    const float *__restrict__ x, int64_t n, int64_t d, int64_t n32, double *__restrict__ partial)
+    const float *__restrict__ x, int64_t n, int64_t d, int64_t n32, int d32, int sgb, double *__restrict__ partial)
 {
-    constexpr int K = 1 << BITS;
-    __shared__ float zs[32];
-    __shared__ double scratch[kLossThreads / kWave + 1];
+    constexpr int K = 1 << BITS, kW = kLoss1Threads / kWave, FC = kLoss1Chunk<BITS>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *const tab = (float *)smem;
+    __shared__ double scratch[kW + 1];
+    __shared__ float zs[kW][64];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int lpg = d32 == 1 ? 32 : 64;                    // lanes per sample group
+    const int gpw = kWave / lpg;                           // sample groups per wave
+    const int sub = lane / lpg, fl = lane & (lpg - 1);
+    const int splits = kW / sgb, slot = wave % sgb, fs = wave / sgb;
     double acc = 0.0;
-    for (int64_t rg = blockIdx.x; rg < n32; rg += gridDim.x) {
+    for (int64_t T = blockIdx.x; T * sgb * gpw < n32; T += gridDim.x) {
+        const int64_t rg = (T * sgb + slot) * gpw + sub, rgc = rg < n32 ? rg : n32 - 1;
         float z[32];
 #pragma unroll
         for (int k = 0; k < 32; ++k) z[k] = 0.0f;
-        for (int64_t j = threadIdx.x; j < d; j += kLossThreads) {
-            const int64_t g = j / 32, cin = j % 32;
-            uint32_t u[BITS];
+        for (int64_t c0 = 0; c0 < d; c0 += FC) {
+            const int nf = d - c0 < FC ? (int)(d - c0) : FC, nfp = (nf + 63) & ~63;
+            for (int e = tid; e < nfp * K; e += kLoss1Threads) {
+                const int j = e / K;
+                tab[e + j] = j < nf ? levels[(c0 + j) * K + e % K] * x[c0 + j] : 0.0f;
+            }
+            __syncthreads();
+            for (int f0 = fs * lpg; f0 < nfp; f0 += splits * lpg) {
+                const int f = f0 + fl;
+                const int64_t j = c0 + f, g = j / 32 < d32 ? j / 32 : 0;   // (a padding group: its table is zero)
+                const uint32_t *src = p1 + ((g * n32 + rgc) * 32 + (int)(j & 31)) * BITS;
+                uint32_t u[BITS];
 #pragma unroll
-            for (int q = 0; q < BITS; ++q) u[q] = p1[((g * n32 + rg) * 32 + cin) * BITS + q];
-            const float xj = x[j];
+                for (int q = 0; q < BITS; ++q) u[q] = __builtin_nontemporal_load(src + q);
+                const float *t = tab + f * (K + 1);
 #pragma unroll
-            for (int k = 0; k < 32; ++k) z[k] = fmaf(levels[j * K + unit_code<BITS>(u, k)], xj, z[k]);
+                for (int k = 0; k < 32; ++k) z[k] += t[unit_code<BITS>(u, k)];
+            }
+            __syncthreads();
         }
-        if (threadIdx.x < 32) zs[threadIdx.x] = 0.0f;
-        __syncthreads();
+        {
+            if (lpg == 64) {
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const float s = wave_sum(z[k]);
-            if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&zs[k], s);
+                for (int k = 0; k < 32; ++k) z[k] += __shfl_xor(z[k], 32, kWave);
+            }
+#pragma unroll
+            for (int h = 16; h >= 1; h >>= 1) {
+                const bool up = (lane & h) != 0;
+#pragma unroll
+                for (int k = 0; k < h; ++k) {
+                    const float mine = up ? z[k + h] : z[k], give = up ? z[k] : z[k + h];
+                    z[k] = mine + __shfl_xor(give, h, kWave);
+                }
+            }
+            zs[wave][lane] = z[0];                         // of sample lane & 31 of the group
         }
         __syncthreads();
-        if (threadIdx.x < 32) {
-            const int64_t i = rg * 32 + threadIdx.x;
-            if (i < n) {
-                const double r = (double)zs[threadIdx.x] - (double)b[i];
+        // one thread per sample: slot tid / 64, in it sub group (tid / 32) % gpw
+        if (tid < sgb * kWave) {
+            const int sl = tid >> 6, ln = tid & (kWave - 1);
+            const int64_t g = (T * sgb + sl) * gpw + ln / lpg, i = g * 32 + (ln & 31);
+            if (ln % lpg < 32 && g < n32 && i < n) {
+                double zt = 0.0;
+                for (int v = 0; v < splits; ++v) zt += (double)zs[v * sgb + sl][ln];
+                const double r = zt - (double)b[i];
                 acc += r * r;
             }
         }
         __syncthreads();
     }
     const double tot = block_sum<double>(acc, scratch);
-    if (threadIdx.x == 0) partial[blockIdx.x] = tot;
+    if (tid == 0) partial[blockIdx.x] = tot;
 }
 
-__global__ void k_loss_final(const double *__restrict__ partial, int count, double scale,
-                             double *__restrict__ out)
-{
-    __shared__ double scratch[kLossThreads / kWave + 1];
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < count; i += blockDim.x) acc += partial[i];
-    const double tot = block_sum<double>(acc, scratch);
-    if (threadIdx.x == 0) out[0] = tot * scale;
-}
+// Pinned host memory for the blocks' partial sums: the kernels store them there directly and the call adds
+// them up after it has waited for the stream, in place of a second kernel and a copy back (a loss over
+// 4,096 x 64 values: 31 -> 19 us).  A call takes a buffer for its duration; at most kMax of them (16 KiB
+// each) are kept for later calls, of any thread and stream.
+class LossBuffer {
+public:
+    LossBuffer()
+    {
+        {
+            std::lock_guard<std::mutex> lock(mutex());
+            if (count() > 0) p = kept()[--count()];
+        }
+        if (!p && HIP_FAILED(hipHostMalloc((void **)&p, kLossMaxBlocks * sizeof(double), hipHostMallocPortable | hipHostMallocMapped)))
+            p = nullptr;
+    }
+    ~LossBuffer()
+    {
+        if (!p) return;
+        {
+            std::lock_guard<std::mutex> lock(mutex());
+            if (count() < kMax) { kept()[count()++] = p; return; }
+        }
+        (void)hipHostFree(p);
+    }
+    LossBuffer(const LossBuffer &) = delete;
+    LossBuffer &operator=(const LossBuffer &) = delete;
+    double *p = nullptr;
+
+private:
+    static constexpr int kMax = 8;
+    static std::mutex &mutex() { static std::mutex m; return m; }
+    static double **kept() { static double *k[kMax]; return k; }
+    static int &count() { static int c = 0; return c; }
+};
 
 template <int BITS>
-static void launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const Layout &lay,
-                               const float *levels, const float *b, const float *x, int blocks,
-                               double *partial)
+static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const Layout &lay, const float *levels,
+                              const float *b, const float *x, LossPrep *prep, int cus, int lds_limit, double *partial)
 {
-    if (copy == 2)
-        hipLaunchKernelGGL(k_loss_copy2<BITS>, dim3(blocks), dim3(kLossThreads), 0, s, p, levels, b,
-                           x, lay.n, lay.d, lay.n_pad, lay.d32, partial);
-    else
-        hipLaunchKernelGGL(k_loss_copy1<BITS>, dim3(blocks), dim3(kLossThreads), 0, s, p, levels, b,
-                           x, lay.n, lay.d, lay.n32, partial);
-}
-
-// Copy 2 on the matrix cores where the code width allows it (the kernel itself falls back to the
-// one-sample-per-thread path if the tables are not evenly spaced).  Returns the number of blocks,
-// 0 if this path does not apply.
-template <int BITS>
-static int launch_loss_mfma(hipStream_t s, const uint32_t *p, const Layout &lay, const float *levels,
-                            const float *b, const float *x, double *partial, int *even, int lds_limit)
-{
-    const int NKB = (int)((lay.d32 + 1) / 2);
-    const size_t shmem = loss_mfma_lds_bytes(NKB);
-    if (shmem > (size_t)lds_limit) return 0;
-    const void *kern = (const void *)k_loss_copy2_mfma<BITS>;
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem) != hipSuccess)
-        return 0;
+    if (copy == 1) {
+        const int gpw = lay.d32 == 1 ? 2 : 1;
+        // as many sample groups per block as leave two blocks per compute unit
+        int sgb = 8;
+        while (sgb > 1 && (lay.n32 + sgb * gpw - 1) / (sgb * gpw) < 2 * cus) sgb >>= 1;
+        const int64_t tiles = (lay.n32 + sgb * gpw - 1) / (sgb * gpw);
+        const int blocks = (int)(tiles < kLossMaxBlocks ? tiles : kLossMaxBlocks);
+        if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy1<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)kLoss1Lds<BITS>)))
+            return ZIPML_ELAUNCH;
+        hipLaunchKernelGGL(k_loss_copy1<BITS>, dim3(blocks), dim3(kLoss1Threads), kLoss1Lds<BITS>, s, p, levels, b, x,
+                           lay.n, lay.d, lay.n32, (int)lay.d32, sgb, partial);
+        return blocks;
+    }
+    int NKB = (int)((lay.d32 + 1) / 2);
+    if (!prep || loss_mfma_lds_bytes(NKB) > (size_t)lds_limit) NKB = 0;   // through the tables, whatever the levels
+    size_t shmem = LossTable<BITS>::kBytes < 4096 ? 4096 : LossTable<BITS>::kBytes;
+    if (NKB > 0 && loss_mfma_lds_bytes(NKB) > shmem) shmem = loss_mfma_lds_bytes(NKB);
+    if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy2<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)))
+        return ZIPML_ELAUNCH;
+    // samples per block on the table path: as many as leave two blocks per compute unit
+    int spb = kLossPackedThreads;
+    while (spb > 64 && (lay.n + spb - 1) / spb < 2 * cus) spb >>= 1;
     const int64_t NT = lay.n_pad / 64;
     const int blocks = (int)(NT < 1024 ? NT : 1024);
-    hipLaunchKernelGGL(k_loss_even, dim3(kLossEvenBlocks), dim3(256), 0, s, levels, lay.d, 1 << BITS, even);
-    hipLaunchKernelGGL(k_loss_copy2_mfma<BITS>, dim3(blocks), dim3(kLossMfmaThreads), shmem, s, p, levels,
-                       b, x, lay.n, lay.d, lay.n_pad, lay.d32, NKB, even, partial);
+    float *y = (float *)(prep + 1);
+    if (NKB > 0)
+        hipLaunchKernelGGL(k_loss_prepare, dim3(kLossPrepBlocks), dim3(256), 0, s, levels, x, lay.d, 1 << BITS,
+                           BITS == 8 ? 128.0f : 0.0f, prep, y);
+    hipLaunchKernelGGL(k_loss_copy2<BITS>, dim3(blocks), dim3(kLossPackedThreads), shmem, s, p, levels, b, x, lay.n,
+                       lay.d, lay.n_pad, lay.d32, NKB, spb, prep, y, partial);
     return blocks;
 }
 
@@ -384,13 +534,18 @@ extern "C" int zipml_loss(void *stream, const float *A_dev, int64_t lda, const v
     if (!workspace_dev || workspace_bytes < (size_t)(kLossMaxBlocks + 1) * sizeof(double))
         return ZIPML_EWORKSPACE;
     if (!aligned16(workspace_dev) || !aligned16(x_dev)) return ZIPML_EALIGN;
-    hipStream_t s = entry_stream(stream);
-    double *partial = (double *)workspace_dev;
-    double *out = partial + kLossMaxBlocks;
-    int blocks = 0;
     if (A_dev) {
         if (lda < d) return ZIPML_EINVAL;
         if (reinterpret_cast<uintptr_t>(A_dev) & 3u) return ZIPML_EALIGN;
+    } else {
+        if (!packed_dev || !levels_dev || !valid_bits(bits) || (copy != 1 && copy != 2)) return ZIPML_EINVAL;
+        if (!aligned16(packed_dev) || !aligned16(levels_dev)) return ZIPML_EALIGN;
+    }
+    hipStream_t s = entry_stream(stream);
+    LossBuffer sums;
+    if (!sums.p) return ZIPML_ELAUNCH;
+    int blocks = 0;
+    if (A_dev) {
         int lpr = 1;
         while (lpr < 64 && lpr * 4 < d) lpr <<= 1;
         const int vec_ok = (lda % 4 == 0) && (d % 4 == 0) && aligned16(A_dev);
@@ -398,52 +553,30 @@ extern "C" int zipml_loss(void *stream, const float *A_dev, int64_t lda, const v
         blocks = (int)((n + rows_per_block - 1) / rows_per_block);
         if (blocks > kLossMaxBlocks) blocks = kLossMaxBlocks;
         hipLaunchKernelGGL(k_loss_fp32, dim3(blocks), dim3(kLossThreads), 0, s, A_dev, lda, b_dev,
-                           x_dev, n, d, lpr, vec_ok, partial);
+                           x_dev, n, d, lpr, vec_ok, sums.p);
     } else {
-        if (!packed_dev || !levels_dev || !valid_bits(bits) || (copy != 1 && copy != 2))
-            return ZIPML_EINVAL;
-        if (!aligned16(packed_dev) || !aligned16(levels_dev)) return ZIPML_EALIGN;
         const Layout lay = make_layout(n, d, bits);
         const uint32_t *p = (const uint32_t *)packed_dev;
-        // copy 2, 2/4/8 bits: matrix-core kernel (needs room for its flags behind the partials)
-        const size_t flags_at = (size_t)(kLossMaxBlocks + 1) * sizeof(double);
-        if (copy == 2 && (bits == 2 || bits == 4 || bits == 8) &&
-            workspace_bytes >= flags_at + kLossEvenBlocks * sizeof(int) && knob(ZIPML_KNOB_NO_MATRIX_CORES) <= 0) {
-            int dev = 0, lds = 0;
-            if (hipGetDevice(&dev) == hipSuccess &&
-                hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) {
-                int *even = (int *)((unsigned char *)workspace_dev + flags_at);
-                blocks = bits == 2 ? launch_loss_mfma<2>(s, p, lay, levels_dev, b_dev, x_dev, partial, even, lds)
-                       : bits == 4 ? launch_loss_mfma<4>(s, p, lay, levels_dev, b_dev, x_dev, partial, even, lds)
-                                   : launch_loss_mfma<8>(s, p, lay, levels_dev, b_dev, x_dev, partial, even, lds);
-            }
+        int dev = 0, cus = 0, lds = 0;
+        if (HIP_FAILED(hipGetDevice(&dev)) ||
+            HIP_FAILED(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) ||
+            HIP_FAILED(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)))
+            return ZIPML_ELAUNCH;
+        // (the matrix-core path needs room for the preparation's results)
+        LossPrep *prep = workspace_bytes >= sizeof(LossPrep) + (size_t)d * 4 && knob(ZIPML_KNOB_NO_MATRIX_CORES) <= 0
+                             ? (LossPrep *)workspace_dev : nullptr;
+#define ZIPML_LOSS(B) case B: blocks = launch_loss_packed<B>(s, p, copy, lay, levels_dev, b_dev, x_dev, prep, cus, lds, sums.p); break
+        switch (bits) {
+            ZIPML_LOSS(1); ZIPML_LOSS(2); ZIPML_LOSS(3); ZIPML_LOSS(4);
+            ZIPML_LOSS(5); ZIPML_LOSS(6); ZIPML_LOSS(7); ZIPML_LOSS(8);
         }
-        const bool launched = blocks > 0;
-        if (launched) {
-            // (the matrix-core kernel has been launched above)
-        } else if (copy == 2) {
-            blocks = (int)((n + kLossThreads - 1) / kLossThreads);
-            if (blocks > kLossMaxBlocks) blocks = kLossMaxBlocks;
-        } else {
-            blocks = (int)(lay.n32 > kLossMaxBlocks ? kLossMaxBlocks : lay.n32);
-        }
-        if (!launched) switch (bits) {
-            case 1: launch_loss_packed<1>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 2: launch_loss_packed<2>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 3: launch_loss_packed<3>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 4: launch_loss_packed<4>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 5: launch_loss_packed<5>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 6: launch_loss_packed<6>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 7: launch_loss_packed<7>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-            case 8: launch_loss_packed<8>(s, p, copy, lay, levels_dev, b_dev, x_dev, blocks, partial); break;
-        }
+#undef ZIPML_LOSS
+        if (blocks < 0) return blocks;
     }
-    if (HIP_FAILED(hipGetLastError())) return ZIPML_ELAUNCH;
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, s, partial, blocks,
-                       1.0 / (2.0 * (double)n), out);
-    if (HIP_FAILED(hipGetLastError())) return ZIPML_ELAUNCH;
-    if (hipMemcpyAsync(loss_host, out, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess)
-        return ZIPML_ELAUNCH;
-    if (hipStreamSynchronize(s) != hipSuccess) return ZIPML_ELAUNCH;
+    const bool launched = !HIP_FAILED(hipGetLastError());
+    if (HIP_FAILED(hipStreamSynchronize(s)) || !launched) return ZIPML_ELAUNCH;
+    double tot = 0.0;
+    for (int i = 0; i < blocks; ++i) tot += sums.p[i];
+    *loss_host = tot / (2.0 * (double)n);
     return ZIPML_OK;
 }

@@ -4,8 +4,8 @@
 // Operand layout of the instruction (checked against a host reference on the device):
 //   A: lane l holds row l%16, k = 16*(l/16) .. +15 (16 bytes);  B: lane l holds column l%16, same k;
 //   C: lane l holds column l%16, rows 4*(l/16) .. +3.
-// A lane's 16 code bytes come from 16*BITS/8 packed bytes; code_slot() says which byte a code of
-// the packed unit lands in, and the digit operands are laid out in LDS with the same map.
+// A lane's 16 codes are half a packed unit; code_slot() says which half and which byte of the operand
+// a code of the unit lands in, and the digit operands are laid out in LDS with the same map.
 #pragma once
 #include "zipml_device.h"
 
@@ -15,27 +15,43 @@ namespace zipml {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
+// The dwords of a unit that hold a half's codes: kOpDwords<BITS> of them from dword h * kOpStride<BITS> on.
+// Odd widths: half 1 begins 16 bits into its first dword (1 bit: both halves read the same dword).
+template <int BITS> constexpr int kOpDwords = (BITS + 1) / 2;
+template <int BITS> constexpr int kOpStride = BITS / 2;
+// the alignment of such an operand in bytes: the largest power of two in the stride, at most 16
+template <int BITS> constexpr int kOpAlign = BITS == 8 ? 16 : BITS == 4 ? 8 : 4;
+// expand_codes' shift for half h
+template <int BITS>
+__device__ __forceinline__ uint32_t op_shift(int h)
+{
+    return BITS == 1 ? 4u * (uint32_t)h : (BITS & 1) ? 16u * (uint32_t)h : 0u;
+}
+
 // Code f (0..31) of a packed unit -> (half: which lane operand of 16 codes, byte inside it).
 template <int BITS>
 __device__ __forceinline__ void code_slot(int f, int &half, int &byte)
 {
-    if (BITS == 8) {            // 4 dwords per half, code = 16*half + byte
-        half = f >> 4;
-        byte = f & 15;
-    } else if (BITS == 4) {     // packed dword pd holds codes 8pd..8pd+7; low nibbles -> one operand
+    if (BITS == 4) {            // packed dword pd holds codes 8pd..8pd+7; low nibbles -> one operand
         const int pd = f >> 3, e = f & 7;    // dword, high nibbles -> the next
         half = pd >> 1;
         byte = (2 * (pd & 1) + (e & 1)) * 4 + (e >> 1);
-    } else {                    // BITS == 2: one packed dword per half; operand dword D = (p >> 2D) & 0x03..
+    } else if (BITS == 2) {     // one packed dword per half; operand dword D = (p >> 2D) & 0x03..
         const int e = f & 15;
         half = f >> 4;
         byte = (e & 3) * 4 + (e >> 2);
+    } else if (BITS == 1) {     // one dword for both halves; operand dword D of half h = (p >> (4h + D)) & 0x01..
+        half = (f >> 2) & 1;
+        byte = (f & 3) * 4 + (f >> 3);
+    } else {                    // in order
+        half = f >> 4;
+        byte = f & 15;
     }
 }
 
-// 16 packed codes (BITS/2 dwords) -> 16 signed bytes (code - off).
+// The 16 codes of a half -> 16 signed bytes (code - off; off = 128 at 8 bits, else 0).  shift: op_shift<BITS>(half).
 template <int BITS>
-__device__ __forceinline__ v4i expand_codes(const uint32_t (&p)[BITS / 2])
+__device__ __forceinline__ v4i expand_codes(const uint32_t (&p)[kOpDwords<BITS>], uint32_t shift = 0)
 {
     v4i r;
     if constexpr (BITS == 8) {
@@ -48,11 +64,36 @@ __device__ __forceinline__ v4i expand_codes(const uint32_t (&p)[BITS / 2])
         r[1] = (int)((p[0] >> 4) & 0x0F0F0F0Fu);
         r[2] = (int)(p[1] & 0x0F0F0F0Fu);
         r[3] = (int)((p[1] >> 4) & 0x0F0F0F0Fu);
-    } else {
+    } else if constexpr (BITS == 2) {
         r[0] = (int)(p[0] & 0x03030303u);
         r[1] = (int)((p[0] >> 2) & 0x03030303u);
         r[2] = (int)((p[0] >> 4) & 0x03030303u);
         r[3] = (int)((p[0] >> 6) & 0x03030303u);
+    } else if constexpr (BITS == 1) {
+        const uint32_t q = p[0] >> shift;
+        r[0] = (int)(q & 0x01010101u);
+        r[1] = (int)((q >> 1) & 0x01010101u);
+        r[2] = (int)((q >> 2) & 0x01010101u);
+        r[3] = (int)((q >> 3) & 0x01010101u);
+    } else {
+        // Four codes of b bits at a time.  x: the 32 bits from the first of them on; t: codes 0 and 1 at
+        // the foot of the low half-word, 2 and 3 of the high one (what lies above them is cut off by
+        // the masks); then the upper code of each pair moves up to its byte.  Some 1.5 operations a code.
+        constexpr int N = kOpDwords<BITS>;
+        constexpr uint32_t kLow = ((1u << BITS) - 1u) * 0x00010001u;
+        uint32_t q[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            q[k] = (BITS & 1) ? __builtin_amdgcn_alignbit(k + 1 < N ? p[k + 1] : 0u, p[k], shift) : p[k];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int bit = 4 * BITS * m, wi = bit >> 5, sh = bit & 31;
+            const uint32_t x = sh == 0 ? q[wi]
+                             : sh + 4 * BITS <= 32 ? q[wi] >> sh
+                                                   : __builtin_amdgcn_alignbit(q[wi + 1 < N ? wi + 1 : wi], q[wi], sh);
+            const uint32_t t = (x & 0x0000FFFFu) | ((x << (16 - 2 * BITS)) & 0xFFFF0000u);
+            r[m] = (int)((t & kLow) | ((t << (8 - BITS)) & (kLow << 8)));
+        }
     }
     return r;
 }

@@ -46,7 +46,7 @@ namespace zipml {
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kMaxUpt = 4;                        // units per thread and pass that fit in registers
-constexpr uint32_t kSpinLimit = 1u << 22;         // default bound of a wait: a lost workgroup ends in ZIPML_ETIMEOUT
+[[maybe_unused]] constexpr uint32_t kSpinLimit = 1u << 22;         // default bound of a wait: a lost workgroup ends in ZIPML_ETIMEOUT
 
 // Exchange word: [63:54] arrival count, [53:0] sum of (value + kBias) over the arrived workgroups.
 // |value| < 2^44 for every contribution, so the low field never carries into the count.

@@ -114,13 +114,13 @@ def _check(code: int, where: str) -> None:
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
     import torch
     s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return s.cuda_stream
 
 
 (KNOB_TARGET_WORKGROUPS, KNOB_NO_MATRIX_CORES, KNOB_CHUNK_SAMPLES, KNOB_MAX_REPLICAS, KNOB_ROWS_MIN_BATCH,

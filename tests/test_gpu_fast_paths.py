@@ -38,3 +38,33 @@ def test_pruned_level_search_equals_the_full_one(M, bits, knobs):
     assert np.array_equal(res[0][0], res[1][0])
     assert np.array_equal(res[0][1], res[1][1])
     assert res[0][2] == res[1][2]
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("n,d", [(1, 1), (63, 31), (130, 32), (129, 33), (700, 65), (40000, 96), (2051, 1030)])
+def test_loss_on_packed_copies_of_every_width(n, d, bits):
+    """Both copies, levels evenly spaced (matrix cores on copy 2) and not (tables in LDS, several chunks of
+    features at 1,030): ragged tiles of samples, odd numbers of feature groups, fewer and more samples than
+    blocks.  A dot product is off by at most (d + 4) 2^-24 times the sum of
+    the magnitudes, for evenly spaced levels those of the two terms lo_j x_j and (hi_j - lo_j) x_j."""
+    rng = np.random.default_rng(bits * 1000 + n + d)
+    K = 1 << bits
+    b = rng.standard_normal(n).astype(np.float32)
+    x = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    lo, hi = rng.uniform(-2, -1, d).astype(np.float32), rng.uniform(1, 2, d).astype(np.float32)
+    even = oracle.levels_uniform(lo, hi, bits)
+    uneven = np.sort(rng.uniform(-1, 1, (d, K)), axis=1).astype(np.float32)
+    for L in (even, uneven):
+        p = GpuProblem(A, b, bits, 32)
+        p.set_levels(L)
+        p.quantize(3, 0)
+        for copy in (1, 2):
+            say("packed loss", n, d, bits, copy, L is even)
+            v = np.take_along_axis(L, p.codes(copy).astype(np.int64).T, axis=1).T.astype(np.float64)
+            ref = float(np.sum((v @ x.astype(np.float64) - b) ** 2) / (2 * n))
+            # the loss moves by the mean of |r| times the error of a dot product
+            mag = float((np.abs(L[:, 0]) + np.abs(L[:, -1] - L[:, 0])).astype(np.float64) @ np.abs(x))
+            band = float(np.mean(np.abs(v @ x - b))) * mag * (d + 4) * 2.0 ** -24
+            got = p.loss(dev(x), packed_copy=copy)
+            assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
