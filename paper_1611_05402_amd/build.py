@@ -11,6 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libzipml.so")
 # (source, further flags, object): the SGD kernels of each code width are a compilation of their own
 UNITS = [("zipml_sgd.hip", [f"-DZIPML_SGD_BITS={b}"], f"zipml_sgd_{b}.o") for b in (8, 4, 2, 7, 6, 5, 3, 1)]
+UNITS += [("zipml_sgd_solo.hip", [f"-DZIPML_SGD_BITS={b}"], f"zipml_sgd_solo_{b}.o") for b in range(1, 9)]
 UNITS += [(s, [], s.replace(".hip", ".o")) for s in ("zipml_sgd.hip", "zipml_quantize.hip", "zipml_loss.hip", "zipml_levels.hip")]
 
 # -ffp-contract=off: fp32/fp64 decision sequences must stay single IEEE operations (fused

@@ -35,6 +35,8 @@
 // features (zipml_sgd_rows.h); run_sgd below chooses.
 #include "zipml_device.h"
 #include "zipml_host.h"
+#include "zipml_prox.h"
+#include "zipml_sgd_solo.h"
 
 #include <math.h>
 #include <algorithm>
@@ -127,21 +129,6 @@ struct SgdArgs {
     float *dbg_r, *dbg_g;
     int dbg_production;    // 1: dbg_r / dbg_g are written by the production launch (matrix-core loop)
 };
-
-// Proximal operator of lr * R at v, coordinate-wise (Sec. 2, x <- prox_{gamma R}(x - gamma g)):
-// l1 norm -> soft threshold at lr * coef; coef/2 ||x||^2 -> v / (1 + lr * coef); the constraint
-// ||x||_inf <= coef -> clamp.  None of them increases |v|, so the magnitude bounds that the step
-// loops track for the model stay valid.
-__device__ __forceinline__ float apply_prox(float v, int kind, float lr, float coef)
-{
-    if (kind == ZIPML_PROX_L1) {
-        const float t = lr * coef;
-        return v > t ? v - t : v < -t ? v + t : 0.0f;
-    }
-    if (kind == ZIPML_PROX_L2SQ) return __fdiv_rn(v, 1.0f + lr * coef);
-    if (kind == ZIPML_PROX_BOX) return fminf(fmaxf(v, -coef), coef);
-    return v;
-}
 
 // LDS arrays of one workgroup.
 struct Lds {
@@ -1462,6 +1449,39 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
     int rc = make_plan(lay.d32, bits, batch, model_bits > 0 && !ident, model_bits == 0, pairs, p);
     const bool stepwise = (flags & ZIPML_SGD_STEPWISE) != 0;
     const bool debug = dbg_m || dbg_acc || dbg_r || dbg_g || dbg_gq;
+    // A problem that fits one workgroup, fp32 model: the kernel made for that (zipml_sgd_solo.hip), where two
+    // steps of packed codes have room in LDS beside its tables
+    if (rc == ZIPML_OK && p.W == 1 && model_bits == 0 && !stepwise && !debug && !avg &&
+        knob(ZIPML_KNOB_NO_MATRIX_CORES) <= 0) {
+        int cus = 0, lds = 0;
+        if (int lrc = device_limits(cus, lds)) return lrc;
+        SoloArgs sa{};
+        if (solo_plan(lay, (int)batch, lds, sa)) {
+            sa.p1 = (const uint32_t *)packed1_dev;
+            sa.p2 = (const uint32_t *)packed2_dev;
+            sa.levels = levels_dev;
+            sa.b = b_dev;
+            sa.x = x_dev;
+            sa.d = (int)d;
+            sa.step0 = step0;
+            sa.nsteps = nsteps;
+            sa.lr = lr;
+            sa.l2 = l2;
+            sa.prox = prox;
+            sa.prox_coef = prox_coef;
+            sa.status = status_dev ? status_dev : (int *)((unsigned char *)workspace_dev + Workspace::kStatus);
+            switch (bits) {
+                case 1: return launch_solo<1>(s, sa);
+                case 2: return launch_solo<2>(s, sa);
+                case 3: return launch_solo<3>(s, sa);
+                case 4: return launch_solo<4>(s, sa);
+                case 5: return launch_solo<5>(s, sa);
+                case 6: return launch_solo<6>(s, sa);
+                case 7: return launch_solo<7>(s, sa);
+                case 8: return launch_solo<8>(s, sa);
+            }
+        }
+    }
     int replicas = 1;
     int64_t forced = 0;
     if (knob(ZIPML_KNOB_CHUNK_SAMPLES) > 0) forced = knob(ZIPML_KNOB_CHUNK_SAMPLES);   // development override: chunk size

@@ -68,3 +68,46 @@ def test_loss_on_packed_copies_of_every_width(n, d, bits):
             band = float(np.mean(np.abs(v @ x - b))) * mag * (d + 4) * 2.0 ** -24
             got = p.loss(dev(x), packed_copy=copy)
             assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
+
+
+SOLO = [(n, d, B) for n, d, B in [(64, 1, 4), (96, 8, 8), (128, 33, 16), (192, 64, 64), (256, 65, 32), (192, 100, 96), (640, 130, 64),
+                                 (640, 255, 160), (512, 256, 256), (1024, 64, 512), (2048, 31, 1024)]]
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("n,d,B", SOLO)
+def test_single_workgroup_epochs_of_every_width(n, d, B, bits):
+    """Problems of one workgroup: every width, evenly spaced and other levels, batches below a sample group,
+    of one block of samples and of several (the last one half full), features of one tile to sixteen; two
+    epochs, plain, with the l2 term and with the l1 step."""
+    rng = np.random.default_rng(bits * 7919 + n + d + B)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    x0 = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    b = (A @ x0 + 0.1 * rng.standard_normal(n)).astype(np.float32)
+    lo, hi = rng.uniform(-1.5, -1, d).astype(np.float32), rng.uniform(1, 1.5, d).astype(np.float32)
+    uneven = np.sort(rng.uniform(-1, 1, (d, 1 << bits)), axis=1).astype(np.float32)
+    lr = 0.3 / d
+    for L in (oracle.levels_uniform(lo, hi, bits), uneven):
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(L)
+        p.quantize(5, 0)
+        c1, c2 = p.codes(1), p.codes(2)
+        args = (p.p1, p.p2, p.levels, p.b, n, d, bits)
+        for form in ("plain", "l2", "l1"):
+            say("one workgroup", n, d, B, bits, form, L is uneven)
+            x, ref = dev(np.zeros(d, np.float32)), np.zeros(d, np.float32)
+            for _ in range(2):
+                if form == "plain":
+                    zipml.sgd_epoch(*args, x, B, lr, p.ws)
+                    ref = oracle.sgd_epoch(c1, c2, L, b, bits, ref, B, lr)
+                elif form == "l2":
+                    zipml.sgd_epoch_l2(*args, x, B, lr, 0.05, p.ws)
+                    ref = oracle.sgd_epoch(c1, c2, L, b, bits, ref, B, lr, l2=0.05)
+                else:
+                    zipml.sgd_epoch_prox(*args, x, B, lr, zipml.PROX_L1, 0.01, p.ws)
+                    ref = oracle.sgd_epoch(c1, c2, L, b, bits, ref, B, lr, prox_kind=oracle.PROX_L1, prox_coef=0.01)
+            assert zipml.sgd_status(p.ws) == 0
+            got = x.cpu().numpy().astype(np.float64)
+            # 1e-5: the library's bound for an fp32 model after an epoch
+            assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref) + 1e-12
+            assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max() + 1e-12
