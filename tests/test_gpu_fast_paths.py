@@ -111,3 +111,32 @@ def test_single_workgroup_epochs_of_every_width(n, d, B, bits):
             # 1e-5: the library's bound for an fp32 model after an epoch
             assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref) + 1e-12
             assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max() + 1e-12
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+def test_single_workgroup_epochs_at_the_ends_of_the_number_range(bits):
+    """Tiny and huge labels keep their digits, levels whose spacing rounds in fp64 are decoded, and an
+    infinite label ends in a model without a finite element (as it does in plain fp32 arithmetic)."""
+    n, d, B = 256, 40, 128
+    rng = np.random.default_rng(bits)
+    L = np.sort(rng.uniform(-1, 1, (d, 1 << bits)), axis=1).astype(np.float32)
+    L[:, 0], L[:, -1] = -1.0, 1e-30
+    L[:, 1:-1] = np.minimum(L[:, 1:-1], 0.0)
+    A = rng.uniform(-1, 0, (n, d)).astype(np.float32)
+    for scale in (1e-20, 1.0, 1e30, np.inf):
+        say("range", bits, scale)
+        b = rng.standard_normal(n).astype(np.float32)
+        b = b * np.float32(scale) if np.isfinite(scale) else b
+        if not np.isfinite(scale):
+            b[7] = np.inf
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(np.sort(L, axis=1))
+        p.quantize(5, 0)
+        x = dev(np.zeros(d, np.float32))
+        zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, n, d, bits, x, B, 0.01, p.ws)
+        got = x.cpu().numpy().astype(np.float64)
+        if not np.isfinite(scale):
+            assert not np.isfinite(got).any()
+            continue
+        ref = oracle.sgd_epoch(p.codes(1), p.codes(2), np.sort(L, axis=1), b, bits, np.zeros(d, np.float32), B, 0.01)
+        assert np.linalg.norm(got / scale - ref / scale) <= 1e-5 * np.linalg.norm(ref / scale)
