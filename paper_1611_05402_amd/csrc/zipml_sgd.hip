@@ -966,7 +966,16 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         if constexpr (INT && FAST) {
             // (a single workgroup is launched on the other instantiation: the host sees to it, so
             // that this one holds the end-to-end loop only and its registers)
-            if (a.W > 1) sgd_steps_e2e<BITS, UPT>(a, L);
+            if (a.W > 1) {
+                // (both hold the step's exact gradient; whole sample groups, at most 16 levels and four feature
+                // groups go to the matrix cores)
+                if constexpr (BITS <= 4) {
+                    if (B >= 32 && a.GQ <= 4) sgd_steps_e2e<BITS, UPT, true>(a, L);
+                    else sgd_steps_e2e<BITS, UPT, false>(a, L);
+                } else {
+                    sgd_steps_e2e<BITS, UPT, false>(a, L);
+                }
+            }
         } else if (INT) {
             sgd_steps<BITS, kInt, FAST, UPT>(a, L);
         } else if (affine) {

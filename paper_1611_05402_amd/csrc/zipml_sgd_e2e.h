@@ -21,9 +21,16 @@
 //
 // Arithmetic per code: the dot pass adds T[j][code] = G[j][code] * m_j, a table rebuilt by the
 // owner of feature j after Q3 (one LDS gather and one integer add per code; for wide level sets
-// the product is formed on the fly); the gradient pass sums L[j][code] * r_i in fp64 (products of
-// two fp32 numbers are exact there), so the mean gradient that Q4 quantises is the exact mean
-// rounded to fp32, whatever the order.
+// the product is formed on the fly).  The mean gradient that Q4 quantises is the exact mean rounded to
+// fp32, whatever the order: the gradient pass adds L[j][code] * r_i either in fp64 (products of two fp32
+// numbers are exact there) or, for at most 16 levels and whole sample groups (MX), in integers on the matrix
+// cores: r in seven signed bytes (its 24 bits stand at the top of 54, so a residual is exact down to 2^-30
+// of the largest one and off by 2^-54 of it below), a feature's levels in six (24 bits at the top of 46).  A lane
+// owns one feature, so a look-up is a byte permute of the level's bytes from registers, four codes at a time;
+// the seven bytes of r fill half of the sixteen rows of v_mfma_i32_16x16x64_i8, one instruction per byte of
+// the levels.  In fp64 the pass took, per code, a field extraction, an LDS gather with bank conflicts, two
+// conversions and a multiply-add: a step of 512 samples x 4,096 features at 3 bits took 12.8 us, 9.6 with this
+// pass and with the draws of the two quantisations made while the norms travel.
 #pragma once
 
 namespace zipml {
@@ -55,9 +62,31 @@ __device__ __forceinline__ double wave_tree_sum_f64(double v)
     return v;
 }
 
+// A float as a fixed-point number whose unit is 2^(emax - 150 - top), emax >= 1 the largest biased exponent
+// that is met: exact where its own exponent is at most `top` below, cut off beyond.
+__device__ __forceinline__ long long fixed_from_float(float v, int emax, int top)
+{
+    const uint32_t b = __float_as_uint(v);
+    const int e = (int)((b >> 23) & 255u);
+    const uint32_t m = (b & 0x7FFFFFu) | (e ? 0x800000u : 0u);
+    const int sh = (e ? e : 1) - emax + top;
+    const long long f = sh >= 0 ? (long long)((uint64_t)m << sh) : (long long)(m >> (sh > -31 ? -sh : 31));
+    return (b >> 31) ? -f : f;
+}
+// N signed base-256 digits, the bytes of the result (|v| < 2^(8 N - 1) - 2^(8 N - 8)).
+template <int N>
+__device__ __forceinline__ uint64_t signed_digits_64(long long v)
+{
+    constexpr uint64_t kHalf = 0x8080808080808080ull >> (8 * (9 - N));       // 128 in the N - 1 lower bytes
+    return ((uint64_t)v + kHalf) ^ kHalf;
+}
+constexpr int kRDigits = 7, kRTop = 30;     // residuals: 24 + 30 bits
+constexpr int kLDigits = 6, kLTop = 22;     // levels: 24 + 22 bits
+
 constexpr int kNormSlots = 256;   // slots per buffer of the norm exchange (>= workgroups)
 
-template <int BITS, int UPT>
+// MX: the gradient pass on the matrix cores (at most 16 levels, B >= 32, GQ <= 4).
+template <int BITS, int UPT, bool MX>
 __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 {
     constexpr int K = 1 << BITS;
@@ -99,6 +128,63 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     const int g_gq = g_c >> 5, g_cin = g_c & 31;
     const bool g_live = g_gq < ngroups;
 
+    // ---- matrix-core gradient pass: the feature tiles of 16 are shared out over the waves, waves that share a
+    // tile take every KSS-th block of 64 samples.  A lane's operand m: half a packed unit.
+    constexpr int HW = kOpDwords<BITS>;
+    constexpr int kOps = 2 * UPT;                    // (B GQ <= 512 UPT: at most this many blocks per wave)
+    constexpr int kPlaneWords = (K + 3) / 4;         // registers that hold one byte of all levels
+    const int n16 = lane & 15, q4 = lane >> 4;
+    const int FT = MX ? 2 * GQ : 8, KSS = kWaves / FT, wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int x_ft = wave_u % FT, x_kh = wave_u / FT;
+    const int xc = 16 * x_ft + n16;                  // this lane's feature, inside the workgroup
+    int8_t *const rdig = reinterpret_cast<int8_t *>(gpart + 2 * kWaves * 16);   // [blocks][8][64], behind the waves' sums
+    uint32_t *const wmax = reinterpret_cast<uint32_t *>(L.wsum + kWaves);
+    uint32_t plane[MX ? kLDigits : 1][MX ? kPlaneWords : 1];
+    int r_pos = 0, el_own = 1;
+    if constexpr (MX) {
+        auto level_exponent = [&](int c) {
+            uint32_t m = 0;
+            for (int q = 0; q < K; ++q) {
+                const uint32_t b = j0 + c < a.d ? __float_as_uint(Lg[(size_t)c * K + q]) & 0x7FFFFFFFu : 0u;
+                m = b > m ? b : m;
+            }
+            return (int)(m >> 23) > 1 ? (int)(m >> 23) : 1;
+        };
+        if (is_owner) el_own = level_exponent(tid);
+        const int el = level_exponent(xc);
+#pragma unroll
+        for (int p = 0; p < kLDigits; ++p)
+#pragma unroll
+            for (int q = 0; q < kPlaneWords; ++q) plane[p][q] = 0u;
+#pragma unroll
+        for (int c = 0; c < K; ++c) {
+            const float lv = j0 + xc < a.d ? Lg[(size_t)xc * K + c] : 0.0f;
+            const uint64_t dg = signed_digits_64<kLDigits>(fixed_from_float(lv, el, kLTop));
+#pragma unroll
+            for (int p = 0; p < kLDigits; ++p) plane[p][c >> 2] |= (uint32_t)((dg >> (8 * p)) & 0xFFu) << (8 * (c & 3));
+        }
+        // sample i: block i / 64, and this byte of each of its digit rows (i = tid + 512 q: the same for every q)
+        int half, byte;
+        code_slot<BITS>(tid & 31, half, byte);
+        r_pos = (tid >> 6) * 512 + (2 * ((tid >> 5) & 1) + half) * 16 + byte;
+        for (int e = tid; e < (B + 63) / 64 * 128; e += kThreads) reinterpret_cast<uint32_t *>(rdig)[e] = 0u;
+        if (tid < kWaves) wmax[tid] = 0u;
+        // (the exchange of the first step has barriers enough before they are used)
+    }
+    auto load_grad_ops = [&](int64_t t, uint32_t (&dst)[kOps][HW]) {
+        const int64_t g = (int64_t)w * GQ + (x_ft >> 1), rg0 = t * B / 32;
+#pragma unroll
+        for (int m = 0; m < kOps; ++m) {
+            const int rg = 2 * (x_kh + KSS * m) + (q4 >> 1);
+            if (rg < nrg && (x_ft >> 1) < ngroups) {
+                const uint32_t *q = static_cast<const uint32_t *>(__builtin_assume_aligned(
+                    a.p1 + ((g * a.n32 + rg0 + rg) * 32 + (xc & 31)) * BITS + (q4 & 1) * kOpStride<BITS>, kOpAlign<BITS>));
+#pragma unroll
+                for (int k = 0; k < HW; ++k) dst[m][k] = q[k];
+            }
+        }
+    };
+
     auto load_dot_units = [&](int64_t t, uint32_t (&dst)[UPT][BITS]) {
         const int64_t row0 = t * B;
 #pragma unroll
@@ -132,7 +218,8 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     bool dead = false;
     // One trip of the norm exchange.  sq: this thread's square (owners; 0 elsewhere), fp64.
     // Returns the l2 norm over all workgroups as fp32, to the owner waves (others get 0).
-    auto exchange_norm = [&](double sq, uint64_t *slots) -> float {
+    // meanwhile(): work of the owner waves that does not need the norm, done while it travels.
+    auto exchange_norm = [&](double sq, uint64_t *slots, auto meanwhile) -> float {
         if (owner_wave) {
             sq = wave_tree_sum_f64(sq);
             if (lane == 0) red[wave] = sq;
@@ -145,6 +232,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
             store_dev(slots + w, (uint64_t)((uint64_t)__double_as_longlong(own) + 1ull));
         }
         if (!owner_wave) return 0.0f;
+        meanwhile();
         uint64_t raw[4] = {1ull, 1ull, 1ull, 1ull};   // (bits of 0.0) + 1 for the slots past W
         uint32_t spins = 0;
 #pragma unroll 1
@@ -171,13 +259,25 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     };
 
     const int64_t t_end = a.step0 + a.nsteps;
-    uint32_t c2cur[UPT][BITS], c2nxt[UPT][BITS], c1cur[UPT][BITS], c1nxt[UPT][BITS];
+    uint32_t c2cur[UPT][BITS], c2nxt[UPT][BITS];
+    uint32_t c1cur[MX ? kOps : UPT][MX ? HW : BITS], c1nxt[MX ? kOps : UPT][MX ? HW : BITS];
+    auto load_grad = [&](int64_t t) {
+        if constexpr (MX) load_grad_ops(t, c1nxt);
+        else load_grad_units(t, c1nxt);
+    };
+    if constexpr (MX) {
+        // (operands that are never loaded meet residual digits that are zero, or features that do not exist)
+#pragma unroll
+        for (int m = 0; m < kOps; ++m)
+#pragma unroll
+            for (int k = 0; k < HW; ++k) c1nxt[m][k] = 0u;
+    }
     float bnext[UPT], bfut[UPT];
 #pragma unroll
     for (int k = 0; k < UPT; ++k) bnext[k] = bfut[k] = 0.0f;
     load_dot_units(a.step0, c2cur);
     if (a.step0 + 1 < t_end) load_dot_units(a.step0 + 1, c2nxt);
-    load_grad_units(a.step0, c1nxt);
+    load_grad(a.step0);
     load_labels(a.step0, bnext);
 
     float x_own = is_owner ? xs[tid] : 0.0f;         // the owner keeps its weight in a register
@@ -194,14 +294,22 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         const int k0 = B >= 32 ? 0 : (int)((t * B) % 32);
 
         // ================= ||x||_2, Q3, the table of the dot pass
-        const float Mx = exchange_norm(live ? (double)x_own * (double)x_own : 0.0, xn);
+        // (the draws of Q3 and Q4 do not depend on the norms: they are made while those travel, 0.2 us each)
+        float draw = 0.0f;
+        auto draw_for = [&](uint32_t stream) {
+            return [&, stream]() {
+                const Philox4 r = philox_block(a.seed, a.epoch, (uint64_t)t, (uint32_t)jme >> 2, stream);
+                draw = u24(philox_word(r, (uint32_t)jme & 3u));
+                asm volatile("" : "+v"(draw));       // (here, not where it is used)
+            };
+        };
+        const float Mx = exchange_norm(live ? (double)x_own * (double)x_own : 0.0, xn, draw_for(3u));
         ZIPML_TICK(0);
         const float sigma = Mx > 0.0f ? __fdiv_rn(Mx, (float)s_m) : 0.0f;
         if (owner_wave) {
             int mine = 0;
             if (live) {
-                const Philox4 r = philox_block(a.seed, a.epoch, (uint64_t)t, (uint32_t)jme >> 2, 3u);
-                mine = qvec_code(x_own, Mx, s_m, u24(philox_word(r, (uint32_t)jme & 3u)));
+                mine = qvec_code(x_own, Mx, s_m, draw);
                 if (a.dbg_m) a.dbg_m[jme] = mine;
             }
             if (is_owner) {
@@ -286,20 +394,24 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         }
         // rotate the register sets; request what later steps need right behind the atomics
 #pragma unroll
+        for (int k = 0; k < (MX ? kOps : UPT); ++k)
+#pragma unroll
+            for (int q = 0; q < (MX ? HW : BITS); ++q) c1cur[k][q] = c1nxt[k][q];
+#pragma unroll
         for (int k = 0; k < UPT; ++k)
 #pragma unroll
-            for (int q = 0; q < BITS; ++q) {
-                c1cur[k][q] = c1nxt[k][q];
-                c2cur[k][q] = c2nxt[k][q];
-            }
+            for (int q = 0; q < BITS; ++q) c2cur[k][q] = c2nxt[k][q];
         if (t + 1 < t_end) {
-            load_grad_units(t + 1, c1nxt);
+            load_grad(t + 1);
             load_labels(t + 1, bfut);
         }
         if (t + 2 < t_end) load_dot_units(t + 2, c2nxt);
         ZIPML_TICK(3);
 
         // ================= residuals: every thread polls the words of its own samples
+        float rown[UPT];
+#pragma unroll
+        for (int q = 0; q < UPT; ++q) rown[q] = 0.0f;
         if (tid < B) {
             uint64_t raw[UPT], rawm = 0;
             uint32_t spins = 0;
@@ -328,7 +440,8 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                     const int av = (int)unpack_sum(raw[q], W);
                     const double z = (double)sigma_b * ((double)a.grid_lo * summ + (double)a.grid_step * (double)av);
                     const float r = (float)z - bnext[q];
-                    rs[k0 + i] = r;
+                    if constexpr (MX) rown[q] = r;
+                    else rs[k0 + i] = r;
                     if (w == 0) {
                         if (a.dbg_acc) a.dbg_acc[i] = av;
                         if (a.dbg_r) a.dbg_r[i] = r;
@@ -338,11 +451,92 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         }
 #pragma unroll
         for (int q = 0; q < UPT; ++q) bnext[q] = bfut[q];
-        lds_barrier();    // rs[]
+        if constexpr (MX) {
+            // the largest residual gives the unit of all, then each becomes digits
+            uint32_t m = 0;
+#pragma unroll
+            for (int q = 0; q < UPT; ++q) {
+                const uint32_t b = __float_as_uint(rown[q]) & 0x7FFFFFFFu;
+                m = b > m ? b : m;
+            }
+            m = wave_reduce_dpp(m, [](uint32_t p, uint32_t q) { return p > q ? p : q; });
+            if (lane == 0) wmax[wave] = m;
+        }
+        lds_barrier();    // rs[], or the waves' largest residuals
+        int er = 1;
+        if constexpr (MX) {
+            uint32_t m = 0;
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) m = wmax[q] > m ? wmax[q] : m;
+            er = (int)(m >> 23) > 1 ? (int)(m >> 23) : 1;
+#pragma unroll
+            for (int q = 0; q < UPT; ++q)
+                if (tid + q * kThreads < B) {
+                    const uint64_t dg = signed_digits_64<kRDigits>(fixed_from_float(rown[q], er, kRTop));
+                    int8_t *at = rdig + q * (kThreads / 64 * 512) + r_pos;
+#pragma unroll
+                    for (int k = 0; k < kRDigits; ++k) at[64 * k] = (int8_t)(dg >> (8 * k));
+                }
+            lds_barrier();    // the digits
+        }
         ZIPML_TICK(4);
 
-        // ================= gradient pass: fp64 sums over the samples of each owned unit
-        {
+        // ================= gradient pass
+        if constexpr (MX) {
+            v4i c[kLDigits];
+#pragma unroll
+            for (int p = 0; p < kLDigits; ++p) c[p] = v4i{0, 0, 0, 0};
+            const uint32_t shift = op_shift<BITS>(q4 & 1);
+#pragma unroll
+            for (int m = 0; m < kOps; ++m) {
+                const int sb = x_kh + KSS * m;
+                if (2 * sb < nrg) {
+                    // (rows 7 .. 15 repeat others or are no digits at all: their results are not used)
+                    const v4i rd = *reinterpret_cast<const v4i *>(rdig + sb * 512 + (n16 & 7) * 64 + q4 * 16);
+                    v4i e = expand_codes<BITS>(c1cur[m], shift), up = {0, 0, 0, 0};
+                    if constexpr (K == 16) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t top = ((uint32_t)e[q] >> 3) & 0x01010101u;
+                            up[q] = (int)((top << 8) - top);          // 0xFF where the code is 8 or more
+                            e[q] &= 0x07070707;
+                        }
+                    }
+#pragma unroll
+                    for (int p = 0; p < kLDigits; ++p) {
+                        v4i lv;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            uint32_t v = __builtin_amdgcn_perm(plane[p][K >= 8 ? 1 : 0], plane[p][0], (uint32_t)e[q]);
+                            if constexpr (K == 16) {
+                                const uint32_t h = __builtin_amdgcn_perm(plane[p][3], plane[p][2], (uint32_t)e[q]);
+                                v = ((uint32_t)up[q] & h) | (~(uint32_t)up[q] & v);
+                            }
+                            lv[q] = (int)v;
+                        }
+                        c[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd, lv, c[p], 0, 0, 0);
+                    }
+                }
+            }
+            // Rows 0 .. 3 are in the first sixteen lanes, rows 4 .. 6 in the next (row 7 is no digit).  Sums of
+            // equal weight first: each below 2^26, so the four lower ones join exactly in a double.
+            if (q4 < 2) {
+                int v[kLDigits + 3];
+#pragma unroll
+                for (int s = 0; s < kLDigits + 3; ++s) v[s] = 0;
+#pragma unroll
+                for (int p = 0; p < kLDigits; ++p) {
+                    v[p] += c[p][0];
+                    v[p + 1] += c[p][1];
+                    v[p + 2] += c[p][2];
+                    v[p + 3] += q4 == 0 ? c[p][3] : 0;
+                }
+                const double lo4 = fma(fma((double)v[3], 256.0, (double)v[2]), 65536.0, fma((double)v[1], 256.0, (double)v[0]));
+                double hi5 = fma(fma((double)v[7], 256.0, (double)v[6]), 65536.0, fma((double)v[5], 256.0, (double)v[4]));
+                hi5 = fma((double)v[8], 4294967296.0, hi5);
+                gpart[(2 * x_kh + q4) * CW + xc] = fma(hi5, 4294967296.0, lo4) * (q4 ? 4294967296.0 : 1.0);
+            }
+        } else {
             double part[UPT];
 #pragma unroll
             for (int k = 0; k < UPT; ++k) {
@@ -378,13 +572,18 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         float g = 0.0f;
         if (is_owner) {
             double sacc = 0.0;
-            for (int r0 = 0; r0 < nrg; r0 += 8) {
+            const int nparts = MX ? 2 * KSS : nrg;
+            for (int r0 = 0; r0 < nparts; r0 += 8) {
                 double v[8];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = gpart[(r0 + q < nrg ? r0 + q : r0) * CW + tid];
+                for (int q = 0; q < 8; ++q) v[q] = gpart[(r0 + q < nparts ? r0 + q : r0) * CW + tid];
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
-                    if (r0 + q < nrg) sacc += v[q];
+                    if (r0 + q < nparts) sacc += v[q];
+            }
+            if constexpr (MX) {
+                sacc = ldexp(sacc, er + el_own - (300 + kRTop + kLTop));
+                if (er == 255) sacc = __longlong_as_double(0x7FF8000000000000ll);    // an infinity or a NaN among the residuals
             }
             g = live ? (float)(sacc / (double)B) : 0.0f;      // the mean, rounded once
             if (a.dbg_g && live) a.dbg_g[jme] = g;
@@ -398,11 +597,10 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         ZIPML_TICK(6);
         // ================= ||g||_2, Q4, update
         if (a.grad_bits > 0) {
-            const float Mg = exchange_norm(is_owner ? (double)g * (double)g : 0.0, gn);
+            const float Mg = exchange_norm(is_owner ? (double)g * (double)g : 0.0, gn, draw_for(4u));
             const float sg = Mg > 0.0f ? __fdiv_rn(Mg, (float)s_g) : 0.0f;
             if (live) {
-                const Philox4 r = philox_block(a.seed, a.epoch, (uint64_t)t, (uint32_t)jme >> 2, 4u);
-                const int code = qvec_code(g, Mg, s_g, u24(philox_word(r, (uint32_t)jme & 3u)));
+                const int code = qvec_code(g, Mg, s_g, draw);
                 if (a.dbg_gq) a.dbg_gq[jme] = code;
                 const float gh = sg * (float)code;
                 const float stp = a.lr * gh;

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_harness import GpuProblem, dev
+from gpu_harness import GpuProblem, dev, e2e_step_check
 from paper_1611_05402_amd import synth, zipml
 
 pytestmark = pytest.mark.gpu
@@ -140,3 +140,28 @@ def test_single_workgroup_epochs_at_the_ends_of_the_number_range(bits):
             continue
         ref = oracle.sgd_epoch(p.codes(1), p.codes(2), np.sort(L, axis=1), b, bits, np.zeros(d, np.float32), B, 0.01)
         assert np.linalg.norm(got / scale - ref / scale) <= 1e-5 * np.linalg.norm(ref / scale)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("d,B", [(300, 32), (290, 1024), (1100, 96), (1100, 480), (4000, 96), (4000, 224)])
+def test_end_to_end_steps_on_the_matrix_cores(d, B, bits):
+    """One, two and four feature groups per workgroup, whole and half blocks of samples, the largest batch;
+    uneven levels; labels that spread the residuals over sixty powers of two."""
+    say("end-to-end on the matrix cores", d, B, bits)
+    rng = np.random.default_rng(bits * 31 + d + B)
+    M, n = 200, 2 * B
+    G = np.stack([np.sort(rng.choice(M - 1, (1 << bits) - 2, replace=False) + 1) if bits > 1 else np.zeros(0, int)
+                  for _ in range(d)])
+    G = np.concatenate([np.zeros((d, 1)), G.reshape(d, -1), np.full((d, 1), M)], axis=1).astype(np.uint16)
+    L = (G / np.float64(M)).astype(np.float32)
+    A = rng.uniform(0, 1, (n, d)).astype(np.float32)
+    b = (rng.standard_normal(n) * 2.0 ** rng.uniform(-40, 20, n)).astype(np.float32)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L, G)
+    p.quantize(4, 0)
+    c1, c2 = p.codes(1), p.codes(2)
+    for scale in (0.0, 0.1):
+        x0 = (rng.standard_normal(d) * scale).astype(np.float32)
+        for step in (0, 1):
+            e2e_step_check(p, oracle, c1, c2, L, G, np.float32(0), np.float32(1.0 / M), M, b, x0, 0.3, 8, 8, 4, 0, step,
+                           zipml.SGD_PRODUCTION)
