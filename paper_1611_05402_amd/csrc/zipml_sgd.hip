@@ -242,6 +242,19 @@ __device__ __forceinline__ float unit_dot_table(const uint32_t (&u)[BITS], const
     return acc;
 }
 
+// The same on a table in memory, which has no rows for the padding features of the last group: those
+// (whose x is zero) read row `last` instead.
+template <int BITS>
+__device__ __forceinline__ float unit_dot_table_mem(const uint32_t (&u)[BITS], const float *L,
+                                                    const float *x, int last, float acc)
+{
+    constexpr int K = 1 << BITS;
+    if (last >= 31) return unit_dot_table<BITS>(u, L, x, acc);
+#pragma unroll
+    for (int k = 0; k < 32; ++k) acc = fmaf(L[(k < last ? k : last) * K + unit_code<BITS>(u, k)], x[k], acc);
+    return acc;
+}
+
 // Gradient pass, table levels: acc = fma(L[code_k], r[k], acc) for k = 0..31 in this order.
 // L points at the levels of the one feature this unit belongs to.
 template <int BITS>
@@ -506,7 +519,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                         pf = unit_fma_codes<BITS>(c2cur[k], ys + jb, pf);
                     } else if (MODE == kTable) {
                         if (a.lds_levels) pf = unit_dot_table<BITS>(c2cur[k], L.Ls + jb * K, xs + jb, pf);
-                        else pf = unit_dot_table<BITS>(c2cur[k], Lg + (size_t)jb * K, xs + jb, pf);
+                        else pf = unit_dot_table_mem<BITS>(c2cur[k], Lg + (size_t)jb * K, xs + jb, a.d - 1 - j0 - jb, pf);
                     } else {
                         pi = unit_dot_int<BITS>(c2cur[k], a.ident_grid ? nullptr : L.Gs + jb * K,
                                                 L.ms + jb, pi);
@@ -668,16 +681,18 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                 const int rgl = g_sl + k * nsl;
                 if (g_live && rgl < nrg) {
                     const float *rr = rs + rgl * 32;
-                    // (LDS and global tables in separate calls: one pointer for both would be generic)
+                    // (LDS and global tables in separate calls: one pointer for both would be generic.  In memory
+                    // there are no rows for padding features: the last one's stands in, the sum is dropped.)
+                    const size_t row = j0 + g_c < a.d ? g_c : a.d - 1 - j0;
                     if constexpr (kIsInt) {
                         if (a.lds_levels) part[k] = unit_grad_table_f64<BITS>(c1cur[k], L.Ls + g_c * K, rr);
-                        else part[k] = unit_grad_table_f64<BITS>(c1cur[k], Lg + (size_t)g_c * K, rr);
+                        else part[k] = unit_grad_table_f64<BITS>(c1cur[k], Lg + row * K, rr);
                     } else if (MODE == kAffine) {
                         part[k] = unit_fma_codes<BITS>(c1cur[k], rr, 0.0f);
                     } else if (a.lds_levels) {
                         part[k] = unit_grad_table<BITS>(c1cur[k], L.Ls + g_c * K, rr, 0.0f);
                     } else {
-                        part[k] = unit_grad_table<BITS>(c1cur[k], Lg + (size_t)g_c * K, rr, 0.0f);
+                        part[k] = unit_grad_table<BITS>(c1cur[k], Lg + row * K, rr, 0.0f);
                     }
                 }
             }

@@ -556,7 +556,8 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                             if ((q & 15) == 15) asm volatile("" ::: "memory");   // sixteen look-ups in flight
                         }
                     } else {
-                        acc = unit_grad_table_f64<BITS>(c1cur[k], Lg + (size_t)g_c * K, rr);
+                        // (no rows for padding features in memory; their sums are dropped)
+                        acc = unit_grad_table_f64<BITS>(c1cur[k], Lg + (size_t)(j0 + g_c < a.d ? g_c : a.d - 1 - j0) * K, rr);
                     }
                     part[k] = acc;
                 }

@@ -165,3 +165,26 @@ def test_end_to_end_steps_on_the_matrix_cores(d, B, bits):
         for step in (0, 1):
             e2e_step_check(p, oracle, c1, c2, L, G, np.float32(0), np.float32(1.0 / M), M, b, x0, 0.3, 8, 8, 4, 0, step,
                            zipml.SGD_PRODUCTION)
+
+
+@pytest.mark.parametrize("bits,d", [(8, 100), (8, 170), (7, 161)])
+def test_level_tables_in_memory_are_not_read_past_their_end(bits, d, knobs):
+    """Tables too large for LDS, a last feature group with padding features: the rows behind the table (NaN
+    here) have no part in the result."""
+    say("level table in memory", bits, d)
+    n, B = 128, 32
+    rng = np.random.default_rng(d)
+    L = np.sort(rng.uniform(-1, 1, (d, 1 << bits)), axis=1).astype(np.float32)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L)
+    p.quantize(5, 0)
+    room = torch.full((d + 64, 1 << bits), float("nan"), device="cuda:0")
+    room[:d] = p.levels
+    knobs(zipml.KNOB_NO_MATRIX_CORES, 1)
+    x = dev(np.zeros(d, np.float32))
+    zipml.sgd_epoch(p.p1, p.p2, room[:d], p.b, n, d, bits, x, B, 0.1 / d, p.ws)
+    ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.1 / d)
+    got = x.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
