@@ -67,6 +67,16 @@ inline bool solo_plan(const Layout &lay, int B, int lds_limit, SoloArgs &a)
 {
     // (the loaders' offsets inside a packed copy are 32 bits wide)
     if (lay.d32 > 8 || B > kSoloMaxBatch || lay.bytes() >= ((size_t)1 << 32)) return false;
+    // Where the general loop is the faster one, on even or uneven levels (us a step here, there): the pair tables
+    // of uneven 3-bit levels are rebuilt every step, whatever the batch (256 features, 32 samples: 3.85, 2.62); the
+    // bytes of wide codes on many features pass through LDS twice (7 bits, 256 features, 128 samples: 6.5, 4.0; 8
+    // bits, 128 features, 8 samples, uneven: 4.6, 3.8); one group of features leaves most waves without a
+    // feature tile when the batch is large (7 bits, 12 features, 1,024 samples: 5.6, 4.2).
+    const bool pow2 = lay.bits == 1 || lay.bits == 2 || lay.bits == 4;
+    if (lay.bits == 3 && (lay.d32 > 4 ? B <= 64 : lay.d32 > 3 && B <= 32)) return false;
+    if (lay.bits >= 5 && lay.d32 > 4) return false;
+    if (lay.bits == 8 && lay.d32 > 2 && B <= 32) return false;
+    if (!pow2 && lay.d32 == 1 && B > 256) return false;
     a.n_pad = lay.n_pad;
     a.n32 = lay.n32;
     a.d32 = (int)lay.d32;
@@ -77,7 +87,8 @@ inline bool solo_plan(const Layout &lay, int B, int lds_limit, SoloArgs &a)
     while (a.loaders < 4 && SoloSlot(a.d32, B, lay.bits, a.loaders).instr > 4) a.loaders *= 2;
     const SoloSlot sl(a.d32, B, lay.bits, a.loaders);
     if (sl.instr > kSoloMaxInstr) return false;
-    const int table = lay.bits <= 3 ? solo_table_bytes(lay.bits, a.d32) : 0;
+    // (a table that gives way to the slots is read from memory: 7 bits, 64 features, 512 samples 13.1, 6.1)
+    const int table = lay.bits > 1 ? solo_table_bytes(lay.bits, a.d32) : 0;
     return solo_fixed_lds(B) + 2048 + table + 2 * sl.bytes <= a.lds_bytes;
 }
 
