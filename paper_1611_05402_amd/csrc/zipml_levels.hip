@@ -306,17 +306,21 @@ constexpr size_t kHistSlabBytes = (size_t)64 << 20;
 // (every j), T / 8 with eight lanes each (between the limits of the round before), then all, a thread
 // each.  2,048 features x 1,024 candidates x 7 intervals: some 100 values of V per thread and k
 // instead of 1,024, 4.34 -> 0.45 ms.
-// LDS: 6 arrays of M+1 doubles and the argmin table (s+1) x (M+1) uint16; two workgroups of 512 threads
-// per compute unit at 1,024 candidates and 3 bits.
+// LDS: 6 arrays of M+1 doubles and the argmin table (s+1) x (M+1) uint16, whose row 0 nothing else uses and
+// which holds the limits that the rounds set; two workgroups of 512 threads per compute unit at 1,024 candidates
+// and 3 bits.  All of it is counted here: tables that end just below the limit of a workgroup (2,046 candidates at
+// 4 bits) leave no room for static LDS beside them.
+constexpr int kDpThreads = 512;
+constexpr int kDpRound1 = kDpThreads / 64, kDpRound2 = kDpThreads / 8;       // end points of the first two rounds
+constexpr int kDpLimits = 2 * (kDpRound1 + kDpRound2);
 __host__ __device__ inline size_t dp_lds_bytes(int M, int s)
 {
-    const size_t W = (size_t)M + 1;
-    return 6 * W * sizeof(double) + (((size_t)s + 1) * W * sizeof(uint16_t) + 15) / 16 * 16 + 64;
+    const size_t W = (size_t)M + 1, row0 = W > kDpLimits ? W : kDpLimits;
+    return 6 * W * sizeof(double) + ((row0 + (size_t)s * W) * sizeof(uint16_t) + 15) / 16 * 16 + 64;
 }
 // With sel / count (the greedy search below): the candidates of feature j are the count[j] + 1 bin
 // edges sel[j][0 .. count[j]] and hist holds the moments of the intervals between them; Mcap is
 // the largest number of intervals a feature can have (it sizes the tables).
-constexpr int kDpThreads = 512;
 __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restrict__ hist,
                                                    const float *__restrict__ lo,
                                                    const float *__restrict__ hi, int64_t d, int Mgrid,
@@ -331,15 +335,16 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restri
     const int Wcap = Mcap + 1;
     double *C = (double *)dp_smem, *S1 = C + Wcap, *S2 = S1 + Wcap, *edge = S2 + Wcap,
            *prev = edge + Wcap, *cur = prev + Wcap;
-    uint16_t *arg = (uint16_t *)(dp_smem + 6 * (size_t)Wcap * sizeof(double));   // [s+1][W]
-    const double INF = __longlong_as_double(0x7FF0000000000000ll);
     // limits on j that the end points of the first two rounds set: the outermost j within tol of the best
-    __shared__ uint16_t lim_lo[kDpThreads / 64 + kDpThreads / 8], lim_hi[kDpThreads / 64 + kDpThreads / 8];
+    uint16_t *const lim_lo = (uint16_t *)(dp_smem + 6 * (size_t)Wcap * sizeof(double));
+    uint16_t *const lim_hi = lim_lo + kDpRound1 + kDpRound2;
+    const double INF = __longlong_as_double(0x7FF0000000000000ll);
     for (int64_t j = blockIdx.x; j < d; j += gridDim.x) {
         const double *mom = hist + (size_t)j * Mgrid * 3;
         const uint16_t *cand = sel ? sel + (size_t)j * (Mgrid + 1) : nullptr;
         const int M = sel ? count[j] : Mgrid;
         const int W = M + 1;
+        uint16_t *const arg = lim_lo + (W < kDpLimits ? kDpLimits - W : 0);    // [1 .. s][W] behind the limits
         prev = edge + Wcap;
         cur = prev + Wcap;
         __syncthreads();

@@ -40,6 +40,54 @@ def test_pruned_level_search_equals_the_full_one(M, bits, knobs):
     assert res[0][2] == res[1][2]
 
 
+def _searches(A, bits, M, knobs):
+    """Grid, levels and objective of the device's search and of the host's."""
+    n, d = A.shape
+    res = []
+    for host in (0, 1):
+        knobs(zipml.KNOB_HOST_DP, host)
+        p = GpuProblem(A, np.zeros(n, np.float32), bits, 32, n_candidates=M)
+        mv = p.make_levels(zipml.OPTIMAL, 0, lo=np.zeros(d), hi=np.ones(d), n_candidates=M, want_mv=True)
+        res.append((p.grid.cpu().numpy().copy(), p.levels.cpu().numpy().copy(), mv))
+    return res
+
+
+@pytest.mark.parametrize("M,bits", [(3148, 1), (3149, 1), (2558, 3), (2559, 3), (2046, 4), (2047, 4), (929, 6), (291, 8),
+                                    (292, 8)])
+def test_level_search_at_the_last_size_that_fits_on_the_chip(M, bits, knobs):
+    """Tables that end just below the limit of a workgroup's memory, and the first that do not fit."""
+    say("level search at the limit", M, bits)
+    u = np.random.default_rng(M).integers(0, 1025, (400, 3))
+    u[:, 1] = u[:, 1] ** 2 // 1024
+    dev_, host = _searches((u / 1024.0).astype(np.float32), bits, M, knobs)
+    assert np.array_equal(dev_[0], host[0]) and np.array_equal(dev_[1], host[1]) and dev_[2] == host[2]
+
+
+@pytest.mark.parametrize("M,bits", [(100, 2), (513, 3), (1024, 4), (2000, 3)])
+def test_pruned_level_search_with_sums_that_round(M, bits, knobs):
+    """At most two values to a bin, anywhere inside it: the bin moments do not depend on the order of their sums,
+    but everything that the search makes of them is rounded, which is what its margin is for.  Columns: two values
+    to every bin, to every third, values crowded at one end, two clusters, almost no variance."""
+    say("pruned level search, inexact sums", M, bits)
+    rng = np.random.default_rng(M + bits)
+    n = 2 * M
+    two = np.repeat(np.arange(M), 2)
+    def at(bins):
+        return (bins + rng.uniform(0.01, 0.99, n)) / M
+    cols = [at(two), at(np.where(two % 3 == 0, two, two // 3 * 3)), at(two) ** 6, np.where(at(two) < 0.5, at(two) * 0.01, 1 - at(two) * 0.01),
+            0.5 + 1e-7 * at(two)]
+    A = np.stack(cols, 1).astype(np.float32)
+    # (no more than two to a bin where a column was bent: the others move to the bottom, whose sum is exact)
+    for j in range(A.shape[1]):
+        t = A[:, j].astype(np.float64)
+        m = np.minimum((t * M).astype(int), M - 1)
+        for b in np.unique(m):
+            rows = np.nonzero(m == b)[0]
+            A[rows[2:], j] = 0.0
+    dev_, host = _searches(A, bits, M, knobs)
+    assert np.array_equal(dev_[0], host[0]) and np.array_equal(dev_[1], host[1]) and dev_[2] == host[2]
+
+
 @pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("n,d", [(1, 1), (63, 31), (130, 32), (129, 33), (700, 65), (40000, 96), (2051, 1030)])
 def test_loss_on_packed_copies_of_every_width(n, d, bits):
