@@ -309,11 +309,14 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     if (tid == 0) partial[blockIdx.x] = tot;
 }
 
-// LDS of k_loss_copy2's matrix-core path.
+// Dynamic LDS of k_loss_copy2's matrix-core path; the kernel's static part (scratch of the block-wide sums and the
+// vote) has to fit beside it.
+constexpr size_t kLossStaticLds = 1024;
 inline size_t loss_mfma_lds_bytes(int NKB)
 {
     return (size_t)NKB * 256 + (kLossPackedThreads / kWave) * 64 * 8 + 16;
 }
+inline bool loss_mfma_fits(int NKB, int lds_limit) { return loss_mfma_lds_bytes(NKB) + kLossStaticLds <= (size_t)lds_limit; }
 
 // Packed copy 1 (feature-major units: one feature x 32 samples).  A lane takes one feature of a group of 64
 // (or of 32, two sample groups to a wave, where the problem has no more) and keeps the 32 partial dot products
@@ -456,7 +459,7 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
         return blocks;
     }
     int NKB = (int)((lay.d32 + 1) / 2);
-    if (!prep || loss_mfma_lds_bytes(NKB) > (size_t)lds_limit) NKB = 0;   // through the tables, whatever the levels
+    if (!prep || !loss_mfma_fits(NKB, lds_limit)) NKB = 0;   // through the tables, whatever the levels
     size_t shmem = LossTable<BITS>::kBytes < 4096 ? 4096 : LossTable<BITS>::kBytes;
     if (NKB > 0 && loss_mfma_lds_bytes(NKB) > shmem) shmem = loss_mfma_lds_bytes(NKB);
     if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy2<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)))

@@ -118,6 +118,26 @@ def test_loss_on_packed_copies_of_every_width(n, d, bits):
             assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
 
 
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("d", [19904, 19905, 39808, 39809, 39872, 39873])
+def test_loss_where_the_digits_of_the_model_just_fit_on_the_chip(d, bits):
+    """The widths around which the digits of the model stop fitting in a workgroup's memory: every one has a result.
+    Levels on [0, 1] and a model of one sign: no cancellation, the sums are off by (d + 4) 2^-24 at most."""
+    say("packed loss of a wide problem", d, bits)
+    rng = np.random.default_rng(d + bits)
+    n = 70
+    A = rng.uniform(0, 1, (n, d)).astype(np.float32)
+    x = (rng.uniform(0.5, 1, d) / d).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    p = GpuProblem(A, b, bits, 32)
+    p.make_levels(zipml.UNIFORM, 0, lo=np.zeros(d), hi=np.ones(d))
+    p.quantize(3, 0)
+    ref = oracle.loss_codes(p.codes(2), p.levels.cpu().numpy(), bits, b, x)
+    got = p.loss(dev(x), packed_copy=2)
+    r = float(np.mean(np.abs(b))) + 1.0
+    assert abs(got - ref) <= r * (d + 4) * 2.0 ** -24, (got, ref)
+
+
 SOLO = [(n, d, B) for n, d, B in [(64, 1, 4), (96, 8, 8), (128, 33, 16), (192, 64, 64), (256, 65, 32), (192, 100, 96), (640, 130, 64),
                                  (640, 255, 160), (512, 256, 256), (1024, 64, 512), (2048, 31, 1024)]]
 
