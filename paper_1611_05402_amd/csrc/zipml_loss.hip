@@ -90,6 +90,7 @@ __global__ __launch_bounds__(256) void k_loss_prepare(const float *__restrict__ 
         const float xj = x[j], yj = dl * xj;
         cq += (lo + off * dl) * xj;
         ymax = fmaxf(ymax, fabsf(yj));
+        ok &= fabsf(yj) < __builtin_inff();                // (no digits for an infinity or a NaN: the tables take it)
         y[j] = yj;
     }
     ymax = wave_reduce_dpp(ymax, [](float u, float v) { return fmaxf(u, v); });
@@ -225,7 +226,7 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
 // sharing one accumulator as in the SGD kernels), the partial sums meet in LDS and wave 0 squares the
 // residuals.  Exact integer sums; the only rounding before the residual is y_j -> fixed point (2^-29 of max
 // |y|).  Other level tables (the flags of k_loss_prepare say so; all blocks alike), and problems whose
-// digits do not fit in LDS (NKB == 0), go through loss_copy2_table.
+// digits do not fit in LDS (NKB == 0), go through loss_copy2_table, and so does a model that has no digits.
 template <int BITS>
 __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     const uint32_t *__restrict__ p2, const float *__restrict__ levels, const float *__restrict__ b,
@@ -255,7 +256,10 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     long long *const zpart = (long long *)(smem + (size_t)NKB * 256);     // [kW][64]
     int8_t *const zeros = (int8_t *)(smem + (size_t)NKB * 256 + kW * 64 * 8);   // [16]
     if (tid < 4) reinterpret_cast<int *>(zeros)[tid] = 0;
-    const int ky = scale_exponent(ymax, 29);
+    // 2^ky |y| < 2^29, however small the model (the sums are scaled back in fp64)
+    int ey = 0;
+    (void)frexpf(ymax, &ey);
+    const int ky = ymax > 0.0f ? 29 - ey : 0;
     for (int j = tid; j < nfeat; j += kLossPackedThreads) {
         int half, byte;
         code_slot<BITS>(j & 31, half, byte);

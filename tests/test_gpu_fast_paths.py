@@ -138,6 +138,36 @@ def test_loss_where_the_digits_of_the_model_just_fit_on_the_chip(d, bits):
     assert abs(got - ref) <= r * (d + 4) * 2.0 ** -24, (got, ref)
 
 
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_loss_of_small_models_and_of_no_numbers(bits):
+    """Model and labels far below one: the loss scales with their square.  An infinite or NaN element ends in a loss
+    that is not finite."""
+    rng = np.random.default_rng(bits)
+    n, d = 200, 512
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    x1, b1 = rng.standard_normal(d) / np.sqrt(d), rng.standard_normal(n)
+    L = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    for scale in (1.0, 1e-12, 1e-16, 1e-24, 1e-32):
+        say("loss of a small model", bits, scale)
+        x, b = (x1 * scale).astype(np.float32), (b1 * scale).astype(np.float32)
+        p = GpuProblem(A, b, bits, 32)
+        p.set_levels(L)
+        p.quantize(3, 0)
+        for copy in (1, 2):
+            v = np.take_along_axis(L, p.codes(copy).astype(np.int64).T, axis=1).T.astype(np.float64)
+            r = v @ x.astype(np.float64) - b
+            ref = float(np.sum(r * r) / (2 * n))
+            band = float(np.mean(np.abs(r)) * 3.0 * np.abs(x.astype(np.float64)).sum()) * (d + 4) * 2.0 ** -24
+            got = p.loss(dev(x), packed_copy=copy)
+            assert abs(got - ref) <= band + 1e-7 * ref, (got, ref, band)
+    for bad in (np.inf, -np.inf, np.nan):
+        x = x1.astype(np.float32)
+        x[77] = bad
+        say("loss of", bad)
+        for copy in (1, 2):
+            assert not np.isfinite(p.loss(dev(x), packed_copy=copy))
+
+
 SOLO = [(n, d, B) for n, d, B in [(64, 1, 4), (96, 8, 8), (128, 33, 16), (192, 64, 64), (256, 65, 32), (192, 100, 96), (640, 130, 64),
                                  (640, 255, 160), (512, 256, 256), (1024, 64, 512), (2048, 31, 1024)]]
 
