@@ -198,6 +198,22 @@ __device__ __forceinline__ T wave_sum_dpp(T v)
     return wave_reduce_dpp(v, [](T x, T y) { return x + y; });
 }
 
+// The same sum for doubles (two moves a step; through __shfl_xor a step costs two LDS round trips).
+__device__ __forceinline__ double wave_sum_dpp(double v)
+{
+    auto moved = [](double x, auto move) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = move((uint32_t)b), hi = move((uint32_t)(b >> 32));
+        return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    v += moved(v, [](uint32_t w) { return dpp_move<0xB1>(w); });
+    v += moved(v, [](uint32_t w) { return dpp_move<0x4E>(w); });
+    v += moved(v, [](uint32_t w) { return dpp_move<0x141>(w); });
+    v += moved(v, [](uint32_t w) { return dpp_move<0x140>(w); });
+    auto row = [&](int l) { return moved(v, [l](uint32_t w) { return (uint32_t)__builtin_amdgcn_readlane((int)w, l); }); };
+    return (row(0) + row(16)) + (row(32) + row(48));
+}
+
 // Sum over the block; every thread gets the result.  scratch: >= blockDim/64 + 1 elements of T.
 template <typename T>
 __device__ __forceinline__ T block_sum(T v, T *scratch)

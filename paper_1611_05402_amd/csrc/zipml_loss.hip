@@ -52,19 +52,21 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_fp32(
 
 // Launch before the packed copy-2 kernel, kLossPrepBlocks blocks: are the level tables evenly spaced (fp64
 // formula, rounded once; the same test as in the preparation of the SGD kernels) -- one flag per block --,
-// y_j = delta_j x_j, and per block the largest |y_j| and the sum of mid_j x_j.  (Every block of the main
-// kernel needs all of y; taking it from the ends of the level rows there, a cache line per feature, was
-// a quarter of its time at 4,096 features.)
+// y_j = delta_j x_j in fp64, and per block the largest and the smallest |y_j| that is not zero (rounded to fp32) and
+// the sum of mid_j x_j.  (Every block of the main kernel needs all of y; taking it from the ends of the level rows
+// there, a cache line per feature, was a quarter of its time at 4,096 features.)
 constexpr int kLossPrepBlocks = 64;
 struct LossPrep {
     int even[kLossPrepBlocks];
-    float ymax[kLossPrepBlocks], midx[kLossPrepBlocks];
+    float ymax[kLossPrepBlocks], ymin[kLossPrepBlocks];
+    double midx[kLossPrepBlocks];
 };
 __global__ __launch_bounds__(256) void k_loss_prepare(const float *__restrict__ levels, const float *__restrict__ x,
-                                                      int64_t d, int K, float off, LossPrep *__restrict__ prep,
-                                                      float *__restrict__ y)
+                                                      int64_t d, int K, double off, LossPrep *__restrict__ prep,
+                                                      double *__restrict__ y)
 {
-    __shared__ float fmax_s[4], fsum_s[4];
+    __shared__ float fmax_s[4], fmin_s[4];
+    __shared__ double fsum_s[4];
     int ok = 1;
     if (K >= 4) {                                          // (two levels are always evenly spaced)
         const int spf = K / 4;
@@ -83,24 +85,29 @@ __global__ __launch_bounds__(256) void k_loss_prepare(const float *__restrict__ 
             ok &= (v.w == (float)(lo + ((double)(c0 + 3) * wdt) / (double)(K - 1)));
         }
     }
-    float ymax = 0.0f, cq = 0.0f;
+    constexpr float kInf = __builtin_inff();
+    float ymax = 0.0f, ymin = kInf;
+    double cq = 0.0;
     for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < d; j += (int64_t)kLossPrepBlocks * 256) {
-        const float lo = levels[j * K], hi = levels[j * K + K - 1];
-        const float dl = (float)(((double)hi - (double)lo) / (double)(K - 1));
-        const float xj = x[j], yj = dl * xj;
+        const double lo = (double)levels[j * K], dl = ((double)levels[j * K + K - 1] - lo) / (double)(K - 1);
+        const double xj = (double)x[j], yj = dl * xj;
+        const float m = fabsf((float)yj);
         cq += (lo + off * dl) * xj;
-        ymax = fmaxf(ymax, fabsf(yj));
-        ok &= fabsf(yj) < __builtin_inff();                // (no digits for an infinity or a NaN: the tables take it)
+        ymax = fmaxf(ymax, m);
+        if (yj != 0.0) ymin = fminf(ymin, m);
+        ok &= m < kInf;                                    // (no digits for an infinity or a NaN: the tables take it)
         y[j] = yj;
     }
     ymax = wave_reduce_dpp(ymax, [](float u, float v) { return fmaxf(u, v); });
+    ymin = wave_reduce_dpp(ymin, [](float u, float v) { return fminf(u, v); });
     cq = wave_sum_dpp(cq);
     const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & (kWave - 1)) == 0) { fmax_s[wave] = ymax; fsum_s[wave] = cq; }
+    if ((threadIdx.x & (kWave - 1)) == 0) { fmax_s[wave] = ymax; fmin_s[wave] = ymin; fsum_s[wave] = cq; }
     ok = __syncthreads_and(ok);
     if (threadIdx.x == 0) {
         prep->even[blockIdx.x] = ok;
         prep->ymax[blockIdx.x] = fmaxf(fmaxf(fmax_s[0], fmax_s[1]), fmaxf(fmax_s[2], fmax_s[3]));
+        prep->ymin[blockIdx.x] = fminf(fminf(fmin_s[0], fmin_s[1]), fminf(fmin_s[2], fmin_s[3]));
         prep->midx[blockIdx.x] = (fsum_s[0] + fsum_s[1]) + (fsum_s[2] + fsum_s[3]);
     }
 }
@@ -118,7 +125,7 @@ template <int BITS> struct LossTable {
     static constexpr int kRow = 1 << (BITS * kPer);        // entries of a look-up's table
     static constexpr int kFeatures = 16384 / kRow * kPer < 512 ? 16384 / kRow * kPer : 512;   // per chunk
     static constexpr size_t kTab = (size_t)kFeatures / kPer * kRow * 4;
-    static constexpr size_t kSingle = kPer == 2 ? (size_t)kFeatures * K * 4 : 0;   // the single tables, on the way
+    static constexpr size_t kSingle = kPer == 2 ? (size_t)kFeatures * (K + 1) * 4 : 0;   // levels and model, on the way
     static constexpr size_t kBytes = kTab + kSingle;
 };
 
@@ -134,7 +141,7 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
     constexpr int K = LT::K, kPer = LT::kPer, kRow = LT::kRow, kT = kLossPackedThreads;
     constexpr int kBatch = BITS <= 4 ? 4 : 2;              // units in use, and as many on the way
     float *const tab = (float *)smem, *const one = (float *)(smem + LT::kTab);
-    float *const zs = (float *)smem;                       // [512 / spb][spb], after the last chunk
+    double *const zs = (double *)smem;                     // [512 / spb][spb], after the last chunk
     const int tid = threadIdx.x, splits = kT / spb;
     const int smp = tid & (spb - 1), fs = tid / spb;       // (whole waves share fs)
     double acc = 0.0;
@@ -157,26 +164,37 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
             };
             request(fs, u);
             // tables (entries of padding features are zero)
-            float *const dst = kPer == 2 ? one : tab;
-            for (int e = tid; e < nfp * K; e += kT) {
-                const int j = e / K;
-                dst[e] = j < nf ? levels[(c0 + j) * K + e % K] * x[c0 + j] : 0.0f;
-            }
-            __syncthreads();
-            if constexpr (kPer == 2) {
+            if constexpr (kPer == 1) {
+                for (int e = tid; e < nfp * K; e += kT) {
+                    const int j = e / K;
+                    tab[e] = j < nf ? levels[(c0 + j) * K + e % K] * x[c0 + j] : 0.0f;
+                }
+                __syncthreads();
+            } else {
+                // the levels and the model first, then a pair's sums, with one rounding each
+                if constexpr (K >= 4) {
+                    const float4 *src = reinterpret_cast<const float4 *>(levels + c0 * K);
+                    for (int e = tid; e < nfp * K / 4; e += kT)
+                        reinterpret_cast<float4 *>(one)[e] = e < nf * K / 4 ? src[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                } else {
+                    for (int e = tid; e < nfp * K; e += kT) one[e] = e < nf * K ? levels[c0 * K + e] : 0.0f;
+                }
+                for (int j = tid; j < nfp; j += kT) one[nfp * K + j] = j < nf ? x[c0 + j] : 0.0f;
+                __syncthreads();
                 for (int r = tid; r < nfp / 2 * K; r += kT) {
                     const int p = r / K, hi = r % K;
-                    const float v = one[(2 * p + 1) * K + hi];
+                    const float x0 = one[nfp * K + 2 * p], v = one[(2 * p + 1) * K + hi] * one[nfp * K + 2 * p + 1];
+                    float *row = tab + p * kRow + hi * K;
+                    if constexpr (K >= 4) {
 #pragma unroll
-                    for (int q = 0; q < K; q += K < 4 ? K : 4) {
-                        if constexpr (K >= 4) {
+                        for (int q = 0; q < K; q += 4) {
                             float4 t = *reinterpret_cast<const float4 *>(one + 2 * p * K + q);
-                            t.x += v; t.y += v; t.z += v; t.w += v;
-                            *reinterpret_cast<float4 *>(tab + p * kRow + hi * K + q) = t;
-                        } else {
-                            tab[p * kRow + hi * K + q] = one[2 * p * K + q] + v;
-                            tab[p * kRow + hi * K + q + 1] = one[2 * p * K + q + 1] + v;
+                            t.x = fmaf(t.x, x0, v); t.y = fmaf(t.y, x0, v); t.z = fmaf(t.z, x0, v); t.w = fmaf(t.w, x0, v);
+                            *reinterpret_cast<float4 *>(row + q) = t;
                         }
+                    } else {
+                        row[0] = fmaf(one[2 * p * K], x0, v);
+                        row[1] = fmaf(one[2 * p * K + 1], x0, v);
                     }
                 }
                 __syncthreads();
@@ -206,11 +224,11 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
             }
             __syncthreads();
         }
-        zs[fs * spb + smp] = (z[0] + z[1]) + (z[2] + z[3]);
+        zs[fs * spb + smp] = ((double)z[0] + (double)z[1]) + ((double)z[2] + (double)z[3]);
         __syncthreads();
         if (tid < spb && i < n) {
             double zt = 0.0;
-            for (int v = 0; v < splits; ++v) zt += (double)zs[v * spb + tid];
+            for (int v = 0; v < splits; ++v) zt += zs[v * spb + tid];
             const double r = zt - (double)b[i];
             acc += r * r;
         }
@@ -220,30 +238,34 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
 }
 
 // Packed copy 2.  Evenly spaced levels go to the matrix cores: a value is mid_j + (code - off) delta_j, so
-// a_i^T x = sum_j mid_j x_j + sum_j (code_ij - off) y_j  with y_j = delta_j x_j.  y goes to 32-bit fixed
-// point in four signed base-256 digits kept in LDS; a workgroup takes tiles of 64 samples, its eight waves
-// split the 64-feature blocks (one v_mfma_i32_16x16x64_i8 per 16 samples x 64 features, four sample tiles
-// sharing one accumulator as in the SGD kernels), the partial sums meet in LDS and wave 0 squares the
-// residuals.  Exact integer sums; the only rounding before the residual is y_j -> fixed point (2^-29 of max
-// |y|).  Other level tables (the flags of k_loss_prepare say so; all blocks alike), and problems whose
-// digits do not fit in LDS (NKB == 0), go through loss_copy2_table, and so does a model that has no digits.
+// a_i^T x = sum_j mid_j x_j + sum_j (code_ij - off) y_j  with y_j = delta_j x_j.  y goes to fixed point in eight
+// signed base-256 digits kept in LDS (as many as the sixteen rows of v_mfma_i32_16x16x64_i8 hold twice over: they
+// cost no instruction more than four, 65,536 x 2,048 codes of 6 bits 44 us a call with either); a workgroup takes
+// tiles of 64 samples, its eight waves split the 64-feature blocks (one instruction per 16 samples x 64 features,
+// two sample tiles sharing an accumulator), the partial sums meet in LDS and wave 0 squares the residuals.  Exact
+// integer sums; the unit of y is 2^-61 of the largest, and a model with an element below 2^-37 of that, which would
+// keep fewer bits than fp32 has, goes through loss_copy2_table.  So do other level tables (the flags of
+// k_loss_prepare say so; all blocks alike), a model with no digits, and problems whose digits do not fit in LDS
+// (NKB == 0: more than 19,904 features).
 template <int BITS>
 __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     const uint32_t *__restrict__ p2, const float *__restrict__ levels, const float *__restrict__ b,
     const float *__restrict__ x, int64_t n, int64_t d, int64_t n_pad, int64_t d32, int NKB, int spb,
-    const LossPrep *__restrict__ prep, const float *__restrict__ y, double *__restrict__ partial)
+    const LossPrep *__restrict__ prep, const double *__restrict__ y, double *__restrict__ partial)
 {
     constexpr int HW = kOpDwords<BITS>, kW = kLossPackedThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double scratch[kW + 1];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int n16 = lane & 15, q4 = lane >> 4;
-    int ok_all = NKB > 0;
-    float ymax = 0.0f, cq = 0.0f;
+    int ok_all = 0;
+    float ymax = 0.0f;
+    double cq = 0.0;
     if (NKB > 0) {
         ok_all = prep->even[lane];                         // (kLossPrepBlocks == kWave)
         ymax = wave_reduce_dpp(prep->ymax[lane], [](float u, float v) { return fmaxf(u, v); });
         cq = wave_sum_dpp(prep->midx[lane]);
+        ok_all &= prep->ymin[lane] >= ldexpf(ymax, -37);
     }
     if (!__syncthreads_and(ok_all)) {
         const double acc = loss_copy2_table<BITS>(p2, levels, b, x, n, d, n_pad, spb, smem);
@@ -251,32 +273,42 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
         if (tid == 0) partial[blockIdx.x] = tot;
         return;
     }
-    const int nfeat = NKB * 64;
-    int8_t *const ydig = (int8_t *)smem;                                  // [NKB][4 digits][4 q][16]
-    long long *const zpart = (long long *)(smem + (size_t)NKB * 256);     // [kW][64]
-    int8_t *const zeros = (int8_t *)(smem + (size_t)NKB * 256 + kW * 64 * 8);   // [16]
+    int8_t *const ydig = (int8_t *)smem;                                  // [NKB][8 digits][4 q][16]
+    longlong2 *const zpart = (longlong2 *)(smem + (size_t)NKB * 512);     // [kW][64]
+    int8_t *const zeros = (int8_t *)(smem + (size_t)NKB * 512 + kW * 64 * 16);   // [16]
     if (tid < 4) reinterpret_cast<int *>(zeros)[tid] = 0;
-    // 2^ky |y| < 2^29, however small the model (the sums are scaled back in fp64)
+    // 2^ky |y| < 2^61, however small the model (the sums are scaled back in fp64)
     int ey = 0;
     (void)frexpf(ymax, &ey);
-    const int ky = ymax > 0.0f ? 29 - ey : 0;
-    for (int j = tid; j < nfeat; j += kLossPackedThreads) {
-        int half, byte;
-        code_slot<BITS>(j & 31, half, byte);
-        const int pos = (2 * ((j >> 5) & 1) + half) * 16 + byte;
-        store_digits(ydig + (j >> 6) * 256 + pos, signed_digits(__float2int_rn(ldexpf(j < d ? y[j] : 0.0f, ky))));
+    const int ky = ymax > 0.0f ? 60 - ey : 0;              // (ymax is rounded: one bit to spare)
+    // four features whose codes are the bytes of one dword at a time: their digits are stored as dwords, too
+    for (int e = tid; e < NKB * 16; e += kLossPackedThreads) {
+        const int unit = e >> 3, half = (e >> 2) & 1, dword = e & 3;      // (unit: a group of 32 features)
+        uint32_t lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = 32 * unit + slot_code<BITS>(half, dword, i);
+            const uint64_t dg = signed_digits_64<8>(__double2ll_rn(ldexp(j < d ? y[j] : 0.0, ky)));
+            lo[i] = (uint32_t)dg;
+            hi[i] = (uint32_t)(dg >> 32);
+        }
+        bytes_transpose(lo);
+        bytes_transpose(hi);
+        uint32_t *const at = reinterpret_cast<uint32_t *>(ydig + (unit >> 1) * 512 + (2 * (unit & 1) + half) * 16) + dword;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { at[16 * k] = lo[k]; at[16 * (k + 4)] = hi[k]; }
     }
     __syncthreads();
 
     // ---- tiles of 64 samples
-    const int dig_off = (n16 & 3) * 64 + q4 * 16, slot_of = n16 >> 2;
+    const int dig_off = (n16 & 7) * 64 + q4 * 16, slot_of = n16 >> 3;
     const int zero_off = (int)(zeros - ydig);
     const uint32_t shift = op_shift<BITS>(q4 & 1);
     const int64_t NT = n_pad / 64;
     double acc = 0.0;
     for (int64_t T = blockIdx.x; T < NT; T += gridDim.x) {
         const int64_t row0 = 64 * T;
-        v4i c = {0, 0, 0, 0};
+        v4i c[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
         for (int kb = wave; kb < NKB; kb += kW) {
             // lane = sample 16 sl + n16 of the tile, 16 codes (half q4 & 1) of feature group 2 kb + q4 / 2;
             // a padding group (odd number of groups) reads the block's first group: its digits are zero
@@ -292,18 +324,25 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
             }
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) {
-                const v4i ad = *reinterpret_cast<const v4i *>(ydig + (slot_of == sl ? kb * 256 + dig_off : zero_off));
-                c = __builtin_amdgcn_mfma_i32_16x16x64_i8(ad, expand_codes<BITS>(w[sl], shift), c, 0, 0, 0);
+                const v4i ad = *reinterpret_cast<const v4i *>(ydig + (slot_of == (sl & 1) ? kb * 512 + dig_off : zero_off));
+                c[sl >> 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ad, expand_codes<BITS>(w[sl], shift), c[sl >> 1], 0, 0, 0);
             }
         }
-        zpart[wave * 64 + lane] = combine_digits(c);      // lane = sample of the tile
+        // this lane: sample tiles q4 / 2 (.x) and 2 + q4 / 2 (.y), the lower (q4 even) or the upper four digits
+        zpart[wave * 64 + lane] = make_longlong2(combine_digits(c[0]), combine_digits(c[1]));
         __syncthreads();
         if (wave == 0) {
-            long long z = 0;
+            // lane = sample 16 q4 + n16 of the tile
+            long long lo = 0, hi = 0;
+            const int from = 32 * (q4 & 1) + n16;
 #pragma unroll
-            for (int v = 0; v < kW; ++v) z += zpart[v * 64 + lane];
+            for (int v = 0; v < kW; ++v) {
+                const longlong2 p = zpart[v * 64 + from], q = zpart[v * 64 + from + 16];
+                lo += q4 & 2 ? p.y : p.x;
+                hi += q4 & 2 ? q.y : q.x;
+            }
             if (row0 + lane < n) {
-                const double r = ldexp((double)z, -ky) + (double)cq - (double)b[row0 + lane];
+                const double r = ldexp(fma((double)hi, 4294967296.0, (double)lo), -ky) + cq - (double)b[row0 + lane];
                 acc += r * r;
             }
         }
@@ -313,14 +352,13 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     if (tid == 0) partial[blockIdx.x] = tot;
 }
 
-// Dynamic LDS of k_loss_copy2's matrix-core path; the kernel's static part (scratch of the block-wide sums and the
-// vote) has to fit beside it.
+// LDS of k_loss_copy2's matrix-core path; the kernel's static part (scratch of the block-wide sums and the vote) has
+// to fit beside it.
 constexpr size_t kLossStaticLds = 1024;
 inline size_t loss_mfma_lds_bytes(int NKB)
 {
-    return (size_t)NKB * 256 + (kLossPackedThreads / kWave) * 64 * 8 + 16;
+    return (size_t)NKB * 512 + (kLossPackedThreads / kWave) * 64 * 16 + 16;
 }
-inline bool loss_mfma_fits(int NKB, int lds_limit) { return loss_mfma_lds_bytes(NKB) + kLossStaticLds <= (size_t)lds_limit; }
 
 // Packed copy 1 (feature-major units: one feature x 32 samples).  A lane takes one feature of a group of 64
 // (or of 32, two sample groups to a wave, where the problem has no more) and keeps the 32 partial dot products
@@ -463,7 +501,7 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
         return blocks;
     }
     int NKB = (int)((lay.d32 + 1) / 2);
-    if (!prep || !loss_mfma_fits(NKB, lds_limit)) NKB = 0;   // through the tables, whatever the levels
+    if (!prep || loss_mfma_lds_bytes(NKB) + kLossStaticLds > (size_t)lds_limit) NKB = 0;   // through the tables, whatever the levels
     size_t shmem = LossTable<BITS>::kBytes < 4096 ? 4096 : LossTable<BITS>::kBytes;
     if (NKB > 0 && loss_mfma_lds_bytes(NKB) > shmem) shmem = loss_mfma_lds_bytes(NKB);
     if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy2<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)))
@@ -473,10 +511,10 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
     while (spb > 64 && (lay.n + spb - 1) / spb < 2 * cus) spb >>= 1;
     const int64_t NT = lay.n_pad / 64;
     const int blocks = (int)(NT < 1024 ? NT : 1024);
-    float *y = (float *)(prep + 1);
+    double *y = (double *)(prep + 1);
     if (NKB > 0)
         hipLaunchKernelGGL(k_loss_prepare, dim3(kLossPrepBlocks), dim3(256), 0, s, levels, x, lay.d, 1 << BITS,
-                           BITS == 8 ? 128.0f : 0.0f, prep, y);
+                           BITS == 8 ? 128.0 : 0.0, prep, y);
     hipLaunchKernelGGL(k_loss_copy2<BITS>, dim3(blocks), dim3(kLossPackedThreads), shmem, s, p, levels, b, x, lay.n,
                        lay.d, lay.n_pad, lay.d32, NKB, spb, prep, y, partial);
     return blocks;
@@ -570,7 +608,7 @@ extern "C" int zipml_loss(void *stream, const float *A_dev, int64_t lda, const v
             HIP_FAILED(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)))
             return ZIPML_ELAUNCH;
         // (the matrix-core path needs room for the preparation's results)
-        LossPrep *prep = workspace_bytes >= sizeof(LossPrep) + (size_t)d * 4 && knob(ZIPML_KNOB_NO_MATRIX_CORES) <= 0
+        LossPrep *prep = workspace_bytes >= sizeof(LossPrep) + (size_t)d * 8 && knob(ZIPML_KNOB_NO_MATRIX_CORES) <= 0
                              ? (LossPrep *)workspace_dev : nullptr;
 #define ZIPML_LOSS(B) case B: blocks = launch_loss_packed<B>(s, p, copy, lay, levels_dev, b_dev, x_dev, prep, cus, lds, sums.p); break
         switch (bits) {

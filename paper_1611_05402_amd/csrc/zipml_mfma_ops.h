@@ -49,6 +49,27 @@ __device__ __forceinline__ void code_slot(int f, int &half, int &byte)
     }
 }
 
+// The other way: the code whose byte is i of dword D of a half.
+template <int BITS>
+__device__ __forceinline__ int slot_code(int half, int D, int i)
+{
+    if (BITS == 4) return 16 * half + 8 * (D >> 1) + 2 * i + (D & 1);
+    if (BITS == 2) return 16 * half + 4 * i + D;
+    if (BITS == 1) return 8 * i + 4 * half + D;
+    return 16 * half + 4 * D + i;
+}
+
+// Byte k of dword i <-> byte i of dword k.
+__device__ __forceinline__ void bytes_transpose(uint32_t (&v)[4])
+{
+    const uint32_t a = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u), b = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u);
+    const uint32_t c = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u), d = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
+    v[0] = __builtin_amdgcn_perm(c, a, 0x05040100u);
+    v[1] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+    v[2] = __builtin_amdgcn_perm(d, b, 0x05040100u);
+    v[3] = __builtin_amdgcn_perm(d, b, 0x07060302u);
+}
+
 // The 16 codes of a half -> 16 signed bytes (code - off; off = 128 at 8 bits, else 0).  shift: op_shift<BITS>(half).
 template <int BITS>
 __device__ __forceinline__ v4i expand_codes(const uint32_t (&p)[kOpDwords<BITS>], uint32_t shift = 0)
@@ -104,6 +125,13 @@ __device__ __forceinline__ v4i expand_codes(const uint32_t (&p)[kOpDwords<BITS>]
 __device__ __forceinline__ uint32_t signed_digits(int v)
 {
     return ((uint32_t)v + 0x00808080u) ^ 0x00808080u;
+}
+// N signed base-256 digits, the bytes of the result (|v| < 2^(8 N - 1) - 2^(8 N - 8)).
+template <int N>
+__device__ __forceinline__ uint64_t signed_digits_64(long long v)
+{
+    constexpr uint64_t kHalf = 0x8080808080808080ull >> (8 * (9 - N));       // 128 in the N - 1 lower bytes
+    return ((uint64_t)v + kHalf) ^ kHalf;
 }
 // Digit k of an element goes to plane k: 64 bytes apart.
 __device__ __forceinline__ void store_digits(int8_t *plane0, uint32_t dg)

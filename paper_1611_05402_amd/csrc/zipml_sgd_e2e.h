@@ -73,13 +73,6 @@ __device__ __forceinline__ long long fixed_from_float(float v, int emax, int top
     const long long f = sh >= 0 ? (long long)((uint64_t)m << sh) : (long long)(m >> (sh > -31 ? -sh : 31));
     return (b >> 31) ? -f : f;
 }
-// N signed base-256 digits, the bytes of the result (|v| < 2^(8 N - 1) - 2^(8 N - 8)).
-template <int N>
-__device__ __forceinline__ uint64_t signed_digits_64(long long v)
-{
-    constexpr uint64_t kHalf = 0x8080808080808080ull >> (8 * (9 - N));       // 128 in the N - 1 lower bytes
-    return ((uint64_t)v + kHalf) ^ kHalf;
-}
 constexpr int kRDigits = 7, kRTop = 30;     // residuals: 24 + 30 bits
 constexpr int kLDigits = 6, kLTop = 22;     // levels: 24 + 22 bits
 

@@ -168,6 +168,36 @@ def test_loss_of_small_models_and_of_no_numbers(bits):
             assert not np.isfinite(p.loss(dev(x), packed_copy=copy))
 
 
+@pytest.mark.parametrize("large", [1e6, 1e15])
+@pytest.mark.parametrize("bits,even", [(b, e) for b in range(1, 9) for e in (True, False) if b > 1 or e])
+def test_loss_of_small_products_beside_a_large_one(bits, even, large):
+    """One element of the model is 10^6 times the others and meets only the level zero: the dot products are those of
+    the others, each to (d + 4) 2^-24 of the sum of its magnitudes.  The labels are the exact dot products, so the
+    loss is the mean square of their errors.  Also 10^15 times: more than the digits of the matrix cores span."""
+    rng = np.random.default_rng(bits)
+    n, d, K = 100, 256, 1 << bits
+    x = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    x[100] = large
+    A = rng.uniform(0, 1, (n, d)).astype(np.float32)
+    A[:, 100] = 0.0
+    L = oracle.levels_uniform(np.zeros(d, np.float32), np.ones(d, np.float32), bits)
+    if not even:
+        L[:, 1:-1] = np.sort(rng.uniform(0, 1, (d, K - 2)), axis=1)
+    p = GpuProblem(A, np.zeros(n, np.float32), bits, 32)
+    p.set_levels(L)
+    p.quantize(3, 0)
+    for copy in (1, 2):
+        say("small products beside a large one", bits, even, large, copy)
+        codes = p.codes(copy)
+        assert not codes[:, 100].any()
+        v = np.take_along_axis(L, codes.astype(np.int64).T, axis=1).T.astype(np.float64)
+        b = (v @ x.astype(np.float64)).astype(np.float32)
+        p.b.copy_(dev(b))
+        mag = np.abs(v) @ np.abs(x.astype(np.float64))
+        got = p.loss(dev(x), packed_copy=copy)
+        assert got <= 0.5 * float(np.mean((mag * (d + 4) * 2.0 ** -24) ** 2)), got
+
+
 SOLO = [(n, d, B) for n, d, B in [(64, 1, 4), (96, 8, 8), (128, 33, 16), (192, 64, 64), (256, 65, 32), (192, 100, 96), (640, 130, 64),
                                  (640, 255, 160), (512, 256, 256), (1024, 64, 512), (2048, 31, 1024)]]
 
