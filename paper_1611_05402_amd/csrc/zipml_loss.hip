@@ -364,9 +364,11 @@ inline size_t loss_mfma_lds_bytes(int NKB)
 // (or of 32, two sample groups to a wave, where the problem has no more) and keeps the 32 partial dot products
 // of its sample group in registers through all its features; the level tables of a chunk of features,
 // multiplied by x, are in LDS with their rows K + 1 words apart (the lanes look up different rows).  At
-// the end the 32 sums of a lane are added over the lanes by halving: a lane hands half of its sums to the lane
-// it is paired with and takes the other half of that lane's, 31 exchanges instead of 32 for each of
-// five or six steps.  A block's eight waves take `sgb` (1 to 8) sample groups, and share the features of
+// the end the 32 sums of a lane are added over the lanes by halving, in fp64: a lane hands half of its sums to the
+// lane it is paired with and takes the other half of that lane's, 31 exchanges instead of 32 for each of
+// five or six steps.  Every eighth product the 32 sums go to second ones: one fp32 chain over every 64th
+// feature had an error of 3.0e-7 of the dot product (8 bits, 16,384 features), this 1.2e-7 -- chains over every
+// 256th would have 1.7e-7 --, and the compiler finds more to overlap (65,536 x 2,048, 3 bits 98 -> 75 us a call).  A block's eight waves take `sgb` (1 to 8) sample groups, and share the features of
 // one where there are fewer groups than that.
 constexpr int kLoss1Threads = 512;
 template <int BITS> constexpr int kLoss1Features = 16384 / ((1 << BITS) + 1) / 64 * 64 < 512 ? 16384 / ((1 << BITS) + 1) / 64 * 64 : 512;
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(kLoss1Threads) void k_loss_copy1(
     extern __shared__ __align__(16) unsigned char smem[];
     float *const tab = (float *)smem;
     __shared__ double scratch[kW + 1];
-    __shared__ float zs[kW][64];
+    __shared__ double zs[kW][64];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int lpg = d32 == 1 ? 32 : 64;                    // lanes per sample group
     const int gpw = kWave / lpg;                           // sample groups per wave
@@ -390,9 +392,10 @@ __global__ __launch_bounds__(kLoss1Threads) void k_loss_copy1(
     double acc = 0.0;
     for (int64_t T = blockIdx.x; T * sgb * gpw < n32; T += gridDim.x) {
         const int64_t rg = (T * sgb + slot) * gpw + sub, rgc = rg < n32 ? rg : n32 - 1;
-        float z[32];
+        float z[32], zlong[32];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) z[k] = 0.0f;
+        for (int k = 0; k < 32; ++k) z[k] = zlong[k] = 0.0f;
+        int terms = 0;
         for (int64_t c0 = 0; c0 < d; c0 += FC) {
             const int nf = d - c0 < FC ? (int)(d - c0) : FC, nfp = (nf + 63) & ~63;
             for (int e = tid; e < nfp * K; e += kLoss1Threads) {
@@ -410,24 +413,31 @@ __global__ __launch_bounds__(kLoss1Threads) void k_loss_copy1(
                 const float *t = tab + f * (K + 1);
 #pragma unroll
                 for (int k = 0; k < 32; ++k) z[k] += t[unit_code<BITS>(u, k)];
+                if ((++terms & 7) == 0) {
+#pragma unroll
+                    for (int k = 0; k < 32; ++k) { zlong[k] += z[k]; z[k] = 0.0f; }
+                }
             }
             __syncthreads();
         }
         {
+            double zd[32];
+#pragma unroll
+            for (int k = 0; k < 32; ++k) zd[k] = (double)zlong[k] + (double)z[k];
             if (lpg == 64) {
 #pragma unroll
-                for (int k = 0; k < 32; ++k) z[k] += __shfl_xor(z[k], 32, kWave);
+                for (int k = 0; k < 32; ++k) zd[k] += __shfl_xor(zd[k], 32, kWave);
             }
 #pragma unroll
             for (int h = 16; h >= 1; h >>= 1) {
                 const bool up = (lane & h) != 0;
 #pragma unroll
                 for (int k = 0; k < h; ++k) {
-                    const float mine = up ? z[k + h] : z[k], give = up ? z[k] : z[k + h];
-                    z[k] = mine + __shfl_xor(give, h, kWave);
+                    const double mine = up ? zd[k + h] : zd[k], give = up ? zd[k] : zd[k + h];
+                    zd[k] = mine + __shfl_xor(give, h, kWave);
                 }
             }
-            zs[wave][lane] = z[0];                         // of sample lane & 31 of the group
+            zs[wave][lane] = zd[0];                        // of sample lane & 31 of the group
         }
         __syncthreads();
         // one thread per sample: slot tid / 64, in it sub group (tid / 32) % gpw
@@ -436,7 +446,7 @@ __global__ __launch_bounds__(kLoss1Threads) void k_loss_copy1(
             const int64_t g = (T * sgb + sl) * gpw + ln / lpg, i = g * 32 + (ln & 31);
             if (ln % lpg < 32 && g < n32 && i < n) {
                 double zt = 0.0;
-                for (int v = 0; v < splits; ++v) zt += (double)zs[v * sgb + sl][ln];
+                for (int v = 0; v < splits; ++v) zt += zs[v * sgb + sl][ln];
                 const double r = zt - (double)b[i];
                 acc += r * r;
             }

@@ -198,6 +198,27 @@ def test_loss_of_small_products_beside_a_large_one(bits, even, large):
         assert got <= 0.5 * float(np.mean((mag * (d + 4) * 2.0 ** -24) ** 2)), got
 
 
+@pytest.mark.parametrize("bits", [3, 6, 8])
+def test_error_of_long_dot_products_on_copy_1(bits):
+    """Root mean square error of the dot products over 16,384 features, against that of 256 fp32 chains of 64 terms
+    whose ends are added pairwise: (256 * 64 * 65 / 2 + 6 * 16384 + 9 * 4096) / 16384 = 40.7 squared roundings of an
+    rms term each, a rounding at most 2^-24 / sqrt(3) in rms.  The labels are the exact dot products."""
+    say("long dot products", bits)
+    rng = np.random.default_rng(bits)
+    n, d = 512, 16384
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    x = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    p = GpuProblem(A, np.zeros(n, np.float32), bits, 32)
+    p.make_levels(zipml.UNIFORM, 0, lo=-np.ones(d), hi=np.ones(d))
+    p.quantize(3, 0)
+    L = p.levels.cpu().numpy()
+    z = np.take_along_axis(L, p.codes(1).astype(np.int64).T, axis=1).T.astype(np.float64) @ x.astype(np.float64)
+    p.b.copy_(dev(z.astype(np.float32)))
+    own = np.mean((z - z.astype(np.float32)) ** 2)                # the rounding of the labels
+    err = np.sqrt(max(0.0, 2.0 * p.loss(dev(x), packed_copy=1) - own)) / np.sqrt(np.mean(z * z))
+    assert err <= np.sqrt(40.7 / 3) * 2.0 ** -24, err
+
+
 SOLO = [(n, d, B) for n, d, B in [(64, 1, 4), (96, 8, 8), (128, 33, 16), (192, 64, 64), (256, 65, 32), (192, 100, 96), (640, 130, 64),
                                  (640, 255, 160), (512, 256, 256), (1024, 64, 512), (2048, 31, 1024)]]
 
