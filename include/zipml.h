@@ -9,7 +9,8 @@
  *
  * General conventions
  *   - Plain C ABI.  Pointers named *_dev are DEVICE pointers owned by the caller; the library never
- *     allocates or frees device memory and keeps no pointer after a call returns.  Pointers named
+ *     allocates or frees device memory and keeps no pointer of the caller's after a call returns
+ *     (zipml_loss keeps some pinned host memory of its own, see there).  Pointers named
  *     *_host are host pointers.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  All device work is
  *     enqueued on it.  Calls that return a host value (zipml_loss, zipml_sgd_status, the OPTIMAL
@@ -258,8 +259,12 @@ int zipml_sgd_status(void *stream, const void *workspace_dev, size_t workspace_b
 
 /* Loss F(x) = 1/(2n) sum_i (a_i^T x - b_i)^2 (Sec. 1 eq. (1) with the square loss).  With A_dev
  * the exact fp32 rows are used; with A_dev == NULL the rows are decoded from one packed copy
- * (`copy` = 1 or 2) and levels_dev.  Dot products in fp32, squares and their sum in fp64.
- * Synchronises the stream and writes *loss_host. */
+ * (`copy` = 1 or 2) and levels_dev.  Dot products in fp32 or better (levels and model keep at least
+ * their fp32 bits: products and sums in fp32, or in exact integer sums for evenly spaced levels),
+ * squares and their sum in fp64.  Synchronises the stream and writes *loss_host; ZIPML_ELAUNCH, with
+ * nothing enqueued, on a stream that is being captured.  The partial sums arrive in pinned host memory of
+ * 16 KiB a call in flight, of which the library keeps up to eight for later calls until the process
+ * ends (its one allocation; nothing of it is on the device). */
 int zipml_loss(void *stream, const float *A_dev, int64_t lda, const void *packed_dev, int copy,
                const float *levels_dev, int bits, const float *b_dev, const float *x_dev,
                int64_t n, int64_t d, double *loss_host, void *workspace_dev,

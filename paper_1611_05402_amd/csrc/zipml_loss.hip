@@ -460,7 +460,8 @@ __global__ __launch_bounds__(kLoss1Threads) void k_loss_copy1(
 // Pinned host memory for the blocks' partial sums: the kernels store them there directly and the call adds
 // them up after it has waited for the stream, in place of a second kernel and a copy back (a loss over
 // 4,096 x 64 values: 31 -> 19 us).  A call takes a buffer for its duration; at most kMax of them (16 KiB
-// each) are kept for later calls, of any thread and stream.
+// each) are kept for later calls, of any thread and stream.  A buffer that a kernel may still write to is never
+// given back: abandon().
 class LossBuffer {
 public:
     LossBuffer()
@@ -469,8 +470,13 @@ public:
             std::lock_guard<std::mutex> lock(mutex());
             if (count() > 0) p = kept()[--count()];
         }
-        if (!p && HIP_FAILED(hipHostMalloc((void **)&p, kLossMaxBlocks * sizeof(double), hipHostMallocPortable | hipHostMallocMapped)))
+        if (p) return;
+        // (an allocation is no part of a graph that another thread may be recording, and must not end its recording)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        if (HIP_FAILED(hipHostMalloc((void **)&p, kLossMaxBlocks * sizeof(double), hipHostMallocPortable | hipHostMallocMapped)))
             p = nullptr;
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     ~LossBuffer()
     {
@@ -481,6 +487,7 @@ public:
         }
         (void)hipHostFree(p);
     }
+    void abandon() { p = nullptr; }
     LossBuffer(const LossBuffer &) = delete;
     LossBuffer &operator=(const LossBuffer &) = delete;
     double *p = nullptr;
@@ -597,6 +604,9 @@ extern "C" int zipml_loss(void *stream, const float *A_dev, int64_t lda, const v
         if (!aligned16(packed_dev) || !aligned16(levels_dev)) return ZIPML_EALIGN;
     }
     hipStream_t s = entry_stream(stream);
+    // a stream that is being recorded cannot be waited for: refused before anything becomes part of the graph
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (HIP_FAILED(hipStreamIsCapturing(s, &capture)) || capture != hipStreamCaptureStatusNone) return ZIPML_ELAUNCH;
     LossBuffer sums;
     if (!sums.p) return ZIPML_ELAUNCH;
     int blocks = 0;
@@ -629,7 +639,11 @@ extern "C" int zipml_loss(void *stream, const float *A_dev, int64_t lda, const v
         if (blocks < 0) return blocks;
     }
     const bool launched = !HIP_FAILED(hipGetLastError());
-    if (HIP_FAILED(hipStreamSynchronize(s)) || !launched) return ZIPML_ELAUNCH;
+    if (HIP_FAILED(hipStreamSynchronize(s))) {
+        sums.abandon();
+        return ZIPML_ELAUNCH;
+    }
+    if (!launched) return ZIPML_ELAUNCH;
     double tot = 0.0;
     for (int i = 0; i < blocks; ++i) tot += sums.p[i];
     *loss_host = tot / (2.0 * (double)n);

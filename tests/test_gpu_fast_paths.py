@@ -219,6 +219,33 @@ def test_error_of_long_dot_products_on_copy_1(bits):
     assert err <= np.sqrt(40.7 / 3) * 2.0 ** -24, err
 
 
+def test_loss_on_a_stream_that_is_being_captured_is_refused():
+    """Before anything is enqueued: the recording goes on, and holds nothing of the call."""
+    say("loss under capture")
+    rng = np.random.default_rng(0)
+    n, d, bits = 300, 40, 3
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b, xh = rng.standard_normal(n).astype(np.float32), rng.standard_normal(d).astype(np.float32)
+    p = GpuProblem(A, b, bits, 32)
+    p.make_levels(zipml.UNIFORM, 0, lo=-np.ones(d), hi=np.ones(d))
+    p.quantize(3, 0)
+    x, t = dev(xh), torch.zeros(64, device="cuda:0")
+    ref = [p.loss(x), p.loss(x, 1), p.loss(x, 2)]
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        t.add_(1.0)
+        for copy in (0, 1, 2):
+            with pytest.raises(zipml.ZipmlError) as e:
+                p.loss(x, copy)
+            assert e.value.code == zipml.ELAUNCH
+    for k in range(3):
+        g.replay()
+        assert [p.loss(x), p.loss(x, 1), p.loss(x, 2)] == ref
+        torch.cuda.synchronize()
+        assert bool((t == k + 1).all())
+
+
 SOLO = [(n, d, B) for n, d, B in [(64, 1, 4), (96, 8, 8), (128, 33, 16), (192, 64, 64), (256, 65, 32), (192, 100, 96), (640, 130, 64),
                                  (640, 255, 160), (512, 256, 256), (1024, 64, 512), (2048, 31, 1024)]]
 
