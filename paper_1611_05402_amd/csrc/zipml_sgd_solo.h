@@ -45,19 +45,20 @@ constexpr int kSoloMaxSlots = 16;
 constexpr int kSoloMaxBatch = 2048;
 
 // LDS beside the ring of slots and the level tables: digits of y (at most 4 blocks of 64 features) and of
-// r, per-block and per-wave figures, residuals, model, the parts of the dot products
-__host__ __device__ inline int solo_fixed_lds(int B)
+// r, per-block and per-wave figures, residuals and model (uneven levels of 4 and more bits), the parts of the dot
+// products
+__host__ __device__ inline int solo_fixed_lds(int B, int bits)
 {
     const int NB = (B + 63) / 64;
-    return 1024 + NB * 256 + NB * 16 + 512 + NB * 256 + 1024 + 4 * 256 * 4 + 64;
+    return 2048 + NB * 512 + NB * 16 + 512 + (bits > 3 ? NB * 256 + 1024 : 0) + 4 * 256 * 4 + 64;
 }
 
-// Bytes of the tables of the uneven-level loop: pair tables of the dot pass (at most 8 levels), or the level
-// rows K + 1 words apart (0: they stay in memory).
+// Bytes of the tables of the uneven-level loop: pair tables of the dot pass and the lower digits of the levels (at most
+// 8 levels), or the level rows K + 1 words apart (0: they stay in memory).
 __host__ __device__ inline int solo_table_bytes(int bits, int d32)
 {
     const int K = 1 << bits, d_pad = 32 * d32;
-    if (K <= 8) return d_pad / 2 * K * K * 4;
+    if (K <= 8) return d_pad / 2 * K * K * 4 + d_pad * 6 * K;
     const int rows = d_pad * (K + 1) * 4;
     return rows <= 72 * 1024 ? (rows + 15) & ~15 : 0;
 }
@@ -67,8 +68,9 @@ inline bool solo_plan(const Layout &lay, int B, int lds_limit, SoloArgs &a)
 {
     // (the loaders' offsets inside a packed copy are 32 bits wide)
     if (lay.d32 > 8 || B > kSoloMaxBatch || lay.bytes() >= ((size_t)1 << 32)) return false;
-    // Where the general loop is the faster one, on even or uneven levels (us a step here, there): the pair tables
-    // of uneven 3-bit levels are rebuilt every step, whatever the batch (256 features, 32 samples: 3.85, 2.62); the
+    // Where the general loop is the faster one (us a step here, there; the line is drawn by uneven levels, and even
+    // ones, which the host cannot tell, follow it): the pair tables of uneven 3-bit levels are rebuilt every step,
+    // whatever the batch (256 features, 32 samples: 3.85, 2.62; 128 samples 5.2, 5.0, even levels 3.4, 3.5); the
     // bytes of wide codes on many features pass through LDS twice (7 bits, 256 features, 128 samples: 6.5, 4.0; 8
     // bits, 128 features, 8 samples, uneven: 4.6, 3.8); one group of features leaves most waves without a
     // feature tile when the batch is large (7 bits, 12 features, 1,024 samples: 5.6, 4.2).
@@ -89,7 +91,7 @@ inline bool solo_plan(const Layout &lay, int B, int lds_limit, SoloArgs &a)
     if (sl.instr > kSoloMaxInstr) return false;
     // (a table that gives way to the slots is read from memory: 7 bits, 64 features, 512 samples 13.1, 6.1)
     const int table = lay.bits > 1 ? solo_table_bytes(lay.bits, a.d32) : 0;
-    return solo_fixed_lds(B) + 2048 + table + 2 * sl.bytes <= a.lds_bytes;
+    return solo_fixed_lds(B, lay.bits) + 2048 + table + 2 * sl.bytes <= a.lds_bytes;
 }
 
 template <int BITS> int launch_solo(hipStream_t s, const SoloArgs &a);

@@ -7,17 +7,24 @@
 //   - loader waves keep a ring of steps in LDS, ahead of the step at work, with loads that go from memory
 //     to LDS directly (no registers, nothing to wait for in the other waves);
 //   - the other waves only ever touch LDS.  Evenly spaced levels run on v_mfma_i32_16x16x64_i8 against
-//     fixed-point digits as in zipml_sgd_mfma.h; the scale of the residuals is that of a block of 64 samples
-//     (one wave's), the scale of y = delta x is a bound that every wave forms from the last step's largest
-//     |y| and |r|, so a step has two workgroup barriers: dot pass and residuals | gradient pass and update.
-//     Where a minibatch and the features fit one wave (64 x 64) that wave runs the whole step and meets the
-//     loader only.
-//   - Uneven levels of 2 or 3 bits (at most 8 levels): the dot pass looks up T_j[c] + T_j'[c'] (T_j = L_j x_j)
+//     fixed-point digits as in zipml_sgd_mfma.h, but eight of them: the general loop on one workgroup computes
+//     in fp32 throughout, and with the 29 bits of four digits a small residual or model element beside a large
+//     one lost bits (one residual in 64 larger by 10^6: worst coordinate of the gradient off by 9e-5 instead of
+//     6e-7).  Eight digits hold all 24 bits of a number down to 2^-35 of the largest, whatever its size; the sixteen
+//     rows of the instruction hold them twice over, so there are no more instructions than with four.  The scale
+//     of the residuals is that of a block of 64 samples (one wave's), the scale of y = delta x is a bound that
+//     every wave forms from the last step's largest |y| and |r|, so a step has two workgroup barriers: dot pass
+//     and residuals | gradient pass and update.  Where a minibatch and the features fit one wave (64 x 64) that
+//     wave runs the whole step and meets the loader only.
+//   - Uneven levels of 2 or 3 bits (at most 8 levels): the dot pass looks up L_j[c] x_j + L_j'[c'] x_j'
 //     of two features at once in LDS; in the gradient pass a lane owns one feature, so that a level look-up is
-//     a byte permute from registers, four codes at a time: the four byte digits of the fixed-point level go to
-//     the matrix cores against the digits of r.  More levels: gathers from a table in LDS in both passes.
-// Measured against the general loop: an epoch of 256 steps, 16 samples x 64 features, 4 bits 549 -> 128 us
-// (0.50 us a step); 512 steps, 256 x 90, 3 bits on optimal levels 2,419 -> 1,201 us (2.3 us a step).
+//     a byte permute from registers, four codes at a time: the byte digits of the fixed-point level go to
+//     the matrix cores against the digits of r, two at a time and only down to the lowest that some level has (two
+//     in all for levels on a grid of 2^12 or fewer steps, six for any fp32 levels within 2^-11 of the largest).  More
+//     levels: gathers from a table in LDS in both passes, in fp32.
+// Measured against the general loop: an epoch of 256 steps, 16 samples x 64 features, 4 bits 549 -> 133 us
+// (0.52 us a step; 128 with four digits); 512 steps, 256 x 90, 3 bits on optimal levels 2,419 -> 1,165 us (2.3 us
+// a step; 1,201 with four digits of every level); 256 x 100, 3 bits, arbitrary levels 5.3 -> 3.3 us a step.
 #include "zipml_device.h"
 #include "zipml_mfma_ops.h"
 #include "zipml_prox.h"
@@ -125,21 +132,39 @@ __device__ __forceinline__ float rows_sum(float v)
     s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
-// Four digit sums, each below 2^22 in magnitude, as one number (two roundings of an fp32 sum).
-__device__ __forceinline__ float digits_value(const v4i &c)
+constexpr float kUpper = 1073741824.0f;            // weight of the upper four digits, see digits_of
+// a and b hold the sums of the lower four digits in the even rows of 16 lanes and of the upper four in the odd rows,
+// each at most 2^22 in magnitude, two to an integer: row r gets those of a (r even) or b (r odd).
+struct DigitSums {
+    int lo[2], hi[2];
+};
+__device__ __forceinline__ DigitSums join_rows(const int (&a)[2], const int (&b)[2])
 {
-    return fmaf((float)(c[2] + (c[3] << 8)), 65536.0f, (float)(c[0] + (c[1] << 8)));
-}
-// Digit sums of four tiles -> those of the tile that this row of 16 lanes looks after.
-__device__ __forceinline__ v4i pick_row(const v4i (&c)[4], int q4)
-{
-    v4i r;
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    DigitSums s;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int lo = q4 & 1 ? c[1][k] : c[0][k], hi = q4 & 1 ? c[3][k] : c[2][k];
-        r[k] = q4 & 2 ? hi : lo;
+    for (int k = 0; k < 2; ++k) {
+        const v2u v = __builtin_amdgcn_permlane16_swap((uint32_t)a[k], (uint32_t)b[k], false, false);
+        s.lo[k] = (int)v[0];
+        s.hi[k] = (int)v[1];
     }
-    return r;
+    return s;
+}
+// Digit sums of four tiles -> the number of the tile that this row looks after.  A row of the sum with one element is
+// exact up to the last step (24 bits of the element stand in the upper digits): one rounding as in a product, two in a
+// sum.
+__device__ __forceinline__ float tile_value(const v4i (&c)[4], int q4)
+{
+    int a[2], b[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int a0 = q4 & 2 ? c[2][2 * k] : c[0][2 * k], a1 = q4 & 2 ? c[2][2 * k + 1] : c[0][2 * k + 1];
+        const int b0 = q4 & 2 ? c[3][2 * k] : c[1][2 * k], b1 = q4 & 2 ? c[3][2 * k + 1] : c[1][2 * k + 1];
+        a[k] = a0 + (a1 << 8);
+        b[k] = b0 + (b1 << 8);
+    }
+    const DigitSums s = join_rows(a, b);
+    return fmaf(fmaf((float)s.hi[1], 65536.0f, (float)s.hi[0]), kUpper, fmaf((float)s.lo[1], 65536.0f, (float)s.lo[0]));
 }
 
 // Reductions of 0 as the neutral element (sums, maxima of unsigned numbers): a row of 16 lanes, or the wave
@@ -168,39 +193,77 @@ struct MaxU { __device__ __forceinline__ uint32_t operator()(uint32_t p, uint32_
 __device__ __forceinline__ uint32_t magnitude(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
 // v < 2^exponent_of(v) for the bits of a finite v >= 0
 __device__ __forceinline__ int exponent_of(uint32_t bits) { return (int)(bits >> 23) - 126; }
-// k such that 2^k v < 2^29 for v < 2^e: every finite v >= 2^-71 has its 29 bits
-__device__ __forceinline__ int scale_for(int e)
+// Fixed point in two words of four signed base-256 digits, upper * 2^30 + lower: k such that 2^k v < 2^59 for
+// v < 2^e ...
+__device__ __forceinline__ int scale_for(int e) { return 59 - e; }
+// ... and the digits of 2^k v, the bytes of the two words (a |v| of one binade more has room, too).  A number down
+// to 2^-35 of 2^e keeps all the bits that it has in fp32; below that it is rounded to 2^-59 of 2^e.
+struct Digits8 {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Digits8 digits_of(float v, int k)
 {
-    const int k = 29 - e;
-    return k > 100 ? 100 : k;
+    const float t = ldexpf(v, k - 30), whole = rintf(t);   // (the difference is exact)
+    return {signed_digits((int)((t - whole) * kUpper)), signed_digits((int)whole)};
 }
+// Where an element stands in an operand of 64 (a plane of 64 bytes) is where its lane stands in the wave: lane l looks
+// after element lane_slot(l) of a group, so that four neighbouring lanes hold the bytes of a dword.  They exchange
+// their digits and store two dwords each; eight byte stores a lane were 70 ns of the smallest step.
+template <int BITS>
+__device__ __forceinline__ int lane_slot(int l)
+{
+    return (l & 32) + slot_code<BITS>((l >> 4) & 1, (l >> 2) & 3, l & 3);
+}
+// lane_slot(16 s + i) = tile_slot(s) + lane_slot(i) for i < 16
+template <int BITS> constexpr int tile_slot(int s) { return BITS == 1 ? 32 * (s >> 1) + 4 * (s & 1) : 16 * s; }
+struct QuadStore {
+    uint32_t sel1, sel2;
+    int at;
+    __device__ __forceinline__ explicit QuadStore(int lane)
+    {
+        sel1 = lane & 1 ? 0x03070105u : 0x06020400u;
+        sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
+        at = 64 * (lane & 3) + (lane & ~3);
+    }
+    __device__ __forceinline__ uint32_t transpose(uint32_t v) const
+    {
+        v = __builtin_amdgcn_perm(dpp_move<0xB1>(v), v, sel1);
+        return __builtin_amdgcn_perm(dpp_move<0x4E>(v), v, sel2);
+    }
+    // digit p of the lane's element -> planes + 64 p + lane (all lanes of the wave)
+    __device__ __forceinline__ void operator()(int8_t *planes, Digits8 dg) const
+    {
+        *reinterpret_cast<uint32_t *>(planes + at) = transpose(dg.lo);
+        *reinterpret_cast<uint32_t *>(planes + at + 256) = transpose(dg.hi);
+    }
+};
 
 struct SoloLds {
-    int8_t *ydig;          // [KB][4 digits][4 q][16]
-    int8_t *rdig;          // [NB][4 digits][4 q][16]
-    float4 *info;          // [NB] (exponent of r, -, -, -)
+    int8_t *ydig;          // [KB][8 digits][4 q][16]
+    int8_t *rdig;          // [NB][8 digits][4 q][16]
+    float4 *info;          // [NB] (scale of r, -, -, -)
     float *wr;             // [16] per wave: sum of r, [8 + w]: bits of the largest |r|
     float *wy;             // [16] per wave: sum of mid x, [8 + w]: bits of the largest |y|
     int8_t *zeros;         // [16]
-    float *rs;             // [NB * 64] residuals
+    float *rs;             // [NB * 64] residuals  (these two for uneven levels of 4 and more bits only)
     float *xs;             // [256] model
     float *zp;             // [1024] parts of the dot products, one per split and sample (splits * NB <= 16)
     unsigned char *table;  // uneven levels
     unsigned char *ring;
 };
-__device__ __forceinline__ SoloLds solo_carve(unsigned char *smem, int B)
+__device__ __forceinline__ SoloLds solo_carve(unsigned char *smem, int B, int bits)
 {
     const int NB = (B + 63) / 64;
     SoloLds L;
     L.ydig = (int8_t *)smem;
-    L.rdig = L.ydig + 1024;
-    L.info = (float4 *)(L.rdig + NB * 256);
+    L.rdig = L.ydig + 2048;
+    L.info = (float4 *)(L.rdig + NB * 512);
     L.wr = (float *)(L.info + NB);
     L.wy = L.wr + 16;
     L.zeros = (int8_t *)(L.wy + 16);
     L.rs = (float *)(L.wr + 128);
-    L.xs = L.rs + NB * 64;
-    L.zp = L.xs + 256;
+    L.xs = L.rs + (bits > 3 ? NB * 64 : 0);
+    L.zp = L.xs + (bits > 3 ? 256 : 0);
     L.table = (unsigned char *)(L.zp + 4 * 256);
     L.ring = L.table;
     return L;
@@ -212,13 +275,13 @@ struct SoloR {
     uint32_t max;
     int k;
 };
-__device__ __forceinline__ SoloR solo_residuals(int8_t *plane0, float r)
+__device__ __forceinline__ SoloR solo_residuals(int8_t *planes, const QuadStore &store, float r)
 {
     SoloR o;
     o.max = wave_total(magnitude(r), MaxU());
     o.sum = wave_total(r, AddF());
     o.k = scale_for(exponent_of(o.max));
-    store_digits(plane0, signed_digits(__float2int_rn(ldexpf(r, o.k))));
+    store(planes, digits_of(r, o.k));
     return o;
 }
 
@@ -245,13 +308,40 @@ __device__ __forceinline__ float solo_update(const SoloArgs &a, float x, float g
     return v;
 }
 
-// One lane operand (16 codes) from a slot.
+// One lane operand (16 codes) from a slot, as one load where its alignment allows: that takes an offset, two loads of
+// a dword at a distance take an address.
 template <int BITS>
 __device__ __forceinline__ void slot_codes(const unsigned char *p, uint32_t (&w)[kOpDwords<BITS>])
 {
-    const uint32_t *q = static_cast<const uint32_t *>(__builtin_assume_aligned(p, kOpAlign<BITS>));
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    if constexpr (BITS == 8) {
+        const v4u q = *reinterpret_cast<const v4u *>(p);
 #pragma unroll
-    for (int k = 0; k < kOpDwords<BITS>; ++k) w[k] = q[k];
+        for (int k = 0; k < 4; ++k) w[k] = q[k];
+    } else if constexpr (BITS == 4) {
+        const v2u q = *reinterpret_cast<const v2u *>(p);
+        w[0] = q[0];
+        w[1] = q[1];
+    } else {
+        const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
+#pragma unroll
+        for (int k = 0; k < kOpDwords<BITS>; ++k) w[k] = q[k];
+    }
+}
+
+// What the sums over codes start from: codes of 8 bits are operands 128 below, so 128 times the sum of the other
+// operand, 64 twice over.  (In integers: with the 128 in the factor of a sum of fp32 numbers, a large element that meets
+// the code zero everywhere would leave its rounding errors.)
+template <int BITS>
+__device__ __forceinline__ v4i code_offset(const v4i &a, v4i c)
+{
+    if constexpr (BITS == 8) {
+        const v4i h = {0x40404040, 0x40404040, 0x40404040, 0x40404040};
+        c = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, h, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, h, c, 0, 0, 0);
+    }
+    return c;
 }
 
 // Evenly spaced levels.  KB: blocks of 64 features.  MANY = false: at most 64 samples, wave w owns the
@@ -267,13 +357,14 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
     constexpr bool kOne = KB == 1 && !MANY;            // one wave does it all
     constexpr int kFt = MANY ? (KB == 4 ? 2 : 1) : 1;  // feature sets of a wave
     constexpr int K = 1 << BITS, HW = kOpDwords<BITS>;
-    constexpr float kOff = BITS == 8 ? 128.0f : 0.0f;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = kOne ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, q4 = lane >> 4;
     const int B = a.B, NB = MANY ? (B + 63) / 64 : 1, nrg = B >= 32 ? B / 32 : 1;
     const SoloSlot sl(a.d32, B, BITS, a.loaders);
     const uint32_t shift = op_shift<BITS>(q4 & 1);
+    const int own = lane_slot<BITS>(lane), own16 = lane_slot<BITS>(n16);   // this lane's element of 64, its column of a tile
+    const QuadStore store(lane);
 
     // ---- this lane's features (the mean over the batch is folded into the gradient's factors)
     float o_dl[kFt], o_mid[kFt], g_dl[kFt], g_mid[kFt], x[kFt];
@@ -282,11 +373,11 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
     float mu = 0.0f, y0 = 0.0f;
 #pragma unroll
     for (int u = 0; u < kFt; ++u) {
-        const int f = MANY ? 16 * (wave + nc * u) + n16 : 64 * wave + lane;
+        const int f = MANY ? 16 * (wave + nc * u) + n16 : 64 * wave + own;
         live[u] = f < a.d;
         const float lo = live[u] ? a.levels[(size_t)f * K] : 0.0f, hi = live[u] ? a.levels[(size_t)f * K + K - 1] : 0.0f;
         o_dl[u] = (float)(((double)hi - (double)lo) / (double)(K - 1));
-        o_mid[u] = lo + kOff * o_dl[u];
+        o_mid[u] = lo;
         g_dl[u] = __fdiv_rn(o_dl[u], (float)B);
         g_mid[u] = __fdiv_rn(o_mid[u], (float)B);
         x[u] = live[u] ? a.x[f] : 0.0f;
@@ -294,27 +385,28 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
         y0 = fmaxf(y0, fabsf(o_dl[u] * x[u]));
         int half, byte;
         code_slot<BITS>(f & 31, half, byte);
-        y_pos[u] = ((f >> 6) & 3) * 256 + (2 * ((f >> 5) & 1) + half) * 16 + byte + (MANY ? 64 * q4 : 0);
+        y_pos[u] = MANY ? ((f >> 6) & 3) * 512 + (2 * ((f >> 5) & 1) + half) * 16 + byte + 64 * q4 : wave * 512;
         if (f >= 64 * KB) y_pos[u] = -1;               // no such feature, not even a padding one
     }
     // digits of y, and the wave's figures of the model
     float cp = 0.0f;
     uint32_t ym = 0u;
     auto publish_y = [&](int ky) __attribute__((always_inline)) {
-        cp = 0.0f;
-        ym = 0u;
 #pragma unroll
         for (int u = 0; u < kFt; ++u) {
             const float y = o_dl[u] * x[u];
-            const uint32_t dg = signed_digits(__float2int_rn(ldexpf(y, ky)));
+            const Digits8 dg = digits_of(y, ky);
             if (MANY) {
-                // (the rows of lanes hold the same feature: each stores one digit)
-                if (y_pos[u] >= 0) L.ydig[y_pos[u]] = (int8_t)(dg >> (8 * q4));
+                // (the rows of lanes hold the same feature: each stores two digits)
+                if (y_pos[u] >= 0) {
+                    L.ydig[y_pos[u]] = (int8_t)(dg.lo >> (8 * q4));
+                    L.ydig[y_pos[u] + 256] = (int8_t)(dg.hi >> (8 * q4));
+                }
             } else {
-                store_digits(L.ydig + y_pos[u], dg);
+                store(L.ydig + y_pos[u], dg);
             }
-            cp += o_mid[u] * x[u];
-            ym = MaxU()(ym, magnitude(y));
+            cp = u == 0 ? o_mid[u] * x[u] : cp + o_mid[u] * x[u];
+            ym = u == 0 ? magnitude(y) : MaxU()(ym, magnitude(y));
         }
         if (!kOne) {
             if (MANY) { cp = row_total(cp, AddF()); ym = row_total(ym, MaxU()); }
@@ -348,21 +440,15 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
         const int g = 2 * kb + (q4 >> 1) < a.d32 ? 2 * kb + (q4 >> 1) : a.d32 - 1;   // (padding: its digits are zero)
-        dot_at[kb] = (g * B + n16) * 4 * BITS + (q4 & 1) * kOpStride<BITS> * 4;
+        dot_at[kb] = (g * B + own16) * 4 * BITS + (q4 & 1) * kOpStride<BITS> * 4;
     }
-    const int dig_at = (n16 & 3) * 64 + q4 * 16;
-    int r_pos;
-    {
-        int half, byte;
-        code_slot<BITS>(lane & 31, half, byte);
-        r_pos = (2 * (lane >> 5) + half) * 16 + byte;
-    }
+    const int dig_at = (n16 & 7) * 64 + q4 * 16;
     int grad_at[kFt][4];
 #pragma unroll
     for (int u = 0; u < kFt; ++u)
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const int f = MANY ? 16 * (wave + nc * u) + n16 : 64 * wave + 16 * s + n16;
+            const int f = MANY ? 16 * (wave + nc * u) + n16 : 64 * wave + tile_slot<BITS>(s) + own16;
             const int g = (f >> 5) < a.d32 ? f >> 5 : a.d32 - 1;
             int rg = (MANY ? 2 * s : 0) + (q4 >> 1);
             rg = rg < nrg ? rg : nrg - 1;
@@ -375,7 +461,7 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
 #pragma unroll
         for (int s = 0; s < T; ++s)
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) slot_codes<BITS>(first + dot_at[kb] + 16 * s * 4 * BITS, w[s][kb]);
+            for (int kb = 0; kb < KB; ++kb) slot_codes<BITS>(first + dot_at[kb] + tile_slot<BITS>(s) * 4 * BITS, w[s][kb]);
     };
     const bool dots = kOne || (MANY ? wave < NB : wave == 0);    // this wave takes part in the dot pass
     const bool early = S >= 3;                         // (the ring is then a step further ahead)
@@ -384,11 +470,13 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
     lds_barrier();                                     // the first step has landed; y, wave figures
     int k0 = (int)((a.step0 * B) & 31);                // where a batch begins in its sample group (0 from 32 samples on)
     int at = 0;
-    const int ring_end = S * sl.bytes;
+    const int slot_bytes = __builtin_amdgcn_readfirstlane(sl.bytes), label_off = __builtin_amdgcn_readfirstlane(sl.label_off);
+    const int ring_end = S * slot_bytes;
     if (early && dots) read_dot(L.ring, MANY ? wave : 0, k0, dop);
-    for (int64_t left = a.nsteps; left > 0; --left) {
+    int64_t left = a.nsteps;                           // (at least one)
+    do {
         const unsigned char *base = L.ring + at;
-        at = at + sl.bytes < ring_end ? at + sl.bytes : 0;
+        at = at + slot_bytes < ring_end ? at + slot_bytes : 0;
         // ================= dot pass, residuals
         SoloR mine = {0.0f, 0u, 0};
         float C = cp, label = 0.0f;
@@ -396,8 +484,8 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
         v4i ad[KB];
         if (dots) {
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) ad[kb] = *reinterpret_cast<const v4i *>(L.ydig + kb * 256 + dig_at);
-            label = *reinterpret_cast<const float *>(base + sl.label_off + 4 * ((MANY ? 64 * wave : 0) + lane - k0));
+            for (int kb = 0; kb < KB; ++kb) ad[kb] = *reinterpret_cast<const v4i *>(L.ydig + kb * 512 + dig_at);
+            label = *reinterpret_cast<const float *>(base + label_off + 4 * ((MANY ? 64 * wave : 0) + own - k0));
             if (!early) read_dot(base, MANY ? wave : 0, k0, dop);
         }
 #pragma unroll
@@ -412,18 +500,21 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
             Y = wave_figures_max(L.wy + 8);
         }
         auto block = [&](int sb) __attribute__((always_inline)) {
-            v4i c[4];
+            v4i c[4], from = {0, 0, 0, 0};
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) from = code_offset<BITS>(ad[kb], from);
 #pragma unroll
             for (int s = 0; s < T; ++s) {
-                c[s] = v4i{0, 0, 0, 0};
+                c[s] = from;
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
                     c[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ad[kb], expand_codes<BITS>(dop[s][kb], shift), c[s], 0, 0, 0);
             }
-            if constexpr (T == 2) { c[2] = c[0]; c[3] = c[1]; }
-            const float z = ldexpf(digits_value(T == 1 ? c[0] : pick_row(c, q4)), -ky) + C;
-            const float r = (uint32_t)(64 * sb + lane - k0) < (uint32_t)B ? z - label : 0.0f;
-            return solo_residuals(L.rdig + sb * 256 + r_pos, r);
+            if constexpr (T == 1) c[1] = c[0];
+            if constexpr (T <= 2) { c[2] = c[0]; c[3] = c[1]; }
+            const float z = ldexpf(tile_value(c, q4), -ky) + C;
+            const float r = (uint32_t)(64 * sb + own - k0) < (uint32_t)B ? z - label : 0.0f;
+            return solo_residuals(L.rdig + sb * 512, store, r);
         };
         if (dots) {
             if constexpr (MANY) {
@@ -436,7 +527,7 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
                     sb += nc;
                     if (sb >= NB) break;
                     read_dot(base, sb, k0, dop);       // (blocks beyond the first)
-                    label = *reinterpret_cast<const float *>(base + sl.label_off + 4 * (64 * sb + lane - k0));
+                    label = *reinterpret_cast<const float *>(base + label_off + 4 * (64 * sb + own - k0));
                 }
             } else {
                 mine = block(0);
@@ -452,7 +543,7 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
         v4i rd[MANY ? 4 : 1];
 #pragma unroll
         for (int s = 0; s < (MANY ? 4 : 1); ++s)
-            rd[s] = *reinterpret_cast<const v4i *>(L.rdig + (s < NB ? s : NB - 1) * 256 + dig_at);
+            rd[s] = *reinterpret_cast<const v4i *>(L.rdig + (s < NB ? s : NB - 1) * 512 + dig_at);
         const int kr = kOne ? mine.k : __float_as_int(L.info[MANY && q4 < NB ? q4 : 0].x);
         float Rsum = mine.sum;
         uint32_t Rmax = mine.max;
@@ -460,15 +551,18 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
         else if constexpr (!kOne) { Rsum = L.wr[0]; Rmax = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(L.wr[8])); }
         const int e_y = exponent_of(Y) + e_l2, e_r = exponent_of(Rmax) + e_step;
         ky = scale_for((e_y > e_r ? e_y : e_r) + 1);
+        v4i from[MANY ? 4 : 1];
+#pragma unroll
+        for (int s = 0; s < (MANY ? 4 : 1); ++s) from[s] = code_offset<BITS>(rd[s], v4i{0, 0, 0, 0});
 #pragma unroll
         for (int u = 0; u < kFt; ++u)
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                c[u][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd[MANY ? s : 0], expand_codes<BITS>(gop[u][s], shift), v4i{0, 0, 0, 0}, 0, 0, 0);
+                c[u][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd[MANY ? s : 0], expand_codes<BITS>(gop[u][s], shift), from[MANY ? s : 0], 0, 0, 0);
         if (early && dots) read_dot(L.ring + at, MANY ? wave : 0, k0, dop);
 #pragma unroll
         for (int u = 0; u < kFt; ++u) {
-            float G = ldexpf(digits_value(pick_row(c[u], q4)), -kr);
+            float G = ldexpf(tile_value(c[u], q4), -kr);
             if constexpr (MANY) {
                 G = q4 < NB ? G : 0.0f;
                 for (int sb0 = 4; sb0 < NB; sb0 += 4) {
@@ -479,13 +573,13 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
                         int more = 2 * sb0;            // sample groups on from grad_at's
                         if (2 * (sb0 + s) + (q4 >> 1) >= nrg) more = 0;   // (past the batch: what is read does not count)
                         slot_codes<BITS>(base + grad_at[u][s] + more * 128 * BITS, w[s]);
-                        rx[s] = *reinterpret_cast<const v4i *>(2 * (sb0 + s) + (q4 >> 1) < nrg ? L.rdig + (sb0 + s) * 256 + dig_at : L.zeros);
+                        rx[s] = *reinterpret_cast<const v4i *>(2 * (sb0 + s) + (q4 >> 1) < nrg ? L.rdig + (sb0 + s) * 512 + dig_at : L.zeros);
                     }
                     const int k = __float_as_int(L.info[sb0 + q4 < NB ? sb0 + q4 : NB - 1].x);
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
-                        e[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rx[s], expand_codes<BITS>(w[s], shift), v4i{0, 0, 0, 0}, 0, 0, 0);
-                    G += ldexpf(digits_value(pick_row(e, q4)), -k);
+                        e[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rx[s], expand_codes<BITS>(w[s], shift), code_offset<BITS>(rx[s], v4i{0, 0, 0, 0}), 0, 0, 0);
+                    G += ldexpf(tile_value(e, q4), -k);
                 }
                 G = rows_sum(G);
             }
@@ -493,23 +587,22 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
         }
         publish_y(ky);
         lds_barrier();
-    }
+    } while (--left != 0);
 #pragma unroll
     for (int u = 0; u < kFt; ++u) {
-        const int f = MANY ? 16 * (wave + nc * u) + n16 : 64 * wave + lane;
+        const int f = MANY ? 16 * (wave + nc * u) + n16 : 64 * wave + own;
         if (live[u] && (!MANY || q4 == 0)) a.x[f] = x[u];
     }
 }
 
-// Uneven levels, eight waves.  A wave owns the feature tiles wave and wave + 8 (16 features, held by all four
-// rows of 16 lanes).
-template <int BITS, bool IN_LDS>
+// Uneven levels, eight waves.  A wave owns the feature tiles wave and, with kFt = 2, wave + 8 (16 features, held by all
+// four rows of 16 lanes).
+template <int BITS, bool IN_LDS, int kFt>
 __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, unsigned char *ring, int S, int splits)
 {
     constexpr int K = 1 << BITS;
     static_assert(BITS >= 2, "two levels are evenly spaced");
     constexpr bool kPairs = K <= 8;
-    constexpr int kFt = 2;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, q4 = lane >> 4;
     const int B = a.B, NB = (B + 63) / 64, nrg = B >= 32 ? B / 32 : 1, nft = (a.d + 15) / 16;
@@ -519,8 +612,12 @@ __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, 
 
     float x[kFt];
     bool live[kFt];
-    uint32_t plane[kFt][4][2];                         // byte p of the fixed-point levels 0..3 and 4..7
-    int kl[kFt];
+    // Bytes 6 and 7 of the eight digits of the levels 0..3 and 4..7; the lower six are in LDS, behind the pair tables
+    // ([feature tile][byte][16 features], K bytes each): levels on a grid of 2^12 or fewer steps have none.
+    constexpr int kPw = kPairs ? K / 4 : 1;
+    uint32_t plane[kFt][2][kPw];
+    uint32_t *const low_planes = (uint32_t *)(L.table + (kPairs ? a.d32 * 16 * K * K * 4 : 0));
+    int kl[kFt], used = 8;                             // (used: the lowest byte that is not zero for all levels)
     float la[kFt][kPairs ? K : 1], lb[kFt][2];         // levels of the pair's first feature; of the second, this lane's
 #pragma unroll
     for (int u = 0; u < kFt; ++u) {
@@ -537,13 +634,25 @@ __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, 
                 la[u][c] = (f & ~1) < a.d ? a.levels[(size_t)(f & ~1) * K + c] : 0.0f;
             }
             kl[u] = scale_for(exponent_of(magnitude(m)));
-#pragma unroll
-            for (int p = 0; p < 4; ++p) plane[u][p][0] = plane[u][p][1] = 0u;
+            uint32_t all[8][kPw] = {};
 #pragma unroll
             for (int c = 0; c < K; ++c) {
-                const uint32_t dg = signed_digits(__float2int_rn(ldexpf(lv[c], kl[u])));
+                const Digits8 dg = digits_of(lv[c], kl[u]);
 #pragma unroll
-                for (int p = 0; p < 4; ++p) plane[u][p][c >> 2] |= ((dg >> (8 * p)) & 0xFFu) << (8 * (c & 3));
+                for (int p = 0; p < 8; ++p) {
+                    const uint32_t byte = ((p < 4 ? dg.lo : dg.hi) >> (8 * (p & 3))) & 0xFFu;
+                    all[p][c >> 2] |= byte << (8 * (c & 3));
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kPw; ++q) {
+#pragma unroll
+                for (int p = 7; p >= 0; --p) {
+                    if (__any(all[p][q] != 0u) && p < used) used = p;
+                    if (p < 6 && wave + 8 * u < 2 * a.d32) low_planes[(((wave + 8 * u) * 6 + p) * 16 + n16) * kPw + q] = all[p][q];
+                }
+                plane[u][0][q] = all[6][q];
+                plane[u][1][q] = all[7][q];
             }
             // eight lanes share a pair's table: entries sub * K K / 8 on
             const int sub = (n16 & 1) * 4 + q4;
@@ -587,16 +696,13 @@ __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, 
     };
     publish_x();
 
-    int r_pos;
-    {
-        int half, byte;
-        code_slot<BITS>(lane & 31, half, byte);
-        r_pos = (2 * (lane >> 5) + half) * 16 + byte;
-    }
-    // the digits of a block of samples, in one row of lanes and zero in the others
-    int dig_at[4];
+    const int own = kPairs ? lane_slot<BITS>(lane) : lane;     // this lane's sample of a block
+    const QuadStore store(lane);
+    // the digits of a block of samples: two blocks to an accumulator
+    int dig_at[2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) dig_at[s] = (n16 >> 2) == s ? (n16 & 3) * 64 + q4 * 16 : -1;
+    for (int s = 0; s < 2; ++s) dig_at[s] = (n16 >> 3) == s ? (n16 & 7) * 64 + q4 * 16 : -1;
+    const int own_block = (q4 & 1) * 2 + (q4 >> 1);    // of four: the one whose sums this row ends up with
     int grad_at[kFt];
 #pragma unroll
     for (int u = 0; u < kFt; ++u) {
@@ -607,7 +713,7 @@ __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, 
     const int dw = wave % (kSoloWaves / splits), nd = kSoloWaves / splits;
     const bool early = S >= 3;                         // (the ring is then a step further ahead)
     const int64_t t_end = a.step0 + a.nsteps;
-    const int lane_unit = lane * (4 * BITS);
+    const int lane_unit = own * (4 * BITS);
     // the unit of this lane's sample of block sb, feature group g (lanes without a sample: whatever is there)
     auto read_dot = [&](const unsigned char *base, int sb, int k0, int g, uint32_t (&w)[BITS]) __attribute__((always_inline)) {
         const uint32_t *q = reinterpret_cast<const uint32_t *>(base + (g < a.d32 ? g : fs) * sl.len2 + (64 * sb - k0) * (4 * BITS) + lane_unit);
@@ -658,14 +764,14 @@ __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, 
         slot = slot + 1 < S ? slot + 1 : 0;
         // ================= dot pass
         auto finish = [&](int sb, float z) {           // residual of this lane's sample of block sb
-            const int i = 64 * sb + lane - k0;
+            const int i = 64 * sb + own - k0;
             const bool ok = i >= 0 && i < B;
             const float label = *reinterpret_cast<const float *>(base + sl.label_off + 4 * (ok ? i : 0));
             const float r = ok ? z - label : 0.0f;
             if constexpr (kPairs) {
                 const uint32_t m = wave_total(magnitude(r), MaxU());
                 const int k = scale_for(exponent_of(m));
-                store_digits(L.rdig + sb * 256 + r_pos, signed_digits(__float2int_rn(ldexpf(r, k))));
+                store(L.rdig + sb * 512, digits_of(r, k));
                 // (an infinity or a NaN has no digits: it reaches the gradient as a NaN)
                 if (lane == 0) L.info[sb] = make_float4(__int_as_float(k), m < 0x7F800000u ? 0.0f : __builtin_nanf(""), 0.0f, 0.0f);
             } else {
@@ -744,28 +850,63 @@ __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, 
             if constexpr (kPairs) {
                 float G = 0.0f;
                 for (int sb0 = 0; sb0 < NB; sb0 += 4) {
-                    v4i c[4], rd[4];
+                    v4i rd[4];
                     if (sb0 > 0) read_grad(base, u, sb0, gop[u]);
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
-                        rd[s] = *reinterpret_cast<const v4i *>(dig_at[s] >= 0 && sb0 + s < NB ? L.rdig + (sb0 + s) * 256 + dig_at[s] : L.zeros);
-                    const float4 block = L.info[sb0 + q4 < NB ? sb0 + q4 : NB - 1];
+                        rd[s] = *reinterpret_cast<const v4i *>(dig_at[s & 1] >= 0 && sb0 + s < NB ? L.rdig + (sb0 + s) * 512 + dig_at[s & 1] : L.zeros);
+                    const float4 block = L.info[sb0 + own_block < NB ? sb0 + own_block : NB - 1];
                     const int k = __float_as_int(block.x);
+                    // two digits of the levels at a time, from the top down to the last that some level has
+                    constexpr bool kHold = kFt == 1;           // (else there are not registers enough)
+                    v4i held[kHold ? 4 : 1];
+                    if constexpr (kHold) {
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) c[p] = v4i{0, 0, 0, 0};
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        const v4i e = expand_codes<BITS>(gop[u][s], shift);
-#pragma unroll
-                        for (int p = 0; p < 4; ++p) {
-                            v4i lv;
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) lv[q] = (int)__builtin_amdgcn_perm(plane[u][p][K == 8 ? 1 : 0], plane[u][p][0], (uint32_t)e[q]);
-                            c[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd[s], lv, c[p], 0, 0, 0);
-                        }
+                        for (int s = 0; s < 4; ++s)
+                            if (s == 0 || sb0 + s < NB) held[s] = expand_codes<BITS>(gop[u][s], shift);
                     }
-                    const float v = fmaf(fmaf(fmaf(digits_value(c[3]), 256.0f, digits_value(c[2])), 256.0f, digits_value(c[1])), 256.0f, digits_value(c[0]));
-                    G += ldexpf(v, -k - kl[u]) + block.y;
+                    double half[2] = {0.0, 0.0};
+                    auto digits = [&](const uint32_t (&pl)[2][kPw], double up) __attribute__((always_inline)) {
+                        v4i c[2][2];
+                        c[0][0] = c[0][1] = c[1][0] = c[1][1] = v4i{0, 0, 0, 0};
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            if (s == 0 || sb0 + s < NB) {
+                                const v4i e = kHold ? held[kHold ? s : 0] : expand_codes<BITS>(gop[u][s], shift);
+#pragma unroll
+                                for (int p = 0; p < 2; ++p) {
+                                    v4i lv;
+#pragma unroll
+                                    for (int q = 0; q < 4; ++q) lv[q] = (int)__builtin_amdgcn_perm(pl[p][kPw - 1], pl[p][0], (uint32_t)e[q]);
+                                    c[p][s >> 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd[s], lv, c[p][s >> 1], 0, 0, 0);
+                                }
+                            }
+                        // sums of equal weight first (two of 2^20 each), two of them to an integer
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const v4i &c0 = c[0][h], &c1 = c[1][h];
+                            const double low = (double)(c0[0] + ((c0[1] + c1[0]) << 8)), mid = (double)((c0[2] + c1[1]) + ((c0[3] + c1[2]) << 8));
+                            half[h] = fma(half[h], up, fma(fma((double)c1[3], 65536.0, mid), 65536.0, low));
+                        }
+                    };
+                    int at = 6;
+                    digits(plane[u], 0.0);
+                    while (at > used) {
+                        at -= 2;
+                        uint32_t pl[2][kPw];
+#pragma unroll
+                        for (int p = 0; p < 2; ++p)
+#pragma unroll
+                            for (int q = 0; q < kPw; ++q) pl[p][q] = low_planes[(((wave + 8 * u) * 6 + at + p) * 16 + n16) * kPw + q];
+                        digits(pl, at == 2 ? 16384.0 : 65536.0);         // (the words are 2^30 apart)
+                    }
+                    // even rows hold the lower digits of r, odd rows the upper ones: to one row
+                    const uint64_t ia = __builtin_bit_cast(uint64_t, half[0]), ib = __builtin_bit_cast(uint64_t, half[1]);
+                    const int a2[2] = {(int)(uint32_t)ia, (int)(uint32_t)(ia >> 32)}, b2[2] = {(int)(uint32_t)ib, (int)(uint32_t)(ib >> 32)};
+                    const DigitSums j = join_rows(a2, b2);
+                    const double lo = __builtin_bit_cast(double, (uint64_t)(uint32_t)j.lo[1] << 32 | (uint32_t)j.lo[0]);
+                    const double hi = __builtin_bit_cast(double, (uint64_t)(uint32_t)j.hi[1] << 32 | (uint32_t)j.hi[0]);
+                    G += (float)ldexp(fma(hi, (double)kUpper, lo), 8 * at - (at >= 4 ? 2 : 0) - k - kl[u]) + block.y;
                 }
                 gp = G;
             } else {
@@ -812,7 +953,7 @@ __global__ __launch_bounds__((kSoloWaves + 4) * kWave) void k_sgd_solo(SoloArgs 
     constexpr int K = 1 << BITS;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    SoloLds L = solo_carve(smem, a.B);
+    SoloLds L = solo_carve(smem, a.B, BITS);
     if (tid == 0) a.status[0] = 0;
     // zero digits (padding features and samples), figures of waves that are not there
     for (int e = tid; e < (int)(L.table - smem) / 4; e += blockDim.x) reinterpret_cast<int *>(smem)[e] = 0;
@@ -834,12 +975,11 @@ __global__ __launch_bounds__((kSoloWaves + 4) * kWave) void k_sgd_solo(SoloArgs 
     if (!affine) table = solo_table_bytes(BITS, a.d32);
     // (2 KiB behind the last slot: lanes without a sample read on)
     const int room = a.lds_bytes - 2048 - (int)(L.table - smem);
-    if (table && room - table < 2 * sl.bytes) table = 0;       // (more than 8 levels only: the host has made sure)
     int S = (room - table) / sl.bytes;
     const int most = 2 + 63 / sl.instr;
     S = S < most ? S : most;
-    S = S < kSoloMaxSlots ? S : kSoloMaxSlots;
-    unsigned char *const ring = L.table + table;
+    S = __builtin_amdgcn_readfirstlane(S < kSoloMaxSlots ? S : kSoloMaxSlots);   // (divisions end in vector registers)
+    unsigned char *const ring = L.table + __builtin_amdgcn_readfirstlane(table);
     L.ring = ring;
     if (affine) {
         const int nc = MANY ? (KB == 1 && a.B <= 256 ? 4 : kSoloWaves) : KB == 4 ? (a.d32 + 1) / 2 : KB;
@@ -858,8 +998,10 @@ __global__ __launch_bounds__((kSoloWaves + 4) * kWave) void k_sgd_solo(SoloArgs 
         int splits = NB >= 8 ? 1 : NB >= 4 ? 2 : NB >= 2 ? 4 : 8;
         while (splits > a.d32) splits >>= 1;
         if (wave < kSoloWaves) {
-            if (table || K <= 8) solo_table<BITS, true>(a, L, ring, S, splits);
-            else if constexpr (K > 8) solo_table<BITS, false>(a, L, ring, S, splits);
+            constexpr int kFt = KB == 4 ? 2 : 1;
+            // (only at 8 bits and more than 64 features there is no room for the table)
+            if (BITS < 8 || table) solo_table<BITS, true, kFt>(a, L, ring, S, splits);
+            else if constexpr (BITS == 8) solo_table<BITS, false, kFt>(a, L, ring, S, splits);
         } else {
             solo_loader<BITS>(a, ring, S, wave - kSoloWaves, splits > 1 ? 3 : 2);
         }
@@ -869,10 +1011,12 @@ __global__ __launch_bounds__((kSoloWaves + 4) * kWave) void k_sgd_solo(SoloArgs 
 template <int BITS>
 int launch_solo(hipStream_t s, const SoloArgs &a)
 {
-    const int KB = a.d32 <= 2 ? 1 : a.d32 <= 4 ? 2 : 4;
+    // (solo_plan has at most 128 features from 5 bits on)
+    constexpr int kMost = BITS < 5 ? 4 : 2;
+    const int KB = a.d32 <= 2 ? 1 : a.d32 <= 4 ? 2 : kMost;
 #define ZIPML_SOLO(MANY, T) (KB == 1 ? (const void *)k_sgd_solo<BITS, 1, MANY, T> : KB == 2 ? (const void *)k_sgd_solo<BITS, 2, MANY, T> \
-                                                                                         : (const void *)k_sgd_solo<BITS, 4, MANY, T>)
-    const void *kern = a.B > 64 ? ZIPML_SOLO(true, 4) : a.B > 32 ? ZIPML_SOLO(false, 4) : a.B > 16 ? ZIPML_SOLO(false, 2) : ZIPML_SOLO(false, 1);
+                                                                                         : (const void *)k_sgd_solo<BITS, kMost, MANY, T>)
+    const void *kern = a.B > 64 ? ZIPML_SOLO(true, 4) : a.B > 32 ? ZIPML_SOLO(false, 4) : a.B > 16 || BITS == 1 ? ZIPML_SOLO(false, 2) : ZIPML_SOLO(false, BITS == 1 ? 2 : 1);
 #undef ZIPML_SOLO
     if (HIP_FAILED(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes))) return ZIPML_ELAUNCH;
     SoloArgs args = a;

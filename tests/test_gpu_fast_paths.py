@@ -289,6 +289,68 @@ def test_single_workgroup_epochs_of_every_width(n, d, B, bits):
             assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max() + 1e-12
 
 
+@pytest.mark.parametrize("even", [True, False])
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_single_workgroup_steps_coordinate_by_coordinate(bits, even):
+    """One step from a given model, every coordinate of the gradient on its own: within (d + B + 8) 2^-24 of the sum
+    of the magnitudes that reach it.  Some residuals are 10^6 or 10^9 times the others, and half of the features have the
+    level zero in those samples; one element of the model is as much larger than the others and meets only zeros."""
+    rng = np.random.default_rng(bits + 100 * even)
+    K = 1 << bits
+    if bits == 1 and not even:
+        return                                         # (two levels are evenly spaced)
+    for d, B in ((64, 16), (60, 64), (100, 8), (120, 64), (64, 256), (90, 160), (96, 256), (40, 128)):
+        for large in (1.0, 1e6, 1e9):
+            say("single step", bits, even, d, B, large)
+            A = rng.uniform(0, 1, (B, d)).astype(np.float32)
+            b = rng.standard_normal(B).astype(np.float32)
+            x0 = (rng.standard_normal(d) * 0.1).astype(np.float32)
+            rows = np.arange(B) % 16 == 3
+            b[rows] *= np.float32(large)
+            A[np.ix_(rows, np.arange(d) % 2 == 0)] = 0.0
+            A[:, 5] = 0.0
+            x0[5] = 0.1 * large
+            L = oracle.levels_uniform(np.zeros(d, np.float32), np.ones(d, np.float32), bits)
+            if not even:
+                L[:, 1:-1] = np.sort(rng.uniform(0, 1, (d, K - 2)), axis=1)
+            p = GpuProblem(A, b, bits, B)
+            p.set_levels(L)
+            p.quantize(3, 0)
+            v1, v2 = (np.take_along_axis(L, p.codes(c).astype(np.int64).T, axis=1).T.astype(np.float64) for c in (1, 2))
+            x64 = x0.astype(np.float64)
+            r = v2 @ x64 - b
+            ref = x64 - v1.T @ r / B
+            mag = np.abs(x64) + v1.T @ (v2 @ np.abs(x64) + np.abs(b)) / B
+            x = dev(x0)
+            zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, B, d, bits, x, B, 1.0, p.ws)
+            err = np.abs(x.cpu().numpy().astype(np.float64) - ref) / mag
+            assert err.max() <= (d + B + 8) * 2.0 ** -24, (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_single_workgroup_epochs_of_small_numbers(bits):
+    """Labels and model far below one: the epoch is linear in them."""
+    rng = np.random.default_rng(bits)
+    for d, B, even in ((40, 128, True), (40, 128, False), (64, 16, True), (100, 32, True), (60, 64, False)):
+        n = 4 * B
+        A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+        b1 = rng.standard_normal(n)
+        L = oracle.levels_uniform(np.full(d, -1, np.float32), np.ones(d, np.float32), bits)
+        if not even:
+            L[:, 1:-1] = np.sort(rng.uniform(-1, 1, (d, (1 << bits) - 2)), axis=1)
+        for scale in (1e-22, 1e-26, 1e-30):
+            say("small numbers", bits, d, B, even, scale)
+            b = (b1 * scale).astype(np.float32)
+            p = GpuProblem(A, b, bits, B)
+            p.set_levels(L)
+            p.quantize(5, 0)
+            x = dev(np.zeros(d, np.float32))
+            zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, n, d, bits, x, B, 0.1 / d, p.ws)
+            got = x.cpu().numpy().astype(np.float64) / scale
+            ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.1 / d) / scale
+            assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
 def test_single_workgroup_epochs_at_the_ends_of_the_number_range(bits):
     """Tiny and huge labels keep their digits, levels whose spacing rounds in fp64 are decoded, and an
