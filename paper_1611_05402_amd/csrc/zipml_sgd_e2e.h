@@ -24,11 +24,13 @@
 // the product is formed on the fly).  The mean gradient that Q4 quantises is the exact mean rounded to
 // fp32, whatever the order: the gradient pass adds L[j][code] * r_i either in fp64 (products of two fp32
 // numbers are exact there) or, for at most 16 levels and whole sample groups (MX), in integers on the matrix
-// cores: r in seven signed bytes (its 24 bits stand at the top of 54, so a residual is exact down to 2^-30
-// of the largest one and off by 2^-54 of it below), a feature's levels in six (24 bits at the top of 46).  A lane
-// owns one feature, so a look-up is a byte permute of the level's bytes from registers, four codes at a time;
-// the seven bytes of r fill half of the sixteen rows of v_mfma_i32_16x16x64_i8, one instruction per byte of
-// the levels.  In fp64 the pass took, per code, a field extraction, an LDS gather with bank conflicts, two
+// cores: r and a feature's levels in eight signed bytes each (24 bits at the top of 62, so that a number is exact
+// down to 2^-38 of the largest residual of the step, or the largest level of the feature, and off by 2^-62 of that
+// below: less than one rounding of the fp64 sum as soon as that largest one has a part in it).  A lane owns one
+// feature, so a look-up is a byte permute of the level's bytes from registers, four codes at a time;
+// the eight bytes of r fill half of the sixteen rows of v_mfma_i32_16x16x64_i8, one instruction per byte of
+// the levels, by pairs down to the lowest byte that some level has (one pair for levels on a grid of 2^14 or fewer
+// steps).  In fp64 the pass took, per code, a field extraction, an LDS gather with bank conflicts, two
 // conversions and a multiply-add: a step of 512 samples x 4,096 features at 3 bits took 12.8 us, 9.6 with this
 // pass and with the draws of the two quantisations made while the norms travel.
 #pragma once
@@ -73,8 +75,7 @@ __device__ __forceinline__ long long fixed_from_float(float v, int emax, int top
     const long long f = sh >= 0 ? (long long)((uint64_t)m << sh) : (long long)(m >> (sh > -31 ? -sh : 31));
     return (b >> 31) ? -f : f;
 }
-constexpr int kRDigits = 7, kRTop = 30;     // residuals: 24 + 30 bits
-constexpr int kLDigits = 6, kLTop = 22;     // levels: 24 + 22 bits
+constexpr int kDigits = 8, kTop = 38;       // residuals and levels: 24 + 38 bits
 
 constexpr int kNormSlots = 256;   // slots per buffer of the norm exchange (>= workgroups)
 
@@ -132,8 +133,8 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     const int xc = 16 * x_ft + n16;                  // this lane's feature, inside the workgroup
     int8_t *const rdig = reinterpret_cast<int8_t *>(gpart + 2 * kWaves * 16);   // [blocks][8][64], behind the waves' sums
     uint32_t *const wmax = reinterpret_cast<uint32_t *>(L.wsum + kWaves);
-    uint32_t plane[MX ? kLDigits : 1][MX ? kPlaneWords : 1];
-    int r_pos = 0, el_own = 1;
+    uint32_t plane[MX ? kDigits : 1][MX ? kPlaneWords : 1];
+    int r_pos = 0, el_own = 1, lowest = kDigits - 2;     // lowest: the lowest pair of bytes that is looked at
     if constexpr (MX) {
         auto level_exponent = [&](int c) {
             uint32_t m = 0;
@@ -146,16 +147,22 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         if (is_owner) el_own = level_exponent(tid);
         const int el = level_exponent(xc);
 #pragma unroll
-        for (int p = 0; p < kLDigits; ++p)
+        for (int p = 0; p < kDigits; ++p)
 #pragma unroll
             for (int q = 0; q < kPlaneWords; ++q) plane[p][q] = 0u;
 #pragma unroll
         for (int c = 0; c < K; ++c) {
             const float lv = j0 + xc < a.d ? Lg[(size_t)xc * K + c] : 0.0f;
-            const uint64_t dg = signed_digits_64<kLDigits>(fixed_from_float(lv, el, kLTop));
+            const uint64_t dg = signed_digits_64<kDigits>(fixed_from_float(lv, el, kTop));
 #pragma unroll
-            for (int p = 0; p < kLDigits; ++p) plane[p][c >> 2] |= (uint32_t)((dg >> (8 * p)) & 0xFFu) << (8 * (c & 3));
+            for (int p = 0; p < kDigits; ++p) plane[p][c >> 2] |= (uint32_t)((dg >> (8 * p)) & 0xFFu) << (8 * (c & 3));
         }
+#pragma unroll
+        for (int p = kDigits - 4; p >= 0; p -= 2)
+#pragma unroll
+            for (int q = 0; q < kPlaneWords; ++q)
+                if (__any((plane[p][q] | plane[p + 1][q]) != 0u)) lowest = p;
+        lowest = __builtin_amdgcn_readfirstlane(lowest);
         // sample i: block i / 64, and this byte of each of its digit rows (i = tid + 512 q: the same for every q)
         int half, byte;
         code_slot<BITS>(tid & 31, half, byte);
@@ -465,10 +472,10 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 #pragma unroll
             for (int q = 0; q < UPT; ++q)
                 if (tid + q * kThreads < B) {
-                    const uint64_t dg = signed_digits_64<kRDigits>(fixed_from_float(rown[q], er, kRTop));
+                    const uint64_t dg = signed_digits_64<kDigits>(fixed_from_float(rown[q], er, kTop));
                     int8_t *at = rdig + q * (kThreads / 64 * 512) + r_pos;
 #pragma unroll
-                    for (int k = 0; k < kRDigits; ++k) at[64 * k] = (int8_t)(dg >> (8 * k));
+                    for (int k = 0; k < kDigits; ++k) at[64 * k] = (int8_t)(dg >> (8 * k));
                 }
             lds_barrier();    // the digits
         }
@@ -476,15 +483,15 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 
         // ================= gradient pass
         if constexpr (MX) {
-            v4i c[kLDigits];
+            v4i c[kDigits];
 #pragma unroll
-            for (int p = 0; p < kLDigits; ++p) c[p] = v4i{0, 0, 0, 0};
+            for (int p = 0; p < kDigits; ++p) c[p] = v4i{0, 0, 0, 0};
             const uint32_t shift = op_shift<BITS>(q4 & 1);
 #pragma unroll
             for (int m = 0; m < kOps; ++m) {
                 const int sb = x_kh + KSS * m;
                 if (2 * sb < nrg) {
-                    // (rows 7 .. 15 repeat others or are no digits at all: their results are not used)
+                    // (rows 8 .. 15 repeat the others: their results are not used)
                     const v4i rd = *reinterpret_cast<const v4i *>(rdig + sb * 512 + (n16 & 7) * 64 + q4 * 16);
                     v4i e = expand_codes<BITS>(c1cur[m], shift), up = {0, 0, 0, 0};
                     if constexpr (K == 16) {
@@ -496,38 +503,40 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                         }
                     }
 #pragma unroll
-                    for (int p = 0; p < kLDigits; ++p) {
-                        v4i lv;
+                    for (int p0 = kDigits - 2; p0 >= 0; p0 -= 2)
+                        if (p0 >= lowest) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            uint32_t v = __builtin_amdgcn_perm(plane[p][K >= 8 ? 1 : 0], plane[p][0], (uint32_t)e[q]);
-                            if constexpr (K == 16) {
-                                const uint32_t h = __builtin_amdgcn_perm(plane[p][3], plane[p][2], (uint32_t)e[q]);
-                                v = ((uint32_t)up[q] & h) | (~(uint32_t)up[q] & v);
+                            for (int p = p0; p < p0 + 2; ++p) {
+                                v4i lv;
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) {
+                                    uint32_t v = __builtin_amdgcn_perm(plane[p][K >= 8 ? 1 : 0], plane[p][0], (uint32_t)e[q]);
+                                    if constexpr (K == 16) {
+                                        const uint32_t h = __builtin_amdgcn_perm(plane[p][3], plane[p][2], (uint32_t)e[q]);
+                                        v = ((uint32_t)up[q] & h) | (~(uint32_t)up[q] & v);
+                                    }
+                                    lv[q] = (int)v;
+                                }
+                                c[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd, lv, c[p], 0, 0, 0);
                             }
-                            lv[q] = (int)v;
                         }
-                        c[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd, lv, c[p], 0, 0, 0);
-                    }
                 }
             }
-            // Rows 0 .. 3 are in the first sixteen lanes, rows 4 .. 6 in the next (row 7 is no digit).  Sums of
-            // equal weight first: each below 2^26, so the four lower ones join exactly in a double.
+            // Rows 0 .. 3 are in the first sixteen lanes, rows 4 .. 7 in the next.  Sums of equal weight first: each
+            // below 2^26, so that four of them join exactly in a double.
             if (q4 < 2) {
-                int v[kLDigits + 3];
+                int v[kDigits + 4];
 #pragma unroll
-                for (int s = 0; s < kLDigits + 3; ++s) v[s] = 0;
+                for (int s = 0; s < kDigits + 4; ++s) v[s] = 0;
 #pragma unroll
-                for (int p = 0; p < kLDigits; ++p) {
-                    v[p] += c[p][0];
-                    v[p + 1] += c[p][1];
-                    v[p + 2] += c[p][2];
-                    v[p + 3] += q4 == 0 ? c[p][3] : 0;
-                }
-                const double lo4 = fma(fma((double)v[3], 256.0, (double)v[2]), 65536.0, fma((double)v[1], 256.0, (double)v[0]));
-                double hi5 = fma(fma((double)v[7], 256.0, (double)v[6]), 65536.0, fma((double)v[5], 256.0, (double)v[4]));
-                hi5 = fma((double)v[8], 4294967296.0, hi5);
-                gpart[(2 * x_kh + q4) * CW + xc] = fma(hi5, 4294967296.0, lo4) * (q4 ? 4294967296.0 : 1.0);
+                for (int p = 0; p < kDigits; ++p)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) v[p + s] += c[p][s];
+                auto four = [&](int s) {
+                    return fma(fma((double)v[s + 3], 256.0, (double)v[s + 2]), 65536.0, fma((double)v[s + 1], 256.0, (double)v[s]));
+                };
+                const double sum = fma(fma(four(8), 4294967296.0, four(4)), 4294967296.0, four(0));
+                gpart[(2 * x_kh + q4) * CW + xc] = sum * (q4 ? 4294967296.0 : 1.0);
             }
         } else {
             double part[UPT];
@@ -576,7 +585,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                     if (r0 + q < nparts) sacc += v[q];
             }
             if constexpr (MX) {
-                sacc = ldexp(sacc, er + el_own - (300 + kRTop + kLTop));
+                sacc = ldexp(sacc, er + el_own - (300 + 2 * kTop));
                 if (er == 255) sacc = __longlong_as_double(0x7FF8000000000000ll);    // an infinity or a NaN among the residuals
             }
             g = live ? (float)(sacc / (double)B) : 0.0f;      // the mean, rounded once

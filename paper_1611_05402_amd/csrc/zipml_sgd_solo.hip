@@ -20,7 +20,7 @@
 //     of two features at once in LDS; in the gradient pass a lane owns one feature, so that a level look-up is
 //     a byte permute from registers, four codes at a time: the byte digits of the fixed-point level go to
 //     the matrix cores against the digits of r, two at a time and only down to the lowest that some level has (two
-//     in all for levels on a grid of 2^12 or fewer steps, six for any fp32 levels within 2^-11 of the largest).  More
+//     in all for levels on a grid of 2^12 or fewer steps, six for any fp32 levels down to 2^-19 of the largest).  More
 //     levels: gathers from a table in LDS in both passes, in fp32.
 // Measured against the general loop: an epoch of 256 steps, 16 samples x 64 features, 4 bits 549 -> 133 us
 // (0.52 us a step; 128 with four digits); 512 steps, 256 x 90, 3 bits on optimal levels 2,419 -> 1,165 us (2.3 us

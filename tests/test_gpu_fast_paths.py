@@ -405,6 +405,30 @@ def test_end_to_end_steps_on_the_matrix_cores(d, B, bits):
                            zipml.SGD_PRODUCTION)
 
 
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("d,B", [(300, 32), (290, 256), (4000, 224)])
+def test_end_to_end_gradient_is_the_exact_mean(d, B, bits):
+    """Levels and residuals of very different size: one level 2^-30 of the largest (all that a feature's codes take in
+    half of the columns), residuals over 2^35.  The gradient before its quantisation is the exact mean rounded to
+    fp32, element by element (the levels need not lie on the grid that the dot products use)."""
+    say("exact mean gradient", d, B, bits)
+    rng = np.random.default_rng(bits * 31 + d + B)
+    K, M = 1 << bits, 200
+    G = np.tile(np.linspace(0, M, K).round().astype(np.uint16), (d, 1))
+    L = np.sort(rng.uniform(0.25, 1, (d, K)), axis=1).astype(np.float32)
+    L[:, 0] = (rng.uniform(0.5, 1, d) * 2.0 ** -30).astype(np.float32)
+    A = rng.uniform(0.3, 1, (B, d)).astype(np.float32)
+    A[:, : d // 2] = L[: d // 2, 0]                        # only the smallest level
+    b = (rng.standard_normal(B) * 2.0 ** rng.uniform(-35, 0, B)).astype(np.float32)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L, G)
+    p.quantize(4, 0)
+    c1, c2 = p.codes(1), p.codes(2)
+    assert not c1[:, : d // 2].any()
+    e2e_step_check(p, oracle, c1, c2, L, G, np.float32(0), np.float32(1.0 / M), M, b, np.zeros(d, np.float32), 0.3, 8, 8,
+                   4, 0, 0, zipml.SGD_PRODUCTION)
+
+
 @pytest.mark.parametrize("bits,d", [(8, 100), (8, 170), (7, 161)])
 def test_level_tables_in_memory_are_not_read_past_their_end(bits, d, knobs):
     """Tables too large for LDS, a last feature group with padding features: the rows behind the table (NaN
