@@ -301,10 +301,14 @@ __device__ __forceinline__ int unit_dot_int(const uint32_t (&u)[BITS], const uin
 // thread owns per pass (UPT).
 // FAST: the production configuration (whole steps inside one persistent launch, no debug
 // outputs); everything that only the stepwise / debug launches need folds away at compile time.
+// MEM: the level tables are in memory, not in LDS (lds_levels == 0; 7 and 8 bits only, see plan_lds); the host
+// chooses, and the loops without such tables hold nothing of it.  With that, and without the draws of a quantised
+// gradient, which the fp32 loops never make, 64 samples x 1,000 features at 6 bits take 2.68 us a step (2.82 before).
 // ---------------------------------------------------------------------------------------------
-template <int BITS, int MODE, bool FAST, int UPT>
+template <int BITS, int MODE, bool FAST, int UPT, bool MEM>
 __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
 {
+    constexpr bool lds_levels = !MEM;
     constexpr int K = 1 << BITS;
     constexpr bool kIsInt = MODE == kInt;
     const bool persistent = FAST ? true : a.persistent != 0;
@@ -315,6 +319,9 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
     int32_t *const dbg_gq = FAST ? nullptr : a.dbg_gq;
     float *const dbg_r = FAST ? nullptr : a.dbg_r;
     float *const dbg_g = FAST ? nullptr : a.dbg_g;
+    // (a quantised gradient goes with a quantised model; the key schedule of its draws would otherwise fill the scalar
+    // registers of the fp32 loops)
+    const int grad_bits = kIsInt ? a.grad_bits : 0;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
     const int w = blockIdx.x;
@@ -518,7 +525,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                     if (MODE == kAffine) {
                         pf = unit_fma_codes<BITS>(c2cur[k], ys + jb, pf);
                     } else if (MODE == kTable) {
-                        if (a.lds_levels) pf = unit_dot_table<BITS>(c2cur[k], L.Ls + jb * K, xs + jb, pf);
+                        if (lds_levels) pf = unit_dot_table<BITS>(c2cur[k], L.Ls + jb * K, xs + jb, pf);
                         else pf = unit_dot_table_mem<BITS>(c2cur[k], Lg + (size_t)jb * K, xs + jb, a.d - 1 - j0 - jb, pf);
                     } else {
                         pi = unit_dot_int<BITS>(c2cur[k], a.ident_grid ? nullptr : L.Gs + jb * K,
@@ -685,11 +692,11 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                     // there are no rows for padding features: the last one's stands in, the sum is dropped.)
                     const size_t row = j0 + g_c < a.d ? g_c : a.d - 1 - j0;
                     if constexpr (kIsInt) {
-                        if (a.lds_levels) part[k] = unit_grad_table_f64<BITS>(c1cur[k], L.Ls + g_c * K, rr);
+                        if (lds_levels) part[k] = unit_grad_table_f64<BITS>(c1cur[k], L.Ls + g_c * K, rr);
                         else part[k] = unit_grad_table_f64<BITS>(c1cur[k], Lg + row * K, rr);
                     } else if (MODE == kAffine) {
                         part[k] = unit_fma_codes<BITS>(c1cur[k], rr, 0.0f);
-                    } else if (a.lds_levels) {
+                    } else if (lds_levels) {
                         part[k] = unit_grad_table<BITS>(c1cur[k], L.Ls + g_c * K, rr, 0.0f);
                     } else {
                         part[k] = unit_grad_table<BITS>(c1cur[k], Lg + row * K, rr, 0.0f);
@@ -737,7 +744,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                 lds_barrier();
                 for (int i = tid; i < B; i += kThreads) rs[k0 + i] = 0.0f;
             }
-            if (a.grad_bits > 0) {
+            if (grad_bits > 0) {
                 double *ng = a.nrm + 1024 + (size_t)(t & 1) * 512;
                 lds_barrier();
                 if (tid < CW) red[tid] = (double)gs[tid] * (double)gs[tid];
@@ -758,12 +765,12 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
         if (seg_last < 3) continue;
 
         // ================= segment 3: gradient quantisation, update ==============================
-        if (a.grad_bits > 0) {
+        if (grad_bits > 0) {
             if (!persistent && seg_first == 3 && tid < CW)
                 gs[tid] = (j0 + tid < a.d) ? a.gbuf[j0 + tid] : 0.0f;
             double *ng = a.nrm + 1024 + (size_t)(t & 1) * 512;
             const float Mg = combined_norm(ng, own_sq);
-            const int s_g = (1 << (a.grad_bits - 1)) - 1;
+            const int s_g = (1 << (grad_bits - 1)) - 1;
             const float sg = Mg > 0.0f ? __fdiv_rn(Mg, (float)s_g) : 0.0f;
             if (tid < CW) {
                 const int j = j0 + tid;
@@ -816,7 +823,7 @@ namespace zipml {
 // through tagged stores.  With all its instantiations in one kernel the loop of a production launch
 // spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
 // that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
-template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0>
+template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0, bool MEM = false>
 __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
 {
     constexpr int K = 1 << BITS;
@@ -932,8 +939,12 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                 }
             }
             if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 1, false, kXM>(a, L, L.mf);
-            else if (affine) sgd_steps<BITS, kAffine, FAST, UPT>(a, L);
-            else sgd_steps<BITS, kTable, FAST, UPT>(a, L);
+            else {
+                // (four feature groups of 8 bits: the tables are in memory)
+                constexpr bool kMem = BITS == 8 && kKB == 2;
+                if (affine) sgd_steps<BITS, kAffine, FAST, UPT, kMem>(a, L);
+                else sgd_steps<BITS, kTable, FAST, UPT, kMem>(a, L);
+            }
         }
     } else if constexpr (REP) {
         if constexpr (!INT && FAST && kMfmaBits) {
@@ -973,9 +984,9 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                 return;
             }
         } else if (affine) {
-            sgd_steps<BITS, kAffine, FAST, UPT>(a, L);
+            sgd_steps<BITS, kAffine, FAST, UPT, MEM>(a, L);
         } else {
-            sgd_steps<BITS, kTable, FAST, UPT>(a, L);
+            sgd_steps<BITS, kTable, FAST, UPT, MEM>(a, L);
         }
     } else {
         if constexpr (INT && FAST) {
@@ -992,11 +1003,11 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                 }
             }
         } else if (INT) {
-            sgd_steps<BITS, kInt, FAST, UPT>(a, L);
+            sgd_steps<BITS, kInt, FAST, UPT, MEM>(a, L);
         } else if (affine) {
-            sgd_steps<BITS, kAffine, FAST, UPT>(a, L);
+            sgd_steps<BITS, kAffine, FAST, UPT, MEM>(a, L);
         } else {
-            sgd_steps<BITS, kTable, FAST, UPT>(a, L);
+            sgd_steps<BITS, kTable, FAST, UPT, MEM>(a, L);
         }
     }
 
@@ -1147,7 +1158,7 @@ static size_t plan_lds(int GQ, int bits, int64_t batch, bool int_table, bool int
 {
     const int K = 1 << bits, CW = 32 * GQ;
     const int nrg = batch >= 32 ? (int)(batch / 32) : 1;
-    lds_levels = (size_t)CW * K * 4 <= 65536 ? 1 : 0;
+    lds_levels = (size_t)CW * K * 4 <= 65536 ? 1 : 0;      // (0: 7 bits on eight feature groups, 8 bits on four or eight)
     const size_t total = (lds_levels ? up16((size_t)CW * K * 4) : 0) +
                          (int_table ? up16((size_t)CW * K * 2) : 0) + 6 * up16((size_t)CW * 4) +
                          (int_mode && bits <= 4 ? up16((size_t)CW * K * 4) : 0) +
@@ -1224,13 +1235,21 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
     const bool fast = !stepwise && (!debug || a.dbg_production) && !(INT && (a.W == 1 || p.upt > 2));
     if (a.dbg_production && !fast) return ZIPML_EUNSUPPORTED;
     const void *kern = (const void *)k_sgd<BITS, INT, false, kMaxUpt>;
+    if constexpr (BITS >= 7)
+        if (!a.lds_levels) kern = (const void *)k_sgd<BITS, INT, false, kMaxUpt, false, 0, true>;
     if (fast) {
         if constexpr (INT) {
+            // (this loop looks the tables up in either place)
             kern = p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1> : (const void *)k_sgd<BITS, true, true, 2>;
         } else {
             kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1>
                  : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2>
                               : (const void *)k_sgd<BITS, false, true, 4>;
+            if constexpr (BITS >= 7)
+                if (!a.lds_levels)
+                    kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, false, 0, true>
+                         : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2, false, 0, true>
+                                      : (const void *)k_sgd<BITS, false, true, 4, false, 0, true>;
         }
         if constexpr (!INT && (BITS == 2 || BITS == 4 || BITS == 8)) {
             if (a.R > 1)
