@@ -301,14 +301,18 @@ __device__ __forceinline__ int unit_dot_int(const uint32_t (&u)[BITS], const uin
 // thread owns per pass (UPT).
 // FAST: the production configuration (whole steps inside one persistent launch, no debug
 // outputs); everything that only the stepwise / debug launches need folds away at compile time.
-// MEM: the level tables are in memory, not in LDS (lds_levels == 0; 7 and 8 bits only, see plan_lds); the host
-// chooses, and the loops without such tables hold nothing of it.  With that, and without the draws of a quantised
-// gradient, which the fp32 loops never make, 64 samples x 1,000 features at 6 bits take 2.68 us a step (2.82 before).
+// TAB: where the level tables are, in LDS or in memory (lds_levels == 0; 7 and 8 bits only, see plan_lds): known where
+// the kernel is (the kernels that hold one matrix-core loop and this one for uneven levels), or asked.  Known, uneven
+// levels of 4 bits, 64 samples x 1,000 features, take 2.9 us a step (3.1 before the guard for tables in memory, 3.5
+// with it asked).  Asked where that is the faster one, by what it does to the scalar registers of the loops around
+// it: in the kernels without a matrix-core loop (6 bits, 64 x 1,000, 2.64 us, known 2.67) and at 2 bits (1,024 x 512,
+// the matrix-core loop, 3.58, known 3.62).
 // ---------------------------------------------------------------------------------------------
-template <int BITS, int MODE, bool FAST, int UPT, bool MEM>
+enum { kTabLds, kTabMem, kTabAsked };
+template <int BITS, int MODE, bool FAST, int UPT, int TAB>
 __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
 {
-    constexpr bool lds_levels = !MEM;
+    const bool lds_levels = TAB == kTabAsked ? a.lds_levels != 0 : TAB == kTabLds;
     constexpr int K = 1 << BITS;
     constexpr bool kIsInt = MODE == kInt;
     const bool persistent = FAST ? true : a.persistent != 0;
@@ -823,7 +827,7 @@ namespace zipml {
 // through tagged stores.  With all its instantiations in one kernel the loop of a production launch
 // spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
 // that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
-template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0, bool MEM = false>
+template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0>
 __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
 {
     constexpr int K = 1 << BITS;
@@ -940,10 +944,10 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
             }
             if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 1, false, kXM>(a, L, L.mf);
             else {
-                // (four feature groups of 8 bits: the tables are in memory)
-                constexpr bool kMem = BITS == 8 && kKB == 2;
-                if (affine) sgd_steps<BITS, kAffine, FAST, UPT, kMem>(a, L);
-                else sgd_steps<BITS, kTable, FAST, UPT, kMem>(a, L);
+                // (four feature groups of 8 bits: in memory; at 2 bits the question stays, see sgd_steps)
+                constexpr int kTab = BITS == 2 ? kTabAsked : BITS == 8 && kKB == 2 ? kTabMem : kTabLds;
+                if (affine) sgd_steps<BITS, kAffine, FAST, UPT, kTab>(a, L);
+                else sgd_steps<BITS, kTable, FAST, UPT, kTab>(a, L);
             }
         }
     } else if constexpr (REP) {
@@ -984,9 +988,9 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                 return;
             }
         } else if (affine) {
-            sgd_steps<BITS, kAffine, FAST, UPT, MEM>(a, L);
+            sgd_steps<BITS, kAffine, FAST, UPT, kTabAsked>(a, L);
         } else {
-            sgd_steps<BITS, kTable, FAST, UPT, MEM>(a, L);
+            sgd_steps<BITS, kTable, FAST, UPT, kTabAsked>(a, L);
         }
     } else {
         if constexpr (INT && FAST) {
@@ -1003,11 +1007,11 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                 }
             }
         } else if (INT) {
-            sgd_steps<BITS, kInt, FAST, UPT, MEM>(a, L);
+            sgd_steps<BITS, kInt, FAST, UPT, kTabAsked>(a, L);
         } else if (affine) {
-            sgd_steps<BITS, kAffine, FAST, UPT, MEM>(a, L);
+            sgd_steps<BITS, kAffine, FAST, UPT, kTabAsked>(a, L);
         } else {
-            sgd_steps<BITS, kTable, FAST, UPT, MEM>(a, L);
+            sgd_steps<BITS, kTable, FAST, UPT, kTabAsked>(a, L);
         }
     }
 
@@ -1235,21 +1239,13 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
     const bool fast = !stepwise && (!debug || a.dbg_production) && !(INT && (a.W == 1 || p.upt > 2));
     if (a.dbg_production && !fast) return ZIPML_EUNSUPPORTED;
     const void *kern = (const void *)k_sgd<BITS, INT, false, kMaxUpt>;
-    if constexpr (BITS >= 7)
-        if (!a.lds_levels) kern = (const void *)k_sgd<BITS, INT, false, kMaxUpt, false, 0, true>;
     if (fast) {
         if constexpr (INT) {
-            // (this loop looks the tables up in either place)
             kern = p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1> : (const void *)k_sgd<BITS, true, true, 2>;
         } else {
             kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1>
                  : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2>
                               : (const void *)k_sgd<BITS, false, true, 4>;
-            if constexpr (BITS >= 7)
-                if (!a.lds_levels)
-                    kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, false, 0, true>
-                         : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2, false, 0, true>
-                                      : (const void *)k_sgd<BITS, false, true, 4, false, 0, true>;
         }
         if constexpr (!INT && (BITS == 2 || BITS == 4 || BITS == 8)) {
             if (a.R > 1)
