@@ -159,7 +159,9 @@ int zipml_sgd_epoch_compact(void *stream, const void *compact_dev, const float *
  *     over features and over samples are accumulated as integers (fixed-point partial sums, and
  *     for evenly spaced 2-, 4- or 8-bit levels exact integer sums of codes times fixed-point
  *     digits), so the result does not depend on the order in which workgroups finish: two calls
- *     with the same arguments give the same bits.
+ *     with the same arguments give the same bits.  A problem that one workgroup holds (up to 256
+ *     features) has no such sums: it runs in fp32, or on digits that keep every fp32 bit of residuals,
+ *     model and levels down to 2^-35 of the largest of them, added in a fixed order.
  *   model_bits in 2..8: the model is stochastically quantised each step with row scaling
  *     (Supp. A.3 eq. (quant2), Supp. C), s = 2^(model_bits-1) - 1 magnitude intervals, and the dot
  *     product becomes an exact integer sum of grid_idx * model code; this needs grid_idx_dev and a

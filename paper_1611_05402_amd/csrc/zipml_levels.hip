@@ -659,7 +659,8 @@ extern "C" size_t zipml_workspace_bytes(int64_t n, int64_t d, int bits, int64_t 
     if (n <= 0 || d <= 0 || !valid_bits(bits) || batch <= 0 || n_candidates < 0) return 0;
     size_t sgd = Workspace::xchg_offset(d, batch) + Workspace::xchg_bytes(d, batch);
     size_t lev = levels_workspace_bytes(d, n_candidates);
-    size_t loss = (2048 + 1) * sizeof(double) + 1024;   // partial sums, result, flags of the level check
+    // the smallest that zipml_loss takes; the preparation of its matrix-core path, y in fp64 for up to 19,904 features
+    size_t loss = std::max<size_t>((2048 + 1) * sizeof(double) + 1024, 2048 + 8 * (size_t)std::min<int64_t>(d, 19904));
     size_t need = std::max(sgd, std::max(lev, loss));
     return (size_t)round_up((int64_t)need, 256);
 }
