@@ -50,12 +50,12 @@ struct Workspace {
     static constexpr size_t kNorm = 8192;         // norm exchange: 2 x 3 x 512 doubles (24 KiB)
     static constexpr size_t kAcc = 8192 + 24576;  // exchange buffers, 64-bit words (see below)
     static constexpr int kAccBuffers = 4;
-    // One set of exchange buffers: kAccBuffers x acc_words(batch of one exchange), with room for
-    // the sums of both code pairs of the symmetrised estimator and the side words.
-    static size_t acc_words(int64_t batch) { return (size_t)round_up(2 * batch + 64, 64); }
+    // One set of exchange buffers: kAccBuffers x acc_words(sums of one exchange), with room for the side words;
+    // eight words side by side, the next eight (8 << sh) words on.
+    static size_t acc_words(int64_t sums, int sh) { return (size_t)round_up(sums + 2, 64) << sh; }
     // A large minibatch is split over up to kMaxReplicas sets of workgroups; every replica has its
-    // own set of exchange buffers for its share of the minibatch (R * acc_words(batch / R) <=
-    // 2 * batch + 64 * R words per buffer), and the replicas exchange gradients through two
+    // own set of exchange buffers for its share of the minibatch (unspread, R * acc_words(2 batch / R, 0)
+    // <= 2 * batch + 64 * R words per buffer), and the replicas exchange gradients through two
     // buffers of kGradWords tagged words (at most 256 workgroups x 128 features), which follow
     // the exchange buffers in use.
     static constexpr int kMaxReplicas = 256;

@@ -70,6 +70,30 @@ __device__ __forceinline__ uint64_t pack_fp(float p, int kexp)
     q = fmin(fmax(q, -lim), lim);
     return pack_int(__double2ll_rn(q));
 }
+// Where word i of an exchange buffer lies: eight words (64 bytes) side by side, the next eight 64 << sh bytes on.  The
+// memory side works through the atomics and polls of one 256-byte stretch one after the other, so words side by side
+// make a queue: 256 words, an atomic add per workgroup and word, then polls, take 1.46 us (32 workgroups), 2.1 (64), 4.0
+// (128); eight words to 256 bytes (sh = 2) 1.0, 1.3 and 2.1, to 128 bytes 1.0, 1.35 and 2.5.  64 samples x 1,000
+// features, 6 bits: 2.64 -> 2.30 us a step; 512 x 4,096, end to end at 3 bits: 9.55 -> 8.70.
+__device__ __forceinline__ int xword(int i, int sh) { return ((i >> 3) << (3 + sh)) | (i & 7); }
+// When a wave asks for the exchange words the first time.  A request costs its round trip (0.5 us) whether or not the
+// words are complete, so one sent a little too early costs nearly another: the wave then waits longer from the next
+// step on, by two units of 64 cycles, and a quarter of a unit less after every step in which the
+// first request was enough.
+// (32 workgroups x 256 words: 0.96 us asked at once, 0.82 with a wait of 12 units; the dense 8-bit step 2.97 -> 2.85.)
+struct FirstPoll {
+    int quarters = 0;                                 // of a unit
+    __device__ __forceinline__ void wait() const
+    {
+#pragma unroll 1
+        for (int n = quarters >> 2; n > 0; --n) __builtin_amdgcn_s_sleep(1);
+    }
+    __device__ __forceinline__ void learn(bool late)
+    {
+        if (late) quarters = quarters < 56 ? quarters + 8 : 64;
+        else quarters = quarters > 0 ? quarters - 1 : 0;
+    }
+};
 __device__ __forceinline__ long long unpack_sum(uint64_t v, int W)
 {
     return (long long)(v & kPayloadMask) - (long long)W * kBias;
@@ -107,7 +131,8 @@ struct SgdArgs {
     uint32_t *sync;
     double *nrm;           // [2 kinds][2 slots][512] (+ 1024 spare)
     uint64_t *acc;         // [4][acc_words] exchange words
-    int acc_words;
+    int acc_words;         // words of a buffer
+    int acc_sh;            // how far the exchange words are spread (xword)
     const double *bound;   // at launch: [0] sum_j maxabs(L_j)|x_j|, [1] sum_j maxabs(L_j)^2,
                            // [2] max_j delta_j|x_j|, [3] max_j delta_j maxabs(L_j)
     int mfma;              // evenly spaced levels may take the matrix-core step loop
@@ -394,6 +419,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
     // ---- grid barrier state (one monotonically increasing arrival counter)
     uint32_t passed = 0;
     bool dead = false;
+    FirstPoll first_poll;
     auto arrive_and_poll = [&]() {   // lane 0 of wave 0, after the workgroup's atomics are done
         ++passed;
         add_dev(a.sync, 1u);
@@ -502,7 +528,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                     int tot = 0;
                     for (int q = 0; q < kWaves; ++q) tot += L.isum[q];
                     if (local) ((int *)L.zl)[B] = tot;
-                    else add_dev(acc + B, pack_int(tot));
+                    else add_dev(acc + xword(B, a.acc_sh), pack_int(tot));
                 }
             }
             // dot pass: the partial sums of a sample over the owned feature groups are combined in
@@ -516,7 +542,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                 if (local) {
                     if (kIsInt) ((int *)L.zl)[i] = pi; else L.zl[i] = pf;
                 } else {
-                    add_dev(acc + i, kIsInt ? pack_int(pi) : pack_fp(pf, kexp));
+                    add_dev(acc + xword(i, a.acc_sh), kIsInt ? pack_int(pi) : pack_fp(pf, kexp));
                 }
             };
             const bool combine = ngroups > 1;
@@ -563,7 +589,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
             if (grid_sync && wave == kWaves - 1) {
                 uint64_t *nxt = a.acc + (size_t)((t + 2) & 3) * a.acc_words;
                 const int per = (B + 1 + a.W - 1) / a.W, hi = (w + 1) * per < B + 1 ? (w + 1) * per : B + 1;
-                for (int i = w * per + lane; i < hi; i += kWave) store_dev(nxt + i, (uint64_t)0);
+                for (int i = w * per + lane; i < hi; i += kWave) store_dev(nxt + xword(i, a.acc_sh), (uint64_t)0);
                 if (!(tid < B)) vm_wait_all();
             }
             ZIPML_TICK(1);
@@ -616,14 +642,15 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                     if (kIsInt) rawm = (uint64_t)(uint32_t)((const int *)L.zl)[B];
                 } else {
                     uint32_t spins = 0;
+                    first_poll.wait();
 #pragma unroll 1
                     for (;;) {
 #pragma unroll
                         for (int q = 0; q < kBpt; ++q) {
                             const int i = tid + q * kThreads;
-                            raw[q] = load_dev(acc + (i < B ? i : B - 1));
+                            raw[q] = load_dev(acc + xword(i < B ? i : B - 1, a.acc_sh));
                         }
-                        if (kIsInt) rawm = load_dev(acc + B);
+                        if (kIsInt) rawm = load_dev(acc + xword(B, a.acc_sh));
                         bool all = !kIsInt || (int)(rawm >> kCountShift) == W;
 #pragma unroll
                         for (int q = 0; q < kBpt; ++q) all = all && (int)(raw[q] >> kCountShift) == W;
@@ -633,6 +660,7 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
                             dead = true;
                         }
                     }
+                    first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
                 }
                 const double summ = !kIsInt ? 0.0
                                   : local ? (double)(int)(uint32_t)rawm : (double)unpack_sum(rawm, W);
@@ -1665,16 +1693,18 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
     a.acc = (uint64_t *)(ws + Workspace::kAcc);
     a.bound = (const double *)(ws + Workspace::kBound);
     a.even = (const int *)(ws + Workspace::kEven);
-    a.acc_words = (int)Workspace::acc_words(micro);
-    a.gx = a.acc + (size_t)replicas * Workspace::kAccBuffers * a.acc_words;
-    // the exchange buffers of all replicas and the gradient exchange words must fit what
-    // zipml_workspace_bytes provides for this batch (they do by construction: checked anyway)
+    // The exchange words are spread as far as the room that zipml_workspace_bytes provides for this batch allows
+    // (the buffers of all replicas and the gradient exchange words have to fit).
     {
-        const size_t used = ((size_t)replicas * Workspace::kAccBuffers * a.acc_words +
-                             (replicas > 1 ? 2 * Workspace::kGradWords : 0)) * 8;
-        if (Workspace::kAcc + used > Workspace::sgd_bytes(batch) ||
+        const size_t grad_words = replicas > 1 ? 2 * Workspace::kGradWords : 0;
+        const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
+        a.acc_sh = p.W > 64 ? 2 : 1;    // (two lines a stretch are enough for few workgroups, and half as many words to poll)
+        while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(pairs * micro, a.acc_sh) + grad_words > room) --a.acc_sh;
+        a.acc_words = (int)Workspace::acc_words(pairs * micro, a.acc_sh);
+        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))
             return ZIPML_EWORKSPACE;
+        a.gx = a.acc + (size_t)replicas * Workspace::kAccBuffers * a.acc_words;
     }
     a.gbuf = (float *)(ws + Workspace::sgd_bytes(batch));
     // Exchange through tagged stores: the matrix-core loop with all eight waves at work and enough

@@ -216,10 +216,11 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     };
 
     bool dead = false;
+    FirstPoll first_poll, first_norm[2];
     // One trip of the norm exchange.  sq: this thread's square (owners; 0 elsewhere), fp64.
     // Returns the l2 norm over all workgroups as fp32, to the owner waves (others get 0).
     // meanwhile(): work of the owner waves that does not need the norm, done while it travels.
-    auto exchange_norm = [&](double sq, uint64_t *slots, auto meanwhile) -> float {
+    auto exchange_norm = [&](double sq, uint64_t *slots, FirstPoll &first, auto meanwhile) -> float {
         if (owner_wave) {
             sq = wave_tree_sum_f64(sq);
             if (lane == 0) red[wave] = sq;
@@ -233,6 +234,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         }
         if (!owner_wave) return 0.0f;
         meanwhile();
+        first.wait();
         uint64_t raw[4] = {1ull, 1ull, 1ull, 1ull};   // (bits of 0.0) + 1 for the slots past W
         uint32_t spins = 0;
 #pragma unroll 1
@@ -250,6 +252,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 dead = true;
             }
         }
+        first.learn(spins != 0);
         double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -303,7 +306,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 asm volatile("" : "+v"(draw));       // (here, not where it is used)
             };
         };
-        const float Mx = exchange_norm(live ? (double)x_own * (double)x_own : 0.0, xn, draw_for(3u));
+        const float Mx = exchange_norm(live ? (double)x_own * (double)x_own : 0.0, xn, first_norm[0], draw_for(3u));
         ZIPML_TICK(0);
         const float sigma = Mx > 0.0f ? __fdiv_rn(Mx, (float)s_m) : 0.0f;
         if (owner_wave) {
@@ -330,7 +333,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         if (tid == 0) {
             int tot = 0;
             for (int q = 0; q < owner_waves; ++q) tot += L.isum[q];
-            add_dev(acc + B, pack_int(tot));
+            add_dev(acc + xword(B, a.acc_sh), pack_int(tot));
         }
 
         // ================= dot pass: acc_i = sum_j G[j][c2_ij] m_j over the owned features
@@ -358,7 +361,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 int tot = 0;
 #pragma unroll
                 for (int k = 0; k < UPT; ++k) tot += pi[k];
-                add_dev(acc + tid, pack_int(tot));
+                add_dev(acc + xword(tid, a.acc_sh), pack_int(tot));
             } else if (ngroups > 1) {
 #pragma unroll
                 for (int k = 0; k < UPT; ++k)
@@ -367,12 +370,12 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 for (int i = tid; i < B; i += kThreads) {
                     int tot = 0;
                     for (int gq = 0; gq < ngroups; ++gq) tot += (int)L.zp[gq * B + i];
-                    add_dev(acc + i, pack_int(tot));
+                    add_dev(acc + xword(i, a.acc_sh), pack_int(tot));
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < UPT; ++k)
-                    if (d_g[k] < ngroups) add_dev(acc + d_i[k], pack_int(pi[k]));
+                    if (d_g[k] < ngroups) add_dev(acc + xword(d_i[k], a.acc_sh), pack_int(pi[k]));
             }
         }
         ZIPML_TICK(2);
@@ -385,7 +388,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         if (wave == kWaves - 1) {
             uint64_t *nxt = a.acc + (size_t)((t + 2) & 3) * a.acc_words;
             const int per = (B + 1 + W - 1) / W, hi = (w + 1) * per < B + 1 ? (w + 1) * per : B + 1;
-            for (int i = w * per + lane; i < hi; i += kWave) store_dev(nxt + i, (uint64_t)0);
+            for (int i = w * per + lane; i < hi; i += kWave) store_dev(nxt + xword(i, a.acc_sh), (uint64_t)0);
             if (lane == 0) {
                 store_dev(slot_base + (size_t)((t + 2) & 3) * kNormSlots + w, (uint64_t)0);
                 store_dev(slot_base + (size_t)(4 + ((t + 2) & 3)) * kNormSlots + w, (uint64_t)0);
@@ -415,14 +418,15 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         if (tid < B) {
             uint64_t raw[UPT], rawm = 0;
             uint32_t spins = 0;
+            first_poll.wait();
 #pragma unroll 1
             for (;;) {
 #pragma unroll
                 for (int q = 0; q < UPT; ++q) {
                     const int i = tid + q * kThreads;
-                    raw[q] = load_dev(acc + (i < B ? i : B - 1));
+                    raw[q] = load_dev(acc + xword(i < B ? i : B - 1, a.acc_sh));
                 }
-                rawm = load_dev(acc + B);
+                rawm = load_dev(acc + xword(B, a.acc_sh));
                 bool all = (int)(rawm >> kCountShift) == W;
 #pragma unroll
                 for (int q = 0; q < UPT; ++q) all = all && (int)(raw[q] >> kCountShift) == W;
@@ -432,6 +436,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                     dead = true;
                 }
             }
+            first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
             const double summ = (double)unpack_sum(rawm, W);
 #pragma unroll
             for (int q = 0; q < UPT; ++q) {
@@ -600,7 +605,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         ZIPML_TICK(6);
         // ================= ||g||_2, Q4, update
         if (a.grad_bits > 0) {
-            const float Mg = exchange_norm(is_owner ? (double)g * (double)g : 0.0, gn, draw_for(4u));
+            const float Mg = exchange_norm(is_owner ? (double)g * (double)g : 0.0, gn, first_norm[1], draw_for(4u));
             const float sg = Mg > 0.0f ? __fdiv_rn(Mg, (float)s_g) : 0.0f;
             if (live) {
                 const int code = qvec_code(g, Mg, s_g, draw);

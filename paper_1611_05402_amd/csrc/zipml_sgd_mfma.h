@@ -158,7 +158,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
             if (wave == kWaves - 1) {
                 // clear this workgroup's share of the exchange words of step t+2 (see zipml_sgd.hip for why now)
                 uint64_t *nxt = acc_base + (size_t)((u + 2) & 3) * a.acc_words;
-                for (int i = clr_lo + lane; i < clr_hi; i += kWave) store_dev(nxt + i, (uint64_t)0);
+                for (int i = clr_lo + lane; i < clr_hi; i += kWave) store_dev(nxt + xword(i, a.acc_sh), (uint64_t)0);
                 vm_wait_all();
             }
             if (xstore)
@@ -326,6 +326,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
     }
 
     bool dead = false;
+    FirstPoll first_poll;
 #ifdef ZIPML_PHASE_TIMING
     long long prof_[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     long long last_ = wall_clock64();
@@ -403,7 +404,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                         const int tile = wave + nw * (4 * gi + q4);
                         if (tile < ntile) {
                             if (xstore) store_dev(pub_xmine + cc * B + 16 * tile + n16, tag_word(pub_xtag, combine_digits(c) + kconst));
-                            else add_dev(pub_acc + cc * B + 16 * tile + n16, pack_int(combine_digits(c) + kconst));
+                            else add_dev(pub_acc + xword(cc * B + 16 * tile + n16, a.acc_sh), pack_int(combine_digits(c) + kconst));
                         }
                     }
                 }
@@ -419,7 +420,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                 }
                 const long long v = lane == 0 ? __double2ll_ru(ldexp((double)bw, ky)) + 1 : (long long)mx;
                 if (xstore) store_dev(pub_xmine + NC * B + lane, tag_word(pub_xtag, v));
-                else add_dev(pub_acc + NC * B + lane, pack_int(v));
+                else add_dev(pub_acc + xword(NC * B + lane, a.acc_sh), pack_int(v));
             }
         }
         // The last wave of every workgroup clears its share of the exchange words of step t+2 (see
@@ -427,7 +428,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
         // idle waves around, one of them does it instead.
         if (!xstore && nw == kWaves && wave == kWaves - 1) {
             uint64_t *nxt = acc_base + (size_t)((uu + 2) & 3) * a.acc_words;
-            for (int i = clr_lo + lane; i < clr_hi; i += kWave) store_dev(nxt + i, (uint64_t)0);
+            for (int i = clr_lo + lane; i < clr_hi; i += kWave) store_dev(nxt + xword(i, a.acc_sh), (uint64_t)0);
             if (!(tid < B)) vm_wait_all();
         }
         ZIPML_TICK(11);
@@ -573,9 +574,10 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                 // (Only then: for a few workgroups the extra round trip costs more than it saves.)
                 const int watch = wave * kWave < B ? wave * kWave : 0;
                 const bool watch_first = (int64_t)W * B >= kWatchFirst;
+                first_poll.wait();
 #pragma unroll 1
                 for (;;) {
-                    if (watch_first && !dead && (int)(load_dev(acc + watch) >> kCountShift) != W) {
+                    if (watch_first && !dead && (int)(load_dev(acc + xword(watch, a.acc_sh)) >> kCountShift) != W) {
                         if (++spins > a.spin_limit) {
                             store_dev(a.status, (int)ZIPML_ETIMEOUT);
                             dead = true;
@@ -587,9 +589,9 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
 #pragma unroll
                         for (int q = 0; q < kBpt; ++q) {
                             const int i = tid + q * nthr;
-                            raw[cc][q] = load_dev(acc + cc * B + (i < B ? i : B - 1));
+                            raw[cc][q] = load_dev(acc + xword(cc * B + (i < B ? i : B - 1), a.acc_sh));
                         }
-                    if (want_side) rawx = load_dev(acc + NC * B + (lane & 1));
+                    if (want_side) rawx = load_dev(acc + xword(NC * B + (lane & 1), a.acc_sh));
                     bool all = !want_side || (int)(rawx >> kCountShift) == W;
 #pragma unroll
                     for (int cc = 0; cc < NC; ++cc)
@@ -602,6 +604,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                     }
                 }
             }
+            first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
             if (want_side && lane < 2) side[lane] = fixed_to_float(unpack_sum(rawx, W), ky_pub) * 1.00001f;
 #pragma unroll
             for (int q = 0; q < kBpt; ++q) {

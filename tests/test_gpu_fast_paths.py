@@ -450,3 +450,31 @@ def test_level_tables_in_memory_are_not_read_past_their_end(bits, d, knobs):
     ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.1 / d)
     got = x.cpu().numpy().astype(np.float64)
     assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("groups", [2, 9, 64, 65, 70])
+@pytest.mark.parametrize("B,bits", [(4, 3), (8, 4), (32, 6), (96, 2), (64, 8), (576, 4)])
+def test_epochs_over_exchange_words_of_every_spacing(B, bits, groups, knobs):
+    """Both spacings of the exchange words (up to 64 workgroups, and more), sums that end inside and at the end of a
+    run of eight words, more steps than exchange buffers; even and uneven levels.  The model of the oracle (fp64 inside
+    a step) to 1e-5, the bound of every epoch test."""
+    say("spread exchange words", B, bits, groups)
+    knobs(zipml.KNOB_TARGET_WORKGROUPS, 128)
+    d, steps = groups * 32 - 5, 9
+    d = max(d, 257)
+    n, K = B * steps, 1 << bits
+    rng = np.random.default_rng(B * 100 + groups)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    even = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    uneven = np.sort(rng.uniform(-1, 1, (d, K)), axis=1).astype(np.float32)
+    for L in (even, uneven):
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(L)
+        p.quantize(5, 0)
+        x = dev(np.zeros(d, np.float32))
+        lr = 0.25 / d
+        p.epoch(x, lr)
+        ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, lr)
+        err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+        assert err <= 1e-5, err
