@@ -304,23 +304,71 @@ constexpr size_t kHistSlabBytes = (size_t)64 << 20;
 // almost no variance have values that all lie within tol: every j is tried then, as it used to be.)
 // Three rounds per k, from few to all end points, T threads: T / 64 end points with a wave each
 // (every j), T / 8 with eight lanes each (between the limits of the round before), then all, a thread
-// each.  2,048 features x 1,024 candidates x 7 intervals: some 100 values of V per thread and k
-// instead of 1,024, 4.34 -> 0.45 ms.
-// LDS: 6 arrays of M+1 doubles and the argmin table (s+1) x (M+1) uint16, whose row 0 nothing else uses and
+// each.
+// What a value costs bounds the kernel (LDS reads and fp64 instructions), so the rounds look at V in a cheaper
+// form first.  Multiplied out,
+//   T(k-1, j) + V(j, m) + [S2_m - d_m S1_m] = A_j + d_j p_m + d_m q_j,
+//   A_j = T(k-1, j) + S2_j - d_j S1_j,   p_m = S1_m - d_m C_m,   q_j = d_j C_j - S1_j:
+// one 16-byte read (A_j, q_j) and two fused operations per value in place of five 8-byte reads and some twenty
+// instructions.  From the same prefix sums it is off by at most 16 N 2^-53, the expression of the host version by 17
+// (roundings of numbers up to 3 N).  So of two values of the cheap form that lie more than tol2 = 128 N 2^-53 apart the
+// larger is not the minimum of the exact one: where the second best is further away than that, the exact
+// expression is evaluated once, at the best j; otherwise for all j that are not out of reach.  (The limits of a
+// round rest on tol, which has the 64 N 2^-50 for it.)  The outermost j within tol are the best ones of the
+// lanes unless a lane has a second one within tol; only then the values are gone through again.
+// 2,048 features x 1,024 candidates x 7 intervals: 4.34 ms with every j tried, 0.49 with the exact expression in
+// three rounds, 0.26 now (the prefix chains and the first loads of a feature included).
+// T(k, .) takes the place of T(k-1, .) in descending blocks of 2 T end points: an end point needs smaller ones only.
+// LDS: 5 arrays of M+1 doubles, A (with q beside it where 7 arrays fit: PAIRS; else q is computed from C and S1), and
+// the argmin table (s+1) x (M+1) uint16, whose row 0 nothing else uses and
 // which holds the limits that the rounds set; two workgroups of 512 threads per compute unit at 1,024 candidates
 // and 3 bits.  All of it is counted here: tables that end just below the limit of a workgroup (2,046 candidates at
 // 4 bits) leave no room for static LDS beside them.
 constexpr int kDpThreads = 512;
+// (the instructions themselves: fmin and fmax put one before them that quiets their operands)
+__device__ __forceinline__ double min_f64(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double max_f64(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(uint32_t)lo | (long long)hi << 32);
+}
+// The minimum over the 8 or 64 lanes of a group (all of them active), to all of them.
+template <int LANES> __device__ __forceinline__ double group_min_f64(double v)
+{
+    v = min_f64(v, dpp_f64<0xB1>(v));        // quad_perm: lane ^ 1
+    v = min_f64(v, dpp_f64<0x4E>(v));        // quad_perm: lane ^ 2
+    v = min_f64(v, dpp_f64<0x141>(v));       // row_half_mirror: the other four of eight
+    if constexpr (LANES == kWave) {
+        v = min_f64(v, dpp_f64<0x140>(v));   // row_mirror: the other eight of sixteen
+        v = min_f64(v, __shfl_xor(v, 16, kWave));
+        v = min_f64(v, __shfl_xor(v, 32, kWave));
+    }
+    return v;
+}
 constexpr int kDpRound1 = kDpThreads / 64, kDpRound2 = kDpThreads / 8;       // end points of the first two rounds
 constexpr int kDpLimits = 2 * (kDpRound1 + kDpRound2);
-__host__ __device__ inline size_t dp_lds_bytes(int M, int s)
+__host__ __device__ inline size_t dp_lds_bytes(int M, int s, bool pairs)
 {
     const size_t W = (size_t)M + 1, row0 = W > kDpLimits ? W : kDpLimits;
-    return 6 * W * sizeof(double) + ((row0 + (size_t)s * W) * sizeof(uint16_t) + 15) / 16 * 16 + 64;
+    return (pairs ? 7 : 6) * W * sizeof(double) + ((row0 + (size_t)s * W) * sizeof(uint16_t) + 15) / 16 * 16 + 64;
 }
 // With sel / count (the greedy search below): the candidates of feature j are the count[j] + 1 bin
 // edges sel[j][0 .. count[j]] and hist holds the moments of the intervals between them; Mcap is
 // the largest number of intervals a feature can have (it sizes the tables).
+template <bool PAIRS>
 __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restrict__ hist,
                                                    const float *__restrict__ lo,
                                                    const float *__restrict__ hi, int64_t d, int Mgrid,
@@ -333,10 +381,11 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restri
     extern __shared__ __align__(16) unsigned char dp_smem[];
     const int K = s + 1, tid = threadIdx.x, T = blockDim.x;    // (T <= kDpThreads: fewer threads for few candidates)
     const int Wcap = Mcap + 1;
-    double *C = (double *)dp_smem, *S1 = C + Wcap, *S2 = S1 + Wcap, *edge = S2 + Wcap,
-           *prev = edge + Wcap, *cur = prev + Wcap;
+    // A: [Wcap], with PAIRS (A, q) [Wcap]
+    double *const A = (double *)dp_smem, *const C = A + (PAIRS ? 2 : 1) * (size_t)Wcap, *const S1 = C + Wcap,
+           *const S2 = S1 + Wcap, *const edge = S2 + Wcap, *const prev = edge + Wcap;
     // limits on j that the end points of the first two rounds set: the outermost j within tol of the best
-    uint16_t *const lim_lo = (uint16_t *)(dp_smem + 6 * (size_t)Wcap * sizeof(double));
+    uint16_t *const lim_lo = (uint16_t *)(prev + Wcap);
     uint16_t *const lim_hi = lim_lo + kDpRound1 + kDpRound2;
     const double INF = __longlong_as_double(0x7FF0000000000000ll);
     for (int64_t j = blockIdx.x; j < d; j += gridDim.x) {
@@ -345,78 +394,105 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restri
         const int M = sel ? count[j] : Mgrid;
         const int W = M + 1;
         uint16_t *const arg = lim_lo + (W < kDpLimits ? kDpLimits - W : 0);    // [1 .. s][W] behind the limits
-        prev = edge + Wcap;
-        cur = prev + Wcap;
         __syncthreads();
         for (int e = tid; e < 3 * M; e += T) C[(size_t)(e % 3) * Wcap + e / 3 + 1] = mom[e];
-        for (int m = tid; m < W; m += T) {
-            edge[m] = (double)(cand ? (int)cand[m] : m) / (double)Mgrid;
-            prev[m] = INF;
-        }
+        for (int m = tid; m < W; m += T) edge[m] = (double)(cand ? (int)cand[m] : m) / (double)Mgrid;
         __syncthreads();
-        // prefix moments, in index order (three chains, one thread each, sixteen terms read ahead)
+        // prefix moments, in index order (three chains, one thread each, the next sixteen terms read ahead)
         if (tid < 3) {
             double *dst = C + (size_t)tid * Wcap;
-            double acc = 0.0;
+            double acc = 0.0, v[16];
             dst[0] = 0.0;
-            for (int m = 1; m <= M; m += 16) {
-                double v[16];
+            int m = 1;
 #pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = dst[m + u <= M ? m + u : M];
+            for (int u = 0; u < 16; ++u) v[u] = dst[1 + u <= M ? 1 + u : M];
+            for (; m + 15 <= M; m += 16) {
+                double nx[16];
 #pragma unroll
-                for (int u = 0; u < 16; ++u)
-                    if (m + u <= M) {
-                        acc = acc + v[u];
-                        dst[m + u] = acc;
-                    }
+                for (int u = 0; u < 16; ++u) nx[u] = dst[m + 16 + u <= M ? m + 16 + u : M];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    acc = acc + v[u];
+                    dst[m + u] = acc;
+                }
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = nx[u];
             }
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (m + u <= M) {
+                    acc = acc + v[u];
+                    dst[m + u] = acc;
+                }
         }
         __syncthreads();
         auto V = [&](int jj, int m) {
             const double dj = edge[jj], dm = edge[m];
             return -(S2[m] - S2[jj]) + (dj + dm) * (S1[m] - S1[jj]) - dj * dm * (C[m] - C[jj]);
         };
-        for (int m = 1 + tid; m <= M; m += T) {
-            prev[m] = V(0, m);
-            arg[1 * W + m] = 0;
+        auto set_value = [&](int m, double v) {          // T(k, m) and what the cheap form needs of it
+            prev[m] = v;
+            const double a = v + fma(-edge[m], S1[m], S2[m]);
+            if constexpr (PAIRS) A[2 * m] = a; else A[m] = a;
+        };
+        for (int m = tid; m <= M; m += T) {
+            set_value(m, m > 0 ? V(0, m) : INF);
+            if (m > 0) arg[1 * W + m] = 0;
+            if constexpr (PAIRS) A[2 * m + 1] = fma(edge[m], C[m], -S1[m]);
         }
         const double tol = (double)(4 * M + 64) * C[M] * (1.0 / 1125899906842624.0);    // 2^-50
+        const double tol2 = C[M] * (1.0 / 70368744177664.0);                            // 2^-46
         __syncthreads();
-        // T(k, m) over j = jlo + q, jlo + q + step, ... <= jhi, the smallest j on ties
-        auto scan = [&](int m, int jlo, int jhi, int q, int step, double &best, int &bj) {
-            const double dm = edge[m], s2m = S2[m], s1m = S1[m], cm = C[m];
+        // the cheap form, less a term of m alone, for one m and any j
+        auto cheap = [&](int m) {
+            const double dm = edge[m], p = S1[m] - dm * C[m];
+            return [=](int jj) {
+                const double dj = edge[jj];
+                if constexpr (PAIRS) {
+                    const double2 aq = *reinterpret_cast<const double2 *>(A + 2 * jj);
+                    return fma(dm, aq.y, fma(dj, p, aq.x));
+                } else {
+                    return fma(dm, fma(dj, C[jj], -S1[jj]), fma(dj, p, A[jj]));
+                }
+            };
+        };
+        // the best and the second best value of the cheap form over j = jlo + q, jlo + q + step, ... <= jhi
+        struct Two { double best, second; int j; };
+        auto scan = [&](auto value, int jlo, int jhi, int q, int step) {
+            Two t{INF, INF, 0x7fff};
 #pragma unroll 4
             for (int jj = jlo + q; jj <= jhi; jj += step) {
-                const double dj = edge[jj];
-                const double vjm = -(s2m - S2[jj]) + (dj + dm) * (s1m - S1[jj]) - dj * dm * (cm - C[jj]);
-                const double v = prev[jj] + vjm;
-                if (v < best) { best = v; bj = jj; }
+                const double v = value(jj);
+                t.second = min_f64(t.second, max_f64(v, t.best));
+                t.j = v < t.best ? jj : t.j;
+                t.best = min_f64(t.best, v);
             }
+            return t;
         };
-        // the same shared out over the `lanes` lanes of a group (a power of two), and the limits it sets
-        auto group_scan = [&](int m, int k, int jlo, int jhi, int lanes, int slot) {
+        // an end point of the first two rounds, by the lanes of a group (8 or 64): the limits it sets
+        auto group_scan = [&](int m, int k, int jlo, int jhi, auto lanes_tag, int slot) {
+            constexpr int lanes = decltype(lanes_tag)::value;
             const int q = tid & (lanes - 1);
-            double best = INF;
-            int bj = 0x7fff;
-            scan(m, jlo, jhi, q, lanes, best, bj);
-            for (int off = lanes / 2; off > 0; off >>= 1) {
-                const double ob = __shfl_xor(best, off, kWave);
-                const int oj = __shfl_xor(bj, off, kWave);
-                if (ob < best || (ob == best && oj < bj)) { best = ob; bj = oj; }
+            const auto value = cheap(m);
+            const Two t = scan(value, jlo, jhi, q, lanes);
+            const double near = group_min_f64<lanes>(t.best) + tol;
+            const bool in_reach = t.best <= near && t.j != 0x7fff, more = !(t.second > near);
+            const uint64_t reaching = __ballot(in_reach) >> (tid & (kWave - lanes));
+            if (!__any(more)) {                          // (the usual case: one lane has the only one within tol)
+                const uint64_t mine = lanes == kWave ? reaching : reaching & ((1ull << (lanes & 63)) - 1);
+                if (__all(mine != 0 && (mine & (mine - 1)) == 0)) {
+                    if (in_reach) lim_lo[slot] = lim_hi[slot] = (uint16_t)t.j;
+                    return;
+                }
             }
             int lo_j = 0x7fff, hi_j = -1;
-            {
-                const double dm = edge[m], s2m = S2[m], s1m = S1[m], cm = C[m];
-                const double near = best + tol;
-#pragma unroll 4
-                for (int jj = jlo + q; jj <= jhi; jj += lanes) {
-                    const double dj = edge[jj];
-                    const double vjm = -(s2m - S2[jj]) + (dj + dm) * (s1m - S1[jj]) - dj * dm * (cm - C[jj]);
-                    if (prev[jj] + vjm <= near) {
+            if (in_reach) lo_j = hi_j = t.j;
+            if (more) {                                  // a second one within tol (or nothing compares)
+                for (int jj = jlo + q; jj <= jhi; jj += lanes)
+                    if (value(jj) <= near) {
                         lo_j = jj < lo_j ? jj : lo_j;
-                        hi_j = jj;
+                        hi_j = jj > hi_j ? jj : hi_j;
                     }
-                }
             }
             for (int off = lanes / 2; off > 0; off >>= 1) {
                 const int ol = __shfl_xor(lo_j, off, kWave), oh = __shfl_xor(hi_j, off, kWave);
@@ -427,6 +503,25 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restri
             if (q == 0) {
                 lim_lo[slot] = (uint16_t)(hi_j >= 0 ? lo_j : k - 1);
                 lim_hi[slot] = (uint16_t)(hi_j >= 0 ? hi_j : m - 1);
+            }
+        };
+        // T(k, m) and its j, the smallest on ties, over jlo <= j <= jhi
+        auto best_of = [&](int m, int jlo, int jhi, double &best, int &bj) {
+            const auto value = cheap(m);
+            const Two t = scan(value, jlo, jhi, 0, 1);
+            if (t.second - t.best > tol2) {
+                const double v = prev[t.j] + V(t.j, m);
+                if (v < INF) {
+                    best = v;
+                    bj = t.j;
+                    return;
+                }
+            }
+            const double reach = t.best + tol2;
+            for (int jj = jlo; jj <= jhi; ++jj) {
+                if (value(jj) > reach) continue;
+                const double v = prev[jj] + V(jj, m);
+                if (v < best) { best = v; bj = jj; }
             }
         };
         // end points of a round: M, M - stride, M - 2 stride, ...
@@ -443,7 +538,7 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restri
         for (int k = 2; k <= s; ++k) {
             {
                 const int m = M - (tid >> 6) * stride1;
-                if (m >= k) group_scan(m, k, k - 1, m - 1, kWave, tid >> 6);
+                if (m >= k) group_scan(m, k, k - 1, m - 1, std::integral_constant<int, kWave>{}, tid >> 6);
             }
             __syncthreads();
             {
@@ -451,22 +546,29 @@ __global__ __launch_bounds__(kDpThreads) void k_dp_levels(const double *__restri
                 int jlo = 0, jhi = -1;
                 if (m >= k) limits(m, k, 0, stride1, jlo, jhi);
                 // (the lanes of a group leave or stay together: they exchange values)
-                if (m >= k) group_scan(m, k, jlo, jhi, 8, nw + (tid >> 3));
+                if (m >= k) group_scan(m, k, jlo, jhi, std::integral_constant<int, 8>{}, nw + (tid >> 3));
             }
             __syncthreads();
-            for (int m = M - tid; m >= 0; m -= T) {
-                double best = INF;
-                int bj = k - 1;
-                if (m >= k) {
-                    int jlo, jhi;
-                    limits(m, k, nw, stride2, jlo, jhi);
-                    scan(m, jlo, jhi, 0, 1, best, bj);
-                    arg[(size_t)k * W + m] = (uint16_t)bj;
+            for (int top = M; top > 0; top -= 2 * T) {        // (T(k, 0) stays infinite)
+                double best[2] = {INF, INF};
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int m = top - h * T - tid;
+                    if (m >= k) {
+                        int jlo, jhi, bj = k - 1;
+                        limits(m, k, nw, stride2, jlo, jhi);
+                        best_of(m, jlo, jhi, best[h], bj);
+                        arg[(size_t)k * W + m] = (uint16_t)bj;
+                    }
                 }
-                cur[m] = best;
+                __syncthreads();                              // (the values of these end points are read until here)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int m = top - h * T - tid;
+                    if (m > 0) set_value(m, best[h]);
+                }
             }
             __syncthreads();
-            double *t = prev; prev = cur; cur = t;
         }
         if (tid == 0) {
             const double total = prev[M];
@@ -771,7 +873,9 @@ extern "C" int zipml_levels(void *stream, const float *A_dev, int64_t n, int64_t
     // the search is the plain one.  Both steps run on the device (no host version).
     const int Mcap = 4 * sI + 1;
     const bool greedy = mode == ZIPML_GREEDY && M > Mcap;
-    const size_t dp_lds = greedy ? dp_lds_bytes(Mcap, sI) : dp_lds_bytes(M, sI);
+    const int dpM = greedy ? Mcap : M;
+    const bool pairs = dp_lds_bytes(dpM, sI, true) <= (size_t)lds_limit;
+    const size_t dp_lds = dp_lds_bytes(dpM, sI, pairs);
     if (greedy && (dp_lds > (size_t)lds_limit || greedy_lds_bytes(M) > (size_t)lds_limit))
         return ZIPML_EUNSUPPORTED;
     if (greedy || (dp_lds <= (size_t)lds_limit && knob(ZIPML_KNOB_HOST_DP) <= 0)) {
@@ -791,13 +895,13 @@ extern "C" int zipml_levels(void *stream, const float *A_dev, int64_t n, int64_t
                                sel_dev, count_dev);
             if (HIP_FAILED(hipGetLastError())) return ZIPML_ELAUNCH;
         }
-        if (HIP_FAILED(hipFuncSetAttribute((const void *)k_dp_levels,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)dp_lds)))
+        auto *const dp = pairs ? k_dp_levels<true> : k_dp_levels<false>;
+        if (HIP_FAILED(hipFuncSetAttribute((const void *)dp, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dp_lds)))
             return ZIPML_ELAUNCH;
         const int dp_threads = greedy ? std::min(kDpThreads, std::max(64, (int)round_up(Mcap + 1, 64))) : kDpThreads;
-        hipLaunchKernelGGL(k_dp_levels, dim3(blocks), dim3(dp_threads), dp_lds, s, hist_dev, lo_dev, hi_dev, d,
+        hipLaunchKernelGGL(dp, dim3(blocks), dim3(dp_threads), dp_lds, s, hist_dev, lo_dev, hi_dev, d,
                            M, sI, levels_dev, grid_dev, objective_dev, (const uint16_t *)sel_dev,
-                           (const int *)count_dev, greedy ? Mcap : M);
+                           (const int *)count_dev, dpM);
         if (HIP_FAILED(hipGetLastError())) return ZIPML_ELAUNCH;
         if (mean_variance_host) {
             std::vector<double> per_feature((size_t)d);
