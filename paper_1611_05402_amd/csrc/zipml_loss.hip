@@ -115,32 +115,37 @@ __global__ __launch_bounds__(256) void k_loss_prepare(const float *__restrict__ 
 // The level tables of a chunk of features, multiplied by x, in LDS.  One look-up serves kPer features:
 // with at most 3 bits the sums T_j[c] + T_j'[c'] of two neighbouring features are tabled, so that a look-up
 // in 16 or 64 words -- words apart, so the lanes' gathers meet no bank conflicts -- takes the place of two,
-// one multiply-add each.  64 KiB of tables (512 features at 3 bits) leave room for two blocks per compute unit.
-// 131,072 x 4,096 codes of 3 bits (201 MB): 632 us a call with a look-up per code in the table in memory, 116 us
-// now, 98 of them the kernel; bound by the LDS gathers and the field extraction (three vector operations
-// and a gather per pair).
+// one multiply-add each.
+// 131,072 x 4,096 codes of 3 bits (201 MB): 632 us a call with a look-up per code in the table in memory, 109 us
+// with chunks of 512 features, 85 with 480; bound by the LDS gathers and the field extraction (three vector operations
+// and a gather per pair).  The 480: at 3 bits the tables of 512 features and what they are built from are 82 KiB, and a
+// compute unit holds one block; of 480 it holds two, one looking up while the other builds.  Where no
+// compute unit has a second block the larger chunks are the fewer (4,096 x 4,096: 46 and 47 us; 8,192 x 16,384: 118 and 122).
 template <int BITS> struct LossTable {
     static constexpr int K = 1 << BITS;
     static constexpr int kPer = BITS <= 3 ? 2 : 1;         // features per look-up
     static constexpr int kRow = 1 << (BITS * kPer);        // entries of a look-up's table
     static constexpr int kFeatures = 16384 / kRow * kPer < 512 ? 16384 / kRow * kPer : 512;   // per chunk
-    static constexpr size_t kTab = (size_t)kFeatures / kPer * kRow * 4;
-    static constexpr size_t kSingle = kPer == 2 ? (size_t)kFeatures * (K + 1) * 4 : 0;   // levels and model, on the way
-    static constexpr size_t kBytes = kTab + kSingle;
+    static constexpr int kFeaturesTwo = BITS == 3 ? 480 : kFeatures;   // where two blocks share a compute unit
+    __host__ __device__ static constexpr size_t tab_bytes(int features) { return (size_t)features / kPer * kRow * 4; }
+    __host__ __device__ static constexpr size_t bytes(int features)      // (levels and model, on the way, behind the tables)
+    {
+        return tab_bytes(features) + (kPer == 2 ? (size_t)features * (K + 1) * 4 : 0);
+    }
 };
 
 // Packed copy 2 (sample-major units) through the tables.  A block takes `spb` samples (64 to 512, a power of
-// two), a thread one of them and every (512 / spb)-th feature group; the parts of a sample meet in LDS.
+// two) and `chunk` features at a time, a thread one of the samples and every (512 / spb)-th feature group; the parts of a sample meet in LDS.
 constexpr int kLossPackedThreads = 512;
 template <int BITS>
 __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ p2, const float *__restrict__ levels,
                                                    const float *__restrict__ b, const float *__restrict__ x, int64_t n,
-                                                   int64_t d, int64_t n_pad, int spb, unsigned char *smem)
+                                                   int64_t d, int64_t n_pad, int spb, int chunk, unsigned char *smem)
 {
     using LT = LossTable<BITS>;
     constexpr int K = LT::K, kPer = LT::kPer, kRow = LT::kRow, kT = kLossPackedThreads;
     constexpr int kBatch = BITS <= 4 ? 4 : 2;              // units in use, and as many on the way
-    float *const tab = (float *)smem, *const one = (float *)(smem + LT::kTab);
+    float *const tab = (float *)smem, *const one = (float *)(smem + LT::tab_bytes(chunk));
     double *const zs = (double *)smem;                     // [512 / spb][spb], after the last chunk
     const int tid = threadIdx.x, splits = kT / spb;
     const int smp = tid & (spb - 1), fs = tid / spb;       // (whole waves share fs)
@@ -148,8 +153,8 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
     for (int64_t T = blockIdx.x; T * spb < n; T += gridDim.x) {
         const int64_t i = T * spb + smp, row = i < n_pad ? i : n_pad - 1;
         float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int64_t c0 = 0; c0 < d; c0 += LT::kFeatures) {
-            const int nf = d - c0 < LT::kFeatures ? (int)(d - c0) : LT::kFeatures, nfp = (nf + 31) & ~31;
+        for (int64_t c0 = 0; c0 < d; c0 += chunk) {
+            const int nf = d - c0 < chunk ? (int)(d - c0) : chunk, nfp = (nf + 31) & ~31;
             // the first units are requested before the tables are built, the next ones before a batch is used
             const uint32_t *src = p2 + ((c0 / 32) * n_pad + row) * BITS;
             const int ng = nfp / 32;
@@ -250,7 +255,7 @@ __device__ __forceinline__ double loss_copy2_table(const uint32_t *__restrict__ 
 template <int BITS>
 __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
     const uint32_t *__restrict__ p2, const float *__restrict__ levels, const float *__restrict__ b,
-    const float *__restrict__ x, int64_t n, int64_t d, int64_t n_pad, int64_t d32, int NKB, int spb,
+    const float *__restrict__ x, int64_t n, int64_t d, int64_t n_pad, int64_t d32, int NKB, int spb, int chunk,
     const LossPrep *__restrict__ prep, const double *__restrict__ y, double *__restrict__ partial)
 {
     constexpr int HW = kOpDwords<BITS>, kW = kLossPackedThreads / kWave;
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
         ok_all &= prep->ymin[lane] >= ldexpf(ymax, -37);
     }
     if (!__syncthreads_and(ok_all)) {
-        const double acc = loss_copy2_table<BITS>(p2, levels, b, x, n, d, n_pad, spb, smem);
+        const double acc = loss_copy2_table<BITS>(p2, levels, b, x, n, d, n_pad, spb, chunk, smem);
         const double tot = block_sum<double>(acc, scratch);
         if (tid == 0) partial[blockIdx.x] = tot;
         return;
@@ -519,13 +524,14 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
     }
     int NKB = (int)((lay.d32 + 1) / 2);
     if (!prep || loss_mfma_lds_bytes(NKB) + kLossStaticLds > (size_t)lds_limit) NKB = 0;   // through the tables, whatever the levels
-    size_t shmem = LossTable<BITS>::kBytes < 4096 ? 4096 : LossTable<BITS>::kBytes;
-    if (NKB > 0 && loss_mfma_lds_bytes(NKB) > shmem) shmem = loss_mfma_lds_bytes(NKB);
-    if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy2<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)))
-        return ZIPML_ELAUNCH;
     // samples per block on the table path: as many as leave two blocks per compute unit
     int spb = kLossPackedThreads;
     while (spb > 64 && (lay.n + spb - 1) / spb < 2 * cus) spb >>= 1;
+    const int chunk = (lay.n + spb - 1) / spb > cus ? LossTable<BITS>::kFeaturesTwo : LossTable<BITS>::kFeatures;
+    size_t shmem = LossTable<BITS>::bytes(chunk) < 4096 ? 4096 : LossTable<BITS>::bytes(chunk);
+    if (NKB > 0 && loss_mfma_lds_bytes(NKB) > shmem) shmem = loss_mfma_lds_bytes(NKB);
+    if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy2<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)))
+        return ZIPML_ELAUNCH;
     const int64_t NT = lay.n_pad / 64;
     const int blocks = (int)(NT < 1024 ? NT : 1024);
     double *y = (double *)(prep + 1);
@@ -533,7 +539,7 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
         hipLaunchKernelGGL(k_loss_prepare, dim3(kLossPrepBlocks), dim3(256), 0, s, levels, x, lay.d, 1 << BITS,
                            BITS == 8 ? 128.0 : 0.0, prep, y);
     hipLaunchKernelGGL(k_loss_copy2<BITS>, dim3(blocks), dim3(kLossPackedThreads), shmem, s, p, levels, b, x, lay.n,
-                       lay.d, lay.n_pad, lay.d32, NKB, spb, prep, y, partial);
+                       lay.d, lay.n_pad, lay.d32, NKB, spb, chunk, prep, y, partial);
     return blocks;
 }
 

@@ -129,6 +129,28 @@ def test_loss_on_packed_copies_of_every_width(n, d, bits):
             assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
 
 
+@pytest.mark.parametrize("n", [16384, 16385])
+@pytest.mark.parametrize("d", [479, 480, 481, 512, 513, 961])
+def test_loss_through_tables_of_both_chunk_sizes(n, d):
+    """3 bits, uneven levels: at 256 compute units chunks of 512 features up to 16,384 samples and of 480 beyond, whole and
+    ragged.  The band is that of the test above."""
+    rng = np.random.default_rng(n + d)
+    say("packed loss, chunks of features", n, d)
+    b = rng.standard_normal(n).astype(np.float32)
+    x = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    L = np.sort(rng.uniform(-1, 1, (d, 8)), axis=1).astype(np.float32)
+    p = GpuProblem(rng.uniform(-1, 1, (n, d)).astype(np.float32), b, 3, 32)
+    p.set_levels(L)
+    p.quantize(3, 0)
+    v = np.take_along_axis(L, p.codes(2).astype(np.int64).T, axis=1).T.astype(np.float64)
+    r = v @ x.astype(np.float64) - b
+    ref = float(np.sum(r ** 2) / (2 * n))
+    mag = float((np.abs(L[:, 0]) + np.abs(L[:, -1] - L[:, 0])).astype(np.float64) @ np.abs(x))
+    band = float(np.mean(np.abs(r))) * mag * (d + 4) * 2.0 ** -24
+    got = p.loss(dev(x), packed_copy=2)
+    assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
+
+
 @pytest.mark.parametrize("bits", [2, 4, 8])
 @pytest.mark.parametrize("d", [19904, 19905, 39808, 39809, 39872, 39873])
 def test_loss_where_the_digits_of_the_model_just_fit_on_the_chip(d, bits):
