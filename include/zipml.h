@@ -309,7 +309,7 @@ int zipml_debug_stream(void *stream, const void *src_dev, void *dst_dev, size_t 
  * sweeps, A/B measurements and tests that steer kernel selection (the library never reads the
  * environment).  value = -1 restores the automatic choice.  Values out of a knob's range are
  * ignored by the code that consults it.  Returns ZIPML_EINVAL for an unknown knob. */
-#define ZIPML_KNOB_TARGET_WORKGROUPS 0  /* preferred number of feature-owner workgroups (default 32)  */
+#define ZIPML_KNOB_TARGET_WORKGROUPS 0  /* most feature-owner workgroups wanted (default: by sizes)    */
 #define ZIPML_KNOB_NO_MATRIX_CORES   1  /* 1: evenly spaced levels stay on the vector-ALU step loop    */
 #define ZIPML_KNOB_CHUNK_SAMPLES     2  /* chunk size of minibatches taken in chunks                    */
 #define ZIPML_KNOB_MAX_REPLICAS      3  /* most replicas of the workgroups that share the chunks        */

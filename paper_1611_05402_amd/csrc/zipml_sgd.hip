@@ -1205,7 +1205,7 @@ static size_t plan_lds(int GQ, int bits, int64_t batch, bool int_table, bool int
 }
 
 // Chooses how many feature groups a workgroup owns.  A step costs one device-wide exchange whose
-// latency grows with the number of workgroups, so small steps want few, fat workgroups; the
+// latency grows with the number of workgroups, so small steps want few, fat workgroups (fewer_workgroups); the
 // registers that hold a thread's units (at most kMaxUpt per pass) and the number of compute units
 // bound the choice from both sides.
 static int target_workgroups()
@@ -1215,12 +1215,37 @@ static int target_workgroups()
     return 32;
 }
 
+// Whether W workgroups of GQ feature groups are too many, and half as many of twice the size better.  What an exchange
+// among twice the workgroups costs more (0.1 to 0.3 us from 32 to 64, 0.4 to 0.8 to 128, 1 to 2 to 256) stands
+// against the phases of a step, which grow with the units (feature groups x samples) of a workgroup.  Up to 32 are never too
+// many.  Measured, us per step (few | many workgroups; 64, 128 or 256 samples, 2 to 8 bits):
+//   matrix cores: 2,048 features 256 x 8 bits, 512 units 2.78 | 2.94, 512 x 8, 1,024 units 4.00 | 3.61; 4,096 features on four groups (two
+//     blocks of 64 features to a workgroup) or on two 2.78 | 2.69, 2.85 | 2.64, 2.99 | 2.69; 128 against 64 workgroups 3.5 | 2.7 (64 x 8).
+//     Eight groups would leave the matrix cores: 8,192 features 3.55 | 2.91, 4.05 | 3.08, 5.66 | 3.20.  Two code pairs at
+//     once: 2,048 features 2.78 | 3.17 (128 units), 3.85 | 3.49 (512), but eight groups are refused.
+//   vector ALU: 33 to 64 workgroups instead of half, 256 units 2.67 | 2.86, 512 units 3.03 | 2.92 and 3.08 | 3.06, 1,024
+//     units 4.52 | 3.52; 65 to 128: 512 units 3.52 | 3.79, 1,024 units 5.19 | 4.63; 129 to 256: 1,024 units 5.2 | 6.5.
+//   end to end (three exchanges): 33 to 64, 512 units 7.06 | 7.37, 1,024 units 8.01 | 7.47; 65 to 128: 8.8 | 9.8.
+// (Levels that are not even leave the matrix cores' loop for the vector ALU's in the same plan: 8,192 features, 4 bits, 256
+// samples 15.5 | 7.6.)
+static bool fewer_workgroups(int64_t W, int GQ, int64_t batch, bool mfma, bool fp32_model, int pairs)
+{
+    const int64_t units = 2 * GQ * batch;                  // of a workgroup of twice the size
+    if (W <= 32) return false;
+    if (pairs == 2) return W > 64 || GQ == 4 || (GQ == 1 && units <= 256);
+    if (mfma) return GQ < 4 ? W > 64 || (GQ == 1 && units <= 512) : W > 128;
+    if (!fp32_model) return W > 64 || units <= 512;
+    return W > 128 || units <= (W > 64 ? 512 : 256);
+}
+
+// per_chunk: for one of several chunks of a minibatch, whose replicas want few workgroups each.
 static int make_plan(int64_t d32, int bits, int64_t batch, bool int_table, bool fp32_model, int pairs,
-                     Plan &p)
+                     bool per_chunk, Plan &p)
 {
     int cus = 0, lds = 0;
     if (int rc = device_limits(cus, lds)) return rc;
     const int kTargetW = target_workgroups();
+    const bool by_target = per_chunk || knob(ZIPML_KNOB_TARGET_WORKGROUPS) >= 1;
     int best = 0;
     for (int GQ = 1; GQ <= 8; GQ <<= 1) {
         const int64_t W = (d32 + GQ - 1) / GQ;
@@ -1246,11 +1271,12 @@ static int make_plan(int64_t d32, int bits, int64_t batch, bool int_table, bool 
         p.GQ = GQ; p.W = (int)W; p.lds_levels = ll; p.shmem = sh; p.mfma = mfma ? 1 : 0;
         const int64_t units = batch * GQ;
         p.upt = units <= kThreads ? 1 : units <= 2 * kThreads ? 2 : 4;
-        // stop at the preferred workgroup count -- unless a single workgroup is within reach:
+        // stop at a good workgroup count -- unless a single workgroup is within reach:
         // it needs no device-wide exchange at all
         const int64_t gq_solo = d32 <= 8 ? (d32 <= 1 ? 1 : d32 <= 2 ? 2 : d32 <= 4 ? 4 : 8) : 0;
         const bool solo_possible = gq_solo && batch * gq_solo <= (int64_t)kMaxUpt * kThreads;
-        if (W <= kTargetW && !(solo_possible && W > 1)) break;
+        const bool fewer = by_target ? W > kTargetW : fewer_workgroups(W, GQ, batch, mfma, fp32_model, pairs);
+        if (!fewer && !(solo_possible && W > 1)) break;
     }
     return best ? ZIPML_OK : ZIPML_EUNSUPPORTED;   // batch too large for one step in registers
 }
@@ -1513,7 +1539,7 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
     Plan p{};
     int64_t chunks = 1, micro = batch;
     const int pairs = avg ? 2 : 1;
-    int rc = make_plan(lay.d32, bits, batch, model_bits > 0 && !ident, model_bits == 0, pairs, p);
+    int rc = make_plan(lay.d32, bits, batch, model_bits > 0 && !ident, model_bits == 0, pairs, false, p);
     const bool stepwise = (flags & ZIPML_SGD_STEPWISE) != 0;
     const bool debug = dbg_m || dbg_acc || dbg_r || dbg_g || dbg_gq;
     // A problem that fits one workgroup, fp32 model: the kernel made for that (zipml_sgd_solo.hip), where two
@@ -1570,7 +1596,7 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
             if (batch % c != 0 || (batch / c) % 64 != 0) continue;
             if (forced > 0 && batch / c != forced) continue;
             Plan q{};
-            if (make_plan(lay.d32, bits, batch / c, false, true, pairs, q) != ZIPML_OK || !q.mfma) continue;
+            if (make_plan(lay.d32, bits, batch / c, false, true, pairs, true, q) != ZIPML_OK || !q.mfma) continue;
             if (!have || q.W <= w_goal) {
                 p = q;
                 chunks = c;

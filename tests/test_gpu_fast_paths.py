@@ -511,3 +511,28 @@ def test_epochs_over_exchange_words_of_every_spacing(B, bits, groups, knobs):
         ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, lr)
         err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
         assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("groups", [33, 64, 65, 128, 129, 257])
+@pytest.mark.parametrize("B,bits", [(128, 3), (160, 3), (256, 8), (320, 4)])
+def test_epochs_on_both_sides_of_the_numbers_of_workgroups(B, bits, groups):
+    """The workgroups that sizes give: either side of 32, 64 and 128 of them and of the units from which more are taken;
+    even and uneven levels.  The model of the oracle (fp64 inside a step) to 1e-5, the bound of every epoch test."""
+    say("number of workgroups", B, bits, groups)
+    d, steps = groups * 32 - 3, 3
+    n, K = B * steps, 1 << bits
+    rng = np.random.default_rng(B * 100 + groups)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    even = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    uneven = np.sort(rng.uniform(-1, 1, (d, K)), axis=1).astype(np.float32)
+    for L in (even, uneven):
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(L)
+        p.quantize(5, 0)
+        x = dev(np.zeros(d, np.float32))
+        lr = 0.25 / d
+        p.epoch(x, lr)
+        ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, lr)
+        err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+        assert err <= 1e-5, err
