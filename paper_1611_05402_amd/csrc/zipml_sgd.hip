@@ -855,6 +855,7 @@ namespace zipml {
 // through tagged stores.  With all its instantiations in one kernel the loop of a production launch
 // spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
 // that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
+// (5, 6: that of two code pairs on replicas, up to two feature groups or four)
 template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0>
 __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
 {
@@ -955,7 +956,12 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         if (blockIdx.x == 0 && tid == 0) store_dev(a.status, (int)ZIPML_EUNSUPPORTED);
         return;
     }
-    if constexpr (SOLO != 0) {
+    if constexpr (SOLO >= 5) {
+        // two code pairs on replicas (anything but the matrix-core loop has been refused above): with the other loops of
+        // the replicas in one kernel its registers spill (8 bits, 2,048 x 4,100: 26.4 us a step, 25.4 by itself; 2,048 x 1,030 10.4 and 9.4)
+        if constexpr (!INT && FAST && kMfmaBits && REP && UPT <= 2)
+            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, SOLO - 4, 2, true, 0>(a, L, L.mf);
+    } else if constexpr (SOLO != 0) {
         // (the host launches this kernel for the plain estimator on the matrix-core plan, without
         // replicas or debug outputs, with the workgroup width and the exchange it was built for)
         if constexpr (!INT && FAST && kMfmaBits && !REP) {
@@ -981,12 +987,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
     } else if constexpr (REP) {
         if constexpr (!INT && FAST && kMfmaBits) {
             if (affine_all && a.mfma) {     // (anything else has been refused above: replicas imply chunks)
-                if (a.avg) {
-                    if constexpr (UPT <= 2) {
-                        if (a.GQ <= 2) sgd_steps_mfma<BITS, UPT, 1, 2, true, 0>(a, L, L.mf);
-                        else sgd_steps_mfma<BITS, UPT, 2, 2, true, 0>(a, L, L.mf);
-                    }
-                } else if (a.xstore) {
+                if (a.xstore) {
                     if (a.GQ <= 2) sgd_steps_mfma<BITS, UPT, 1, 1, true, 1>(a, L, L.mf);
                     else sgd_steps_mfma<BITS, UPT, 2, 1, true, 1>(a, L, L.mf);
                 } else {
@@ -1302,7 +1303,11 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
                               : (const void *)k_sgd<BITS, false, true, 4>;
         }
         if constexpr (!INT && (BITS == 2 || BITS == 4 || BITS == 8)) {
-            if (a.R > 1)
+            if (a.R > 1 && a.avg) {
+                if (p.upt > 2) return ZIPML_EUNSUPPORTED;  // (the plan keeps two code pairs to these)
+                if (a.GQ <= 2) kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, true, 5> : (const void *)k_sgd<BITS, false, true, 2, true, 5>;
+                else kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, true, 6> : (const void *)k_sgd<BITS, false, true, 2, true, 6>;
+            } else if (a.R > 1)
                 kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, true>
                      : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2, true>
                                   : (const void *)k_sgd<BITS, false, true, 4, true>;
