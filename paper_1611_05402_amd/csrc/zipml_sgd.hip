@@ -80,7 +80,9 @@ __device__ __forceinline__ int xword(int i, int sh) { return ((i >> 3) << (3 + s
 // words are complete, so one sent a little too early costs nearly another: the wave then waits longer from the next
 // step on, by two units of 64 cycles, and a quarter of a unit less after every step in which the
 // first request was enough.
-// (32 workgroups x 256 words: 0.96 us asked at once, 0.82 with a wait of 12 units; the dense 8-bit step 2.97 -> 2.85.)
+// (The exchange alone, 32 workgroups x 256 words: 0.96 us asked at once, 0.82 with a wait of 12 units.  A step of 512
+// samples x 2,048 features, 8 bits: 3.62 -> 3.55 us.  Where a step has little else to do the bookkeeping costs more than
+// that: kSmall in zipml_sgd_mfma.h goes without.)
 struct FirstPoll {
     int quarters = 0;                                 // of a unit
     __device__ __forceinline__ void wait() const
@@ -1729,10 +1731,13 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
     {
         const size_t grad_words = replicas > 1 ? 2 * Workspace::kGradWords : 0;
         const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
-        a.acc_sh = p.W > 64 ? 2 : 1;    // (two lines a stretch are enough for few workgroups, and half as many words to poll)
+        // (two lines a stretch are enough for few workgroups, and half as many words to poll; the smallest steps of the
+        // matrix-core loop know their spacing, kSmall in zipml_sgd_mfma.h, and have the room for it)
+        const bool small = p.mfma && !avg && p.upt == 1 && p.GQ <= 2;
+        a.acc_sh = p.W > 64 && !small ? 2 : 1;
         while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(pairs * micro, a.acc_sh) + grad_words > room) --a.acc_sh;
         a.acc_words = (int)Workspace::acc_words(pairs * micro, a.acc_sh);
-        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room ||
+        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room || (small && a.acc_sh != 1) ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))
             return ZIPML_EWORKSPACE;
         a.gx = a.acc + (size_t)replicas * Workspace::kAccBuffers * a.acc_words;

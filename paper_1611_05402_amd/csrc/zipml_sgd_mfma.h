@@ -86,6 +86,21 @@ template <int BITS, int UPT, int KB, int NC, bool REP, int XM>
 __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, unsigned char *mf)
 {
     constexpr bool kDbg = XM == 2;
+    // Smallest steps (64 features and at most 512 units a workgroup): what is left of a step besides the exchange is
+    // instructions, so the loop does without what pays in longer ones.  The spacing of the exchange words is a constant
+    // (the host gives such launches no other), and there is no wait before the first poll: its bookkeeping costs 0.05 to
+    // 0.09 us a step (16 to 64 workgroups x 64 or 128 samples) and saves at most 0.03 (64 x 256).  Us per step at 8 bits, with
+    // the spacing in a register, waits and pointers | now: 256 samples x 2,048 features 2.99 | 2.91, 64 x 512 2.40 | 2.31, 64 x
+    // 4,096 2.68 | 2.59, 128 x 1,000 2.46 | 2.37, 256 x 1,024 2.75 | 2.68.  (Where the loop's instructions lie within 32 bytes
+    // moves these by up to 2 %.)
+    constexpr bool kSmall = NC == 1 && KB == 1 && UPT == 1;
+    // Where a lane's units lie: one offset a lane and copy, the rest uniform (or a pointer for every unit).
+    constexpr bool kOnePlace = kSmall;
+    // No load of a step is pending when the next begins, and the compiler is to know it: the loads stand in branches
+    // (p2ok, p1ok), their results are used in others, and what may be pending at the loop's head it waits for in full,
+    // whatever else is on its way.  An explicit wait where all has arrived anyway (a poll returns after the loads sent
+    // before it) and one in front of the loop take that away.
+    constexpr bool kSettle = kOnePlace;
     constexpr int HW = BITS / 2;                       // packed dwords per lane operand
     constexpr int kSlots = KB == 1 ? UPT : (UPT + 3) / 4;   // groups of four 16-sample tiles per wave
     constexpr int kTiles = 4 * kSlots;                 // 16-sample tiles per wave, at most
@@ -135,7 +150,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
     // A thread's exchange words: B and the threads are multiples of 64, so words so far apart are that many
     // << sh apart, and one register holds where the thread polls, another where it publishes (xword() of every
     // index: 64 x 512 features x 8 bits 2.53 us a step, 2.47 now; 512 x 2,048 x 8 3.95 and 3.87).
-    const int sh = a.acc_sh;
+    const int sh = kSmall ? 1 : a.acc_sh;
     const int poll_at = xword(tid, sh), publish_at = xword(16 * (wave + nw * q4) + n16, sh);
     const int wave_at = __builtin_amdgcn_readfirstlane(wave * kWave);
     uint64_t *const acc_base = a.acc + (size_t)rep * Workspace::kAccBuffers * a.acc_words;
@@ -228,7 +243,13 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                                                         // R chunks from one chunk of this replica to its next
     const int64_t row_begin = (u_begin * R + rep) * B;  // first sample of this replica's first chunk
     uint32_t c2cur[NC][kTiles][KB][HW], c2nxt[kT2][KB][HW], c1[NC][kNG][HW], c1nxt[kG2][HW];
-    const uint32_t *p2ptr[NC][kTiles][KB], *p1ptr[NC][kNG];
+    constexpr int kPtrs = kOnePlace ? 0 : NC;           // (pairs whose units have pointers)
+    const uint32_t *p2ptr[kOnePlace ? 1 : NC][kTiles][KB], *p1ptr[kOnePlace ? 1 : NC][kNG];
+    const int64_t p2lane = ((int64_t)(w * GQ + (q4 >> 1)) * a.nb64 * 64 + row_begin + 16 * wave + n16) * BITS + (q4 & 1) * HW;
+    const int64_t p1lane = (((int64_t)(w * GQ + (g_ft >> 1)) * a.n32 + row_begin / 32 + 2 * g_kh + (q4 >> 1)) * 32 +
+                            16 * (g_ft & 1) + n16) * BITS + (q4 & 1) * HW;
+    const int64_t p2block = 2 * a.nb64 * 64 * BITS;     // from one block of 64 features to the next
+    int64_t p2step = 0, p1step = 0;                     // from the first chunk to the one the loads stand at
     bool p2ok[kTiles][KB], p1ok[kNG];
     float bnext[kBpt], bfut[kBpt];
 #pragma unroll
@@ -241,7 +262,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
             const int64_t row = row_begin + 16 * tile + n16;
             const int64_t g = (int64_t)w * GQ + gq;
 #pragma unroll
-            for (int cc = 0; cc < NC; ++cc)
+            for (int cc = 0; cc < kPtrs; ++cc)
                 p2ptr[cc][ti][kb] = p2ok[ti][kb] ? p2base[cc] + (g * a.nb64 * 64 + row) * BITS + (q4 & 1) * HW
                                                  : p2base[cc];
         }
@@ -254,7 +275,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
         const int64_t g = (int64_t)w * GQ + gq;
         const int64_t rg = row_begin / 32 + 2 * ks + (q4 >> 1);
 #pragma unroll
-        for (int cc = 0; cc < NC; ++cc)
+        for (int cc = 0; cc < kPtrs; ++cc)
             p1ptr[cc][m] = p1ok[m] ? p1base[cc] + ((g * a.n32 + rg) * 32 + cin) * BITS + (q4 & 1) * HW
                                    : p1base[cc];
     }
@@ -264,8 +285,9 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
         for (int ti = 0; ti < kTiles; ++ti)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                const uint32_t *q = static_cast<const uint32_t *>(
-                    __builtin_assume_aligned(p2ptr[cc][ti][kb] + ahead * step_dwords, 4 * HW));
+                const uint32_t *q = static_cast<const uint32_t *>(__builtin_assume_aligned(
+                    kOnePlace ? p2base[cc] + (p2step + ahead * step_dwords + (int64_t)16 * nw * ti * BITS + kb * p2block) + p2lane
+                              : p2ptr[kOnePlace ? 0 : cc][ti][kb] + ahead * step_dwords, 4 * HW));
                 if (p2ok[ti][kb]) {
 #pragma unroll
                     for (int k = 0; k < HW; ++k) dst[ti][kb][k] = q[k];
@@ -275,8 +297,9 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
     auto load_grad = [&](int cc, int ahead, auto &dst) {
 #pragma unroll
         for (int m = 0; m < kNG; ++m) {
-            const uint32_t *q = static_cast<const uint32_t *>(
-                __builtin_assume_aligned(p1ptr[cc][m] + ahead * step_dwords, 4 * HW));
+            const uint32_t *q = static_cast<const uint32_t *>(__builtin_assume_aligned(
+                kOnePlace ? p1base[cc] + (p1step + ahead * step_dwords + (int64_t)64 * KSS * m * BITS) + p1lane
+                          : p1ptr[kOnePlace ? 0 : cc][m] + ahead * step_dwords, 4 * HW));
             if (p1ok[m]) {
 #pragma unroll
                 for (int k = 0; k < HW; ++k) dst[m][k] = q[k];
@@ -338,6 +361,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
     long long last_ = wall_clock64();
 #endif
 
+    if constexpr (kSettle) vm_wait_all();
     float rmax_step = 0.0f, gsum = 0.0f;
     int64_t t = a.step0;                                        // minibatch step
     int chunk = 0;
@@ -383,7 +407,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
             const float cq = ((c0.x + c0.y) + (c0.z + c0.w)) + ((c1v.x + c1v.y) + (c1v.z + c1v.w));
             // cq * 2^ky as an integer (|.| < 2^43) without fp64: high part, then the exact rest
             const float sc = ldexpf(cq, ky - 24), sc_hi = truncf(sc);
-            const long long kconst = ((long long)(int)sc_hi << 24) + (long long)__float2int_rn(ldexpf(sc - sc_hi, 24));
+            long long kconst = ((long long)(int)sc_hi << 24) + (long long)__float2int_rn(ldexpf(sc - sc_hi, 24));
             // Four sample tiles share one accumulator: the digits of tile slot s sit in rows
             // 4s..4s+3 of its digit operand (zeros elsewhere), so its sums land in lanes
             // 16s..16s+15 and one combine / one atomic instruction serves all 64 lanes.
@@ -408,6 +432,8 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                             }
                         }
                         const int tile = wave + nw * (4 * gi + q4);
+                        // (here, while the matrix instructions run, and not in the branch behind them)
+                        if constexpr (kOnePlace) asm volatile("" : "+v"(kconst));
                         if (tile < ntile) {
                             if (xstore) store_dev(pub_xmine + cc * B + 16 * tile + n16, tag_word(pub_xtag, combine_digits(c) + kconst));
                             else add_dev(pub_acc + (publish_at + ((cc * B + 64 * nw * gi) << sh)), pack_int(combine_digits(c) + kconst));
@@ -452,8 +478,9 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                     for (int k = 0; k < HW; ++k) c2cur[0][ti][kb][k] = c2nxt[ti][kb][k];
                 }
 #pragma unroll
-                for (int cc = 0; cc < NC; ++cc) p2ptr[cc][ti][kb] += step_dwords;   // now at step t+1
+                for (int cc = 0; cc < kPtrs; ++cc) p2ptr[cc][ti][kb] += step_dwords;   // now at step t+1
             }
+        p2step += step_dwords;
         if constexpr (kDouble) {
             if (uu + 2 < u_end) load_dot(0, 1, c2nxt);
             if (uu + 1 < u_end) load_grad(0, 1, c1nxt);
@@ -552,6 +579,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                     }
                 }
             }
+            if constexpr (kSettle) vm_wait_all();
             if (want_side && lane < 2) side[lane] = fixed_to_float(tagged_value(rawx), ky) * 1.00001f;
 #pragma unroll
             for (int q = 0; q < kBpt; ++q) {
@@ -580,7 +608,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                 // (Only then: for a few workgroups the extra round trip costs more than it saves.)
                 const int watch = wave * kWave < B ? wave * kWave : 0;
                 const bool watch_first = (int64_t)W * B >= kWatchFirst;
-                first_poll.wait();
+                if constexpr (!kSmall) first_poll.wait();
 #pragma unroll 1
                 for (;;) {
                     if (watch_first && !dead && (int)(load_dev(acc + (watch << sh)) >> kCountShift) != W) {
@@ -610,7 +638,8 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                     }
                 }
             }
-            first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
+            if constexpr (!kSmall) first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
+            if constexpr (kSettle) vm_wait_all();
             if (want_side && lane < 2) side[lane] = fixed_to_float(unpack_sum(rawx, W), ky_pub) * 1.00001f;
 #pragma unroll
             for (int q = 0; q < kBpt; ++q) {
@@ -696,12 +725,13 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
 #pragma unroll
             for (int m = 0; m < kNG; ++m) {
 #pragma unroll
-                for (int cc = 0; cc < NC; ++cc) p1ptr[cc][m] += step_dwords;
+                for (int cc = 0; cc < kPtrs; ++cc) p1ptr[cc][m] += step_dwords;
                 if constexpr (kDouble) {
 #pragma unroll
                     for (int k = 0; k < HW; ++k) c1[0][m][k] = c1nxt[m][k];
                 }
             }
+            p1step += step_dwords;
             if constexpr (!kDouble) {
                 if (u + 1 < u_end) {
 #pragma unroll
