@@ -857,7 +857,9 @@ namespace zipml {
 // through tagged stores.  With all its instantiations in one kernel the loop of a production launch
 // spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
 // that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
-// (5, 6: that of two code pairs on replicas, up to two feature groups or four)
+// 5 + (KB - 1) + 2 XM: the same of two code pairs (the symmetrised estimator), with replicas (atomics only) or without.
+// (Us per step, in one kernel with all other loops | by itself: 128 samples x 2,048 features, 2 bits 3.08 | 2.88; 1,024 x
+// 2,048, 8 bits 6.66 | 6.39.)
 template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0>
 __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
 {
@@ -959,10 +961,11 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         return;
     }
     if constexpr (SOLO >= 5) {
-        // two code pairs on replicas (anything but the matrix-core loop has been refused above): with the other loops of
-        // the replicas in one kernel its registers spill (8 bits, 2,048 x 4,100: 26.4 us a step, 25.4 by itself; 2,048 x 1,030 10.4 and 9.4)
-        if constexpr (!INT && FAST && kMfmaBits && REP && UPT <= 2)
-            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, SOLO - 4, 2, true, 0>(a, L, L.mf);
+        // two code pairs (anything but the matrix-core loop has been refused above)
+        if constexpr (!INT && FAST && kMfmaBits && UPT <= 2) {
+            constexpr int kKB = 1 + ((SOLO - 5) & 1), kXM = (SOLO - 5) >> 1;
+            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 2, REP, kXM>(a, L, L.mf);
+        }
     } else if constexpr (SOLO != 0) {
         // (the host launches this kernel for the plain estimator on the matrix-core plan, without
         // replicas or debug outputs, with the workgroup width and the exchange it was built for)
@@ -1000,21 +1003,11 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         }
     } else if constexpr (!INT && FAST && kMfmaBits) {
         if (affine_all && a.mfma) {
-            if (a.avg) {
-                if constexpr (UPT <= 2) {      // the plan keeps the symmetrised estimator to these
-                    if (a.GQ <= 2) {
-                        if (a.xstore) sgd_steps_mfma<BITS, UPT, 1, 2, false, 1>(a, L, L.mf);
-                        else sgd_steps_mfma<BITS, UPT, 1, 2, false, 0>(a, L, L.mf);
-                    } else {
-                        if (a.xstore) sgd_steps_mfma<BITS, UPT, 2, 2, false, 1>(a, L, L.mf);
-                        else sgd_steps_mfma<BITS, UPT, 2, 2, false, 0>(a, L, L.mf);
-                    }
-                }
-            } else if (a.dbg_production) {
+            if (a.dbg_production) {
                 if (a.GQ <= 2) sgd_steps_mfma<BITS, UPT, 1, 1, false, 2>(a, L, L.mf);
                 else sgd_steps_mfma<BITS, UPT, 2, 1, false, 2>(a, L, L.mf);
             } else {
-                // (the plain estimator runs on the kernels that hold one instantiation each: SOLO)
+                // (everything else runs on the kernels that hold one instantiation each: SOLO)
                 if (blockIdx.x == 0 && tid == 0) store_dev(a.status, (int)ZIPML_EUNSUPPORTED);
                 return;
             }
@@ -1305,15 +1298,22 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
                               : (const void *)k_sgd<BITS, false, true, 4>;
         }
         if constexpr (!INT && (BITS == 2 || BITS == 4 || BITS == 8)) {
-            if (a.R > 1 && a.avg) {
-                if (p.upt > 2) return ZIPML_EUNSUPPORTED;  // (the plan keeps two code pairs to these)
-                if (a.GQ <= 2) kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, true, 5> : (const void *)k_sgd<BITS, false, true, 2, true, 5>;
-                else kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, true, 6> : (const void *)k_sgd<BITS, false, true, 2, true, 6>;
+            if (a.avg) {
+                // two code pairs: likewise (the plan keeps them to two units a thread)
+                if (!a.mfma || p.upt > 2 || (a.R > 1 && a.xstore)) return ZIPML_EUNSUPPORTED;
+                const int solo = 5 + (a.GQ <= 2 ? 0 : 1) + 2 * (a.xstore ? 1 : 0);
+#define ZIPML_PAIRS(U) (a.R > 1 ? (solo == 5 ? (const void *)k_sgd<BITS, false, true, U, true, 5> : (const void *)k_sgd<BITS, false, true, U, true, 6>) \
+                      : solo == 5 ? (const void *)k_sgd<BITS, false, true, U, false, 5> \
+                      : solo == 6 ? (const void *)k_sgd<BITS, false, true, U, false, 6> \
+                      : solo == 7 ? (const void *)k_sgd<BITS, false, true, U, false, 7> \
+                                  : (const void *)k_sgd<BITS, false, true, U, false, 8>)
+                kern = p.upt == 1 ? ZIPML_PAIRS(1) : ZIPML_PAIRS(2);
+#undef ZIPML_PAIRS
             } else if (a.R > 1)
                 kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1, true>
                      : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2, true>
                                   : (const void *)k_sgd<BITS, false, true, 4, true>;
-            else if (a.mfma && !a.avg && !a.dbg_production) {
+            else if (a.mfma && !a.dbg_production) {
                 // the plain estimator: the kernel that holds just its instantiation of the loop
                 const int solo = 1 + (a.GQ <= 2 ? 0 : 1) + 2 * (a.xstore ? 1 : 0);
 #define ZIPML_SOLO(U) (solo == 1 ? (const void *)k_sgd<BITS, false, true, U, false, 1> \

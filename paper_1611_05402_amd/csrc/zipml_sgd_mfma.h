@@ -94,13 +94,18 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
     // 4,096 2.68 | 2.59, 128 x 1,000 2.46 | 2.37, 256 x 1,024 2.75 | 2.68.  (Where the loop's instructions lie within 32 bytes
     // moves these by up to 2 %.)
     constexpr bool kSmall = NC == 1 && KB == 1 && UPT == 1;
-    // Where a lane's units lie: one offset a lane and copy, the rest uniform (or a pointer for every unit).
-    constexpr bool kOnePlace = kSmall;
+    // Where a lane's units lie: a pointer for every unit, or one offset a lane and copy and the rest uniform.  The pointers
+    // of two code pairs (up to 48 registers) or of 64 dwords of codes a lane no longer fit beside the codes.
+    constexpr bool kOnePlace = kSmall || (NC == 2 && (REP || UPT * KB > 1)) || (NC == 1 && BITS == 8 && KB == 1 && (REP || UPT == 4));
     // No load of a step is pending when the next begins, and the compiler is to know it: the loads stand in branches
     // (p2ok, p1ok), their results are used in others, and what may be pending at the loop's head it waits for in full,
-    // whatever else is on its way.  An explicit wait where all has arrived anyway (a poll returns after the loads sent
-    // before it) and one in front of the loop take that away.
-    constexpr bool kSettle = kOnePlace;
+    // whatever else is on its way -- where addresses and codes share registers, before every single load.  An explicit
+    // wait where all has arrived anyway (a poll returns after the loads sent before it) and one in front of the loop take
+    // that away.  (Not for the small steps of 128 features: their waves without samples do not poll and would wait for memory.)
+    // Us per step, pointers and implicit waits | now: two code pairs at 8 bits, 2,048 samples x 4,100 features 23.9 | 15.5, x 9,001
+    // 59 | 30.7, x 1,030 8.70 | 8.38, 1,024 x 2,048 7.56 | 6.62; one pair, 4,096 x 600, 8 bits 10.2 | 8.4, 2 bits 8.0 | 7.3;
+    // 1,024 x 4,096, 4 bits 5.17 | 4.88; 512 x 16,384, 4 bits 6.06 | 5.94.
+    constexpr bool kSettle = kOnePlace || (NC == 1 && UPT > 2);
     constexpr int HW = BITS / 2;                       // packed dwords per lane operand
     constexpr int kSlots = KB == 1 ? UPT : (UPT + 3) / 4;   // groups of four 16-sample tiles per wave
     constexpr int kTiles = 4 * kSlots;                 // 16-sample tiles per wave, at most

@@ -536,3 +536,65 @@ def test_epochs_on_both_sides_of_the_numbers_of_workgroups(B, bits, groups):
         ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, lr)
         err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
         assert err <= 1e-5, err
+
+
+def _averaged(B, d, bits, steps, lr, seed=5):
+    """An epoch of the symmetrised estimator on random data and even levels, and the oracle's."""
+    n = B * steps
+    rng = np.random.default_rng(B * 100 + d)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    L = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L)
+    p.quantize(seed, 0)
+    p1s, p2s = torch.zeros_like(p.p1), torch.zeros_like(p.p2)
+    zipml.quantize_swapped(p.A, n, d, d, 0, n, p.levels, bits, seed, 0, p1s, p2s)
+    x = dev(np.zeros(d, np.float32))
+    zipml.sgd_epoch_avg(p.p1, p.p2, p1s, p2s, p.levels, p.b, n, d, bits, x, B, lr, p.ws)
+    assert zipml.sgd_status(p.ws) == 0
+    ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, lr, symmetric=True)
+    return x.cpu().numpy().astype(np.float64), ref
+
+
+@pytest.mark.parametrize("B,d,bits,chunk,steps", [
+    (2048, 4100, 8, 0, 3),       # replicas, four feature groups, two units a thread
+    (2048, 600, 8, 0, 6),        # replicas, one group, two units
+    (512, 4090, 4, 128, 6),      # replicas, four groups, one unit
+    (512, 600, 2, 128, 6),       # replicas, one group, one unit
+    (512, 2040, 2, 0, 6),        # no replicas: 64 workgroups, one unit
+    (1024, 2100, 4, 0, 4),       # 66 workgroups: the wider spacing of the exchange words, two units
+    (256, 4100, 4, 0, 5),        # four groups, two units
+    (1024, 4100, 2, 0, 3),       # exchange through tagged stores, one group
+    (256, 16400, 2, 0, 3),       # the same, four groups
+])
+def test_symmetrised_epochs_of_every_kernel(B, d, bits, chunk, steps, knobs):
+    """The kernels of two code pairs, each by itself.  The model of the oracle (fp64 inside a step) to 1e-5, the bound
+    of every epoch test."""
+    say("two code pairs", B, d, bits, chunk)
+    if chunk:
+        knobs(zipml.KNOB_CHUNK_SAMPLES, chunk)
+    got, ref = _averaged(B, d, bits, steps, 0.25 / d)
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("B,d,bits", [(4096, 600, 8), (4096, 1030, 8), (2048, 600, 4), (2048, 4100, 2), (1024, 4100, 4)])
+def test_large_epochs_of_one_pair(B, d, bits):
+    """Four units a thread, and replicas: one place a lane for its units, or a pointer each.  The bound as above."""
+    say("large minibatches", B, d, bits)
+    steps = 3
+    n = B * steps
+    rng = np.random.default_rng(B + d)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    L = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L)
+    p.quantize(5, 0)
+    x = dev(np.zeros(d, np.float32))
+    p.epoch(x, 0.25 / d)
+    assert zipml.sgd_status(p.ws) == 0
+    ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.25 / d)
+    err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+    assert err <= 1e-5, err
