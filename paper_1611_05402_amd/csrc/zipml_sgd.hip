@@ -1218,7 +1218,7 @@ static int target_workgroups()
 //   matrix cores: 2,048 features 256 x 8 bits, 512 units 2.78 | 2.94, 512 x 8, 1,024 units 4.00 | 3.61; 4,096 features on four groups (two
 //     blocks of 64 features to a workgroup) or on two 2.78 | 2.69, 2.85 | 2.64, 2.99 | 2.69; 128 against 64 workgroups 3.5 | 2.7 (64 x 8).
 //     Eight groups would leave the matrix cores: 8,192 features 3.55 | 2.91, 4.05 | 3.08, 5.66 | 3.20.  Two code pairs at
-//     once: 2,048 features 2.78 | 3.17 (128 units), 3.85 | 3.49 (512), but eight groups are refused.
+//     once: 2,048 features 2.78 | 3.17 (128 units), 3.85 | 3.49 (512); at most four groups.
 //   vector ALU: 33 to 64 workgroups instead of half, 256 units 2.67 | 2.86, 512 units 3.03 | 2.92 and 3.08 | 3.06, 1,024
 //     units 4.52 | 3.52; 65 to 128: 512 units 3.52 | 3.79, 1,024 units 5.19 | 4.63; 129 to 256: 1,024 units 5.2 | 6.5.
 //   end to end (three exchanges): 33 to 64, 512 units 7.06 | 7.37, 1,024 units 8.01 | 7.47; 65 to 128: 8.8 | 9.8.
@@ -1228,7 +1228,7 @@ static bool fewer_workgroups(int64_t W, int GQ, int64_t batch, bool mfma, bool f
 {
     const int64_t units = 2 * GQ * batch;                  // of a workgroup of twice the size
     if (W <= 32) return false;
-    if (pairs == 2) return W > 64 || GQ == 4 || (GQ == 1 && units <= 256);
+    if (pairs == 2) return W > 64 || (GQ == 1 && units <= 256);
     if (mfma) return GQ < 4 ? W > 64 || (GQ == 1 && units <= 512) : W > 128;
     if (!fp32_model) return W > 64 || units <= 512;
     return W > 128 || units <= (W > 64 ? 512 : 256);
@@ -1248,6 +1248,8 @@ static int make_plan(int64_t d32, int bits, int64_t batch, bool int_table, bool 
         if (W > cus || W > 512) continue;
         // units per thread; two code pairs take twice the registers
         if (batch * GQ > (int64_t)(pairs == 2 ? 2 : kMaxUpt) * kThreads) break;
+        // (which run on the matrix cores only: no plan that leaves them in place of one that does not)
+        if (pairs == 2 && GQ > 4 && W > 1) break;
         // end-to-end mode: its production loop holds at most two units per thread and pass; take
         // more, thinner workgroups instead where the device has them
         if (!fp32_model && best && batch * GQ > 2 * (int64_t)kThreads) break;
@@ -1604,6 +1606,9 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
             if (forced > 0 && batch / c != forced) continue;
             Plan q{};
             if (make_plan(lay.d32, bits, batch / c, false, true, pairs, true, q) != ZIPML_OK || !q.mfma) continue;
+            // (two code pairs on more than 4,096 features: chunks of 64 or 128 samples only where there are no larger ones;
+            // 2,240 samples x 5,000 features, 2 bits, in 7 or in 35 chunks: 25 and 100 us a step)
+            if (avg && have && batch / c <= 128 && q.W > target_workgroups()) continue;
             if (!have || q.W <= w_goal) {
                 p = q;
                 chunks = c;

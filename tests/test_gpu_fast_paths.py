@@ -598,3 +598,13 @@ def test_large_epochs_of_one_pair(B, d, bits):
     ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.25 / d)
     err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
     assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("B", [64, 128])
+@pytest.mark.parametrize("d", [4096, 4097, 8192, 8193, 16390])
+def test_symmetrised_epochs_of_small_minibatches_on_wide_problems(B, d):
+    """More than 32 workgroups of four feature groups, which eight groups could replace but for the matrix cores."""
+    say("two code pairs, wide", B, d)
+    got, ref = _averaged(B, d, 4, 5, 0.25 / d)
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert err <= 1e-5, err
