@@ -319,7 +319,7 @@ constexpr size_t kHistSlabBytes = (size_t)64 << 20;
 // 2,048 features x 1,024 candidates x 7 intervals: 4.34 ms with every j tried, 0.49 with the exact expression in
 // three rounds, 0.26 now (the prefix chains and the first loads of a feature included).
 // T(k, .) takes the place of T(k-1, .) in descending blocks of 2 T end points: an end point needs smaller ones only.
-// LDS: 5 arrays of M+1 doubles, A (with q beside it where 7 arrays fit: PAIRS; else q is computed from C and S1), and
+// LDS: 5 arrays of M+1 doubles, A (with q beside it: PAIRS, or q is computed from C and S1), and
 // the argmin table (s+1) x (M+1) uint16, whose row 0 nothing else uses and
 // which holds the limits that the rounds set; two workgroups of 512 threads per compute unit at 1,024 candidates
 // and 3 bits.  All of it is counted here: tables that end just below the limit of a workgroup (2,046 candidates at
@@ -874,7 +874,10 @@ extern "C" int zipml_levels(void *stream, const float *A_dev, int64_t n, int64_t
     const int Mcap = 4 * sI + 1;
     const bool greedy = mode == ZIPML_GREEDY && M > Mcap;
     const int dpM = greedy ? Mcap : M;
-    const bool pairs = dp_lds_bytes(dpM, sI, true) <= (size_t)lds_limit;
+    // both coefficients of a candidate in LDS unless that costs a compute unit its second workgroup (its registers have
+    // room for two): 1,000 candidates at 4 bits, 2,048 features 1,272 us a search with, 902 without; 700 candidates 611 and 678
+    const size_t dp_pairs = dp_lds_bytes(dpM, sI, true);
+    const bool pairs = dp_pairs <= (size_t)lds_limit && (2 * dp_pairs <= (size_t)lds_limit || 2 * dp_lds_bytes(dpM, sI, false) > (size_t)lds_limit);
     const size_t dp_lds = dp_lds_bytes(dpM, sI, pairs);
     if (greedy && (dp_lds > (size_t)lds_limit || greedy_lds_bytes(M) > (size_t)lds_limit))
         return ZIPML_EUNSUPPORTED;

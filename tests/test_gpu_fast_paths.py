@@ -74,6 +74,18 @@ def test_level_search_with_and_without_room_for_pairs(M, bits, knobs):
     assert np.array_equal(dev_[0], host[0]) and np.array_equal(dev_[1], host[1]) and dev_[2] == host[2]
 
 
+@pytest.mark.parametrize("M,bits", [(929, 4), (930, 4), (1022, 4), (1023, 4), (1135, 3), (1136, 3), (1278, 3), (1279, 3)])
+def test_level_search_where_pairs_cost_a_workgroup(M, bits, knobs):
+    """The last and the first size at which two workgroups of a compute unit hold both coefficients of a candidate, and
+    at which they hold one of them."""
+    say("level search, pairs or a second workgroup", M, bits)
+    u = np.random.default_rng(M).integers(0, 1025, (400, 3))
+    u[:, 1] = u[:, 1] ** 2 // 1024
+    u[:, 2] = np.where(u[:, 2] < 600, u[:, 2] // 128 * 128, 1000)
+    dev_, host = _searches((u / 1024.0).astype(np.float32), bits, M, knobs)
+    assert np.array_equal(dev_[0], host[0]) and np.array_equal(dev_[1], host[1]) and dev_[2] == host[2]
+
+
 @pytest.mark.parametrize("M,bits", [(100, 2), (513, 3), (1024, 4), (2000, 3)])
 def test_pruned_level_search_with_sums_that_round(M, bits, knobs):
     """At most two values to a bin, anywhere inside it: the bin moments do not depend on the order of their sums,
