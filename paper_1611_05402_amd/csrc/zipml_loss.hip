@@ -360,6 +360,7 @@ __global__ __launch_bounds__(kLossPackedThreads) void k_loss_copy2(
 // LDS of k_loss_copy2's matrix-core path; the kernel's static part (scratch of the block-wide sums and the vote) has
 // to fit beside it.
 constexpr size_t kLossStaticLds = 1024;
+constexpr size_t kLossScratchLds = 384;      // (336 bytes are what it takes: where two blocks share the LDS of a compute unit)
 inline size_t loss_mfma_lds_bytes(int NKB)
 {
     return (size_t)NKB * 512 + (kLossPackedThreads / kWave) * 64 * 16 + 16;
@@ -527,9 +528,13 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
     // samples per block on the table path: as many as leave two blocks per compute unit
     int spb = kLossPackedThreads;
     while (spb > 64 && (lay.n + spb - 1) / spb < 2 * cus) spb >>= 1;
-    const int chunk = (lay.n + spb - 1) / spb > cus ? LossTable<BITS>::kFeaturesTwo : LossTable<BITS>::kFeatures;
-    size_t shmem = LossTable<BITS>::bytes(chunk) < 4096 ? 4096 : LossTable<BITS>::bytes(chunk);
-    if (NKB > 0 && loss_mfma_lds_bytes(NKB) > shmem) shmem = loss_mfma_lds_bytes(NKB);
+    // the smaller chunks only where two blocks do share a compute unit: enough of them, and room beside the even levels'
+    // digits (at 3 bits none from 9,153 features on: 16,896 x 12,000 165 us with the larger ones, 169 with the smaller)
+    const size_t least = std::max<size_t>(4096, NKB > 0 ? loss_mfma_lds_bytes(NKB) : 0);
+    const bool two = (lay.n + spb - 1) / spb > cus &&
+                     2 * (std::max(LossTable<BITS>::bytes(LossTable<BITS>::kFeaturesTwo), least) + kLossScratchLds) <= (size_t)lds_limit;
+    const int chunk = two ? LossTable<BITS>::kFeaturesTwo : LossTable<BITS>::kFeatures;
+    const size_t shmem = std::max(LossTable<BITS>::bytes(chunk), least);
     if (HIP_FAILED(hipFuncSetAttribute((const void *)k_loss_copy2<BITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)))
         return ZIPML_ELAUNCH;
     const int64_t NT = lay.n_pad / 64;

@@ -163,6 +163,34 @@ def test_loss_through_tables_of_both_chunk_sizes(n, d):
     assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
 
 
+@pytest.mark.parametrize("d", [9152, 9153])
+def test_loss_through_tables_where_a_second_block_just_fits(d):
+    """3 bits, uneven levels, more tiles than compute units: chunks of 480 features as long as the digits of even levels
+    leave room for a second block, of 512 beyond.  The band is that of the test above."""
+    n = 16385
+    rng = np.random.default_rng(d)
+    say("packed loss, second block", n, d)
+    b = rng.standard_normal(n).astype(np.float32)
+    x = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    L = np.sort(rng.uniform(-1, 1, (d, 8)), axis=1).astype(np.float32)
+    p = GpuProblem(rng.random((n, d), dtype=np.float32) * np.float32(2) - np.float32(1), b, 3, 32)
+    p.set_levels(L)
+    p.quantize(3, 0)
+    codes = torch.zeros(n, d, dtype=torch.uint8, device="cuda:0")
+    zipml.unpack_codes(p.p2, 2, n, d, 3, codes)
+    Ld, xd = dev(L).double(), dev(x).double()
+    z = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+    for j0 in range(0, d, 1024):
+        c = codes[:, j0:j0 + 1024].T.long()
+        z += xd[j0:j0 + 1024] @ torch.gather(Ld[j0:j0 + 1024], 1, c)
+    r = z.cpu().numpy() - b
+    ref = float(np.sum(r ** 2) / (2 * n))
+    mag = float((np.abs(L[:, 0]) + np.abs(L[:, -1] - L[:, 0])).astype(np.float64) @ np.abs(x))
+    band = float(np.mean(np.abs(r))) * mag * (d + 4) * 2.0 ** -24
+    got = p.loss(dev(x), packed_copy=2)
+    assert abs(got - ref) <= band + 1e-7 * ref + 1e-14, (got, ref, band)
+
+
 @pytest.mark.parametrize("bits", [2, 4, 8])
 @pytest.mark.parametrize("d", [19904, 19905, 39808, 39809, 39872, 39873])
 def test_loss_where_the_digits_of_the_model_just_fit_on_the_chip(d, bits):
