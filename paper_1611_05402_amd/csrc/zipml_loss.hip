@@ -529,7 +529,7 @@ static int launch_loss_packed(hipStream_t s, const uint32_t *p, int copy, const 
     int spb = kLossPackedThreads;
     while (spb > 64 && (lay.n + spb - 1) / spb < 2 * cus) spb >>= 1;
     // the smaller chunks only where two blocks do share a compute unit: enough of them, and room beside the even levels'
-    // digits (at 3 bits none from 9,153 features on: 16,896 x 12,000 165 us with the larger ones, 169 with the smaller)
+    // digits (at 3 bits none from 9,153 features on: 16,896 x 12,000 163 us with the larger ones, 168 with the smaller)
     const size_t least = std::max<size_t>(4096, NKB > 0 ? loss_mfma_lds_bytes(NKB) : 0);
     const bool two = (lay.n + spb - 1) / spb > cus &&
                      2 * (std::max(LossTable<BITS>::bytes(LossTable<BITS>::kFeaturesTwo), least) + kLossScratchLds) <= (size_t)lds_limit;

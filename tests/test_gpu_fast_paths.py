@@ -532,9 +532,9 @@ def test_epochs_over_exchange_words_of_every_spacing(B, bits, groups, knobs):
     run of eight words, more steps than exchange buffers; even and uneven levels.  The model of the oracle (fp64 inside
     a step) to 1e-5, the bound of every epoch test."""
     say("spread exchange words", B, bits, groups)
-    knobs(zipml.KNOB_TARGET_WORKGROUPS, 128)
-    d, steps = groups * 32 - 5, 9
-    d = max(d, 257)
+    # (so few groups as two would be one workgroup's: sixteen then, on two workgroups, on eight at 576 samples)
+    knobs(zipml.KNOB_TARGET_WORKGROUPS, 2 if groups == 2 else 128)
+    d, steps = (16 if groups == 2 else groups) * 32 - 5, 9
     n, K = B * steps, 1 << bits
     rng = np.random.default_rng(B * 100 + groups)
     A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
