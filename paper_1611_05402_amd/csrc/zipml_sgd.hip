@@ -82,7 +82,7 @@ __device__ __forceinline__ int xword(int i, int sh) { return ((i >> 3) << (3 + s
 // first request was enough.
 // (The exchange alone, 32 workgroups x 256 words: 0.96 us asked at once, 0.82 with a wait of 12 units.  A step of 512
 // samples x 2,048 features, 8 bits: 3.62 -> 3.55 us.  Where a step has little else to do the bookkeeping costs more than
-// that: kSmall in zipml_sgd_mfma.h goes without.)
+// that: SMALL in zipml_sgd_mfma.h goes without.)
 struct FirstPoll {
     int quarters = 0;                                 // of a unit
     __device__ __forceinline__ void wait() const
@@ -135,6 +135,7 @@ struct SgdArgs {
     uint64_t *acc;         // [4][acc_words] exchange words
     int acc_words;         // words of a buffer
     int acc_sh;            // how far the exchange words are spread (xword)
+    int small;             // 1: the matrix-core loop for small steps (SMALL in zipml_sgd_mfma.h) runs even levels
     const double *bound;   // at launch: [0] sum_j maxabs(L_j)|x_j|, [1] sum_j maxabs(L_j)^2,
                            // [2] max_j delta_j|x_j|, [3] max_j delta_j maxabs(L_j)
     int mfma;              // evenly spaced levels may take the matrix-core step loop
@@ -857,6 +858,7 @@ namespace zipml {
 // through tagged stores.  With all its instantiations in one kernel the loop of a production launch
 // spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
 // that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
+// 9: that for small steps (SMALL).
 // 5 + (KB - 1) + 2 XM: the same of two code pairs (the symmetrised estimator), with replicas (atomics only) or without.
 // (Us per step, in one kernel with all other loops | by itself: 128 samples x 2,048 features, 2 bits 3.08 | 2.88; 1,024 x
 // 2,048, 8 bits 6.66 | 6.39.)
@@ -960,7 +962,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         if (blockIdx.x == 0 && tid == 0) store_dev(a.status, (int)ZIPML_EUNSUPPORTED);
         return;
     }
-    if constexpr (SOLO >= 5) {
+    if constexpr (SOLO >= 5 && SOLO <= 8) {
         // two code pairs (anything but the matrix-core loop has been refused above)
         if constexpr (!INT && FAST && kMfmaBits && UPT <= 2) {
             constexpr int kKB = 1 + ((SOLO - 5) & 1), kXM = (SOLO - 5) >> 1;
@@ -970,7 +972,8 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         // (the host launches this kernel for the plain estimator on the matrix-core plan, without
         // replicas or debug outputs, with the workgroup width and the exchange it was built for)
         if constexpr (!INT && FAST && kMfmaBits && !REP) {
-            constexpr int kKB = 1 + ((SOLO - 1) & 1), kXM = (SOLO - 1) >> 1;
+            constexpr bool kSmall = SOLO == 9;
+            constexpr int kKB = kSmall ? 1 : 1 + ((SOLO - 1) & 1), kXM = kSmall ? 0 : (SOLO - 1) >> 1;
             if constexpr (kXM == 1) {
                 if ((int)blockIdx.x >= a.W + a.nred) {  // a workgroup that only prefetches (a.npref > 0)
                     if (affine_all && a.mfma) sgd_prefetchers<BITS>(a);
@@ -981,7 +984,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                     return;
                 }
             }
-            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 1, false, kXM>(a, L, L.mf);
+            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 1, false, kXM, kSmall>(a, L, L.mf);
             else {
                 // (four feature groups of 8 bits: in memory; at 2 bits the question stays, see sgd_steps)
                 constexpr int kTab = BITS == 2 ? kTabAsked : BITS == 8 && kKB == 2 ? kTabMem : kTabLds;
@@ -1327,7 +1330,8 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
                      : solo == 2 ? (const void *)k_sgd<BITS, false, true, U, false, 2> \
                      : solo == 3 ? (const void *)k_sgd<BITS, false, true, U, false, 3> \
                                  : (const void *)k_sgd<BITS, false, true, U, false, 4>)
-                kern = p.upt == 1 ? ZIPML_SOLO(1) : p.upt == 2 ? ZIPML_SOLO(2) : ZIPML_SOLO(4);
+                kern = a.small ? (const void *)k_sgd<BITS, false, true, 1, false, 9>
+                     : p.upt == 1 ? ZIPML_SOLO(1) : p.upt == 2 ? ZIPML_SOLO(2) : ZIPML_SOLO(4);
 #undef ZIPML_SOLO
                 // idle compute units take the reducing of the tagged partial sums (sgd_reducers), where
                 // the loop really exchanges that way (all eight waves at work, as the kernel decides too)
@@ -1742,12 +1746,12 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
         const size_t grad_words = replicas > 1 ? 2 * Workspace::kGradWords : 0;
         const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
         // (two lines a stretch are enough for few workgroups, and half as many words to poll; the smallest steps of the
-        // matrix-core loop know their spacing, kSmall in zipml_sgd_mfma.h, and have the room for it)
-        const bool small = p.mfma && !avg && p.upt == 1 && p.GQ <= 2;
-        a.acc_sh = p.W > 64 && !small ? 2 : 1;
+        // matrix-core loop know their spacing, and have the room for it)
+        a.small = p.mfma && !avg && !production && replicas == 1 && p.upt == 1 && p.GQ <= 2 && micro <= 256;
+        a.acc_sh = p.W > 64 && !a.small ? 2 : 1;
         while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(pairs * micro, a.acc_sh) + grad_words > room) --a.acc_sh;
         a.acc_words = (int)Workspace::acc_words(pairs * micro, a.acc_sh);
-        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room || (small && a.acc_sh != 1) ||
+        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room || (a.small && a.acc_sh != 1) ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))
             return ZIPML_EWORKSPACE;
         a.gx = a.acc + (size_t)replicas * Workspace::kAccBuffers * a.acc_words;

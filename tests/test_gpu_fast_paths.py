@@ -671,3 +671,26 @@ def test_epochs_where_the_width_of_the_codes_decides_the_workgroups(B, bits, gro
     ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.25 / d)
     err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
     assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("B,d", [(64, 2047), (192, 4100), (256, 290), (256, 2049), (320, 290), (512, 600)])
+def test_epochs_on_both_sides_of_the_small_steps(B, d, bits):
+    """Up to 256 samples and 64 features a workgroup, and beyond; even and uneven levels.  The bound as above."""
+    say("small steps", B, d, bits)
+    steps = 6
+    n, K = B * steps, 1 << bits
+    rng = np.random.default_rng(B + d + bits)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    even = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    for L in (even, np.sort(rng.uniform(-1, 1, (d, K)), axis=1).astype(np.float32)):
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(L)
+        p.quantize(5, 0)
+        x = dev(np.zeros(d, np.float32))
+        p.epoch(x, 0.25 / d)
+        assert zipml.sgd_status(p.ws) == 0
+        ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.25 / d)
+        err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+        assert err <= 1e-5, err
