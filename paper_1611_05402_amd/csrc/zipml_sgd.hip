@@ -1218,26 +1218,21 @@ static int target_workgroups()
 // among twice the workgroups costs more (0.1 to 0.3 us from 32 to 64, 0.4 to 0.8 to 128, 1 to 2 to 256) stands
 // against the phases of a step, which grow with the units (feature groups x samples) of a workgroup.  Up to 32 are never too
 // many.  Measured, us per step (few | many workgroups; 64, 128 or 256 samples, 2 to 8 bits):
-//   matrix cores: 2,048 features 256 x 8 bits, 512 units 3.06 | 3.19, 512 x 8, 1,024 units 3.98 | 3.87; at 2 and 4 bits, where
-//     the phases are shorter, it depends on the exchange too: 1,024 units, 33, 47, 54 or 64 workgroups 3.26 | 3.02, 3.25 |
-//     3.20, 3.26 | 3.27, 3.28 | 3.74 (2 bits), 640 units, 33, 41, 47, 64 of them 3.17 | 3.14, 3.19 | 3.25, 3.21 | 3.35, 3.21 | 3.44.
-//     4,096 features on four groups (two blocks of 64 features to a workgroup) or on two 2.78 | 2.69, 2.85 | 2.64, 2.99 |
-//     2.69; 128 against 64 workgroups 3.5 | 2.7 (64 x 8).
+//   matrix cores: 2,048 features 256 x 8 bits, 512 units 2.78 | 2.94, 512 x 8, 1,024 units 4.00 | 3.61; 4,096 features on four groups (two
+//     blocks of 64 features to a workgroup) or on two 2.78 | 2.69, 2.85 | 2.64, 2.99 | 2.69; 128 against 64 workgroups 3.5 | 2.7 (64 x 8).
 //     Eight groups would leave the matrix cores: 8,192 features 3.55 | 2.91, 4.05 | 3.08, 5.66 | 3.20.  Two code pairs at
-//     once (at most four groups), 2,048 features: 256 units 2.99 | 3.38 (2 bits), 3.45 | 3.62 (8); 512 units 3.09 | 3.49, 3.61 |
-//     3.74 (1,030 features 3.08 | 3.15, 3.51 | 3.40); 640 units 4.00 | 3.97, 4.46 | 4.22.
+//     once: 2,048 features 2.78 | 3.17 (128 units), 3.85 | 3.49 (512); at most four groups.
 //   vector ALU: 33 to 64 workgroups instead of half, 256 units 2.67 | 2.86, 512 units 3.03 | 2.92 and 3.08 | 3.06, 1,024
 //     units 4.52 | 3.52; 65 to 128: 512 units 3.52 | 3.79, 1,024 units 5.19 | 4.63; 129 to 256: 1,024 units 5.2 | 6.5.
 //   end to end (three exchanges): 33 to 64, 512 units 7.06 | 7.37, 1,024 units 8.01 | 7.47; 65 to 128: 8.8 | 9.8.
 // (Levels that are not even leave the matrix cores' loop for the vector ALU's in the same plan: 8,192 features, 4 bits, 256
 // samples 15.5 | 7.6.)
-static bool fewer_workgroups(int64_t W, int GQ, int bits, int64_t batch, bool mfma, bool fp32_model, int pairs)
+static bool fewer_workgroups(int64_t W, int GQ, int64_t batch, bool mfma, bool fp32_model, int pairs)
 {
     const int64_t units = 2 * GQ * batch;                  // of a workgroup of twice the size
     if (W <= 32) return false;
-    if (pairs == 2) return W > 64 || (GQ == 1 && (units <= 256 || (units <= 512 && (bits < 8 || W > 48))));
-    if (mfma && GQ == 1) return W > 64 || units <= 512 || (bits < 8 && units <= 1024 && W > (units < 1024 ? 40 : 48));
-    if (mfma) return W > (GQ < 4 ? 64 : 128);
+    if (pairs == 2) return W > 64 || (GQ == 1 && units <= 256);
+    if (mfma) return GQ < 4 ? W > 64 || (GQ == 1 && units <= 512) : W > 128;
     if (!fp32_model) return W > 64 || units <= 512;
     return W > 128 || units <= (W > 64 ? 512 : 256);
 }
@@ -1281,7 +1276,7 @@ static int make_plan(int64_t d32, int bits, int64_t batch, bool int_table, bool 
         // it needs no device-wide exchange at all
         const int64_t gq_solo = d32 <= 8 ? (d32 <= 1 ? 1 : d32 <= 2 ? 2 : d32 <= 4 ? 4 : 8) : 0;
         const bool solo_possible = gq_solo && batch * gq_solo <= (int64_t)kMaxUpt * kThreads;
-        const bool fewer = by_target ? W > kTargetW : fewer_workgroups(W, GQ, bits, batch, mfma, fp32_model, pairs);
+        const bool fewer = by_target ? W > kTargetW : fewer_workgroups(W, GQ, batch, mfma, fp32_model, pairs);
         if (!fewer && !(solo_possible && W > 1)) break;
     }
     return best ? ZIPML_OK : ZIPML_EUNSUPPORTED;   // batch too large for one step in registers
