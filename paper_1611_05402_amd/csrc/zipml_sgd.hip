@@ -1218,10 +1218,12 @@ static int target_workgroups()
 // among twice the workgroups costs more (0.1 to 0.3 us from 32 to 64, 0.4 to 0.8 to 128, 1 to 2 to 256) stands
 // against the phases of a step, which grow with the units (feature groups x samples) of a workgroup.  Up to 32 are never too
 // many.  Measured, us per step (few | many workgroups; 64, 128 or 256 samples, 2 to 8 bits):
-//   matrix cores: 2,048 features 256 x 8 bits, 512 units 2.78 | 2.94, 512 x 8, 1,024 units 4.00 | 3.61; 4,096 features on four groups (two
-//     blocks of 64 features to a workgroup) or on two 2.78 | 2.69, 2.85 | 2.64, 2.99 | 2.69; 128 against 64 workgroups 3.5 | 2.7 (64 x 8).
+//   matrix cores (epochs of hundreds of steps, data no cache holds): 2,048 features, 512 units 2.49 | 2.62 (2 bits), 2.78 |
+//     2.75 (8 bits), 1,024 units 3.26 | 3.14 and 3.99 | 3.30;
+//     4,096 features on four groups (two blocks of 64 features to a workgroup) or on two 2.78 | 2.69, 2.85 | 2.64, 2.99 |
+//     2.69; 128 against 64 workgroups 3.5 | 2.7 (64 x 8).
 //     Eight groups would leave the matrix cores: 8,192 features 3.55 | 2.91, 4.05 | 3.08, 5.66 | 3.20.  Two code pairs at
-//     once: 2,048 features 2.78 | 3.17 (128 units), 3.85 | 3.49 (512); at most four groups.
+//     once (at most four groups), 2,048 features: 256 units 2.91 | 3.12 (2 bits), 3.03 | 3.20 (8), 512 units 3.22 | 3.23, 3.72 | 3.37.
 //   vector ALU: 33 to 64 workgroups instead of half, 256 units 2.67 | 2.86, 512 units 3.03 | 2.92 and 3.08 | 3.06, 1,024
 //     units 4.52 | 3.52; 65 to 128: 512 units 3.52 | 3.79, 1,024 units 5.19 | 4.63; 129 to 256: 1,024 units 5.2 | 6.5.
 //   end to end (three exchanges): 33 to 64, 512 units 7.06 | 7.37, 1,024 units 8.01 | 7.47; 65 to 128: 8.8 | 9.8.

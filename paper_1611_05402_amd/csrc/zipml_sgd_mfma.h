@@ -70,7 +70,12 @@ __device__ __forceinline__ long long tagged_value(uint64_t word)
 {
     return (long long)(word << 16) >> 16;                  // sign-extends the 48-bit field
 }
-constexpr int64_t kWatchFirst = 32768;   // exchange words x workgroups from which a wave polls one word first
+// Samples x workgroups from which a wave polls one word first.  With the words spread the polls get less into the way of
+// the atomics than they did side by side, and up to 65,536 asking for all at once is faster (one word first | all): 512
+// samples on 64 workgroups, 2 bits 3.43 | 3.14 us a step, 8 bits 3.51 | 3.30; 1,024 on 47 3.81 | 3.63, on 64 3.94 | 3.82.  Two
+// code pairs poll twice as many words (512 samples on 64 workgroups, 8 bits 4.76 | 4.88, 2 bits 4.01 | 3.91), and with
+// replicas several sets of workgroups poll at once (8,192 samples x 680 features, 2 bits 21.1 | 21.9).
+template <int NC, bool REP> constexpr int64_t kWatchFirst = NC == 1 && !REP ? 65537 : 32768;
 
 // KB: 64-feature blocks per workgroup (1: GQ <= 2, 2: GQ == 4).
 // NC: 1 = the estimator of eq. (5), g = mean_i Q1(a_i) (Q2(a_i)^T x - b_i);
@@ -613,7 +618,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                 // of the poll compete with the atomics they are waiting for.
                 // (Only then: for a few workgroups the extra round trip costs more than it saves.)
                 const int watch = wave * kWave < B ? wave * kWave : 0;
-                const bool watch_first = (int64_t)W * B >= kWatchFirst;
+                const bool watch_first = (int64_t)W * B >= kWatchFirst<NC, REP>;
                 if constexpr (!SMALL) first_poll.wait();
 #pragma unroll 1
                 for (;;) {
