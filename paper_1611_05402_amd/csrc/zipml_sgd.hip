@@ -80,9 +80,8 @@ __device__ __forceinline__ int xword(int i, int sh) { return ((i >> 3) << (3 + s
 // words are complete, so one sent a little too early costs nearly another: the wave then waits longer from the next
 // step on, by two units of 64 cycles, and a quarter of a unit less after every step in which the
 // first request was enough.
-// (The exchange alone, 32 workgroups x 256 words: 0.96 us asked at once, 0.82 with a wait of 12 units.  A step of 512
-// samples x 2,048 features, 8 bits: 3.62 -> 3.55 us.  Where a step has little else to do the bookkeeping costs more than
-// that: SMALL in zipml_sgd_mfma.h goes without.)
+// (The exchange alone, 32 workgroups x 256 words: 1.03 us asked at once, 0.90 with a wait of 16 units; 512 words 1.30, 0.94.
+// A step of 512 samples x 2,048 features, 8 bits, of the loop in zipml_sgd_mfma.h: 3.62 -> 3.55 us.)
 struct FirstPoll {
     int quarters = 0;                                 // of a unit
     __device__ __forceinline__ void wait() const
@@ -135,9 +134,11 @@ struct SgdArgs {
     uint64_t *acc;         // [4][acc_words] exchange words
     int acc_words;         // words of a buffer
     int acc_sh;            // how far the exchange words are spread (xword)
-    int small;             // 1: the matrix-core loop for small steps (SMALL in zipml_sgd_mfma.h) runs even levels
+    int wave_w;            // workgroups (two feature groups each) where the loop of zipml_sgd_wave.h runs even levels
+    int wave_sh, wave_split, wave_sub;   // its exchange words: how far they are spread, words for a sample, from one to the next
     const double *bound;   // at launch: [0] sum_j maxabs(L_j)|x_j|, [1] sum_j maxabs(L_j)^2,
                            // [2] max_j delta_j|x_j|, [3] max_j delta_j maxabs(L_j)
+    int wave_early;        // 1: it requests copy 1 as soon as the sums have arrived
     int mfma;              // evenly spaced levels may take the matrix-core step loop
     const int *even;       // [kEvenBlocks] 1: the levels of that block of features are evenly spaced
     int chunks;            // a minibatch is chunks * B samples (matrix-core loop only)
@@ -234,6 +235,7 @@ __device__ __forceinline__ void load_unit(const uint32_t *__restrict__ p, uint32
 
 }  // namespace zipml
 #include "zipml_sgd_mfma.h"
+#include "zipml_sgd_wave.h"
 #include "zipml_sgd_rows.h"
 #include "zipml_sgd_rows_compact.h"
 #include "zipml_sgd_rows_fp4.h"
@@ -848,44 +850,19 @@ __device__ __forceinline__ void sgd_steps(const SgdArgs &a, const Lds &L)
 #include "zipml_sgd_e2e.h"
 namespace zipml {
 
-// ---------------------------------------------------------------------------------------------
-// The epoch kernel: LDS carve, one-time set-up, then the step loop of the right mode.
-// ---------------------------------------------------------------------------------------------
-// REP: the launch has replicas of the workgroups (a.R > 1; matrix-core loop only).  A kernel of
-// its own, so that the code of the replicas costs the ordinary launch no registers.
-// SOLO: 0, or the one instantiation of the matrix-core loop that this kernel holds for the plain
-// estimator -- 1 + (KB - 1) + 2 XM: 64 or 128 features per workgroup, exchange through atomics or
-// through tagged stores.  With all its instantiations in one kernel the loop of a production launch
-// spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
-// that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
-// 9: that for small steps (SMALL).
-// 5 + (KB - 1) + 2 XM: the same of two code pairs (the symmetrised estimator), with replicas (atomics only) or without.
-// (Us per step, in one kernel with all other loops | by itself: 128 samples x 2,048 features, 2 bits 3.08 | 2.88; 1,024 x
-// 2,048, 8 bits 6.66 | 6.39.)
-template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0>
-__global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
+// LDS of a workgroup of the loops in this file, its level and model slice; true: the levels of its features are evenly spaced.
+template <int BITS, bool INT, bool FAST>
+__device__ __forceinline__ bool sgd_setup(const SgdArgs &a, Lds &L, unsigned char *smem)
 {
     constexpr int K = 1 << BITS;
-    extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
-    const int w = blockIdx.x % a.W;                // feature block; blockIdx.x / a.W: replica (matrix-core loop)
-    const int CW = 32 * a.GQ;
-    const int B = a.B;
+    const int CW = 32 * a.GQ, B = a.B;
     const int nrg = B >= 32 ? B / 32 : 1;
     const int Rlen = nrg * 32;                     // residual slots (zero outside the batch)
-    const int j0 = w * CW;
-#ifdef ZIPML_PHASE_TIMING
-    // where this workgroup runs: XCC id (HW_REG_XCC_ID) and the HW_ID register (SE / CU / SIMD fields)
-    if (tid == 0) {
-        ((long long *)(a.nrm + 2048))[16 + 2 * blockIdx.x] = __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20);
-        ((long long *)(a.nrm + 2048))[17 + 2 * blockIdx.x] = __builtin_amdgcn_s_getreg((31 << 11) | (0 << 6) | 4);
-    }
-#endif
-
+    const int j0 = (int)(blockIdx.x % a.W) * CW;
     size_t off = 0;
     auto carve = [&](size_t bytes) { void *p = smem + off; off += (bytes + 15) & ~(size_t)15; return p; };
-    Lds L;
     L.Ls = (float *)carve(a.lds_levels ? (size_t)CW * K * 4 : 0);
     L.Gs = (uint16_t *)carve(INT && !a.ident_grid ? (size_t)CW * K * 2 : 0);
     L.xs = (float *)carve(CW * 4);
@@ -929,12 +906,6 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         }
     }
     const bool affine = __syncthreads_and(ok) && !INT;
-    // ... and of every feature of the problem (found by the preparation kernel)?  Workgroups on
-    // the matrix-core loop and on the vector loop scale their contributions differently, so that
-    // choice has to be the same everywhere.
-    int ok_all = 1;
-    if (a.mfma && tid < Workspace::kEvenBlocks) ok_all = a.even[tid];
-    const bool affine_all = __syncthreads_and(ok_all) && a.mfma != 0;
     for (int c = tid; c < CW; c += kThreads) {
         const bool live = j0 + c < a.d;
         const float lo = live ? Lg[(size_t)c * K] : 0.0f, hi = live ? Lg[(size_t)c * K + K - 1] : 0.0f;
@@ -951,7 +922,47 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         const float part = wave_sum_dpp(tid < CW ? L.los[tid] * L.xs[tid] : 0.0f);
         if (lane == 0) L.wsum[kWaves + wave] = part;
     }
+    return affine;
+}
 
+// ---------------------------------------------------------------------------------------------
+// The epoch kernel: LDS carve, one-time set-up, then the step loop of the right mode.
+// ---------------------------------------------------------------------------------------------
+// REP: the launch has replicas of the workgroups (a.R > 1; matrix-core loop only).  A kernel of
+// its own, so that the code of the replicas costs the ordinary launch no registers.
+// SOLO: 0, or the one instantiation of the matrix-core loop that this kernel holds for the plain
+// estimator -- 1 + (KB - 1) + 2 XM: 64 or 128 features per workgroup, exchange through atomics or
+// through tagged stores.  With all its instantiations in one kernel the loop of a production launch
+// spilled some 900 scalar registers into vector lanes (85 reloads inside one loop body); a kernel
+// that holds one of them spills 200, and the dense 8-bit step went from 2.97 to 2.88 us.
+// 5 + (KB - 1) + 2 XM: the same of two code pairs (the symmetrised estimator), with replicas (atomics only) or without.
+// (Us per step, in one kernel with all other loops | by itself: 128 samples x 2,048 features, 2 bits 3.08 | 2.88; 1,024 x
+// 2,048, 8 bits 6.66 | 6.39.)
+template <int BITS, bool INT, bool FAST, int UPT, bool REP = false, int SOLO = 0>
+__global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+    const int w = blockIdx.x % a.W;                // feature block; blockIdx.x / a.W: replica (matrix-core loop)
+    const int CW = 32 * a.GQ;
+    const int B = a.B;
+    const int j0 = w * CW;
+#ifdef ZIPML_PHASE_TIMING
+    // where this workgroup runs: XCC id (HW_REG_XCC_ID) and the HW_ID register (SE / CU / SIMD fields)
+    if (tid == 0) {
+        ((long long *)(a.nrm + 2048))[16 + 2 * blockIdx.x] = __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20);
+        ((long long *)(a.nrm + 2048))[17 + 2 * blockIdx.x] = __builtin_amdgcn_s_getreg((31 << 11) | (0 << 6) | 4);
+    }
+#endif
+
+    Lds L;
+    const bool affine = sgd_setup<BITS, INT, FAST>(a, L, smem);
+    // ... and of every feature of the problem (found by the preparation kernel)?  Workgroups on
+    // the matrix-core loop and on the vector loop scale their contributions differently, so that
+    // choice has to be the same everywhere.
+    int ok_all = 1;
+    if (a.mfma && tid < Workspace::kEvenBlocks) ok_all = a.even[tid];
+    const bool affine_all = __syncthreads_and(ok_all) && a.mfma != 0;
     constexpr bool kMfmaBits = BITS == 2 || BITS == 4 || BITS == 8;
     const bool on_mfma_loop = !INT && FAST && kMfmaBits && affine_all && a.mfma;
     const bool on_e2e_loop = INT && FAST && a.W > 1;
@@ -972,8 +983,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         // (the host launches this kernel for the plain estimator on the matrix-core plan, without
         // replicas or debug outputs, with the workgroup width and the exchange it was built for)
         if constexpr (!INT && FAST && kMfmaBits && !REP) {
-            constexpr bool kSmall = SOLO == 9;
-            constexpr int kKB = kSmall ? 1 : 1 + ((SOLO - 1) & 1), kXM = kSmall ? 0 : (SOLO - 1) >> 1;
+            constexpr int kKB = 1 + ((SOLO - 1) & 1), kXM = (SOLO - 1) >> 1;
             if constexpr (kXM == 1) {
                 if ((int)blockIdx.x >= a.W + a.nred) {  // a workgroup that only prefetches (a.npref > 0)
                     if (affine_all && a.mfma) sgd_prefetchers<BITS>(a);
@@ -984,7 +994,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                     return;
                 }
             }
-            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 1, false, kXM, kSmall>(a, L, L.mf);
+            if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 1, false, kXM>(a, L, L.mf);
             else {
                 // (four feature groups of 8 bits: in memory; at 2 bits the question stays, see sgd_steps)
                 constexpr int kTab = BITS == 2 ? kTabAsked : BITS == 8 && kKB == 2 ? kTabMem : kTabLds;
@@ -1048,6 +1058,39 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
             if (j0 + c < a.d) a.x[j0 + c] = L.xs[c];
 }
 
+// The plain estimator, fp32 model, minibatches of at most 512 SB samples: zipml_sgd_wave.h where all levels are evenly spaced,
+// else the vector loop; each has a number of workgroups and a width of its own, and what one does not need of the grid leaves.
+// UPT 0: no vector loop, the intermediates of a step to the debug outputs.
+template <int BITS, int SB, int UPT>
+__global__ __launch_bounds__(kThreads) void k_sgd_wave(SgdArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+    int ok = 1;
+    if (tid < Workspace::kEvenBlocks) ok = a.even[tid];
+    if (__syncthreads_and(ok)) {
+        if ((int)blockIdx.x < a.wave_w) sgd_steps_wave<BITS, SB, UPT == 0>(a, smem);
+        return;
+    }
+    if constexpr (UPT == 0) {
+        if (blockIdx.x == 0 && tid == 0) store_dev(a.status, (int)ZIPML_EUNSUPPORTED);
+    } else {
+        if ((int)blockIdx.x >= a.W) return;
+        Lds L;
+        (void)sgd_setup<BITS, false, true>(a, L, smem);
+        // (7 and 8 bits: the tables of many features stay in memory; at 2 bits the question stays, see sgd_steps)
+        if constexpr (BITS >= 7) {
+            if (a.lds_levels) sgd_steps<BITS, kTable, true, UPT, kTabLds>(a, L);
+            else sgd_steps<BITS, kTable, true, UPT, kTabMem>(a, L);
+        } else {
+            sgd_steps<BITS, kTable, true, UPT, BITS == 2 ? kTabAsked : kTabLds>(a, L);
+        }
+        const int CW = 32 * a.GQ, j0 = blockIdx.x * CW;
+        for (int c = tid; c < CW; c += kThreads)
+            if (j0 + c < a.d) a.x[j0 + c] = L.xs[c];
+    }
+}
+
 // Launch preparation: clears the barrier counter, the status word and exchange words, checks
 // block by block (kEvenBlocks of them) whether the levels are evenly spaced; one more block takes
 // the magnitude bounds of the dot exchange from the levels and the current model,
@@ -1106,6 +1149,11 @@ static __global__ __launch_bounds__(kPrepThreads) void k_sgd_prepare(int *status
             ok &= (v.z == (float)(lo + ((double)(c0 + 2) * wdt) / (double)(K - 1)));
             ok &= (v.w == (float)(lo + ((double)(c0 + 3) * wdt) / (double)(K - 1)));
         }
+        if (K == 2)                                              // (two levels: is hi - lo exact?)
+            for (int64_t j = (int64_t)blockIdx.x * kPrepThreads + threadIdx.x; j < d; j += (int64_t)Workspace::kEvenBlocks * kPrepThreads) {
+                const double lo = (double)levels[j * 2], hi = (double)levels[j * 2 + 1];
+                ok &= (double)(float)(hi - lo) == hi - lo;
+            }
         ok = __syncthreads_and(ok);
         if (threadIdx.x == 0) even[blockIdx.x] = ok;
     }
@@ -1327,8 +1375,7 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
                      : solo == 2 ? (const void *)k_sgd<BITS, false, true, U, false, 2> \
                      : solo == 3 ? (const void *)k_sgd<BITS, false, true, U, false, 3> \
                                  : (const void *)k_sgd<BITS, false, true, U, false, 4>)
-                kern = a.small ? (const void *)k_sgd<BITS, false, true, 1, false, 9>
-                     : p.upt == 1 ? ZIPML_SOLO(1) : p.upt == 2 ? ZIPML_SOLO(2) : ZIPML_SOLO(4);
+                kern = p.upt == 1 ? ZIPML_SOLO(1) : p.upt == 2 ? ZIPML_SOLO(2) : ZIPML_SOLO(4);
 #undef ZIPML_SOLO
                 // idle compute units take the reducing of the tagged partial sums (sgd_reducers), where
                 // the loop really exchanges that way (all eight waves at work, as the kernel decides too)
@@ -1356,17 +1403,30 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
             }
         }
     }
+    size_t shmem = p.shmem;
+    int grid = a.W * a.R + a.nred + a.npref;
+    if constexpr (!INT) {
+        if (fast && a.wave_w > 0) {
+            const bool many = a.B > kWaves * kWave;
+#define ZIPML_WAVE(U) (many ? (const void *)k_sgd_wave<BITS, 2, U> : (const void *)k_sgd_wave<BITS, 1, U>)
+            kern = a.dbg_production ? ZIPML_WAVE(0) : p.upt == 1 ? ZIPML_WAVE(1) : p.upt == 2 ? ZIPML_WAVE(2) : ZIPML_WAVE(4);
+#undef ZIPML_WAVE
+            shmem = std::max(shmem, (size_t)kWaveLds<BITS, 2>);
+            grid = std::max(a.W, a.wave_w);
+        }
+    }
     if (a.R > 1 && !(fast && !INT && (BITS == 2 || BITS == 4 || BITS == 8))) return ZIPML_EUNSUPPORTED;
     if (HIP_FAILED(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)p.shmem)))
+                                       (int)shmem)))
         return ZIPML_ELAUNCH;
     // exchange buffers of every replica, and the gradient exchange words behind them
-    const int words = a.R * Workspace::kAccBuffers * a.acc_words + (a.R > 1 ? 2 * (int)Workspace::kGradWords : 0);
+    const int words = std::max(a.R * Workspace::kAccBuffers * a.acc_words + (a.R > 1 ? 2 * (int)Workspace::kGradWords : 0),
+                               2 * a.wave_split * a.wave_sub);
     const int K = 1 << BITS;
     double *bound = const_cast<double *>(a.bound);
     hipLaunchKernelGGL(k_sgd_prepare, dim3(Workspace::kEvenBlocks + 1), dim3(kPrepThreads), 0, s, a.status, a.sync,
                        a.acc, words, 1, a.levels, a.x, a.d, K, bound,
-                       a.mfma ? const_cast<int *>(a.even) : nullptr, (float *)nullptr, (float *)nullptr, 0, 0.0f,
+                       a.mfma || a.wave_w ? const_cast<int *>(a.even) : nullptr, (float *)nullptr, (float *)nullptr, 0, 0.0f,
                        INT && !stepwise ? reinterpret_cast<uint64_t *>(a.nrm) : (uint64_t *)nullptr,
                        INT && !stepwise ? 8 * kNormSlots : 0,
                        a.xstore ? a.xpart : (uint64_t *)nullptr,
@@ -1377,7 +1437,7 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
         a.seg_first = 0;
         a.seg_last = 3;
         void *params[] = {&a};
-        return launch_resident(kern, a.W * a.R + a.nred + a.npref, params, p.shmem, s);
+        return launch_resident(kern, grid, params, shmem, s);
     }
     // stepwise: every segment of every step is its own launch; kernel boundaries replace barriers
     const int64_t first = a.step0, count = a.nsteps;
@@ -1742,13 +1802,11 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
     {
         const size_t grad_words = replicas > 1 ? 2 * Workspace::kGradWords : 0;
         const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
-        // (two lines a stretch are enough for few workgroups, and half as many words to poll; the smallest steps of the
-        // matrix-core loop know their spacing, and have the room for it)
-        a.small = p.mfma && !avg && !production && replicas == 1 && p.upt == 1 && p.GQ <= 2 && micro <= 256;
-        a.acc_sh = p.W > 64 && !a.small ? 2 : 1;
+        // (two lines a stretch are enough for few workgroups, and half as many words to poll)
+        a.acc_sh = p.W > 64 ? 2 : 1;
         while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(pairs * micro, a.acc_sh) + grad_words > room) --a.acc_sh;
         a.acc_words = (int)Workspace::acc_words(pairs * micro, a.acc_sh);
-        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room || (a.small && a.acc_sh != 1) ||
+        if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))
             return ZIPML_EWORKSPACE;
         a.gx = a.acc + (size_t)replicas * Workspace::kAccBuffers * a.acc_words;
@@ -1774,6 +1832,40 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
         a.xres = a.xpart + (size_t)2 * p.W * a.xrow;
         if (a.xstore && (p.W > 256 || NCwords_ok(avg ? 2 : 1, micro, a.xrow) == false)) a.xstore = 0;
         if (a.xstore && (size_t)replicas * 2 * (p.W + 1) * a.xrow * 8 > Workspace::xchg_bytes(d, batch)) a.xstore = 0;
+    }
+    // Evenly spaced levels on minibatches of one exchange: the loop of zipml_sgd_wave.h, 64 features to a workgroup, up to a
+    // workgroup for every compute unit (a kernel that holds the vector loop for uneven levels, too; a knob that chooses
+    // between the exchanges of zipml_sgd_mfma.h keeps that).
+    if (model_bits == 0 && !stepwise && (!debug || production) && !avg && chunks == 1 && replicas == 1 && p.W > 1 &&
+        micro <= 2 * kWaves * kWave && knob(ZIPML_KNOB_NO_MATRIX_CORES) <= 0 && knob(ZIPML_KNOB_STORE_EXCHANGE_MIN) < 0) {
+        const int W = (int)((lay.d32 + 1) / 2), waves = (int)((micro + kWave - 1) / kWave);
+        int cus = 0, lds = 0;
+        if (int lrc = device_limits(cus, lds)) return lrc;
+        // Adds to one word follow each other at some 11 ns, so from a number of workgroups on a sample has two or four
+        // words, which are then polled all of them (what that costs grows with the waves).  Us per step at 2 bits, 1 | 2 | 4
+        // words: 64 samples x 1,024 features (16 workgroups) 1.33 | 1.36 | 1.44, x 2,048 1.51 | 1.41 | 1.42, x 4,096 1.90 | 1.61 |
+        // 1.53, x 8,192 2.66 | 2.04 | 1.77; 256 x 1,024 1.55 | 1.59 | 1.69, x 2,048 1.73 | 1.65 | 1.73, x 8,192 2.97 | 2.37 | 2.15;
+        // 512 x 2,048 2.11 | 2.13 | 2.33, x 4,096 2.49 | 2.28 | 2.49, x 8,192 3.33 | 2.74 | 2.79, x 16,384 5.54 | 4.02 | 3.82.
+        int split = W <= (waves > 4 ? 32 : 16) ? 1 : W <= (waves > 4 ? 128 : waves > 2 ? 64 : 32) ? 2 : 4;
+        const int sh = W > 64 ? 2 : 1;
+        const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
+        const size_t sub = Workspace::acc_words(round_up(micro, micro > kWaves * kWave ? 2 * kWave : kWave), sh);
+        while (split > 1 && 2 * split * sub > room) split /= 2;
+        // (the offsets in two groups of a copy and in the labels are 32 bits wide)
+        if (W <= cus && W <= 256 && 2 * split * sub <= room && 2 * lay.n_pad * bits * 4 < ((int64_t)7 << 29) && lay.n_pad * 4 < ((int64_t)7 << 29)) {
+            a.xstore = 0;
+            a.wave_w = W;
+            a.wave_sh = sh;
+            a.wave_split = split;
+            a.wave_sub = (int)sub;
+            // Copy 1 behind the atomics or as soon as the sums are there: by what a compute unit has to take in of a copy in
+            // a step, while the atomics of few workgroups leave the memory's side to it; codes whose expansion fills the time
+            // of the exchange from half as much on.  Us per step, behind | early: 256 samples x 1,000 features, 8 bits 1.93 |
+            // 1.73, x 2,048 2.04 | 2.14; 512 x 512, 8 bits 2.57 | 2.16, x 4,096 2.99 | 2.60, 2 bits, x 4,096 2.28 | 2.64; 6 bits,
+            // 256 x 2,048 2.20 | 2.10; 256 samples x 16,384, 8 bits 3.63 | 4.09.
+            const bool odd = !(bits == 1 || bits == 2 || bits == 4 || bits == 8);
+            a.wave_early = W <= 128 && micro * bits * 8 >= (odd ? 8192 : W <= 16 ? 16384 : 16385);
+        }
     }
     a.dbg_m = dbg_m; a.dbg_acc = dbg_acc; a.dbg_r = dbg_r; a.dbg_g = dbg_g; a.dbg_gq = dbg_gq;
     switch (bits) {

@@ -1,5 +1,6 @@
 // Step loop of the epoch kernel on the matrix cores: evenly spaced levels, fp32 model, 2-, 4- or
-// 8-bit codes (included by zipml_sgd.hip; uses its SgdArgs / Lds / exchange-word helpers).
+// 8-bit codes (included by zipml_sgd.hip; uses its SgdArgs / Lds / exchange-word helpers): minibatches in
+// chunks, two code pairs, more than 16,384 features.  (zipml_sgd_wave.h has the others.)
 //
 // With evenly spaced levels a value is lo_j + code * delta_j = mid_j + (code - off) * delta_j
 // (off = 128 for 8-bit codes, which re-centres them into a signed byte, else 0), so both passes of
@@ -87,22 +88,13 @@ template <int NC, bool REP> constexpr int64_t kWatchFirst = NC == 1 && !REP ? 65
 //     2 = the plain loop that also writes the residuals and the gradient of its steps to the
 //     debug outputs (zipml_debug_step with ZIPML_SGD_PRODUCTION).  Instantiations of their own, so
 //     that neither costs the plain loop registers.
-// SMALL: at most 256 samples and 64 features a workgroup (four waves work in the loop), atomics, no replicas.  What is
-//     left of such a step besides the exchange is instructions, so the loop does without what pays in longer ones: the
-//     spacing of the exchange words is a constant (the host gives such launches no other), and there is no wait before the
-//     first poll, whose bookkeeping costs 0.05 to 0.09 us a step (16 to 64 workgroups x 64 or 128 samples) and saves at most
-//     0.03 (64 x 256).  Us per step at 8 bits, general form | now: 256 samples x 2,048 features 2.99 | 2.91, 64 x 512 2.40 |
-//     2.31, 64 x 4,096 2.68 | 2.59, 128 x 1,000 2.46 | 2.37, 256 x 1,024 2.75 | 2.68.  With all eight waves at work (320 to 512
-//     samples) it is the slower form: 320 x 1,000, 4 bits 2.85 | 3.11.  (Where the loop's instructions lie within 32 bytes
-//     moves these by up to 2 %.)
-template <int BITS, int UPT, int KB, int NC, bool REP, int XM, bool SMALL = false>
+template <int BITS, int UPT, int KB, int NC, bool REP, int XM>
 __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, unsigned char *mf)
 {
     constexpr bool kDbg = XM == 2;
-    static_assert(!SMALL || (NC == 1 && KB == 1 && UPT == 1 && !REP && XM == 0), "");
     // Where a lane's units lie: a pointer for every unit, or one offset a lane and copy and the rest uniform.  The pointers
     // of two code pairs (up to 48 registers) or of 64 dwords of codes a lane no longer fit beside the codes.
-    constexpr bool kOnePlace = SMALL || (NC == 2 && (REP || UPT * KB > 1)) || (NC == 1 && BITS == 8 && KB == 1 && (REP || UPT == 4));
+    constexpr bool kOnePlace = (NC == 2 && (REP || UPT * KB > 1)) || (NC == 1 && BITS == 8 && KB == 1 && (REP || UPT == 4));
     // No load of a step is pending when the next begins, and the compiler is to know it: the loads stand in branches
     // (p2ok, p1ok), their results are used in others, and what may be pending at the loop's head it waits for in full,
     // whatever else is on its way -- where addresses and codes share registers, before every single load.  An explicit
@@ -161,7 +153,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
     // A thread's exchange words: B and the threads are multiples of 64, so words so far apart are that many
     // << sh apart, and one register holds where the thread polls, another where it publishes (xword() of every
     // index: 64 x 512 features x 8 bits 2.53 us a step, 2.47 now; 512 x 2,048 x 8 3.95 and 3.87).
-    const int sh = SMALL ? 1 : a.acc_sh;
+    const int sh = a.acc_sh;
     const int poll_at = xword(tid, sh), publish_at = xword(16 * (wave + nw * q4) + n16, sh);
     const int wave_at = __builtin_amdgcn_readfirstlane(wave * kWave);
     uint64_t *const acc_base = a.acc + (size_t)rep * Workspace::kAccBuffers * a.acc_words;
@@ -619,7 +611,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                 // (Only then: for a few workgroups the extra round trip costs more than it saves.)
                 const int watch = wave * kWave < B ? wave * kWave : 0;
                 const bool watch_first = (int64_t)W * B >= kWatchFirst<NC, REP>;
-                if constexpr (!SMALL) first_poll.wait();
+                first_poll.wait();
 #pragma unroll 1
                 for (;;) {
                     if (watch_first && !dead && (int)(load_dev(acc + (watch << sh)) >> kCountShift) != W) {
@@ -649,7 +641,7 @@ __device__ __forceinline__ void sgd_steps_mfma(const SgdArgs &a, const Lds &L, u
                     }
                 }
             }
-            if constexpr (!SMALL) first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
+            first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
             if constexpr (kSettle) vm_wait_all();
             if (want_side && lane < 2) side[lane] = fixed_to_float(unpack_sum(rawx, W), ky_pub) * 1.00001f;
 #pragma unroll

@@ -132,24 +132,6 @@ __device__ __forceinline__ float rows_sum(float v)
     s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
-constexpr float kUpper = 1073741824.0f;            // weight of the upper four digits, see digits_of
-// a and b hold the sums of the lower four digits in the even rows of 16 lanes and of the upper four in the odd rows,
-// each at most 2^22 in magnitude, two to an integer: row r gets those of a (r even) or b (r odd).
-struct DigitSums {
-    int lo[2], hi[2];
-};
-__device__ __forceinline__ DigitSums join_rows(const int (&a)[2], const int (&b)[2])
-{
-    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-    DigitSums s;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const v2u v = __builtin_amdgcn_permlane16_swap((uint32_t)a[k], (uint32_t)b[k], false, false);
-        s.lo[k] = (int)v[0];
-        s.hi[k] = (int)v[1];
-    }
-    return s;
-}
 // Digit sums of four tiles -> the number of the tile that this row looks after.  A row of the sum with one element is
 // exact up to the last step (24 bits of the element stand in the upper digits): one rounding as in a product, two in a
 // sum.
@@ -166,77 +148,6 @@ __device__ __forceinline__ float tile_value(const v4i (&c)[4], int q4)
     const DigitSums s = join_rows(a, b);
     return fmaf(fmaf((float)s.hi[1], 65536.0f, (float)s.hi[0]), kUpper, fmaf((float)s.lo[1], 65536.0f, (float)s.lo[0]));
 }
-
-// Reductions of 0 as the neutral element (sums, maxima of unsigned numbers): a row of 16 lanes, or the wave
-// by two row broadcasts more, the result in lane 63 and from there in a scalar register.  Magnitudes are
-// compared as bit patterns, which takes one instruction per step where fmaxf takes three.
-template <typename T, typename Op>
-__device__ __forceinline__ T row_total(T v, Op op)
-{
-    v = op(v, dpp_move<0xB1>(v));
-    v = op(v, dpp_move<0x4E>(v));
-    v = op(v, dpp_move<0x141>(v));
-    return op(v, dpp_move<0x140>(v));
-}
-template <typename T, typename Op>
-__device__ __forceinline__ T wave_total(T v, Op op)
-{
-    v = row_total(v, op);
-    int i = __builtin_bit_cast(int, v);
-    v = op(v, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, i, 0x142, 0xA, 0xF, false)));   // row_bcast15 into rows 1, 3
-    i = __builtin_bit_cast(int, v);
-    v = op(v, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, i, 0x143, 0xC, 0xF, false)));   // row_bcast31 into rows 2, 3
-    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-struct AddF { __device__ __forceinline__ float operator()(float p, float q) const { return p + q; } };
-struct MaxU { __device__ __forceinline__ uint32_t operator()(uint32_t p, uint32_t q) const { return p > q ? p : q; } };
-__device__ __forceinline__ uint32_t magnitude(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
-// v < 2^exponent_of(v) for the bits of a finite v >= 0
-__device__ __forceinline__ int exponent_of(uint32_t bits) { return (int)(bits >> 23) - 126; }
-// Fixed point in two words of four signed base-256 digits, upper * 2^30 + lower: k such that 2^k v < 2^59 for
-// v < 2^e ...
-__device__ __forceinline__ int scale_for(int e) { return 59 - e; }
-// ... and the digits of 2^k v, the bytes of the two words (a |v| of one binade more has room, too).  A number down
-// to 2^-35 of 2^e keeps all the bits that it has in fp32; below that it is rounded to 2^-59 of 2^e.
-struct Digits8 {
-    uint32_t lo, hi;
-};
-__device__ __forceinline__ Digits8 digits_of(float v, int k)
-{
-    const float t = ldexpf(v, k - 30), whole = rintf(t);   // (the difference is exact)
-    return {signed_digits((int)((t - whole) * kUpper)), signed_digits((int)whole)};
-}
-// Where an element stands in an operand of 64 (a plane of 64 bytes) is where its lane stands in the wave: lane l looks
-// after element lane_slot(l) of a group, so that four neighbouring lanes hold the bytes of a dword.  They exchange
-// their digits and store two dwords each; eight byte stores a lane were 70 ns of the smallest step.
-template <int BITS>
-__device__ __forceinline__ int lane_slot(int l)
-{
-    return (l & 32) + slot_code<BITS>((l >> 4) & 1, (l >> 2) & 3, l & 3);
-}
-// lane_slot(16 s + i) = tile_slot(s) + lane_slot(i) for i < 16
-template <int BITS> constexpr int tile_slot(int s) { return BITS == 1 ? 32 * (s >> 1) + 4 * (s & 1) : 16 * s; }
-struct QuadStore {
-    uint32_t sel1, sel2;
-    int at;
-    __device__ __forceinline__ explicit QuadStore(int lane)
-    {
-        sel1 = lane & 1 ? 0x03070105u : 0x06020400u;
-        sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
-        at = 64 * (lane & 3) + (lane & ~3);
-    }
-    __device__ __forceinline__ uint32_t transpose(uint32_t v) const
-    {
-        v = __builtin_amdgcn_perm(dpp_move<0xB1>(v), v, sel1);
-        return __builtin_amdgcn_perm(dpp_move<0x4E>(v), v, sel2);
-    }
-    // digit p of the lane's element -> planes + 64 p + lane (all lanes of the wave)
-    __device__ __forceinline__ void operator()(int8_t *planes, Digits8 dg) const
-    {
-        *reinterpret_cast<uint32_t *>(planes + at) = transpose(dg.lo);
-        *reinterpret_cast<uint32_t *>(planes + at + 256) = transpose(dg.hi);
-    }
-};
 
 struct SoloLds {
     int8_t *ydig;          // [KB][8 digits][4 q][16]

@@ -671,3 +671,103 @@ def test_epochs_on_both_sides_of_the_small_steps(B, d, bits):
         ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.25 / d)
         err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
         assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("B,d,steps", [
+    (4, 290, 21), (8, 600, 5), (16, 1000, 3), (32, 257, 20), (64, 320, 1), (64, 2100, 35), (96, 1030, 2), (160, 4100, 3),
+    (256, 2060, 17), (320, 8200, 2), (512, 300, 2), (512, 4130, 2), (544, 700, 3), (992, 1100, 2), (1024, 2080, 2)])
+def test_epochs_with_samples_owned_by_waves(B, d, steps, bits):
+    """Minibatches inside a group of 32 samples, of odd numbers of groups, of one wave, of all eight and of two blocks a wave;
+    a last workgroup with one group of features; one, two and four exchange words a sample; steps before, at and after the
+    refresh of the bounds; copy 1 requested at either place.  The model of the oracle (fp64 inside a step) to 1e-5, the
+    bound of every epoch test."""
+    say("waves own samples", B, d, steps, bits)
+    n = B * steps
+    rng = np.random.default_rng(B + d + bits)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    x0 = (rng.standard_normal(d) / d ** 0.5).astype(np.float32)
+    L = oracle.levels_uniform(-rng.uniform(0.5, 1, d).astype(np.float32), rng.uniform(0.5, 1, d).astype(np.float32), bits)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L)
+    p.quantize(5, 0)
+    lr = 0.25 / d
+    for form in ("plain", "l2", "prox"):
+        x, ref = dev(x0), x0.copy()
+        args = (p.p1, p.p2, p.levels, p.b, n, d, bits)
+        if form == "plain":
+            zipml.sgd_epoch(*args, x, B, lr, p.ws)
+            ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, ref, B, lr)
+        elif form == "l2":
+            zipml.sgd_epoch_l2(*args, x, B, lr, 0.05, p.ws)
+            ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, ref, B, lr, l2=0.05)
+        else:
+            zipml.sgd_epoch_prox(*args, x, B, lr, zipml.PROX_L1, 0.01, p.ws)
+            ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, ref, B, lr, prox_kind=oracle.PROX_L1, prox_coef=0.01)
+        assert zipml.sgd_status(p.ws) == 0
+        got = x.cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+        if d * n > 1 << 21:
+            break                                      # (the oracle's time)
+
+
+@pytest.mark.parametrize("bits", [1, 3, 5, 6, 7])
+def test_steps_with_samples_owned_by_waves_coordinate_by_coordinate(bits):
+    """One step from a given model at the widths that the vector loop computed in fp32, every coordinate of the
+    gradient on its own: within (d + B + 8) 2^-24 of the sum of the magnitudes that reach it.  Some residuals are 10^6 or
+    10^9 times the others, and half of the features have the level zero in those samples; one element of the model is 10^6
+    times the others and meets only zeros (2^-42 of it is what the exchange resolves)."""
+    rng = np.random.default_rng(bits)
+    for d, B in ((290, 64), (1000, 16), (520, 96), (300, 256), (300, 576)):
+        for large in (1.0, 1e6, 1e9):
+            say("single step of waves", bits, d, B, large)
+            A = rng.uniform(0, 1, (B, d)).astype(np.float32)
+            b = rng.standard_normal(B).astype(np.float32)
+            x0 = (rng.standard_normal(d) * 0.1).astype(np.float32)
+            rows = np.arange(B) % 16 == 3
+            b[rows] *= np.float32(large)
+            A[np.ix_(rows, np.arange(d) % 2 == 0)] = 0.0
+            A[:, 5] = 0.0
+            x0[5] = 0.1 * min(large, 1e6)
+            L = oracle.levels_uniform(np.zeros(d, np.float32), np.ones(d, np.float32), bits)
+            p = GpuProblem(A, b, bits, B)
+            p.set_levels(L)
+            p.quantize(3, 0)
+            v1, v2 = (np.take_along_axis(L, p.codes(c).astype(np.int64).T, axis=1).T.astype(np.float64) for c in (1, 2))
+            x64 = x0.astype(np.float64)
+            ref = x64 - v1.T @ (v2 @ x64 - b) / B
+            mag = np.abs(x64) + v1.T @ (v2 @ np.abs(x64) + np.abs(b)) / B
+            x = dev(x0)
+            zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, B, d, bits, x, B, 1.0, p.ws)
+            err = np.abs(x.cpu().numpy().astype(np.float64) - ref) / mag
+            assert err.max() <= (d + B + 8) * 2.0 ** -24, (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_epochs_with_samples_owned_by_waves_at_the_ends_of_the_number_range(bits):
+    """Tiny and huge labels keep their digits; an infinite label, and one that is no number, end in a model without a
+    finite element."""
+    n, d, B = 288, 300, 96
+    rng = np.random.default_rng(bits)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    L = oracle.levels_uniform(np.full(d, -1, np.float32), np.ones(d, np.float32), bits)
+    for scale in (1e-30, 1e-20, 1.0, 1e30, np.inf, np.nan):
+        say("range of waves", bits, scale)
+        b = rng.standard_normal(n).astype(np.float32)
+        if np.isfinite(scale):
+            b *= np.float32(scale)
+        else:
+            b[7] = scale
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(L)
+        p.quantize(5, 0)
+        x = dev(np.zeros(d, np.float32))
+        zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, n, d, bits, x, B, 0.1 / d, p.ws)
+        assert zipml.sgd_status(p.ws) == 0
+        got = x.cpu().numpy().astype(np.float64)
+        if not np.isfinite(scale):
+            assert not np.isfinite(got).any()
+            continue
+        ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.1 / d)
+        assert np.linalg.norm(got / scale - ref / scale) <= 1e-5 * np.linalg.norm(ref / scale)
