@@ -134,6 +134,7 @@ struct SgdArgs {
     uint64_t *acc;         // [4][acc_words] exchange words
     int acc_words;         // words of a buffer
     int acc_sh;            // how far the exchange words are spread (xword)
+    int acc_split;         // words for a sample (end-to-end loop: 1 or 2)
     int wave_w;            // workgroups (two feature groups each) where the loop of zipml_sgd_wave.h runs even levels
     int wave_sh, wave_split, wave_sub;   // its exchange words: how far they are spread, words for a sample, from one to the next
     const double *bound;   // at launch: [0] sum_j maxabs(L_j)|x_j|, [1] sum_j maxabs(L_j)^2,
@@ -159,13 +160,20 @@ struct SgdArgs {
     int dbg_production;    // 1: dbg_r / dbg_g are written by the production launch (matrix-core loop)
 };
 
+// What the dot pass of the end-to-end loop takes from the model: G[j][c] * m_j, or the digits of 2^bits - 1 products of 64 features.
+__host__ __device__ inline size_t e2e_table_bytes(int CW, int bits)
+{
+    const size_t table = (size_t)CW * 4 << bits, digits = bits <= 3 ? (((size_t)1 << bits) - 1) * 256 : 0;
+    return table > digits ? table : digits;
+}
+
 // LDS arrays of one workgroup.
 struct Lds {
     float *Ls;        // level slice [CW][K]        (lds_levels only)
     uint16_t *Gs;     // grid-index slice [CW][K]   (integer mode with a non-identity grid)
     float *xs, *ys, *los, *dls, *gs;   // model slice, delta*x, lo, delta, gradient slice  [CW]
     int *ms;          // model codes [CW]
-    int *tq;          // G[j][c] * m_j [CW][K]   (end-to-end production loop, at most 4-bit codes)
+    int *tq;          // G[j][c] * m_j [CW][K], or digits   (end-to-end production loop, at most 4-bit codes)
     float *Lp;        // level slice with rows K + 1 apart (end-to-end production loop, lds_levels only)
     float *rs;        // residuals [Rlen]
     float *zl;        // local dot products [B+4]   (single workgroup only)
@@ -871,7 +879,7 @@ __device__ __forceinline__ bool sgd_setup(const SgdArgs &a, Lds &L, unsigned cha
     L.dls = (float *)carve(CW * 4);
     L.gs = (float *)carve(CW * 4);
     L.ms = (int *)carve(CW * 4);
-    L.tq = (int *)carve(INT && FAST && BITS <= 4 ? (size_t)CW * K * 4 : 0);
+    L.tq = (int *)carve(INT && FAST && BITS <= 4 ? e2e_table_bytes(CW, BITS) : 0);
     L.Lp = (float *)carve(INT && FAST && a.lds_levels ? (size_t)CW * (K + 1) * 4 : 0);
     L.rs = (float *)carve((size_t)Rlen * 4);
     L.zl = (float *)carve(a.W == 1 ? (size_t)(B + 4) * 4 : 0);
@@ -945,7 +953,6 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
     const int tid = threadIdx.x;
     const int w = blockIdx.x % a.W;                // feature block; blockIdx.x / a.W: replica (matrix-core loop)
     const int CW = 32 * a.GQ;
-    const int B = a.B;
     const int j0 = w * CW;
 #ifdef ZIPML_PHASE_TIMING
     // where this workgroup runs: XCC id (HW_REG_XCC_ID) and the HW_ID register (SE / CU / SIMD fields)
@@ -973,13 +980,13 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
         if (blockIdx.x == 0 && tid == 0) store_dev(a.status, (int)ZIPML_EUNSUPPORTED);
         return;
     }
-    if constexpr (SOLO >= 5 && SOLO <= 8) {
+    if constexpr (SOLO >= 5 && SOLO <= 8 && !INT) {
         // two code pairs (anything but the matrix-core loop has been refused above)
         if constexpr (!INT && FAST && kMfmaBits && UPT <= 2) {
             constexpr int kKB = 1 + ((SOLO - 5) & 1), kXM = (SOLO - 5) >> 1;
             if (affine_all && a.mfma) sgd_steps_mfma<BITS, UPT, kKB, 2, REP, kXM>(a, L, L.mf);
         }
-    } else if constexpr (SOLO != 0) {
+    } else if constexpr (SOLO != 0 && !INT) {
         // (the host launches this kernel for the plain estimator on the matrix-core plan, without
         // replicas or debug outputs, with the workgroup width and the exchange it was built for)
         if constexpr (!INT && FAST && kMfmaBits && !REP) {
@@ -1034,14 +1041,9 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
             // (a single workgroup is launched on the other instantiation: the host sees to it, so
             // that this one holds the end-to-end loop only and its registers)
             if (a.W > 1) {
-                // (both hold the step's exact gradient; whole sample groups, at most 16 levels and four feature
-                // groups go to the matrix cores)
-                if constexpr (BITS <= 4) {
-                    if (B >= 32 && a.GQ <= 4) sgd_steps_e2e<BITS, UPT, true>(a, L);
-                    else sgd_steps_e2e<BITS, UPT, false>(a, L);
-                } else {
-                    sgd_steps_e2e<BITS, UPT, false>(a, L);
-                }
+                // (SOLO: 1 both passes on the matrix cores, 2 the gradient pass, 0 neither; 4 on top: two exchange words for a sample.
+                // All hold the step's exact gradient.)
+                sgd_steps_e2e<BITS, UPT, (SOLO & 3) != 0, (SOLO & 3) == 1, (SOLO & 4) != 0>(a, L);
             }
         } else if (INT) {
             sgd_steps<BITS, kInt, FAST, UPT, kTabAsked>(a, L);
@@ -1240,7 +1242,7 @@ static size_t plan_lds(int GQ, int bits, int64_t batch, bool int_table, bool int
     lds_levels = (size_t)CW * K * 4 <= 65536 ? 1 : 0;      // (0: 7 bits on eight feature groups, 8 bits on four or eight)
     const size_t total = (lds_levels ? up16((size_t)CW * K * 4) : 0) +
                          (int_table ? up16((size_t)CW * K * 2) : 0) + 6 * up16((size_t)CW * 4) +
-                         (int_mode && bits <= 4 ? up16((size_t)CW * K * 4) : 0) +
+                         (int_mode && bits <= 4 ? up16(e2e_table_bytes(CW, bits)) : 0) +
                          (int_mode && lds_levels ? up16((size_t)CW * (K + 1) * 4) : 0) +
                          up16((size_t)nrg * 32 * 4) +
                          (solo ? up16((size_t)(batch + 4) * 4) : 0) +
@@ -1346,7 +1348,22 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
     const void *kern = (const void *)k_sgd<BITS, INT, false, kMaxUpt>;
     if (fast) {
         if constexpr (INT) {
-            kern = p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1> : (const void *)k_sgd<BITS, true, true, 2>;
+            // Whole sample groups, at most 16 levels and four feature groups: the gradient pass on the matrix cores; with 64
+            // features to a workgroup and at most eight levels the dot pass, too (32 features: 512 samples x 600, 3 bits 6.8 us a
+            // step, with it 7.3: half of the instructions' features are not there); kernels of their own.
+            // (The lanes' offsets in copy 2 are 32 bits wide.)
+            const bool grad_mx = BITS <= 4 && a.B >= 32 && a.GQ <= 4;
+            const bool dot_mx = BITS <= 3 && grad_mx && a.B <= kThreads && a.GQ == 2 && a.nb64 * 64 * 2 * BITS * 4 < ((int64_t)7 << 29);
+#define ZIPML_E2E(S) (a.acc_split > 1 ? (p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, 4 + S> : (const void *)k_sgd<BITS, true, true, 2, false, 4 + S>) \
+                                      : (p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, S> : (const void *)k_sgd<BITS, true, true, 2, false, S>))
+            kern = ZIPML_E2E(0);
+            if constexpr (BITS <= 4) {
+                if (grad_mx) kern = ZIPML_E2E(2);
+            }
+            if constexpr (BITS <= 3) {
+                if (dot_mx) kern = ZIPML_E2E(1);
+            }
+#undef ZIPML_E2E
         } else {
             kern = p.upt == 1 ? (const void *)k_sgd<BITS, false, true, 1>
                  : p.upt == 2 ? (const void *)k_sgd<BITS, false, true, 2>
@@ -1804,8 +1821,12 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
         const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
         // (two lines a stretch are enough for few workgroups, and half as many words to poll)
         a.acc_sh = p.W > 64 ? 2 : 1;
-        while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(pairs * micro, a.acc_sh) + grad_words > room) --a.acc_sh;
-        a.acc_words = (int)Workspace::acc_words(pairs * micro, a.acc_sh);
+        const int64_t sums = pairs * micro + (model_bits > 0 && p.W > 32 ? 8 * kWaves : 0);
+        while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(sums, a.acc_sh) + grad_words > room) --a.acc_sh;
+        a.acc_words = (int)Workspace::acc_words(sums, a.acc_sh);
+        // (end to end: adds to one word follow each other at some 11 ns)
+        a.acc_split = model_bits > 0 && !stepwise && p.W > 32 && 2 * (size_t)Workspace::kAccBuffers * a.acc_words <= room ? 2 : 1;
+        a.acc_words *= a.acc_split;
         if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))
             return ZIPML_EWORKSPACE;

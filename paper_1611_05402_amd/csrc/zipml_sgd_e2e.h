@@ -19,9 +19,13 @@
 // then waves, then workgroups, pairwise), so the fp32 norm has the same bits on every workgroup
 // and as a plain pairwise sum over the padded vector.
 //
-// Arithmetic per code: the dot pass adds T[j][code] = G[j][code] * m_j, a table rebuilt by the
-// owner of feature j after Q3 (one LDS gather and one integer add per code; for wide level sets
-// the product is formed on the fly).  The mean gradient that Q4 quantises is the exact mean rounded to
+// Arithmetic per code: the dot pass adds G[j][code] * m_j.  On the matrix cores (DX: at most eight levels, 64 features to
+// a workgroup) the grid index is a polynomial of the code's bits, G[j][c] = sum over the subsets s of the bits of a_js
+// (1 where all bits of s are set in c), so the sum is 2^bits - 1 products of 0/1 bytes with the digits of a_js m_j, in exact
+// integers like the others.  Else from a table T[j][code] = G[j][code] * m_j, rebuilt by the owner of feature j after Q3 (one
+// LDS gather and one integer add per code; for wide level sets the product is formed on the fly): 512 samples x 64
+// features, 3 bits 1.56 us from the table, 0.66 so; the whole step of 512 x 4,096 with that and with two exchange words for
+// a sample 8.43 -> 7.93.  The mean gradient that Q4 quantises is the exact mean rounded to
 // fp32, whatever the order: the gradient pass adds L[j][code] * r_i either in fp64 (products of two fp32
 // numbers are exact there) or, for at most 16 levels and whole sample groups (MX), in integers on the matrix
 // cores: r and a feature's levels in eight signed bytes each (24 bits at the top of 62, so that a number is exact
@@ -77,14 +81,22 @@ __device__ __forceinline__ long long fixed_from_float(float v, int emax, int top
 }
 constexpr int kDigits = 8, kTop = 38;       // residuals and levels: 24 + 38 bits
 
-constexpr int kNormSlots = 256;   // slots per buffer of the norm exchange (>= workgroups)
+// Slots per buffer of the norm exchange: up to 64 workgroups eight to 256 bytes, up to 128 eight to 128 (xword; everybody
+// asks for all of them, and the memory side answers for one stretch after the other).
+constexpr int kNormSlots = 256;
+__device__ __forceinline__ int norm_slot(int w, int W) { return xword(w, W <= 64 ? 2 : W <= 128 ? 1 : 0); }
+
+// The monomials of up to three bits: bit b of `set` says whether bit b of the code is a factor.
+template <int BITS> constexpr int kMonomials = (1 << BITS) - 1;
 
 // MX: the gradient pass on the matrix cores (at most 16 levels, B >= 32, GQ <= 4).
-template <int BITS, int UPT, bool MX>
+// DX: the dot pass, too (at most 8 levels, GQ <= 2, 32 <= B <= 512, and the lanes' offsets in copy 2 within 32 bits).
+// SPLIT: two exchange words for a sample (asked of the host at run time it cost the launches of few workgroups 3 %).
+template <int BITS, int UPT, bool MX, bool DX, bool SPLIT>
 __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 {
     constexpr int K = 1 << BITS;
-    constexpr bool kTable = BITS <= 4;               // T[j][c] = G[j][c] * m_j kept in LDS
+    constexpr bool kTable = BITS <= 4 && !DX;        // T[j][c] = G[j][c] * m_j kept in LDS
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
     const int w = blockIdx.x;
@@ -105,6 +117,12 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     const int s_m = (1 << (a.model_bits - 1)) - 1;
     const int s_g = a.grad_bits > 0 ? (1 << (a.grad_bits - 1)) - 1 : 1;
     const int nq = (W + kWave - 1) / kWave;          // norm slots per lane (W <= 256: at most 4)
+    // exchange words of a sample: one, or two of them, apart by `sub`, and the workgroups in turn add to either
+    constexpr int split = SPLIT ? 2 : 1;
+    const int sub = a.acc_words / split, mine_at = (w % split) * sub;
+    // The sum of the model's codes: one word behind the samples', or among many workgroups one for each of the waves that ask
+    // for it, apart (one for all would be asked for eight times as often as any other).
+    constexpr int apart = SPLIT ? 8 : 0;
 
     // ---- the units this thread owns, the same in every step (as in sgd_steps)
     int d_i[UPT], d_g[UPT];
@@ -185,6 +203,54 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         }
     };
 
+    // ---- matrix-core dot pass: a wave takes a block of 64 samples (zipml_sgd_wave.h: how the operands are loaded, and which
+    // sample and feature a lane looks after)
+    constexpr int NL = kWaveLoads<BITS>, LW = kWaveDwords<BITS>, kSets = DX ? kMonomials<BITS> : 1;
+    const int own = wave_element<BITS>(q4, n16);
+    int8_t *const mdig = reinterpret_cast<int8_t *>(tq);           // [kSets][4 digits][64 features]
+    uint32_t at2[NL], codes2[NL][LW];
+    v4i bits2[4][DX ? BITS : 1];                       // a bit of the codes each, in a byte
+    int coef[kSets], coef0 = 0;                        // of the grid indices of feature `own`, as a polynomial of the bits
+    __amdgpu_buffer_rsrc_t src2;
+    if constexpr (DX) {
+        const uint32_t group_bytes = (uint32_t)(a.nb64 * 64 * 4 * BITS);
+        src2 = __builtin_amdgcn_make_buffer_rsrc((unsigned char *)a.p2 + (int64_t)w * GQ * group_bytes, 0, (int)0xE0000000u, 0x00020000);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const int row = wave_load_row<BITS>(q4, n16, l), s = 2 * wave + (row >> 5);
+            at2[l] = (q4 >> 1) < ngroups && s < nrg ? (uint32_t)(q4 >> 1) * group_bytes + (uint32_t)((s * 32 + (row & 31)) * 4 * BITS) : 0xF0000000u;
+        }
+        auto grid = [&](int c) { return own >= CW || j0 + own >= a.d ? 0 : a.ident_grid ? c : (int)a.grid[(size_t)(j0 + own) * K + c]; };
+        coef0 = grid(0);
+#pragma unroll
+        for (int set = 1; set < K; ++set) {
+            int v = 0;                                 // sum over the subsets, signs by how many bits are left out
+#pragma unroll
+            for (int c = 0; c < K; ++c)
+                if ((c & set) == c) v += __builtin_popcount(set ^ c) & 1 ? -grid(c) : grid(c);
+            coef[set - 1] = v;
+        }
+    }
+    auto load_dot_codes = [&](int64_t t) __attribute__((always_inline)) {
+        const uint32_t step = (uint32_t)(t * B) * (4 * BITS);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) buffer_fetch<LW>(src2, at2[l], step, codes2[l]);
+    };
+    auto expand_dot_codes = [&]() __attribute__((always_inline)) {
+        if constexpr (DX) {
+            v4i e[4];
+            wave_operands<BITS>(codes2, op_shift<BITS>(q4 & 1), e);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int b = 0; b < BITS; ++b) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) bits2[s][b][q] = (int)(((uint32_t)e[s][q] >> b) & 0x01010101u);
+                    asm volatile("" : "+v"(bits2[s][b]));
+                }
+        }
+    };
+
     auto load_dot_units = [&](int64_t t, uint32_t (&dst)[UPT][BITS]) {
         const int64_t row0 = t * B;
 #pragma unroll
@@ -221,16 +287,22 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     // Returns the l2 norm over all workgroups as fp32, to the owner waves (others get 0).
     // meanwhile(): work of the owner waves that does not need the norm, done while it travels.
     auto exchange_norm = [&](double sq, uint64_t *slots, FirstPoll &first, auto meanwhile) -> float {
-        if (owner_wave) {
-            sq = wave_tree_sum_f64(sq);
-            if (lane == 0) red[wave] = sq;
-        }
-        lds_barrier();
-        if (tid == 0) {
-            double own = red[0];
-            if (owner_waves == 2) own = red[0] + red[1];
-            else if (owner_waves == 4) own = (red[0] + red[1]) + (red[2] + red[3]);
-            store_dev(slots + w, (uint64_t)((uint64_t)__double_as_longlong(own) + 1ull));
+        // (one owner wave needs nobody: the barriers of a step are enough for what else it shares)
+        if (owner_waves == 1) {
+            if (owner_wave) {
+                sq = wave_tree_sum_f64(sq);
+                if (lane == 0) store_dev(slots + norm_slot(w, W), (uint64_t)((uint64_t)__double_as_longlong(sq) + 1ull));
+            }
+        } else {
+            if (owner_wave) {
+                sq = wave_tree_sum_f64(sq);
+                if (lane == 0) red[wave] = sq;
+            }
+            lds_barrier();
+            if (tid == 0) {
+                const double own = owner_waves == 2 ? red[0] + red[1] : (red[0] + red[1]) + (red[2] + red[3]);
+                store_dev(slots + norm_slot(w, W), (uint64_t)((uint64_t)__double_as_longlong(own) + 1ull));
+            }
         }
         if (!owner_wave) return 0.0f;
         meanwhile();
@@ -243,7 +315,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (q < nq && lane + kWave * q < W) {
-                    raw[q] = load_dev(slots + lane + kWave * q);
+                    raw[q] = load_dev(slots + norm_slot(lane + kWave * q, W));
                     all = all && raw[q] != 0ull;
                 }
             if (__builtin_amdgcn_ballot_w64(!all) == 0ull || dead) break;
@@ -278,8 +350,16 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     float bnext[UPT], bfut[UPT];
 #pragma unroll
     for (int k = 0; k < UPT; ++k) bnext[k] = bfut[k] = 0.0f;
-    load_dot_units(a.step0, c2cur);
-    if (a.step0 + 1 < t_end) load_dot_units(a.step0 + 1, c2nxt);
+    if constexpr (DX) {
+        load_dot_codes(a.step0);
+        if (wave_u == 0) {
+            expand_dot_codes();
+            if (a.step0 + 1 < t_end) load_dot_codes(a.step0 + 1);
+        }
+    } else {
+        load_dot_units(a.step0, c2cur);
+        if (a.step0 + 1 < t_end) load_dot_units(a.step0 + 1, c2nxt);
+    }
     load_grad(a.step0);
     load_labels(a.step0, bnext);
 
@@ -308,6 +388,9 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         };
         const float Mx = exchange_norm(live ? (double)x_own * (double)x_own : 0.0, xn, first_norm[0], draw_for(3u));
         ZIPML_TICK(0);
+        if constexpr (DX) {
+            if (wave_u != 0) expand_dot_codes();
+        }
         const float sigma = Mx > 0.0f ? __fdiv_rn(Mx, (float)s_m) : 0.0f;
         if (owner_wave) {
             int mine = 0;
@@ -323,6 +406,16 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                         tq[tid * K + c] = (a.ident_grid ? c : (int)L.Gs[tid * K + c]) * mine;
                 }
             }
+            if constexpr (DX) {
+                // what multiplies a monomial: an integer below 2^25 in magnitude, in four digits
+                const int m = __shfl(mine, own, kWave);
+                const QuadStore quad(lane);
+                int8_t *const at = mdig + wave_digits_at<BITS>(q4, n16);
+#pragma unroll
+                for (int k = 0; k < kSets; ++k) *reinterpret_cast<uint32_t *>(at + 256 * k) = quad.transpose(signed_digits(coef[k] * m));
+                const int low = wave_sum_dpp(coef0 * m);
+                if (lane == 0) L.isum[1] = low;
+            }
             const int part = wave_sum_dpp(mine);
             if (lane == 0) L.isum[wave] = part;
             if (tid == 0) L.wsum[0] = sigma;          // for the threads outside the owner waves
@@ -330,14 +423,38 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         lds_barrier();      // ms / tq / isum / sigma
         const float sigma_b = L.wsum[0];
         ZIPML_TICK(1);
-        if (tid == 0) {
+        if (tid == 0 || (SPLIT && tid < kWaves && tid * kWave < B)) {
             int tot = 0;
             for (int q = 0; q < owner_waves; ++q) tot += L.isum[q];
-            add_dev(acc + xword(B, a.acc_sh), pack_int(tot));
+            add_dev(acc + mine_at + xword(B + apart * tid, a.acc_sh), pack_int(tot));
         }
 
         // ================= dot pass: acc_i = sum_j G[j][c2_ij] m_j over the owned features
-        {
+        if constexpr (DX) {
+            const int low = L.isum[1];
+            v4i md[kSets];
+#pragma unroll
+            for (int k = 0; k < kSets; ++k) md[k] = *reinterpret_cast<const v4i *>(mdig + 256 * k + (n16 & 3) * 64 + q4 * 16);
+            const int i = 64 * wave + own;
+            if (64 * wave_u < B) {
+                v4i c[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    c[s] = v4i{0, 0, 0, 0};
+#pragma unroll
+                    for (int set = 1; set < K; ++set) {
+                        v4i e = {-1, -1, -1, -1};
+#pragma unroll
+                        for (int b = 0; b < BITS; ++b)
+                            if (set >> b & 1) e &= bits2[s][b];
+                        c[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(md[set - 1], e, c[s], 0, 0, 0);
+                    }
+                }
+                int sum[2];
+                pick_tile(c, q4, sum);
+                if (i < B) add_dev(acc + mine_at + xword(i, a.acc_sh), pack_int((long long)sum[0] + ((long long)sum[1] << 16) + low));
+            }
+        } else {
             int pi[UPT];
 #pragma unroll
             for (int k = 0; k < UPT; ++k) {
@@ -361,7 +478,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 int tot = 0;
 #pragma unroll
                 for (int k = 0; k < UPT; ++k) tot += pi[k];
-                add_dev(acc + xword(tid, a.acc_sh), pack_int(tot));
+                add_dev(acc + mine_at + xword(tid, a.acc_sh), pack_int(tot));
             } else if (ngroups > 1) {
 #pragma unroll
                 for (int k = 0; k < UPT; ++k)
@@ -370,12 +487,12 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 for (int i = tid; i < B; i += kThreads) {
                     int tot = 0;
                     for (int gq = 0; gq < ngroups; ++gq) tot += (int)L.zp[gq * B + i];
-                    add_dev(acc + xword(i, a.acc_sh), pack_int(tot));
+                    add_dev(acc + mine_at + xword(i, a.acc_sh), pack_int(tot));
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < UPT; ++k)
-                    if (d_g[k] < ngroups) add_dev(acc + xword(d_i[k], a.acc_sh), pack_int(pi[k]));
+                    if (d_g[k] < ngroups) add_dev(acc + mine_at + xword(d_i[k], a.acc_sh), pack_int(pi[k]));
             }
         }
         ZIPML_TICK(2);
@@ -387,11 +504,14 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         // any later exchange, and nobody reaches step t+2 without those contributions.
         if (wave == kWaves - 1) {
             uint64_t *nxt = a.acc + (size_t)((t + 2) & 3) * a.acc_words;
-            const int per = (B + 1 + W - 1) / W, hi = (w + 1) * per < B + 1 ? (w + 1) * per : B + 1;
-            for (int i = w * per + lane; i < hi; i += kWave) store_dev(nxt + xword(i, a.acc_sh), (uint64_t)0);
+            const int words = B + 1 + (kWaves - 1) * apart, per = (words + W - 1) / W, hi = (w + 1) * per < words ? (w + 1) * per : words;
+            for (int i = w * per + lane; i < hi; i += kWave) {
+                store_dev(nxt + xword(i, a.acc_sh), (uint64_t)0);
+                if (split > 1) store_dev(nxt + sub + xword(i, a.acc_sh), (uint64_t)0);
+            }
             if (lane == 0) {
-                store_dev(slot_base + (size_t)((t + 2) & 3) * kNormSlots + w, (uint64_t)0);
-                store_dev(slot_base + (size_t)(4 + ((t + 2) & 3)) * kNormSlots + w, (uint64_t)0);
+                store_dev(slot_base + (size_t)((t + 2) & 3) * kNormSlots + norm_slot(w, W), (uint64_t)0);
+                store_dev(slot_base + (size_t)(4 + ((t + 2) & 3)) * kNormSlots + norm_slot(w, W), (uint64_t)0);
             }
             if (!(tid < B)) vm_wait_all();
         }
@@ -400,15 +520,28 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
         for (int k = 0; k < (MX ? kOps : UPT); ++k)
 #pragma unroll
             for (int q = 0; q < (MX ? HW : BITS); ++q) c1cur[k][q] = c1nxt[k][q];
+        if constexpr (!DX) {
 #pragma unroll
-        for (int k = 0; k < UPT; ++k)
+            for (int k = 0; k < UPT; ++k)
 #pragma unroll
-            for (int q = 0; q < BITS; ++q) c2cur[k][q] = c2nxt[k][q];
+                for (int q = 0; q < BITS; ++q) c2cur[k][q] = c2nxt[k][q];
+        }
         if (t + 1 < t_end) {
             load_grad(t + 1);
             load_labels(t + 1, bfut);
         }
-        if (t + 2 < t_end) load_dot_units(t + 2, c2nxt);
+        if constexpr (DX) {
+            // the wave that owns the features expands the codes of the next step here, requested in the last one; the others
+            // have time when it waits for the norm of the model
+            if (wave_u == 0) {
+                expand_dot_codes();
+                if (t + 2 < t_end) load_dot_codes(t + 2);
+            } else if (t + 1 < t_end) {
+                load_dot_codes(t + 1);
+            }
+        } else {
+            if (t + 2 < t_end) load_dot_units(t + 2, c2nxt);
+        }
         ZIPML_TICK(3);
 
         // ================= residuals: every thread polls the words of its own samples
@@ -426,7 +559,18 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                     const int i = tid + q * kThreads;
                     raw[q] = load_dev(acc + xword(i < B ? i : B - 1, a.acc_sh));
                 }
-                rawm = load_dev(acc + xword(B, a.acc_sh));
+                rawm = load_dev(acc + xword(B + apart * wave_u, a.acc_sh));
+                if (split > 1) {
+                    uint64_t second[UPT];
+#pragma unroll
+                    for (int q = 0; q < UPT; ++q) {
+                        const int i = tid + q * kThreads;
+                        second[q] = load_dev(acc + sub + xword(i < B ? i : B - 1, a.acc_sh));
+                    }
+                    rawm += load_dev(acc + sub + xword(B + apart * wave_u, a.acc_sh));
+#pragma unroll
+                    for (int q = 0; q < UPT; ++q) raw[q] += second[q];
+                }
                 bool all = (int)(rawm >> kCountShift) == W;
 #pragma unroll
                 for (int q = 0; q < UPT; ++q) all = all && (int)(raw[q] >> kCountShift) == W;
@@ -437,6 +581,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 }
             }
             first_poll.learn(__builtin_amdgcn_ballot_w64(spins != 0) != 0);
+            ZIPML_TICK(8);
             const double summ = (double)unpack_sum(rawm, W);
 #pragma unroll
             for (int q = 0; q < UPT; ++q) {
@@ -467,7 +612,9 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
             m = wave_reduce_dpp(m, [](uint32_t p, uint32_t q) { return p > q ? p : q; });
             if (lane == 0) wmax[wave] = m;
         }
+        ZIPML_TICK(9);
         lds_barrier();    // rs[], or the waves' largest residuals
+        ZIPML_TICK(10);
         int er = 1;
         if constexpr (MX) {
             uint32_t m = 0;

@@ -82,6 +82,25 @@ __device__ __forceinline__ int wave_digits_at(int q4, int n16)
     const int dword = BITS == 1 ? 8 * (n16 >> 3) + 4 * ((n16 >> 2) & 1) + q4 : BITS == 2 ? 4 * (n16 >> 2) + q4 : 4 * q4 + (n16 >> 2);
     return 64 * (n16 & 3) + 4 * dword;
 }
+// The row (of 64) that a lane's load l begins at.
+template <int BITS>
+__device__ __forceinline__ int wave_load_row(int q4, int n16, int l)
+{
+    if (BITS <= 2) return wave_element<BITS>(0, n16) + (BITS == 2 ? 2 * (q4 & 1) : 0);
+    return BITS <= 4 ? wave_element<BITS>(2 * l + (q4 & 1), n16) : wave_element<BITS>(l, n16);
+}
+// Sums of four digits, two to an integer, of the tile that a row of lanes looks after.
+__device__ __forceinline__ void pick_tile(const v4i (&c)[4], int q4, int (&sum)[2])
+{
+    const bool sel1 = q4 & 1, sel2 = q4 & 2;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        int p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p[q] = c[q][2 * k] + (c[q][2 * k + 1] << 8);
+        sum[k] = sel2 ? (sel1 ? p[3] : p[2]) : (sel1 ? p[1] : p[0]);
+    }
+}
 // Loads -> the operands of the four tiles (code bytes).
 template <int BITS>
 __device__ __forceinline__ void wave_operands(const uint32_t (&c)[kWaveLoads<BITS>][kWaveDwords<BITS>], uint32_t shift, v4i (&e)[4])
@@ -141,7 +160,6 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
     const int own = wave_element<BITS>(q4, n16);
     const uint32_t shift = op_shift<BITS>(q4 & 1);
     const QuadStore quad(lane);
-    const bool sel1 = q4 & 1, sel2 = q4 & 2;
 
     // ---- LDS
     int8_t *const rdig = (int8_t *)smem + wave * ((1 + SB) * ND * 64);
@@ -164,24 +182,21 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
     };
     auto pick = [&](const v4i (&c)[4]) __attribute__((always_inline)) {
         Sums s = {};
-        int p[2][4];
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) p[k][q] = c[q][2 * k] + (c[q][2 * k + 1] << 8);
         if constexpr (ND == 8) {
             int x[2], y[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                x[k] = sel2 ? p[k][2] : p[k][0];
-                y[k] = sel2 ? p[k][3] : p[k][1];
+                int p[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) p[q] = c[q][2 * k] + (c[q][2 * k + 1] << 8);
+                x[k] = q4 & 2 ? p[2] : p[0];
+                y[k] = q4 & 2 ? p[3] : p[1];
             }
             const DigitSums j = join_rows(x, y);
 #pragma unroll
             for (int k = 0; k < 2; ++k) { s.lo[k] = j.lo[k]; s.hi[k] = j.hi[k]; }
         } else {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) s.lo[k] = sel2 ? (sel1 ? p[k][3] : p[k][2]) : (sel1 ? p[k][1] : p[k][0]);
+            pick_tile(c, q4, s.lo);
         }
         return s;
     };
@@ -234,9 +249,8 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
     for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
-            // the row (of 64) of this lane's load, and how far into its unit the load begins
-            const int row = BITS == 1 ? own - q4 : BITS == 2 ? own - q4 + 2 * (q4 & 1)
-                          : BITS <= 4 ? wave_element<BITS>(2 * l + (q4 & 1), n16) : wave_element<BITS>(l, n16);
+            // the row of this lane's load, and how far into its unit the load begins
+            const int row = wave_load_row<BITS>(q4, n16, l);
             const int in_unit = BITS <= 4 ? 0 : (q4 & 1) * kOpStride<BITS> * 4, s0 = 2 * (wave * SB + sb);
             auto at = [&](int f, int s) {
                 return f < ngroups && s < nrg ? (uint32_t)f * group_bytes + (uint32_t)((s * 32 + (row & 31)) * 4 * BITS + in_unit) : 0xF0000000u;

@@ -771,3 +771,31 @@ def test_epochs_with_samples_owned_by_waves_at_the_ends_of_the_number_range(bits
             continue
         ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.1 / d)
         assert np.linalg.norm(got / scale - ref / scale) <= 1e-5 * np.linalg.norm(ref / scale)
+
+
+@pytest.mark.parametrize("d,B,bits", [(2111, 512, 3), (4030, 512, 2), (4095, 32, 1), (4100, 480, 3), (2111, 96, 3), (8190, 96, 3)])
+def test_end_to_end_epochs_with_the_dot_pass_on_the_matrix_cores(d, B, bits):
+    """Grid indices from a lowest one that is not zero up to thousands, an odd last group of features, whole and half blocks of
+    samples, one and two exchange words a sample.  The integers of a step are the oracle's, and an epoch of more steps than
+    exchange buffers is that of its steps launched one by one, bit for bit."""
+    say("end-to-end dot pass", d, B, bits)
+    rng = np.random.default_rng(d + B + bits)
+    K, M, n = 1 << bits, 1900, 9 * B
+    G = np.sort(np.stack([rng.choice(M, K, replace=False) + 1 for _ in range(d)]), axis=1).astype(np.uint16)
+    L = (G / np.float64(M)).astype(np.float32)
+    A = rng.uniform(0, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    x0 = (rng.standard_normal(d) * 0.1).astype(np.float32)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(L, G)
+    p.quantize(4, 0)
+    e2e_step_check(p, oracle, p.codes(1)[:2 * B], p.codes(2)[:2 * B], L, G, np.float32(0), np.float32(1.0 / M), M, b, x0, 0.3, 8, 8,
+                   4, 0, 1, zipml.SGD_PRODUCTION)
+    kw = dict(grid_idx=p.grid, grid_lo=0.0, grid_step=1.0 / M, grid_max=M, grad_bits=8, model_bits=8, seed=4, epoch=0)
+    x, y = dev(x0), dev(x0)
+    zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, n, d, bits, x, B, 0.01, p.ws, **kw)
+    assert zipml.sgd_status(p.ws) == 0
+    r = torch.zeros(B, dtype=torch.float32, device=y.device)
+    for step in range(9):
+        zipml.debug_step(p.p1, p.p2, p.levels, p.b, n, d, bits, y, B, 0.01, step, p.ws, flags=zipml.SGD_PRODUCTION, r=r, **kw)
+    assert torch.equal(x, y)
