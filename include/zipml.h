@@ -325,7 +325,10 @@ int zipml_debug_stream(void *stream, const void *src_dev, void *dst_dev, size_t 
                                             the sums travel through tagged stores and reducer
                                             workgroups instead of atomics (0: wherever the loop can; a
                                             huge value: never; by itself the library asks for 32768
-                                            and at least 128 workgroups)                           */
+                                            and at least 128 workgroups).  Any value keeps epochs on
+                                            even levels on the loop that can exchange so, which by
+                                            itself has minibatches in chunks, two code pairs and more
+                                            than 16,384 features                                   */
 #define ZIPML_KNOB_COOPERATIVE_LAUNCH 11 /* 1: the epoch kernels go through the runtime's cooperative
                                             launch (it checks that the grid can be resident, as the
                                             library does itself, and queues such launches apart from

@@ -30,6 +30,8 @@
 //   - workgroup barriers inside a step order LDS traffic only (lds_barrier).
 // End-to-end mode adds two small exchanges per step (the l2 norms of model and gradient), each
 // closed by a grid barrier (one monotonically increasing arrival counter).
+// Evenly spaced levels and an fp32 model, the ordinary case, are on the matrix cores, in a loop of their own in which
+// waves own samples (zipml_sgd_wave.h).
 // Minibatches too large for one exchange are taken in chunks, shared out over replicas of the
 // workgroups (zipml_sgd_mfma.h), and very large ones by workgroups that own samples instead of
 // features (zipml_sgd_rows.h); run_sgd below chooses.
@@ -1279,6 +1281,9 @@ static int target_workgroups()
 //   end to end (three exchanges): 33 to 64, 512 units 7.06 | 7.37, 1,024 units 8.01 | 7.47; 65 to 128: 8.8 | 9.8.
 // (Levels that are not even leave the matrix cores' loop for the vector ALU's in the same plan: 8,192 features, 4 bits, 256
 // samples 15.5 | 7.6.)
+// (Epochs on even levels of an fp32 model with one exchange a step have a division of their own, run_sgd's: 64 features to
+// a workgroup.  The figures of the matrix cores are those of the loop of zipml_sgd_mfma.h, which had them, and
+// keeps two pairs, chunks and what the division does not fit.)
 static bool fewer_workgroups(int64_t W, int GQ, int64_t batch, bool mfma, bool fp32_model, int pairs)
 {
     const int64_t units = 2 * GQ * batch;                  // of a workgroup of twice the size
