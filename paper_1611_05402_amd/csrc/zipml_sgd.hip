@@ -1082,12 +1082,14 @@ __global__ __launch_bounds__(kThreads) void k_sgd_wave(SgdArgs a)
         if ((int)blockIdx.x >= a.W) return;
         Lds L;
         (void)sgd_setup<BITS, false, true>(a, L, smem);
-        // (7 and 8 bits: the tables of many features stay in memory; at 2 bits the question stays, see sgd_steps)
+        // (7 and 8 bits: the tables of many features stay in memory; at 2 bits, and up to 5 bits on at most 512 samples, the
+        // question stays, see sgd_steps: us per step without | with it, 512 samples x 536, 3 bits 3.96 | 3.82, 256 x 1,500 3.22 |
+        // 3.15, 4 bits 4.20 | 4.13, 5 bits 3.78 | 3.70; 928 x 1,328, 3 bits 6.86 | 6.98)
         if constexpr (BITS >= 7) {
             if (a.lds_levels) sgd_steps<BITS, kTable, true, UPT, kTabLds>(a, L);
             else sgd_steps<BITS, kTable, true, UPT, kTabMem>(a, L);
         } else {
-            sgd_steps<BITS, kTable, true, UPT, BITS == 2 ? kTabAsked : kTabLds>(a, L);
+            sgd_steps<BITS, kTable, true, UPT, BITS == 2 || (SB == 1 && BITS <= 5) ? kTabAsked : kTabLds>(a, L);
         }
         const int CW = 32 * a.GQ, j0 = blockIdx.x * CW;
         for (int c = tid; c < CW; c += kThreads)
@@ -1361,7 +1363,7 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
             const bool dot_mx = BITS <= 3 && grad_mx && a.B <= kThreads && a.GQ == 2 && a.nb64 * 64 * 2 * BITS * 4 < ((int64_t)7 << 29);
 #define ZIPML_E2E(S) (a.acc_split > 1 ? (p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, 4 + S> : (const void *)k_sgd<BITS, true, true, 2, false, 4 + S>) \
                                       : (p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, S> : (const void *)k_sgd<BITS, true, true, 2, false, S>))
-            kern = ZIPML_E2E(0);
+            kern = p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, 0> : (const void *)k_sgd<BITS, true, true, 2, false, 0>;
             if constexpr (BITS <= 4) {
                 if (grad_mx) kern = ZIPML_E2E(2);
             }
@@ -1829,8 +1831,9 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
         const int64_t sums = pairs * micro + (model_bits > 0 && p.W > 32 ? 8 * kWaves : 0);
         while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(sums, a.acc_sh) + grad_words > room) --a.acc_sh;
         a.acc_words = (int)Workspace::acc_words(sums, a.acc_sh);
-        // (end to end: adds to one word follow each other at some 11 ns)
-        a.acc_split = model_bits > 0 && !stepwise && p.W > 32 && 2 * (size_t)Workspace::kAccBuffers * a.acc_words <= room ? 2 : 1;
+        // (end to end: adds to one word follow each other at some 11 ns; not where the look-ups of a step are longer, 5 bits, 160
+        // samples x 4,523 8.92 us a step with one word, 9.14 with two, nor on fat workgroups, 2 bits, 192 x 4,978 7.24 and 7.41)
+        a.acc_split = model_bits > 0 && !stepwise && bits <= 4 && batch >= 32 && p.GQ <= 2 && p.W > 32 && 2 * (size_t)Workspace::kAccBuffers * a.acc_words <= room ? 2 : 1;
         a.acc_words *= a.acc_split;
         if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))

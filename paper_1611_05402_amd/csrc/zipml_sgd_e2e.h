@@ -81,10 +81,12 @@ __device__ __forceinline__ long long fixed_from_float(float v, int emax, int top
 }
 constexpr int kDigits = 8, kTop = 38;       // residuals and levels: 24 + 38 bits
 
-// Slots per buffer of the norm exchange: up to 64 workgroups eight to 256 bytes, up to 128 eight to 128 (xword; everybody
-// asks for all of them, and the memory side answers for one stretch after the other).
+// Slots per buffer of the norm exchange: beside the matrix-core dot pass up to 64 workgroups eight to 256 bytes, up to 128 eight
+// to 128 (xword; everybody asks for all of them, and the memory side answers for one stretch after the other); else side
+// by side (5 bits, 160 samples x 179 8.23 us a step spread, 8.13 so).
 constexpr int kNormSlots = 256;
-__device__ __forceinline__ int norm_slot(int w, int W) { return xword(w, W <= 64 ? 2 : W <= 128 ? 1 : 0); }
+template <bool SPREAD>
+__device__ __forceinline__ int norm_slot(int w, int W) { return SPREAD ? xword(w, W <= 64 ? 2 : W <= 128 ? 1 : 0) : w; }
 
 // The monomials of up to three bits: bit b of `set` says whether bit b of the code is a factor.
 template <int BITS> constexpr int kMonomials = (1 << BITS) - 1;
@@ -283,15 +285,19 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 
     bool dead = false;
     FirstPoll first_poll, first_norm[2];
+    // (Without a barrier in front of its slot the owner is sooner on its way, and the other waves sooner at what stands in the
+    // way of its polls.  Us per step with it | without: 4 bits, 96 samples x 294 6.98 | 6.79, 192 x 376 7.21 | 6.96; look-ups,
+    // 2 bits, 256 x 244 6.90 | 7.03, 5 bits, 160 x 179 8.13 | 8.23.)
+    constexpr bool kAlone = DX || (MX && BITS >= 3);
     // One trip of the norm exchange.  sq: this thread's square (owners; 0 elsewhere), fp64.
     // Returns the l2 norm over all workgroups as fp32, to the owner waves (others get 0).
     // meanwhile(): work of the owner waves that does not need the norm, done while it travels.
     auto exchange_norm = [&](double sq, uint64_t *slots, FirstPoll &first, auto meanwhile) -> float {
         // (one owner wave needs nobody: the barriers of a step are enough for what else it shares)
-        if (owner_waves == 1) {
+        if (kAlone && owner_waves == 1) {
             if (owner_wave) {
                 sq = wave_tree_sum_f64(sq);
-                if (lane == 0) store_dev(slots + norm_slot(w, W), (uint64_t)((uint64_t)__double_as_longlong(sq) + 1ull));
+                if (lane == 0) store_dev(slots + norm_slot<DX>(w, W), (uint64_t)((uint64_t)__double_as_longlong(sq) + 1ull));
             }
         } else {
             if (owner_wave) {
@@ -300,8 +306,8 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
             }
             lds_barrier();
             if (tid == 0) {
-                const double own = owner_waves == 2 ? red[0] + red[1] : (red[0] + red[1]) + (red[2] + red[3]);
-                store_dev(slots + norm_slot(w, W), (uint64_t)((uint64_t)__double_as_longlong(own) + 1ull));
+                const double own = owner_waves == 1 ? red[0] : owner_waves == 2 ? red[0] + red[1] : (red[0] + red[1]) + (red[2] + red[3]);
+                store_dev(slots + norm_slot<DX>(w, W), (uint64_t)((uint64_t)__double_as_longlong(own) + 1ull));
             }
         }
         if (!owner_wave) return 0.0f;
@@ -315,7 +321,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (q < nq && lane + kWave * q < W) {
-                    raw[q] = load_dev(slots + norm_slot(lane + kWave * q, W));
+                    raw[q] = load_dev(slots + norm_slot<DX>(lane + kWave * q, W));
                     all = all && raw[q] != 0ull;
                 }
             if (__builtin_amdgcn_ballot_w64(!all) == 0ull || dead) break;
@@ -510,8 +516,8 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
                 if (split > 1) store_dev(nxt + sub + xword(i, a.acc_sh), (uint64_t)0);
             }
             if (lane == 0) {
-                store_dev(slot_base + (size_t)((t + 2) & 3) * kNormSlots + norm_slot(w, W), (uint64_t)0);
-                store_dev(slot_base + (size_t)(4 + ((t + 2) & 3)) * kNormSlots + norm_slot(w, W), (uint64_t)0);
+                store_dev(slot_base + (size_t)((t + 2) & 3) * kNormSlots + norm_slot<DX>(w, W), (uint64_t)0);
+                store_dev(slot_base + (size_t)(4 + ((t + 2) & 3)) * kNormSlots + norm_slot<DX>(w, W), (uint64_t)0);
             }
             if (!(tid < B)) vm_wait_all();
         }
