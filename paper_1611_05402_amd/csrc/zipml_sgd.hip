@@ -1043,9 +1043,10 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
             // (a single workgroup is launched on the other instantiation: the host sees to it, so
             // that this one holds the end-to-end loop only and its registers)
             if (a.W > 1) {
-                // (SOLO: 1 both passes on the matrix cores, 2 the gradient pass, 0 neither; 4 on top: two exchange words for a sample.
-                // All hold the step's exact gradient.)
-                sgd_steps_e2e<BITS, UPT, (SOLO & 3) != 0, (SOLO & 3) == 1, (SOLO & 4) != 0>(a, L);
+                // (SOLO: 1 both passes on the matrix cores, 2 the gradient pass, 3 likewise with four feature groups, 0 neither; 4 on top:
+                // two exchange words for a sample.  All hold the step's exact gradient.)
+                constexpr int kOn = SOLO & 3;
+                sgd_steps_e2e<BITS, UPT, kOn != 0, kOn == 1, (SOLO & 4) != 0, kOn == 1 || (kOn == 2 && BITS >= 3)>(a, L);
             }
         } else if (INT) {
             sgd_steps<BITS, kInt, FAST, UPT, kTabAsked>(a, L);
@@ -1366,6 +1367,10 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
             kern = p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, 0> : (const void *)k_sgd<BITS, true, true, 2, false, 0>;
             if constexpr (BITS <= 4) {
                 if (grad_mx) kern = ZIPML_E2E(2);
+            }
+            if constexpr (BITS == 3 || BITS == 4) {
+                if (grad_mx && a.GQ > 2)
+                    kern = p.upt == 1 ? (const void *)k_sgd<BITS, true, true, 1, false, 3> : (const void *)k_sgd<BITS, true, true, 2, false, 3>;
             }
             if constexpr (BITS <= 3) {
                 if (dot_mx) kern = ZIPML_E2E(1);
@@ -1828,12 +1833,14 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
         const size_t room = (Workspace::sgd_bytes(batch) - Workspace::kAcc) / 8;
         // (two lines a stretch are enough for few workgroups, and half as many words to poll)
         a.acc_sh = p.W > 64 ? 2 : 1;
-        const int64_t sums = pairs * micro + (model_bits > 0 && p.W > 32 ? 8 * kWaves : 0);
+        // (End to end two words for a sample, and one for every wave's sum of codes: adds to one word follow each other at some 11 ns;
+        // not where the look-ups of a step are longer, 5 bits, 160 samples x 4,523 8.92 us a step with one word, 9.14 with two, nor on
+        // fat workgroups, 2 bits, 192 x 4,978 7.24 and 7.41.)
+        const bool two_words = model_bits > 0 && !stepwise && bits <= 4 && batch >= 32 && p.GQ <= 2 && p.W > 32;
+        const int64_t sums = pairs * micro + (two_words ? 8 * kWaves : 0);
         while (a.acc_sh > 0 && (size_t)replicas * Workspace::kAccBuffers * Workspace::acc_words(sums, a.acc_sh) + grad_words > room) --a.acc_sh;
         a.acc_words = (int)Workspace::acc_words(sums, a.acc_sh);
-        // (end to end: adds to one word follow each other at some 11 ns; not where the look-ups of a step are longer, 5 bits, 160
-        // samples x 4,523 8.92 us a step with one word, 9.14 with two, nor on fat workgroups, 2 bits, 192 x 4,978 7.24 and 7.41)
-        a.acc_split = model_bits > 0 && !stepwise && bits <= 4 && batch >= 32 && p.GQ <= 2 && p.W > 32 && 2 * (size_t)Workspace::kAccBuffers * a.acc_words <= room ? 2 : 1;
+        a.acc_split = two_words && 2 * (size_t)Workspace::kAccBuffers * a.acc_words <= room ? 2 : 1;
         a.acc_words *= a.acc_split;
         if ((size_t)replicas * Workspace::kAccBuffers * a.acc_words + grad_words > room ||
             (replicas > 1 && (size_t)replicas * p.W * 32 * p.GQ > Workspace::kGradWords))

@@ -94,7 +94,8 @@ template <int BITS> constexpr int kMonomials = (1 << BITS) - 1;
 // MX: the gradient pass on the matrix cores (at most 16 levels, B >= 32, GQ <= 4).
 // DX: the dot pass, too (at most 8 levels, GQ <= 2, 32 <= B <= 512, and the lanes' offsets in copy 2 within 32 bits).
 // SPLIT: two exchange words for a sample (asked of the host at run time it cost the launches of few workgroups 3 %).
-template <int BITS, int UPT, bool MX, bool DX, bool SPLIT>
+// ALONE: one wave owns all features of a workgroup (at most 64).
+template <int BITS, int UPT, bool MX, bool DX, bool SPLIT, bool ALONE>
 __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 {
     constexpr int K = 1 << BITS;
@@ -288,13 +289,12 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     // (Without a barrier in front of its slot the owner is sooner on its way, and the other waves sooner at what stands in the
     // way of its polls.  Us per step with it | without: 4 bits, 96 samples x 294 6.98 | 6.79, 192 x 376 7.21 | 6.96; look-ups,
     // 2 bits, 256 x 244 6.90 | 7.03, 5 bits, 160 x 179 8.13 | 8.23.)
-    constexpr bool kAlone = DX || (MX && BITS >= 3);
     // One trip of the norm exchange.  sq: this thread's square (owners; 0 elsewhere), fp64.
     // Returns the l2 norm over all workgroups as fp32, to the owner waves (others get 0).
     // meanwhile(): work of the owner waves that does not need the norm, done while it travels.
     auto exchange_norm = [&](double sq, uint64_t *slots, FirstPoll &first, auto meanwhile) -> float {
         // (one owner wave needs nobody: the barriers of a step are enough for what else it shares)
-        if (kAlone && owner_waves == 1) {
+        if constexpr (ALONE) {
             if (owner_wave) {
                 sq = wave_tree_sum_f64(sq);
                 if (lane == 0) store_dev(slots + norm_slot<DX>(w, W), (uint64_t)((uint64_t)__double_as_longlong(sq) + 1ull));
