@@ -799,3 +799,9 @@ def test_end_to_end_epochs_with_the_dot_pass_on_the_matrix_cores(d, B, bits):
     for step in range(9):
         zipml.debug_step(p.p1, p.p2, p.levels, p.b, n, d, bits, y, B, 0.01, step, p.ws, flags=zipml.SGD_PRODUCTION, r=r, **kw)
     assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d,B,bits", [(2999, 128, 4), (2999, 128, 3), (2999, 128, 2), (4523, 160, 5), (2047, 512, 4), (300, 96, 4), (4097, 96, 4)])
+def test_end_to_end_epochs_by_the_forms_of_the_norm_exchange(d, B, bits):
+    """One and two waves that own features, levels beyond the matrix cores, one and two exchange words a sample: likewise."""
+    test_end_to_end_epochs_with_the_dot_pass_on_the_matrix_cores(d, B, bits)
