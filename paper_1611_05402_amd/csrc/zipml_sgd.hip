@@ -1065,8 +1065,8 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
 
 // The plain estimator, fp32 model, minibatches of at most 512 SB samples: zipml_sgd_wave.h where all levels are evenly spaced,
 // else the vector loop; each has a number of workgroups and a width of its own, and what one does not need of the grid leaves.
-// UPT 0: no vector loop, the intermediates of a step to the debug outputs.
-template <int BITS, int SB, int UPT>
+// FULL: as many digits as fp32 numbers have (there).  UPT 0: no vector loop, the intermediates of a step to the debug outputs.
+template <int BITS, int SB, bool FULL, int UPT>
 __global__ __launch_bounds__(kThreads) void k_sgd_wave(SgdArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1074,7 +1074,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd_wave(SgdArgs a)
     int ok = 1;
     if (tid < Workspace::kEvenBlocks) ok = a.even[tid];
     if (__syncthreads_and(ok)) {
-        if ((int)blockIdx.x < a.wave_w) sgd_steps_wave<BITS, SB, UPT == 0>(a, smem);
+        if ((int)blockIdx.x < a.wave_w) sgd_steps_wave<BITS, SB, FULL, UPT == 0>(a, smem);
         return;
     }
     if constexpr (UPT == 0) {
@@ -1436,11 +1436,19 @@ static int launch_sgd(hipStream_t s, SgdArgs &a, const Plan &p, bool stepwise)
     int grid = a.W * a.R + a.nred + a.npref;
     if constexpr (!INT) {
         if (fast && a.wave_w > 0) {
+            // four digits where the plan is one of the matrix-core loop, which has as many, else eight (kWaveDigits); the debug outputs
+            // are those of such a plan (asked for elsewhere they have been refused); more than 512 samples are two units a thread or more
             const bool many = a.B > kWaves * kWave;
-#define ZIPML_WAVE(U) (many ? (const void *)k_sgd_wave<BITS, 2, U> : (const void *)k_sgd_wave<BITS, 1, U>)
-            kern = a.dbg_production ? ZIPML_WAVE(0) : p.upt == 1 ? ZIPML_WAVE(1) : p.upt == 2 ? ZIPML_WAVE(2) : ZIPML_WAVE(4);
+#define ZIPML_WAVE(F) (many ? (p.upt == 2 ? (const void *)k_sgd_wave<BITS, 2, F, 2> : (const void *)k_sgd_wave<BITS, 2, F, 4>) \
+                            : p.upt == 1 ? (const void *)k_sgd_wave<BITS, 1, F, 1> \
+                            : p.upt == 2 ? (const void *)k_sgd_wave<BITS, 1, F, 2> : (const void *)k_sgd_wave<BITS, 1, F, 4>)
+            kern = ZIPML_WAVE(true);
+            if constexpr (BITS == 2 || BITS == 4 || BITS == 8) {
+                if (a.dbg_production) kern = many ? (const void *)k_sgd_wave<BITS, 2, false, 0> : (const void *)k_sgd_wave<BITS, 1, false, 0>;
+                else if (p.mfma) kern = ZIPML_WAVE(false);
+            }
 #undef ZIPML_WAVE
-            shmem = std::max(shmem, (size_t)kWaveLds<BITS, 2>);
+            shmem = std::max(shmem, (size_t)kWaveLds<2, true>);
             grid = std::max(a.W, a.wave_w);
         }
     }

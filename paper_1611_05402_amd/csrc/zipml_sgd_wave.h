@@ -26,15 +26,20 @@
 
 namespace zipml {
 
-// Digits of r: four (29 bits below the wave's largest) where the loop on minibatches of chunks has four, else eight, so
-// that no number has fewer bits than in the vector loop, which computes in fp32 (see zipml_sgd_solo.hip).  Digits of y
-// there: six, 46 bits below the largest; what is published of their sums ends 42 bits below a larger number.
-template <int BITS> constexpr int kWaveDigits = BITS == 2 || BITS == 4 || BITS == 8 ? 4 : 8;
+// Digits of r and y.  FULL = false, for the plans of zipml_sgd_mfma.h (2, 4 and 8 bits, whole blocks of 64 samples): four, as
+// there.  FULL = true, for the plans of the vector loop, which computes in fp32: eight of r, which hold all bits of a number
+// down to 2^-35 of the wave's largest, and six of y, 46 bits below the sum of the workgroups' largest; what is published
+// of their sums ends 42 bits below a larger number.  With four, numbers beside a much larger one lose bits (see
+// zipml_sgd_solo.hip): 96 samples x 520 features, 8 bits, one residual in 16 larger by 10^6, worst coordinate of the gradient
+// relative to the magnitudes that reach it 1.7e-4 (four digits), 1.5e-7 (the vector loop), 9.3e-8 (eight).  What the
+// eight cost, us per step with four | eight | in the vector loop: 96 samples x 300 features, 4 bits 1.34 | 1.38 | 2.28; 160 x 3,000,
+// 8 bits 1.82 | 1.91 | 3.22; 736 x 1,500, 2 bits 2.09 | 2.20 | 3.78, 8 bits (no more registers) 2.95 | 3.41 | 4.40.
+template <bool FULL> constexpr int kWaveDigits = FULL ? 8 : 4;
 constexpr int kWaveBounds = 16;        // steps between exact refreshes of the magnitude bounds
 
 // LDS bytes: digits of r and y per wave, two sets of gradient parts and of the waves' figures
-template <int BITS, int SB>
-constexpr int kWaveLds = kWaves * (1 + SB) * kWaveDigits<BITS> * 64 + 2 * kWaves * 64 * 8 + 2 * kWaves * 4;
+template <int SB, bool FULL>
+constexpr int kWaveLds = kWaves * (1 + SB) * kWaveDigits<FULL> * 64 + 2 * kWaves * 64 * 8 + 2 * kWaves * 4;
 
 // An operand's dwords from a buffer, as one load.
 template <int N>
@@ -142,11 +147,14 @@ __device__ __forceinline__ void wave_operands(const uint32_t (&c)[kWaveLoads<BIT
     }
 }
 
-template <int BITS, int SB, bool DBG>
+template <int BITS, int SB, bool FULL, bool DBG>
 __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *smem)
 {
-    constexpr int NL = kWaveLoads<BITS>, LW = kWaveDwords<BITS>, ND = kWaveDigits<BITS>, K = 1 << BITS;
-    constexpr int kOff = BITS == 8 ? 128 : 0;
+    constexpr int NL = kWaveLoads<BITS>, LW = kWaveDwords<BITS>, ND = kWaveDigits<FULL>, K = 1 << BITS;
+    // Codes of 8 bits are operands 128 below.  FULL: 128 times the sum of the other operand is added to the integers (in the
+    // factor of a sum of fp32 numbers a large element that meets the code zero everywhere would leave its rounding errors).
+    constexpr int kOff = BITS == 8 && !FULL ? 128 : 0;
+    constexpr bool kOffset = BITS == 8 && FULL;
     constexpr double kMagic = 6755399441055744.0;       // 3 2^51: an integer below 2^51 in magnitude added to it is its foot
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -180,7 +188,7 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
     struct Sums {
         int lo[2], hi[2];
     };
-    auto pick = [&](const v4i (&c)[4]) __attribute__((always_inline)) {
+    auto pick = [&](const v4i (&c)[4], const v4i &half) __attribute__((always_inline)) {
         Sums s = {};
         if constexpr (ND == 8) {
             int x[2], y[2];
@@ -191,6 +199,11 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
                 for (int q = 0; q < 4; ++q) p[q] = c[q][2 * k] + (c[q][2 * k + 1] << 8);
                 x[k] = q4 & 2 ? p[2] : p[0];
                 y[k] = q4 & 2 ? p[3] : p[1];
+                if constexpr (kOffset) {                // (the same for all tiles)
+                    const int on = 2 * (half[2 * k] + (half[2 * k + 1] << 8));
+                    x[k] += on;
+                    y[k] += on;
+                }
             }
             const DigitSums j = join_rows(x, y);
 #pragma unroll
@@ -199,6 +212,15 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
             pick_tile(c, q4, s.lo);
         }
         return s;
+    };
+
+    // 64 times the sum of a digit operand
+    auto offset = [&](const v4i &digits, v4i half) __attribute__((always_inline)) {
+        if constexpr (kOffset) {
+            const v4i h = {0x40404040, 0x40404040, 0x40404040, 0x40404040};
+            half = __builtin_amdgcn_mfma_i32_16x16x64_i8(digits, h, half, 0, 0, 0);
+        }
+        return half;
     };
 
     // ---- bounds that fix the fixed-point scale of a step; every workgroup forms the same numbers (see zipml_sgd_mfma.h)
@@ -350,12 +372,13 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
         {
             // what every sample gets on top, rounded to an integer
             const double base = ldexp((double)cq, kp) + kMagic;
+            const v4i half = offset(yd, v4i{0, 0, 0, 0});
 #pragma unroll
             for (int sb = 0; sb < SB; ++sb) {
                 v4i c[4];
 #pragma unroll
                 for (int s = 0; s < 4; ++s) c[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(yd, e2[sb][s], v4i{0, 0, 0, 0}, 0, 0, 0);
-                const Sums s = pick(c);
+                const Sums s = pick(c, half);
                 uint64_t q;
                 if constexpr (ND == 4) {
                     q = (uint64_t)__double_as_longlong(base) + (uint64_t)((long long)s.lo[0] + ((long long)s.lo[1] << 16));
@@ -506,14 +529,16 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
         // ============ gradient pass: this wave's part of the mean gradient
         double G;
         {
-            v4i c[4];
+            v4i c[4], half = {0, 0, 0, 0};
+#pragma unroll
+            for (int sb = 0; sb < SB; ++sb) half = offset(rd[sb], half);
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 c[s] = v4i{0, 0, 0, 0};
 #pragma unroll
                 for (int sb = 0; sb < SB; ++sb) c[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(rd[sb], e1[sb][s], c[s], 0, 0, 0);
             }
-            const Sums s = pick(c);
+            const Sums s = pick(c, half);
             double v = fma((double)s.lo[1], 65536.0, (double)s.lo[0]);
             if constexpr (ND == 8) v = fma(fma((double)s.hi[1], 65536.0, (double)s.hi[0]), (double)kUpper, v);
             G = fma(g_dl, ldexp(v, -kr), g_mid * (double)rsum);
