@@ -27,9 +27,11 @@
 namespace zipml {
 
 // Digits of r and y.  FULL = false, for the plans of zipml_sgd_mfma.h (2, 4 and 8 bits, whole blocks of 64 samples): four, as
-// there.  FULL = true, for the plans of the vector loop, which computes in fp32: eight of r, which hold all bits of a number
-// down to 2^-35 of the wave's largest, and six of y, 46 bits below the sum of the workgroups' largest; what is published
-// of their sums ends 42 bits below a larger number.  With four, numbers beside a much larger one lose bits (see
+// there: 30 bits below the wave's largest r, and 30 below the bound of y, which behind a refresh is the sum of the workgroups'
+// largest.  (There 29 and 29.  The bit more of y is the one that the sum over twice the workgroups takes from 4,097 features
+// on: 512 samples x 16,384 features, 4 bits, equal elements: a step's model off by 3.8e-7 with 29, 4e-8 with 30.)  FULL = true, for
+// the plans of the vector loop, which computes in fp32: eight of r, which hold all bits of a number down to 2^-35 of the
+// wave's largest, and six of y, 46 bits below its bound; what is published of their sums ends 42 bits below a larger number.  With four, numbers beside a much larger one lose bits (see
 // zipml_sgd_solo.hip): 96 samples x 520 features, 8 bits, one residual in 16 larger by 10^6, worst coordinate of the gradient
 // relative to the magnitudes that reach it 1.7e-4 (four digits), 1.5e-7 (the vector loop), 9.3e-8 (eight).  What the
 // eight cost, us per step with four | eight | in the vector loop: 96 samples x 300 features, 4 bits 1.34 | 1.38 | 2.28; 160 x 3,000,
@@ -231,7 +233,7 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
     int kp, kd, ks;                                     // scales of the published sums, of the digits of y, of a published max |y|
     auto set_scales = [&]() __attribute__((always_inline)) {
         const int eb = exponent_of(__float_as_uint(beta)), ey = exponent_of(__float_as_uint(ymax));
-        ks = 29 - ey;
+        ks = 30 - ey;
         if constexpr (ND == 4) { kp = 42 - eb < ks ? 42 - eb : ks; kd = kp; }
         else { kp = 42 - eb; kd = 46 - ey; }
     };

@@ -746,6 +746,35 @@ def test_steps_with_samples_owned_by_waves_coordinate_by_coordinate(bits):
             assert err.max() <= (d + B + 8) * 2.0 ** -24, (int(err.argmax()), float(err.max()))
 
 
+@pytest.mark.parametrize("d,B,bits", [(8192, 64, 2), (8192, 256, 4), (16384, 128, 2), (16384, 512, 4)])
+def test_digits_of_the_model_behind_a_refresh_of_the_bounds(d, B, bits):
+    """The refreshed bound of y is the sum of the maxima of W workgroups of 64 features, and half as many of 128 features
+    would have half the sum: y is to be resolved as finely as there, to 2^-30 of the power of two above that sum.  All
+    elements of the model are 1.25 and that unit, which half the resolution would round the same way in every product.  17
+    minibatches of zeros leave the model as it is and refresh the bounds; the next step's model, relative to itself in L2:
+    fp32 roundings of z, the gradient and the model, at most 2^-24 each and of either sign, below 2^-23 in all, against
+    2^-21 / 1.25 (16,384 features) and 2^-22 / 1.25 with half the resolution."""
+    say("digits of y", d, B, bits)
+    K, W = 1 << bits, d // 64
+    unit = 2.0 ** (int(np.ceil(np.log2(W * 1.25 * 1.001))) - 30)
+    rng = np.random.default_rng(d + B + bits)
+    A = np.zeros((18 * B, d), np.float32)
+    A[17 * B:] = rng.uniform(0, K - 1, (B, d))
+    x0 = np.full(d, 1.25 + unit, np.float32)
+    L = oracle.levels_uniform(np.zeros(d, np.float32), np.full(d, K - 1, np.float32), bits)
+    p = GpuProblem(A, np.zeros(18 * B, np.float32), bits, B)
+    p.set_levels(L)
+    p.quantize(3, 0)
+    c1, c2 = (p.codes(c)[17 * B:].astype(np.float64) for c in (1, 2))
+    ref = x0.astype(np.float64) - c1.T @ (c2 @ x0.astype(np.float64)) / B
+    x = dev(x0)
+    zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, 18 * B, d, bits, x, B, 1.0, p.ws)
+    assert zipml.sgd_status(p.ws) == 0
+    err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+    say("error", err)
+    assert err <= 2.0 ** -23, err
+
+
 @pytest.mark.parametrize("bits", range(1, 9))
 def test_epochs_with_samples_owned_by_waves_at_the_ends_of_the_number_range(bits):
     """Tiny and huge labels keep their digits; an infinite label, and one that is no number, end in a model without a
