@@ -1102,7 +1102,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd_wave(SgdArgs a)
 // block by block (kEvenBlocks of them) whether the levels are evenly spaced; one more block takes
 // the magnitude bounds of the dot exchange from the levels and the current model,
 //   bound[0] = sum_j maxabs(L_j) |x_j|,   bound[1] = sum_j maxabs(L_j)^2,
-//   bound[2] = max_j delta_j |x_j|,       bound[3] = max_j delta_j maxabs(L_j),
+//   bound[2] = max_j |delta_j x_j|,       bound[3] = max_j |delta_j| maxabs(L_j),
 // (delta_j: spacing of evenly spaced levels) in fp64 with a fixed order.
 // (1024 threads: a block's share of the level tables is then two loads per thread, all in flight
 // together; with 256 the launch took 10 us on 2,048 x 256 levels, now 5.5.  The bounds' block reads a
@@ -1170,7 +1170,7 @@ static __global__ __launch_bounds__(kPrepThreads) void k_sgd_prepare(int *status
     for (int j = threadIdx.x; j < d; j += kPrepThreads) {
         const double lo = (double)levels[(size_t)j * K], hi = (double)levels[(size_t)j * K + K - 1];
         const double m = fmax(fabs(lo), fabs(hi));
-        const double delta = (double)(float)((hi - lo) / (double)(K - 1));
+        const double delta = fabs((double)(float)((hi - lo) / (double)(K - 1)));       // (levels may descend)
         pb += m * fabs((double)x[j]);
         pl += m * m;
         py = fmax(py, delta * fabs((double)x[j]));

@@ -292,7 +292,7 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
         g_dl[u] = __fdiv_rn(o_dl[u], (float)B);
         g_mid[u] = __fdiv_rn(o_mid[u], (float)B);
         x[u] = live[u] ? a.x[f] : 0.0f;
-        mu = fmaxf(mu, o_dl[u] * fmaxf(fabsf(lo), fabsf(hi)));
+        mu = fmaxf(mu, fabsf(o_dl[u]) * fmaxf(fabsf(lo), fabsf(hi)));
         y0 = fmaxf(y0, fabsf(o_dl[u] * x[u]));
         int half, byte;
         code_slot<BITS>(f & 31, half, byte);

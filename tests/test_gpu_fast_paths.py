@@ -806,6 +806,31 @@ def test_epochs_with_samples_owned_by_waves_at_the_ends_of_the_number_range(bits
         assert np.linalg.norm(got / scale - ref / scale) <= 1e-5 * np.linalg.norm(ref / scale)
 
 
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("d,B", [(60, 16), (100, 256), (300, 96), (300, 64), (2100, 256)])
+def test_epochs_on_levels_that_descend(d, B, bits):
+    """Evenly spaced levels from the highest to the lowest, on one workgroup and on several: the bounds of y are of
+    magnitudes, at the launch and from step to step (one workgroup begins at a model of zeros).  The model of the oracle (fp64
+    inside a step) to 1e-5, the bound of every epoch test."""
+    say("descending levels", d, B, bits)
+    n = 3 * B
+    rng = np.random.default_rng(d + B + bits)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    x0 = (rng.standard_normal(d) / d ** 0.5).astype(np.float32) if d > 256 else np.zeros(d, np.float32)
+    p = GpuProblem(A, b, bits, B)
+    p.set_levels(oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits))
+    p.quantize(5, 0)
+    L = oracle.levels_uniform(np.full(d, 1, np.float32), np.full(d, -1, np.float32), bits)
+    p.set_levels(L)
+    x = dev(x0)
+    zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, n, d, bits, x, B, 0.25 / d, p.ws)
+    assert zipml.sgd_status(p.ws) == 0
+    ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, x0.copy(), B, 0.25 / d)
+    err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+    assert err <= 1e-5, err
+
+
 @pytest.mark.parametrize("d,B,bits", [(2111, 512, 3), (4030, 512, 2), (4095, 32, 1), (4100, 480, 3), (2111, 96, 3), (8190, 96, 3)])
 def test_end_to_end_epochs_with_the_dot_pass_on_the_matrix_cores(d, B, bits):
     """Grid indices from a lowest one that is not zero up to thousands, an odd last group of features, whole and half blocks of
