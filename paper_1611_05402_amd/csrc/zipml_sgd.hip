@@ -1902,13 +1902,22 @@ static int run_sgd(void *stream, const void *packed1_dev, const void *packed2_de
             a.wave_sh = sh;
             a.wave_split = split;
             a.wave_sub = (int)sub;
-            // Copy 1 behind the atomics or as soon as the sums are there: by what a compute unit has to take in of a copy in
-            // a step, while the atomics of few workgroups leave the memory's side to it; codes whose expansion fills the time
-            // of the exchange from half as much on.  Us per step, behind | early: 256 samples x 1,000 features, 8 bits 1.93 |
-            // 1.73, x 2,048 2.04 | 2.14; 512 x 512, 8 bits 2.57 | 2.16, x 4,096 2.99 | 2.60, 2 bits, x 4,096 2.28 | 2.64; 6 bits,
-            // 256 x 2,048 2.20 | 2.10; 256 samples x 16,384, 8 bits 3.63 | 4.09.
-            const bool odd = !(bits == 1 || bits == 2 || bits == 4 || bits == 8);
-            a.wave_early = W <= 128 && micro * bits * 8 >= (odd ? 8192 : W <= 16 ? 16384 : 16385);
+            // Copy 1 behind the atomics or as soon as the sums are there: by the bytes of a copy that a compute unit takes in in a
+            // step.  Few of them arrive while the sums travel; more of them, or codes whose expansion fills that time, keep the
+            // polls waiting when they stand in front of them.  Where the memory's side is at work for many workgroups the time behind
+            // the sums is too short for them.  Us per step, behind | early (256 samples x 8 bits are 16,384 bytes):
+            //   8 bits, 16 workgroups: 128 samples 1.42 | 1.43, 192 1.46 | 1.47, 256 1.56 | 1.53, 320 2.08 | 1.81; 32: 192 1.76 | 1.69,
+            //     256 2.05 | 1.80; 64: 256 2.20 | 2.01, 384 2.64 | 2.51, 512 3.09 | 3.13; 90: 256 | 2 % slower; 125: 256 2.53 | 2.74, 384
+            //     3.23 | 3.63, but 1,024 (two blocks a wave) 4 % faster;
+            //   4 bits, 32 workgroups: 256 samples 1.66 | 1.62, 320 1.90 | 1.89, 384 2.04 | 1.99, 512 2.27 | 2.09; 125: 256 2.15 | 2.19, 320
+            //     2.60 | 2.55, 512 2.84 | 2.76; 256: 512 samples 8 % slower, 1,024 30 %; 2 bits likewise by bytes;
+            //   the other widths: 3 bits, 128 samples even, 192 2 % faster, 512 2 to 4 %; 6 bits, 64 samples 1 % faster, 128 5 %, 512 12 %;
+            //     from 128 workgroups on 200: 512 samples 6 to 16 % faster, 1,024 at 6 bits 9 % slower, on 256 512 samples at 6 bits 2 %.
+            const int64_t bytes = micro * bits * 8;
+            const bool one_block = micro <= kWaves * kWave;
+            if (bits == 1 || bits == 2 || bits == 4) a.wave_early = bytes > 8192 && W <= 128;
+            else if (bits == 8) a.wave_early = bytes > 12288 && W <= (one_block ? 64 : 128);
+            else a.wave_early = bytes >= 4096 && W <= (one_block ? 200 : 128);
         }
     }
     a.dbg_m = dbg_m; a.dbg_acc = dbg_acc; a.dbg_r = dbg_r; a.dbg_g = dbg_g; a.dbg_gq = dbg_gq;
