@@ -1046,7 +1046,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(SgdArgs a)
                 // (SOLO: 1 both passes on the matrix cores, 2 the gradient pass, 3 likewise with four feature groups, 0 neither; 4 on top:
                 // two exchange words for a sample.  All hold the step's exact gradient.)
                 constexpr int kOn = SOLO & 3;
-                sgd_steps_e2e<BITS, UPT, kOn != 0, kOn == 1, (SOLO & 4) != 0, kOn == 1 || (kOn == 2 && BITS >= 3)>(a, L);
+                sgd_steps_e2e<BITS, UPT, kOn != 0, kOn == 1, (SOLO & 4) != 0, kOn == 3 ? 2 : kOn == 1 || (kOn == 2 && BITS >= 3) ? 1 : 0>(a, L);
             }
         } else if (INT) {
             sgd_steps<BITS, kInt, FAST, UPT, kTabAsked>(a, L);

@@ -94,8 +94,10 @@ template <int BITS> constexpr int kMonomials = (1 << BITS) - 1;
 // MX: the gradient pass on the matrix cores (at most 16 levels, B >= 32, GQ <= 4).
 // DX: the dot pass, too (at most 8 levels, GQ <= 2, 32 <= B <= 512, and the lanes' offsets in copy 2 within 32 bits).
 // SPLIT: two exchange words for a sample (asked of the host at run time it cost the launches of few workgroups 3 %).
-// ALONE: one wave owns all features of a workgroup (at most 64).
-template <int BITS, int UPT, bool MX, bool DX, bool SPLIT, bool ALONE>
+// OWNERS: so many waves own the features of a workgroup: 1 (at most 64 features, no barrier before a norm), 2 (128 features),
+// 0: not known here.  (Us per step, asked at run time | known: 128 samples x 3,000 features, 4 bits 7.79 | 7.38, 64 x 4,000, 3
+// bits 7.10 | 6.64, 512 x 4,096, 3 bits 7.79 | 7.66.)
+template <int BITS, int UPT, bool MX, bool DX, bool SPLIT, int OWNERS>
 __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
 {
     constexpr int K = 1 << BITS;
@@ -103,7 +105,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
     const int w = blockIdx.x;
-    const int W = a.W, GQ = a.GQ, CW = 32 * GQ, B = a.B;
+    const int W = a.W, GQ = OWNERS == 2 ? 4 : a.GQ, CW = 32 * GQ, B = a.B;
     const int nrg = B >= 32 ? B / 32 : 1;
     const int j0 = w * CW;
     const int ngroups = (a.d32 - w * GQ) < GQ ? (a.d32 - w * GQ) : GQ;
@@ -113,7 +115,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     double *const gpart = reinterpret_cast<double *>(L.gpart);
     int *const tq = L.tq;
     const bool is_owner = tid < CW;                  // this thread owns feature j0 + tid
-    const int owner_waves = (CW + kWave - 1) / kWave;
+    const int owner_waves = OWNERS ? OWNERS : (CW + kWave - 1) / kWave;
     const bool owner_wave = wave < owner_waves;
     const int jme = j0 + tid;
     const bool live = is_owner && jme < a.d;
@@ -294,7 +296,7 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
     // meanwhile(): work of the owner waves that does not need the norm, done while it travels.
     auto exchange_norm = [&](double sq, uint64_t *slots, FirstPoll &first, auto meanwhile) -> float {
         // (one owner wave needs nobody: the barriers of a step are enough for what else it shares)
-        if constexpr (ALONE) {
+        if constexpr (OWNERS == 1) {
             if (owner_wave) {
                 sq = wave_tree_sum_f64(sq);
                 if (lane == 0) store_dev(slots + norm_slot<DX>(w, W), (uint64_t)((uint64_t)__double_as_longlong(sq) + 1ull));
@@ -306,7 +308,10 @@ __device__ __forceinline__ void sgd_steps_e2e(const SgdArgs &a, const Lds &L)
             }
             lds_barrier();
             if (tid == 0) {
-                const double own = owner_waves == 1 ? red[0] : owner_waves == 2 ? red[0] + red[1] : (red[0] + red[1]) + (red[2] + red[3]);
+                // (as one expression the choice is made after four reads: 160 samples x 3,684, 5 bits 7.79 us a step, so 7.60)
+                double own = red[0];
+                if (owner_waves == 2) own = red[0] + red[1];
+                else if (owner_waves == 4) own = (red[0] + red[1]) + (red[2] + red[3]);
                 store_dev(slots + norm_slot<DX>(w, W), (uint64_t)((uint64_t)__double_as_longlong(own) + 1ull));
             }
         }
