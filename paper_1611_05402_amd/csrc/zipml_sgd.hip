@@ -1073,28 +1073,41 @@ __global__ __launch_bounds__(kThreads) void k_sgd_wave(SgdArgs a)
     const int tid = threadIdx.x;
     int ok = 1;
     if (tid < Workspace::kEvenBlocks) ok = a.even[tid];
-    if (__syncthreads_and(ok)) {
-        if ((int)blockIdx.x < a.wave_w) sgd_steps_wave<BITS, SB, FULL, UPT == 0>(a, smem);
-        return;
+    // The loop that stands first moves the other one, and where a loop lies is worth some percent to it.  Vector loop second |
+    // first, on uneven levels: 480 samples x 2,500 features, 3 bits 4.97 | 4.74, 96 x 2,944 3.15 | 3.10; 256 x 1,500, 4 bits 4.13 | 4.05,
+    // 128 x 9,500 5.02 | 4.89; 64 x 700, 5 bits 2.45 | 2.49, 96 x 2,944 3.49 | 3.54.
+    constexpr bool kVectorFirst = UPT != 0 && (BITS == 3 || BITS == 4);
+    const bool even = __syncthreads_and(ok);
+    if constexpr (!kVectorFirst) {
+        if (even) {
+            if ((int)blockIdx.x < a.wave_w) sgd_steps_wave<BITS, SB, FULL, UPT == 0>(a, smem);
+            return;
+        }
     }
     if constexpr (UPT == 0) {
         if (blockIdx.x == 0 && tid == 0) store_dev(a.status, (int)ZIPML_EUNSUPPORTED);
     } else {
-        if ((int)blockIdx.x >= a.W) return;
-        Lds L;
-        (void)sgd_setup<BITS, false, true>(a, L, smem);
-        // (7 and 8 bits: the tables of many features stay in memory; at 2 bits, and up to 5 bits on at most 512 samples, the
-        // question stays, see sgd_steps: us per step without | with it, 512 samples x 536, 3 bits 3.96 | 3.82, 256 x 1,500 3.22 |
-        // 3.15, 4 bits 4.20 | 4.13, 5 bits 3.78 | 3.70; 928 x 1,328, 3 bits 6.86 | 6.98)
-        if constexpr (BITS >= 7) {
-            if (a.lds_levels) sgd_steps<BITS, kTable, true, UPT, kTabLds>(a, L);
-            else sgd_steps<BITS, kTable, true, UPT, kTabMem>(a, L);
-        } else {
-            sgd_steps<BITS, kTable, true, UPT, BITS == 2 || (SB == 1 && BITS <= 5) ? kTabAsked : kTabLds>(a, L);
+        if (!kVectorFirst || !even) {
+            if ((int)blockIdx.x >= a.W) return;
+            Lds L;
+            (void)sgd_setup<BITS, false, true>(a, L, smem);
+            // (7 and 8 bits: the tables of many features stay in memory; at 2 bits, and up to 6 bits on at most 512 samples, the
+            // question stays, see sgd_steps: us per step without | with it, 512 samples x 536, 3 bits 3.96 | 3.82, 256 x 1,500 3.22 |
+            // 3.15, 4 bits 4.20 | 4.13, 5 bits 3.78 | 3.70, 6 bits 3.19 | 3.10; 928 x 1,328, 3 bits 6.86 | 6.98)
+            if constexpr (BITS >= 7) {
+                if (a.lds_levels) sgd_steps<BITS, kTable, true, UPT, kTabLds>(a, L);
+                else sgd_steps<BITS, kTable, true, UPT, kTabMem>(a, L);
+            } else {
+                sgd_steps<BITS, kTable, true, UPT, BITS == 2 || (SB == 1 && BITS <= 6) ? kTabAsked : kTabLds>(a, L);
+            }
+            const int CW = 32 * a.GQ, j0 = blockIdx.x * CW;
+            for (int c = tid; c < CW; c += kThreads)
+                if (j0 + c < a.d) a.x[j0 + c] = L.xs[c];
+            return;
         }
-        const int CW = 32 * a.GQ, j0 = blockIdx.x * CW;
-        for (int c = tid; c < CW; c += kThreads)
-            if (j0 + c < a.d) a.x[j0 + c] = L.xs[c];
+    }
+    if constexpr (kVectorFirst) {
+        if ((int)blockIdx.x < a.wave_w) sgd_steps_wave<BITS, SB, FULL, false>(a, smem);
     }
 }
 
