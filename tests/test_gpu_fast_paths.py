@@ -529,7 +529,8 @@ def test_level_tables_in_memory_are_not_read_past_their_end(bits, d, knobs):
 @pytest.mark.parametrize("B,bits", [(4, 3), (8, 4), (32, 6), (96, 2), (64, 8), (576, 4)])
 def test_epochs_over_exchange_words_of_every_spacing(B, bits, groups, knobs):
     """Both spacings of the exchange words (up to 64 workgroups, and more), sums that end inside and at the end of a
-    run of eight words, more steps than exchange buffers; even and uneven levels.  The model of the oracle (fp64 inside
+    run of eight words, more steps than exchange buffers; even levels in the loop in which waves own samples (64 features to
+    a workgroup, whatever the knob) and in the loops that follow it, uneven levels.  The model of the oracle (fp64 inside
     a step) to 1e-5, the bound of every epoch test."""
     say("spread exchange words", B, bits, groups)
     # (so few groups as two would be one workgroup's: sixteen then, on two workgroups, on eight at 576 samples)
@@ -545,12 +546,14 @@ def test_epochs_over_exchange_words_of_every_spacing(B, bits, groups, knobs):
         p = GpuProblem(A, b, bits, B)
         p.set_levels(L)
         p.quantize(5, 0)
-        x = dev(np.zeros(d, np.float32))
         lr = 0.25 / d
-        p.epoch(x, lr)
         ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, lr)
-        err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
-        assert err <= 1e-5, err
+        for xmin in (-1, 1 << 40) if L is even else (-1,):
+            knobs(zipml.KNOB_STORE_EXCHANGE_MIN, xmin)
+            x = dev(np.zeros(d, np.float32))
+            p.epoch(x, lr)
+            err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+            assert err <= 1e-5, err
 
 
 @pytest.mark.parametrize("groups", [33, 64, 65, 128, 129, 257])
@@ -746,6 +749,65 @@ def test_steps_with_samples_owned_by_waves_coordinate_by_coordinate(bits):
             zipml.sgd_epoch(p.p1, p.p2, p.levels, p.b, B, d, bits, x, B, 1.0, p.ws)
             err = np.abs(x.cpu().numpy().astype(np.float64) - ref) / mag
             assert err.max() <= (d + B + 8) * 2.0 ** -24, (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("d", [16384, 16385, 20000])
+@pytest.mark.parametrize("B,bits", [(64, 8), (96, 4), (256, 2), (512, 4), (512, 8)])
+def test_epochs_on_both_sides_of_the_widest_problems(d, B, bits):
+    """Up to 256 workgroups of 64 features waves own samples; on more features the matrix-core loop runs, with the reducers
+    and the workgroups that read ahead that the library chooses from 128 workgroups x 256 samples on, and the vector loop on
+    minibatches that are not whole blocks of 64.  Even and uneven levels; the model of the oracle (fp64 inside a step) to
+    1e-5, the bound of every epoch test."""
+    say("widest problems", d, B, bits)
+    n, K = 3 * B, 1 << bits
+    rng = np.random.default_rng(d + B + bits)
+    A = rng.uniform(-1, 1, (n, d)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    for even in (True, False):
+        L = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+        if not even:
+            L[d - 1] = np.sort(rng.uniform(-1, 1, K)).astype(np.float32)
+        p = GpuProblem(A, b, bits, B)
+        p.set_levels(L)
+        p.quantize(5, 0)
+        x = dev(np.zeros(d, np.float32))
+        p.epoch(x, 0.25 / d)
+        ref = oracle.sgd_epoch(p.codes(1), p.codes(2), L, b, bits, np.zeros(d, np.float32), B, 0.25 / d)
+        err = np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+        assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("n", [58_719_744, 58_720_256])
+def test_step_at_the_end_of_the_largest_copies(n):
+    """Offsets of codes at the last multiple of a minibatch for which two groups of a copy lie within 7 * 2^29 bytes, and
+    beyond, where the matrix-core loop runs.  Only the last 1,024 samples are written; the last step's residuals and
+    gradient against fp64, to 1e-5 like every production step."""
+    say("largest copies", n)
+    d, bits, B, rows = 290, 8, 512, 1024
+    groups = (d + 31) // 32
+    rng = np.random.default_rng(n)
+    A = rng.uniform(-1, 1, (rows, d)).astype(np.float32)
+    b = rng.standard_normal(rows).astype(np.float32)
+    x0 = (rng.standard_normal(d) / d ** 0.5).astype(np.float32)
+    L = oracle.levels_uniform(np.full(d, -1, np.float32), np.full(d, 1, np.float32), bits)
+    p1, p2 = (torch.empty(zipml.packed_bytes(n, d, bits), dtype=torch.uint8, device="cuda:0") for _ in (1, 2))
+    labels = torch.empty(n, dtype=torch.float32, device="cuda:0")
+    labels[n - rows:] = dev(b)
+    levels = dev(L)
+    ws = torch.zeros(zipml.workspace_bytes(n, d, bits, B), dtype=torch.uint8, device="cuda:0")
+    zipml.quantize(dev(A), rows, d, d, n - rows, n, levels, bits, 3, 0, p1, p2)
+    # (copy 2: samples x 32 features in a group; copy 1: groups of 32 samples, 32 features x 32 samples in each)
+    c2 = p2.view(groups, n, 32)[:, n - B:].permute(1, 0, 2).reshape(B, groups * 32)[:, :d].cpu().numpy()
+    c1 = p1.view(groups, n // 32, 32, 32)[:, (n - B) // 32:].permute(1, 3, 0, 2).reshape(B, groups * 32)[:, :d].cpu().numpy()
+    v1, v2 = (np.take_along_axis(L.T, c.astype(np.int64), axis=0).astype(np.float64) for c in (c1, c2))
+    r_ref = v2 @ x0.astype(np.float64) - b[rows - B:]
+    g_ref = v1.T @ r_ref / B
+    x = dev(x0)
+    r, g = torch.zeros(B, device="cuda:0"), torch.zeros(d, device="cuda:0")
+    zipml.debug_step(p1, p2, levels, labels, n, d, bits, x, B, 0.05, n // B - 1, ws, r=r, g=g, flags=zipml.SGD_PRODUCTION)
+    assert zipml.sgd_status(ws) == 0
+    for got, want in ((r, r_ref), (g, g_ref), (x, x0 - np.float32(0.05) * g_ref)):
+        assert np.linalg.norm(got.cpu().numpy().astype(np.float64) - want) <= 1e-5 * np.linalg.norm(want)
 
 
 @pytest.mark.parametrize("d,B,bits", [(8192, 64, 2), (8192, 256, 4), (16384, 128, 2), (16384, 512, 4)])

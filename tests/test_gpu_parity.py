@@ -608,11 +608,13 @@ def test_exchange_through_tagged_stores(name, factory, kw, lr, avg, knobs):
     assert rel_l2(res[1], x_ref) <= TOL and max_abs_ok(res[1], x_ref, TOL)
 
 
-def test_sgd_fp32_one_feature_not_evenly_spaced():
-    """Evenly spaced levels take the matrix-core loop; a single feature with other levels must
-    send every workgroup down the table path (workgroups on different loops would scale their
+@pytest.mark.parametrize("xmin", [-1, 1 << 40])
+def test_sgd_fp32_one_feature_not_evenly_spaced(xmin, knobs):
+    """Evenly spaced levels take the loop in which waves own samples, or the matrix-core loop; a single feature with other
+    levels must send every workgroup down the table path (workgroups on different loops would scale their
     contributions to the exchange differently)."""
-    say("sgd fp32, 8-bit, one feature with uneven levels")
+    say("sgd fp32, 8-bit, one feature with uneven levels", xmin)
+    knobs(zipml.KNOB_STORE_EXCHANGE_MIN, xmin)
     w = synth.dense8(n=4096, d=288, batch=256)
     A, b = w.full()
     L = _levels_for(w, A).copy()
@@ -651,12 +653,14 @@ def test_sgd_fp32_with_non_uniform_levels():
 
 
 # ------------------------------------------------------------------ the production step, element by element
+@pytest.mark.parametrize("xmin", [-1, 1 << 40])
 @pytest.mark.parametrize("bits", [8, 4, 2])
-def test_production_step_residuals_and_gradient_element_by_element(bits):
-    """One step of the headline shape's width (batch 256, d = 2048) in the launch and on the
-    matrix-core loop that zipml_sgd_epoch takes, residuals and gradient compared element by
+def test_production_step_residuals_and_gradient_element_by_element(bits, xmin, knobs):
+    """One step of the headline shape's width (batch 256, d = 2048) in the launch that zipml_sgd_epoch takes and on the
+    loop that it takes there, and on the matrix-core loop, residuals and gradient compared element by
     element with the definition (eq. (5), Sec. 2.2) in fp64 on the oracle's codes; d + 13 covers
     a ragged last block of features."""
+    knobs(zipml.KNOB_STORE_EXCHANGE_MIN, xmin)
     for d in (2048, 2048 + 13):
         say("production step: bits", bits, "d", d)
         B, n = 256, 1024
@@ -705,7 +709,7 @@ def test_production_step_refusals():
     x = torch.zeros(64, dtype=torch.float32, device=DEV)
     r = torch.zeros(64, dtype=torch.float32, device=DEV)
     mo = torch.zeros(64, dtype=torch.int32, device=DEV)
-    with pytest.raises(zipml.ZipmlError) as e:      # 3-bit codes never take the matrix-core loop
+    with pytest.raises(zipml.ZipmlError) as e:      # (asked of the plans of the matrix-core loop only)
         zipml.debug_step(p.p1, p.p2, p.levels, p.b, w.n, 64, 3, x, 64, 0.1, 0, p.ws, r=r,
                          flags=zipml.SGD_PRODUCTION)
     assert e.value.code == zipml.EUNSUPPORTED
@@ -987,12 +991,15 @@ def test_epoch_on_the_compact_record_refusals():
 
 # ------------------------------------------------------------------ least-squares SVM
 @pytest.mark.parametrize("name,kw", [
-    ("lssvm_8bit", dict()),                                   # matrix-core loop
+    ("lssvm_8bit", dict()),                                   # waves own samples
+    ("lssvm_8bit_chunk_loop", dict()),                        # matrix-core loop
     ("lssvm_5bit_wide", dict(n=2048, d=1056, bits=5, batch=64)),   # vector loop, many workgroups
     ("lssvm_small", dict(n=1024, d=96, bits=4, batch=32)),    # single workgroup
 ])
-def test_least_squares_svm_epochs_match_oracle(name, kw):
+def test_least_squares_svm_epochs_match_oracle(name, kw, knobs):
     say("ls-svm", name)
+    if name.endswith("chunk_loop"):
+        knobs(zipml.KNOB_STORE_EXCHANGE_MIN, 1 << 40)
     w = synth.lssvm(**kw)
     A, b = w.full()
     assert set(np.unique(b)) == {-1.0, 1.0}
@@ -1023,8 +1030,10 @@ def test_least_squares_svm_epochs_match_oracle(name, kw):
 
 # ------------------------------------------------------------------ proximal step
 @pytest.mark.parametrize("name,factory,kw,lr", [
-    ("dense8_small", synth.dense8, dict(n=4096, d=288, batch=256), 0.02),          # matrix-core loop
-    ("b5_wide", synth.tiny, dict(n=2048, d=1056, batch=64, bits=5), 0.01),          # vector loop
+    ("dense8_small", synth.dense8, dict(n=4096, d=288, batch=256), 0.02),          # waves own samples
+    ("dense8_small_chunk_loop", synth.dense8, dict(n=4096, d=288, batch=256), 0.02),   # matrix-core loop
+    ("b5_wide", synth.tiny, dict(n=2048, d=1056, batch=64, bits=5), 0.01),          # waves own samples
+    ("b5_wide_chunk_loop", synth.tiny, dict(n=2048, d=1056, batch=64, bits=5), 0.01),   # vector loop
     ("tiny_one_workgroup", synth.tiny, dict(n=2048, d=64, batch=16, bits=4), 0.01),  # no exchange
     ("dense8_replicas", synth.dense8, dict(n=8192, d=288, batch=4096), 0.1),        # chunks on replicas
     ("dense8_sample_owners", synth.dense8, dict(n=16384, d=288, batch=16384), 0.2),
@@ -1034,6 +1043,8 @@ def test_proximal_step_matches_oracle(name, factory, kw, lr, kind, coef, knobs):
     """x <- prox_{lr R}(x - lr g) (Sec. 2) on every step loop, for the three regularisers."""
     say("prox", name, kind)
     knobs(zipml.KNOB_ROWS_MIN_BATCH, 16384)
+    if name.endswith("chunk_loop"):
+        knobs(zipml.KNOB_STORE_EXCHANGE_MIN, 1 << 40)
     w = factory(**kw)
     A, b = w.full()
     L = _levels_for(w, A)
@@ -1088,8 +1099,10 @@ def test_proximal_step_refusals():
 
 # ------------------------------------------------------------------ failure handling
 @pytest.mark.parametrize("name,factory,kw", [
-    ("dense8_small", synth.dense8, dict(n=4096, d=288, batch=256)),          # matrix-core loop
-    ("b5_wide", synth.tiny, dict(n=2048, d=1056, batch=64, bits=5)),         # vector loop, 33 groups
+    ("dense8_small", synth.dense8, dict(n=4096, d=288, batch=256)),          # waves own samples
+    ("dense8_small_chunk_loop", synth.dense8, dict(n=4096, d=288, batch=256)),   # matrix-core loop
+    ("b5_wide", synth.tiny, dict(n=2048, d=1056, batch=64, bits=5)),         # waves own samples, 33 groups
+    ("b5_wide_chunk_loop", synth.tiny, dict(n=2048, d=1056, batch=64, bits=5)),   # vector loop
     ("dense8_replicas", synth.dense8, dict(n=8192, d=288, batch=4096)),      # chunks on two replicas
     ("dense8_sample_owners", synth.dense8, dict(n=16384, d=288, batch=16384)),
     ("dense8_tagged_stores", synth.dense8, dict(n=2048, d=1100, batch=512)),
@@ -1102,6 +1115,8 @@ def test_wait_that_gives_up_is_reported_not_hung(name, factory, kw, knobs):
     knobs(zipml.KNOB_ROWS_MIN_BATCH, 16384)    # (for the sample-owner case)
     if name == "dense8_tagged_stores":
         knobs(zipml.KNOB_STORE_EXCHANGE_MIN, 0)
+    if name.endswith("chunk_loop"):
+        knobs(zipml.KNOB_STORE_EXCHANGE_MIN, 1 << 40)
     w = factory(**kw)
     A, b = w.full()
     p = GpuProblem(A, b, w.bits, w.batch)
