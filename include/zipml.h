@@ -157,11 +157,13 @@ int zipml_sgd_epoch_compact(void *stream, const void *compact_dev, const float *
  * x <- x - lr * g every step (Supp. E: the update is in full precision).
  *   model_bits = grad_bits = 0: full-precision (fp32) model, residuals and gradient.  The sums
  *     over features and over samples are accumulated as integers (fixed-point partial sums, and
- *     for evenly spaced 2-, 4- or 8-bit levels exact integer sums of codes times fixed-point
- *     digits), so the result does not depend on the order in which workgroups finish: two calls
- *     with the same arguments give the same bits.  A problem that one workgroup holds (up to 256
- *     features) has no such sums: it runs in fp32, or on digits that keep every fp32 bit of residuals,
- *     model and levels down to 2^-35 of the largest of them, added in a fixed order.
+ *     for evenly spaced levels exact integer sums of codes times fixed-point digits) or added in a
+ *     fixed order, so the result does not depend on the order in which workgroups finish: two calls
+ *     with the same arguments give the same bits.  The digits keep every fp32 bit of residuals, model
+ *     and levels down to 2^-35 of the largest residual and 2^-22 of a bound on the largest product of
+ *     model and spacing; at 2, 4 and 8 bits, minibatches a multiple of 64 and more than 256 features
+ *     they end 29 bits below these.  A problem that one workgroup holds (up to 256 features) runs in
+ *     fp32, or on digits of the first kind, to 2^-35 of the largest throughout.
  *   model_bits in 2..8: the model is stochastically quantised each step with row scaling
  *     (Supp. A.3 eq. (quant2), Supp. C), s = 2^(model_bits-1) - 1 magnitude intervals, and the dot
  *     product becomes an exact integer sum of grid_idx * model code; this needs grid_idx_dev and a
@@ -284,11 +286,11 @@ int zipml_unpack_codes(void *stream, const void *packed_dev, int copy, int64_t n
  * r_dev[batch] the residuals Q2(a_i)^T x - b_i, g_dev[d] the mean gradient before Q4.
  * Without flags the step runs in a launch of its own kind (the vector loop).  With
  * ZIPML_SGD_PRODUCTION it runs in the persistent launch and on the step loop that zipml_sgd_epoch
- * uses: the matrix-core loop for evenly spaced 2-, 4- or 8-bit levels and an fp32 model (only r_dev
- * and g_dev may be asked for then, ZIPML_EINVAL otherwise), or the end-to-end loop for
- * model_bits > 0 on more than one workgroup (all five outputs).  Shapes or level tables that
- * zipml_sgd_epoch would not run on one of these loops return ZIPML_EUNSUPPORTED (for the level
- * tables through zipml_sgd_status, with x_dev left untouched). */
+ * uses: one of the two matrix-core loops for evenly spaced 2-, 4- or 8-bit levels, batch a multiple
+ * of 64, an fp32 model and more than one workgroup (only r_dev and g_dev may be asked for then,
+ * ZIPML_EINVAL otherwise), or the end-to-end loop for model_bits > 0 on more than one workgroup
+ * (all five outputs).  Other shapes return ZIPML_EUNSUPPORTED (other level tables through
+ * zipml_sgd_status, with x_dev left untouched). */
 int zipml_debug_step(void *stream, const void *packed1_dev, const void *packed2_dev,
                      const float *levels_dev, const uint16_t *grid_idx_dev, float grid_lo,
                      float grid_step, int grid_max, const float *b_dev, int64_t n, int64_t d,
@@ -309,7 +311,9 @@ int zipml_debug_stream(void *stream, const void *src_dev, void *dst_dev, size_t 
  * sweeps, A/B measurements and tests that steer kernel selection (the library never reads the
  * environment).  value = -1 restores the automatic choice.  Values out of a knob's range are
  * ignored by the code that consults it.  Returns ZIPML_EINVAL for an unknown knob. */
-#define ZIPML_KNOB_TARGET_WORKGROUPS 0  /* most feature-owner workgroups wanted (default: by sizes)    */
+#define ZIPML_KNOB_TARGET_WORKGROUPS 0  /* most feature-owner workgroups wanted (default: by sizes; without
+                                            effect on epochs on even levels with one exchange a step, at up
+                                            to 1,024 samples and 16,384 features: 64 features to each)    */
 #define ZIPML_KNOB_NO_MATRIX_CORES   1  /* 1: evenly spaced levels stay on the vector-ALU step loop    */
 #define ZIPML_KNOB_CHUNK_SAMPLES     2  /* chunk size of minibatches taken in chunks                    */
 #define ZIPML_KNOB_MAX_REPLICAS      3  /* most replicas of the workgroups that share the chunks        */

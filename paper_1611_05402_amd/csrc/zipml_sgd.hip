@@ -162,10 +162,11 @@ struct SgdArgs {
     int dbg_production;    // 1: dbg_r / dbg_g are written by the production launch (matrix-core loop)
 };
 
-// What the dot pass of the end-to-end loop takes from the model: G[j][c] * m_j, or the digits of 2^bits - 1 products of 64 features.
+// What the dot pass of the end-to-end loop takes from the model: G[j][c] * m_j, or the digits of 2^bits - 1 products (64
+// features to a workgroup).
 __host__ __device__ inline size_t e2e_table_bytes(int CW, int bits)
 {
-    const size_t table = (size_t)CW * 4 << bits, digits = bits <= 3 ? (((size_t)1 << bits) - 1) * 256 : 0;
+    const size_t table = (size_t)CW * 4 << bits, digits = bits <= 3 && CW == 64 ? (((size_t)1 << bits) - 1) * 256 : 0;
     return table > digits ? table : digits;
 }
 

@@ -26,16 +26,18 @@
 
 namespace zipml {
 
-// Digits of r and y.  FULL = false, for the plans of zipml_sgd_mfma.h (2, 4 and 8 bits, whole blocks of 64 samples): four, as
-// there: 30 bits below the wave's largest r, and 30 below the bound of y, which behind a refresh is the sum of the workgroups'
-// largest.  (There 29 and 29.  The bit more of y is the one that the sum over twice the workgroups takes from 4,097 features
-// on: 512 samples x 16,384 features, 4 bits, equal elements: a step's model off by 3.8e-7 with 29, 4e-8 with 30.)  FULL = true, for
-// the plans of the vector loop, which computes in fp32: eight of r, which hold all bits of a number down to 2^-35 of the
-// wave's largest, and six of y, 46 bits below its bound; what is published of their sums ends 42 bits below a larger number.  With four, numbers beside a much larger one lose bits (see
-// zipml_sgd_solo.hip): 96 samples x 520 features, 8 bits, one residual in 16 larger by 10^6, worst coordinate of the gradient
-// relative to the magnitudes that reach it 1.7e-4 (four digits), 1.5e-7 (the vector loop), 9.3e-8 (eight).  What the
-// eight cost, us per step with four | eight | in the vector loop: 96 samples x 300 features, 4 bits 1.34 | 1.38 | 2.28; 160 x 3,000,
-// 8 bits 1.82 | 1.91 | 3.22; 736 x 1,500, 2 bits 2.09 | 2.20 | 3.78, 8 bits (no more registers) 2.95 | 3.41 | 4.40.
+// Digits of r and y.
+// FULL = false, for the plans of zipml_sgd_mfma.h (2, 4 and 8 bits, whole blocks of 64 samples): four, as there, 30 bits below
+// the wave's largest r, and 30 below the bound of y, which behind a refresh is the sum of the workgroups' largest.  (There 29
+// and 29.  The bit more of y is the one that the sum over twice the workgroups takes from 4,097 features on: 512 samples x
+// 16,384 features, 4 bits, equal elements: a step's model off by 3.8e-7 with 29, 4e-8 with 30.)
+// FULL = true, for the plans of the vector loop, which computes in fp32: eight of r, which hold all bits of a number down
+// to 2^-35 of the wave's largest, and six of y, 46 bits below its bound; what is published of their sums ends 42 bits below a
+// larger number.  With four, numbers beside a much larger one lose bits (see zipml_sgd_solo.hip): 96 samples x 520 features,
+// 8 bits, one residual in 16 larger by 10^6, worst coordinate of the gradient relative to the magnitudes that reach it 1.7e-4
+// (four digits), 1.5e-7 (the vector loop), 9.3e-8 (eight).  What the eight cost, us per step with four | eight | in the vector
+// loop: 96 samples x 300 features, 4 bits 1.34 | 1.38 | 2.28; 160 x 3,000, 8 bits 1.82 | 1.91 | 3.22; 736 x 1,500, 2 bits 2.09 |
+// 2.20 | 3.78, 8 bits (no more registers) 2.95 | 3.41 | 4.40.
 template <bool FULL> constexpr int kWaveDigits = FULL ? 8 : 4;
 constexpr int kWaveBounds = 16;        // steps between exact refreshes of the magnitude bounds
 
@@ -268,8 +270,9 @@ __device__ __forceinline__ void sgd_steps_wave(const SgdArgs &a, unsigned char *
         cq = wave_total(mid * x, AddF());
     };
 
-    // ---- where the operands lie.  Groups of samples or features that are not there lie past the end of the buffer: zeros, and
-    // nothing is read.
+    // ---- where the operands lie.  Groups of samples or features that are not there lie past the end of the buffer (0xF0000000
+    // of 0xE0000000 bytes): zeros, and nothing is read, whether the range check counts a step's scalar offset to the lane's, takes
+    // it off the size, or leaves it out; for what is there the two stay below 0xE0000000 together (run_sgd).
     uint32_t at2[SB][NL], at1[SB][NL];
     const uint32_t group_bytes = (uint32_t)(a.nb64 * 64 * 4 * BITS);                // of either copy
 #pragma unroll
