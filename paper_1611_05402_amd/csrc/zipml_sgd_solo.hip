@@ -511,6 +511,13 @@ __device__ __forceinline__ void solo_affine(const SoloArgs &a, const SoloLds &L,
 template <int BITS, bool IN_LDS, int kFt>
 __device__ __forceinline__ void solo_table(const SoloArgs &a, const SoloLds &L, unsigned char *ring, int S, int splits)
 {
+    // Where the loop lies within 32 bytes is worth up to 6 % of a step to it, so it is set here, whatever code precedes it.  Us
+    // per step at 0, 4, ... 28 bytes: 256 samples x 90 features, 3 bits 2.07, 2.06, 2.08, 2.07, 2.04, 2.07, 2.05, 2.08 (4 bits: within
+    // 1 %); 128 x 100, 6 bits 2.44, 2.44, 2.44, 2.48, 2.49, 2.49, 2.50, 2.46, 16 x 64 1.61, 1.58, 1.61, 1.63, 1.66, 1.68, 1.65, 1.69.
+    // (64 x 64, 2 bits at 16 and 20 bytes 1.31, 1.27.)
+    if constexpr (BITS == 2) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    else if constexpr (BITS <= 5) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    else if constexpr (BITS == 6) asm volatile(".p2align 5\n\ts_nop 0");
     constexpr int K = 1 << BITS;
     static_assert(BITS >= 2, "two levels are evenly spaced");
     constexpr bool kPairs = K <= 8;
