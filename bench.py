@@ -56,9 +56,15 @@ def parse():
     return ap.parse_args()
 
 
+def epoch_kernel(workload):
+    """The kernel that runs this workload's epochs at its own sizes, by the name it has in a trace."""
+    return {"e2e": "k_sgd", "tiny": "k_sgd_solo"}.get(workload, "k_sgd_wave")
+
+
 def recorded_traffic(workload, batch, note=False):
     """HBM bytes per epoch launch measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), as
-    recorded in the text summary under profiles/ for this workload; None if there is none.
+    recorded in the text summary under profiles/ for this workload; None if there is none, or if it
+    was recorded with another kernel.
     note=True: the remark recorded with it (what the counters include), or None."""
     path = os.path.join(ROOT, "profiles", f"sgd_epoch_{workload}_hbm_traffic.txt")
     value, remark = None, None
@@ -70,6 +76,8 @@ def recorded_traffic(workload, batch, note=False):
                     if len(fields) >= 4 and fields[2] == "batch" and int(fields[3]) != batch:
                         return None
                     value = float(fields[1])
+                elif line.startswith("traffic_kernel:") and line.split()[1] != epoch_kernel(workload):
+                    return None
                 elif line.startswith("traffic_note:"):
                     remark = line[len("traffic_note:"):].strip()
     except OSError:
@@ -350,7 +358,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": head["packed_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": head["frac_hbm_peak"], "traffic": head["hbm_traffic_bytes_per_epoch"],
                      "traffic_note": head.get("hbm_traffic_note"),
-                     "kernel": f"k_sgd<{head['bits']}> (persistent epoch kernel, one launch per epoch)",
+                     "kernel": f"{epoch_kernel(headline)}<{head['bits']}> (persistent epoch kernel, one launch per epoch)",
                      "kernel_ms": head["ms_per_epoch"],
                      "us_per_minibatch_step": head["us_per_minibatch_step"],
                      "measured_stream_read_GBps": read_ceiling,
