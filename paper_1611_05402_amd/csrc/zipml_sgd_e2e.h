@@ -25,7 +25,7 @@
 // integers like the others.  Else from a table T[j][code] = G[j][code] * m_j, rebuilt by the owner of feature j after Q3 (one
 // LDS gather and one integer add per code; for wide level sets the product is formed on the fly): 512 samples x 64
 // features, 3 bits 1.56 us from the table, 0.66 so; the whole step of 512 x 4,096 with that and with two exchange words for
-// a sample 8.43 -> 7.81.  The mean gradient that Q4 quantises is the exact mean rounded to
+// a sample 8.43 -> 7.66.  The mean gradient that Q4 quantises is the exact mean rounded to
 // fp32, whatever the order: the gradient pass adds L[j][code] * r_i either in fp64 (products of two fp32
 // numbers are exact there) or, for at most 16 levels and whole sample groups (MX), in integers on the matrix
 // cores: r and a feature's levels in eight signed bytes each (24 bits at the top of 62, so that a number is exact
